@@ -664,6 +664,11 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     const bool dense = dense_supported(P, co) && !force_gather;
     int n_chunks = 0;
     if (e == hipSuccess && loop && dense) e = launch_dense_prepare(P, W, kChunkTokens, &n_chunks, st);
+    float kappa[COLBANDIT_MAX_ROUNDS + 1] = {};      // radius per unit sigma_hat of each round
+    for (int r = 1; r <= R; ++r) {
+        const double kap = colbandit_radius_prefactor(alpha_ef, delta, T, N, r * kn.B < T ? r * kn.B : T);
+        kappa[r] = isinf(kap) ? 0.f : (float)kap;    // unused by the kernels when n <= 1
+    }
     unsigned long long round_thr[COLBANDIT_MAX_ROUNDS + 2];
     for (int r = 0; r <= R + 1; ++r) round_thr[r] = ~0ull;
     for (int r = 1; e == hipSuccess && loop && r <= R; ++r) {
@@ -673,8 +678,6 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         rr.nb = (r * kn.B < T ? r * kn.B : T) - rr.lo;
         rr.n_prev = rr.lo;
         rr.n = rr.lo + rr.nb;
-        const double kap = colbandit_radius_prefactor(alpha_ef, delta, T, N, rr.n);
-        rr.kappa = isinf(kap) ? 0.f : (float)kap;   // unused by the kernels when n <= 1
         int G = 1;
         while (G < rr.nb) G <<= 1;
         rr.dense_thr = ~0ull;
@@ -689,7 +692,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
             if (e == hipSuccess && r >= 2) e = launch_gather_cells(P, W, rr, co, st);
         }
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
-        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, tr, st);
+        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, tr, st);
         pt.mark(PH_SELECT);
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact

@@ -31,7 +31,8 @@ struct QueryCtl {
     int implicit;  // 1: A = [0,N) and no list exists
     int active;    // 1: the query still takes part in elimination rounds
     int mode;      // 0: list entries are document ids; 1: they are slots of the cell cache
-    int pad0, pad1, pad2;
+    int bound;     // round 1: order-preserving key of a lower threshold (k_select_sample)
+    int pad1, pad2;
 };
 
 // Device-side choice of a later round's reveal path (uniform over the launch): true = the
@@ -572,7 +573,7 @@ __device__ __forceinline__ void merge_stats(float& S, float& M2, int n_prev, flo
         M2 = m2b;
         return;
     }
-    const float dm = sb / (float)nb - S / (float)n_prev;
+    const float dm = div_count(sb, nb) - div_count(S, n_prev);
     M2 = M2 + m2b + dm * dm * ((float)n_prev * (float)nb / (float)(n_prev + nb));
     S += sb;
 }
@@ -601,7 +602,7 @@ __device__ __forceinline__ void interval(float S, float M2, int n, int T, float 
         lcb = S;
         ucb = S;
     } else {
-        const float shat = (float)T * (S / (float)n);
+        const float shat = (float)T * div_count(S, n);
         const float sigma = sqrtf(fmaxf(M2, 0.f) / (float)(n - 1));
         const float r = kappa * sigma;
         lcb = fmaxf(lb, shat - r);

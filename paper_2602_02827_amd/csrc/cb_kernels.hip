@@ -2,6 +2,7 @@
 // small control kernels.  gfx950 only.
 #include <type_traits>
 
+#include "../../include/colbandit.h"
 #include "cb_launch.h"
 
 namespace cb {
@@ -30,7 +31,7 @@ __global__ void k_init(QueryCtl* ctl, int32_t* pi, const int32_t* user_pi, int32
     c.implicit = 1;
     c.active = N > (int64_t)KM;
     c.mode = 0;
-    c.pad0 = c.pad1 = c.pad2 = 0;
+    c.bound = c.pad1 = c.pad2 = 0;
     ctl[q] = c;
     for (int r = 0; r <= R; ++r) {
         cnt_hist[r * nq + q] = (int)N;
@@ -441,42 +442,74 @@ hipError_t launch_cached_score(const Problem& P, const Work& W, float* out, hipS
 // =====================================================================================
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WAVES = SEL_THREADS / 64;
-constexpr int SEL_ITEMS = 4;                       // consecutive entries per thread per chunk
+constexpr int SEL_ITEMS = 4;                       // consecutive entries per thread per chunk (long lists)
 constexpr int SEL_CHUNK = SEL_THREADS * SEL_ITEMS;
-constexpr int SEL_ITEMS_WIDE = 8;                  // the same for the one streaming pass over a long list
-constexpr int SEL_SAMPLE = 16384;                 // sample behind the pre-filter
-constexpr int SEL_PREFILTER_MIN = 8 * SEL_SAMPLE;  // lists longer than this are pre-filtered
-constexpr int SEL_RUN = 16;                        // the sample is taken in runs of adjacent entries
+constexpr int SEL_RUN = 16;                        // samples are taken in runs of adjacent entries
+// Lists longer than SEL_TILE are first cut down tile by tile (k_select_segments,
+// k_topk_segments).  k_topk holds what is left in registers, SEL_E entries per thread; k_select_prune,
+// which needs more registers per entry, SEL_REGS, and takes longer lists from memory.
+constexpr int SEL_E = 16;
+constexpr int SEL_TILE = SEL_E * SEL_THREADS;
+static_assert(SEL_TILE == 16384, "the cell cache's slots per query must fit one tile");
+// Tile of the pre-filter kernels: half as many registers, so that two workgroups share a CU.
+constexpr int SEG_E = 8;
+constexpr int SEG_TILE = SEG_E * SEL_THREADS;
+constexpr int SEG_MAX = 64;                        // segments of a long list
+constexpr int SEL_REGS = 8;
+constexpr int SEL_BINS = 2048;
+constexpr int SEL_FEW = 1024;
 
-// Position of sample j in a list of `count` > SEL_PREFILTER_MIN entries: SEL_SAMPLE / SEL_RUN
-// evenly spaced runs of SEL_RUN adjacent entries (whole cache lines instead of one entry per
-// line; any subset gives a valid lower threshold).
-__device__ __forceinline__ int sample_pos(int j, int count) {
-    const int run_stride = count / (SEL_SAMPLE / SEL_RUN);
-    return (j / SEL_RUN) * run_stride + (j % SEL_RUN);
+struct SelShared {
+    uint32_t hist[SEL_BINS];
+    int wtot[SEL_WAVES];
+    int pick[2];
+    int cnt[SEL_WAVES];                            // kept entries per wavefront
+    uint32_t group[64];                            // largest key of each 16 lanes
+    uint32_t few[SEL_FEW];                         // keys that reach the lower bound, in any order
+    int n_few;
+    int round_count[COLBANDIT_MAX_ROUNDS];         // survivors and threshold of the rounds run
+    float round_tau[COLBANDIT_MAX_ROUNDS];
+};
+
+// Inclusive sum over the wavefront's lanes, in lane order (DPP: shifts by 1, 2, 4, 8 inside the
+// rows of 16 lanes, then the rows' totals are passed on).
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return v;
+}
+
+// the same inside each row of 16 lanes
+__device__ __forceinline__ int row_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    return v;
+}
+// this thread's wavefront, as a scalar
+__device__ __forceinline__ int my_wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+// sum of the wavefronts' totals before this wavefront, and of all (wtot: LDS, one per wavefront)
+__device__ __forceinline__ int waves_before(const int* wtot, int& total) {
+    const int x = wtot[threadIdx.x & (SEL_WAVES - 1)];
+    const int incl = row_incl_scan(x);
+    const int wave = my_wave();
+    total = __builtin_amdgcn_readlane(incl, SEL_WAVES - 1);
+    return __builtin_amdgcn_readlane(incl, wave) - __builtin_amdgcn_readlane(x, wave);
 }
 
 // Exclusive scan of v over the block in thread order; returns the thread's offset and the
 // block total.  wtot: LDS int[SEL_WAVES].  Two barriers.
 __device__ __forceinline__ int block_excl_scan(int v, int* wtot, int& total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-    }
-    if (lane == 63) wtot[wave] = incl;
+    const int incl = wave_incl_scan(v);
+    if ((threadIdx.x & 63) == 63) wtot[threadIdx.x >> 6] = incl;
     __syncthreads();
-    int base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) {
-        const int x = wtot[w];
-        if (w < wave) base += x;
-        tot += x;
-    }
+    const int base = waves_before(wtot, total);
     __syncthreads();
-    total = tot;
     return base + incl - v;
 }
 
@@ -489,7 +522,7 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, int bin, bool on) {
 #pragma unroll 1
     for (int it = 0; it < 4 && pending != 0ull; ++it) {
         const int leader = __ffsll((long long)pending) - 1;
-        const int lbin = __shfl(bin, leader);
+        const int lbin = __builtin_amdgcn_readlane(bin, leader);
         const unsigned long long same = __ballot(on && bin == lbin) & pending;
         if ((int)(threadIdx.x & 63) == leader) atomicAdd(&hist[lbin], (uint32_t)__popcll(same));
         pending &= ~same;
@@ -497,24 +530,173 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, int bin, bool on) {
     if ((pending >> (threadIdx.x & 63)) & 1ull) atomicAdd(&hist[bin], 1u);
 }
 
-// Key of the K-th largest element (1 <= K <= count) of key_of(0..count-1): three radix
-// passes (11+11+10 bits) over the candidates with an LDS histogram each.  Each thread
-// takes SEL_ITEMS strided entries per trip so that several loads are in flight.
-// hist: LDS uint32[2048]; pick: LDS int[2].
-template <class KeyFn>
-__device__ uint32_t block_kth_largest(int count, int K, KeyFn key_of, uint32_t* hist, int* pick) {
+// One digit of the radix selection.  The histogram of the digit is complete (the caller's
+// barrier): finds the bin, counted from the highest down, that holds the kk-th entry, moves kk to
+// the rank inside that bin, and leaves the histogram cleared.  Every thread takes its two
+// neighbouring bins (one for 1,024), so that no two lanes of a read share a bank beyond the
+// two-word stride; one wavefront reading 32 bins per lane was a 32-way conflict and took
+// longer than the histogram itself.  Two barriers.
+__device__ __forceinline__ int pick_digit(SelShared& sh, int nbins, int& kk) {
+    const int per = nbins / SEL_THREADS;
+    const int hi = nbins - 1 - (int)threadIdx.x * per;
+    const int c0 = (int)sh.hist[hi];
+    sh.hist[hi] = 0u;
+    int c1 = 0;
+    if (per == 2) {
+        c1 = (int)sh.hist[hi - 1];
+        sh.hist[hi - 1] = 0u;
+    }
+    const int local = c0 + c1;
+    const int incl = wave_incl_scan(local);
+    if ((threadIdx.x & 63) == 63) sh.wtot[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    int all;
+    const int excl = waves_before(sh.wtot, all) + incl - local;
+    if (excl < kk && kk <= excl + local) {          // exactly one thread
+        const bool first = excl + c0 >= kk;
+        sh.pick[0] = first ? hi : hi - 1;
+        sh.pick[1] = first ? kk - excl : kk - excl - c0;
+    }
+    __syncthreads();
+    kk = sh.pick[1];
+    return sh.pick[0];
+}
+
+// clears the histogram (pick_digit leaves it clear afterwards); the caller's next barrier publishes
+__device__ __forceinline__ void clear_hist(SelShared& sh) {
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) sh.hist[i] = 0u;
+    if (threadIdx.x == 0) {
+        sh.pick[0] = 0;
+        sh.pick[1] = 1;
+        sh.n_few = 0;
+    }
+    __syncthreads();
+}
+
+// K-th largest (K >= 1) of the 64 lanes' keys, bit by bit from the top: a step is one comparison
+// and a count of its mask.  BITS < 32: only the leading bits, i.e. a lower bound.
+template <int BITS>
+__device__ __forceinline__ uint32_t wave_kth_largest(uint32_t v, int K) {
+    uint32_t best = 0;
+#pragma unroll
+    for (int bit = 31; bit > 31 - BITS; --bit) {
+        const uint32_t test = best | (1u << bit);
+        if (__popcll(__ballot(v >= test)) >= K) best = test;
+    }
+    return best;
+}
+
+// Radix selection of the K-th largest (1 <= K <= number of set bits over the block) of the keys
+// whose bit in `on` is set: three passes (11+11+10 bits), any distribution of keys.
+template <int NK>
+__device__ __forceinline__ uint32_t kth_largest_radix(const uint32_t (&key)[NK], unsigned on, int K, SelShared& sh) {
     uint32_t prefix = 0, pmask = 0;
     int kk = K;
 #pragma unroll 1
     for (int p = 0; p < 3; ++p) {
         const int shift = p == 0 ? 21 : (p == 1 ? 10 : 0);
         const int nbins = p == 2 ? 1024 : 2048;
-        for (int i = threadIdx.x; i < 2048; i += SEL_THREADS) hist[i] = 0;
-        if (threadIdx.x == 0) {
-            pick[0] = 0;
-            pick[1] = 1;
-        }
+#pragma unroll
+        for (int u = 0; u < NK; ++u)
+            hist_add(sh.hist, (int)((key[u] >> shift) & (nbins - 1)),
+                     ((on >> u) & 1u) && (key[u] & pmask) == prefix);
         __syncthreads();
+        prefix |= (uint32_t)pick_digit(sh, nbins, kk) << shift;
+        pmask |= (uint32_t)(nbins - 1) << shift;
+    }
+    return prefix;
+}
+
+// A lower bound of the K-th largest key over the block, given each thread's largest (0: it has
+// none): the K-th largest of a set of maxima, which are keys of K different entries.  0 when the
+// set is smaller than K.  The few largest keys seldom share a group, so the bound is close.
+// K <= 32: 64 groups of 16 lanes, one barrier; else the threads themselves.
+__device__ __forceinline__ uint32_t lower_bound_key(uint32_t top, int K, SelShared& sh) {
+    if (K > 32) {
+        const uint32_t k1[1] = {top};
+        return kth_largest_radix<1>(k1, 1u, K, sh);
+    }
+    auto ror_max = [](uint32_t v, auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF, 0xF, false);
+        return o > v ? o : v;
+    };
+    top = ror_max(top, std::integral_constant<int, DPP_ROW_ROR + 8>{});
+    top = ror_max(top, std::integral_constant<int, DPP_ROW_ROR + 4>{});
+    top = ror_max(top, std::integral_constant<int, DPP_ROW_ROR + 2>{});
+    top = ror_max(top, std::integral_constant<int, DPP_ROW_ROR + 1>{});
+    if ((threadIdx.x & 15) == 0) sh.group[threadIdx.x >> 4] = top;
+    __syncthreads();
+    return wave_kth_largest<22>(sh.group[threadIdx.x & 63], K);
+}
+
+// appends the lanes' keys to the collected ones (n_few counts on beyond SEL_FEW)
+__device__ __forceinline__ void collect_few(uint32_t key, bool hit, SelShared& sh) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long m = __ballot(hit);
+    if (m != 0ull) {                                // uniform over the wavefront
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&sh.n_few, __popcll(m));
+        at = __builtin_amdgcn_readlane(at, 0) + __popcll(m & ((1ull << lane) - 1ull));
+        if (hit && at < SEL_FEW) sh.few[at] = key;
+    }
+}
+// K-th largest of the collected keys (at least K of them), which are cleared; false if there were
+// too many to keep.  Two barriers.
+__device__ __forceinline__ bool kth_of_few(int K, uint32_t& kth, SelShared& sh) {
+    const int lane = threadIdx.x & 63;
+    __syncthreads();
+    const int n = sh.n_few;
+    if (n <= 64) {
+        kth = wave_kth_largest<32>(lane < n ? sh.few[lane] : 0u, K);
+    } else if (n <= SEL_FEW && (int)threadIdx.x < n) {
+        const uint32_t mine = sh.few[threadIdx.x];
+        int above = 0, equal = 0;
+        for (int j = 0; j < n; ++j) {
+            const uint32_t x = sh.few[j];
+            above += x > mine;
+            equal += x == mine;
+        }
+        if (above < K && K <= above + equal) sh.pick[0] = (int)mine;   // all writers hold the same key
+    }
+    __syncthreads();                                // n_few and few have been read
+    if (threadIdx.x == 0) sh.n_few = 0;             // the next use is behind a barrier of its own
+    if (n > 64) kth = (uint32_t)sh.pick[0];
+    return n <= SEL_FEW;
+}
+
+// Key of the K-th largest (1 <= K <= number of set bits over the block) of the keys whose bit in
+// `on` is set, NK per thread.  The keys that reach a lower bound of it, a little more than K, are
+// collected and ranked; only when they are many (ties, or K near the size of the list) does the
+// radix selection run over all keys.  A histogram pass of that costs about 100 instructions per
+// key of a thread, this selection about 100 in all: threshold and prune of round 1 at
+// 128 queries x 500,000 documents 76 -> 34 us, seven cached rounds of lists of 1,800 entries
+// 7 launches of 31 us -> one of 99 us.
+template <int NK>
+__device__ __forceinline__ uint32_t kth_largest_regs(const uint32_t (&key)[NK], unsigned on, int K, SelShared& sh) {
+    uint32_t top = 0;
+#pragma unroll
+    for (int u = 0; u < NK; ++u) {
+        const uint32_t k = (on >> u) & 1u ? key[u] : 0u;
+        top = k > top ? k : top;
+    }
+    const uint32_t bound = lower_bound_key(top, K, sh);
+#pragma unroll
+    for (int u = 0; u < NK; ++u) collect_few(key[u], ((on >> u) & 1u) && key[u] >= bound, sh);
+    uint32_t kth;
+    if (!kth_of_few(K, kth, sh)) kth = kth_largest_radix<NK>(key, on, K, sh);
+    return kth;
+}
+
+// The same over key_of(0..count-1) of a list of any length: the keys are evaluated again in each
+// pass, SEL_ITEMS strided entries per thread and trip so that several loads are in flight.
+template <class KeyFn>
+__device__ uint32_t kth_largest_list(int count, int K, KeyFn key_of, SelShared& sh) {
+    uint32_t prefix = 0, pmask = 0;
+    int kk = K;
+#pragma unroll 1
+    for (int p = 0; p < 3; ++p) {
+        const int shift = p == 0 ? 21 : (p == 1 ? 10 : 0);
+        const int nbins = p == 2 ? 1024 : 2048;
         for (int base = 0; base < count; base += SEL_CHUNK) {
             uint32_t key[SEL_ITEMS];
 #pragma unroll
@@ -525,146 +707,118 @@ __device__ uint32_t block_kth_largest(int count, int K, KeyFn key_of, uint32_t* 
 #pragma unroll
             for (int u = 0; u < SEL_ITEMS; ++u) {
                 const int idx = base + u * SEL_THREADS + threadIdx.x;
-                hist_add(hist, (int)((key[u] >> shift) & (nbins - 1)),
+                hist_add(sh.hist, (int)((key[u] >> shift) & (nbins - 1)),
                          idx < count && (key[u] & pmask) == prefix);
             }
         }
         __syncthreads();
-        if (threadIdx.x < 64) {
-            const int lane = threadIdx.x;
-            const int per = nbins / 64;
-            const int hi = nbins - 1 - lane * per;       // this lane's bins, descending
-            int local = 0;
-            for (int j = 0; j < per; ++j) local += (int)hist[hi - j];
-            int incl = local;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(incl, o);
-                if (lane >= o) incl += t;
-            }
-            const int excl = incl - local;
-            if (excl < kk && kk <= incl) {
-                int run = excl;
-                for (int j = 0; j < per; ++j) {
-                    const int c = (int)hist[hi - j];
-                    if (run + c >= kk) {
-                        pick[0] = hi - j;
-                        pick[1] = kk - run;
-                        break;
-                    }
-                    run += c;
-                }
-            }
-        }
-        __syncthreads();
-        prefix |= (uint32_t)pick[0] << shift;
+        prefix |= (uint32_t)pick_digit(sh, nbins, kk) << shift;
         pmask |= (uint32_t)(nbins - 1) << shift;
-        kk = pick[1];
-        __syncthreads();
     }
     return prefix;
 }
 
-// The same selection over SEL_SAMPLE keys that each thread computes once and keeps in
-// registers for all three passes (thread t holds keys t, t + SEL_THREADS, ...).
-constexpr int SEL_SAMPLE_PER_THREAD = SEL_SAMPLE / SEL_THREADS;
-template <class KeyFn>
-__device__ uint32_t block_kth_largest_sample(int K, KeyFn key_of, uint32_t* hist, int* pick) {
-    uint32_t key[SEL_SAMPLE_PER_THREAD];
-#pragma unroll
-    for (int u = 0; u < SEL_SAMPLE_PER_THREAD; ++u) key[u] = key_of(u * SEL_THREADS + (int)threadIdx.x);
-    uint32_t prefix = 0, pmask = 0;
-    int kk = K;
-#pragma unroll 1
-    for (int p = 0; p < 3; ++p) {
-        const int shift = p == 0 ? 21 : (p == 1 ? 10 : 0);
-        const int nbins = p == 2 ? 1024 : 2048;
-        for (int i = threadIdx.x; i < 2048; i += SEL_THREADS) hist[i] = 0;
-        if (threadIdx.x == 0) {
-            pick[0] = 0;
-            pick[1] = 1;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < SEL_SAMPLE_PER_THREAD; ++u)
-            hist_add(hist, (int)((key[u] >> shift) & (nbins - 1)), (key[u] & pmask) == prefix);
-        __syncthreads();
-        if (threadIdx.x < 64) {
-            const int lane = threadIdx.x;
-            const int per = nbins / 64;
-            const int hi = nbins - 1 - lane * per;       // this lane's bins, descending
-            int local = 0;
-            for (int j = 0; j < per; ++j) local += (int)hist[hi - j];
-            int incl = local;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(incl, o);
-                if (lane >= o) incl += t;
-            }
-            const int excl = incl - local;
-            if (excl < kk && kk <= incl) {
-                int run = excl;
-                for (int j = 0; j < per; ++j) {
-                    const int c = (int)hist[hi - j];
-                    if (run + c >= kk) {
-                        pick[0] = hi - j;
-                        pick[1] = kk - run;
-                        break;
-                    }
-                    run += c;
-                }
-            }
-        }
-        __syncthreads();
-        prefix |= (uint32_t)pick[0] << shift;
-        pmask |= (uint32_t)(nbins - 1) << shift;
-        kk = pick[1];
-        __syncthreads();
+// Layout of n <= E * SEL_THREADS list entries over the block: each wavefront takes `span`
+// consecutive ones (whole groups of 64, the same for all wavefronts), thread `lane` the entries
+// u * 64 + lane of them.  Entry order is then (wavefront, u, lane), and the places of kept entries
+// need one exchange of 16 counts.
+struct Spread {
+    int first, n, span;      // this thread's first entry; entries in all; entries per wavefront
+    __device__ __forceinline__ explicit Spread(int n_) : n(n_) {
+        span = (n_ + SEL_THREADS - 1) / SEL_THREADS * 64;
+        first = my_wave() * span + (int)(threadIdx.x & 63);
     }
-    return prefix;
+    // list position of the thread's u-th entry (past the end: the last one again)
+    __device__ __forceinline__ int at(int u) const {
+        const int i = first + u * 64;
+        return i < n ? i : n - 1;
+    }
+    // which of the thread's E entries exist
+    template <int E> __device__ __forceinline__ unsigned mask() const {
+        unsigned m = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) m |= (u * 64 < span && first + u * 64 < n ? 1u : 0u) << u;
+        return m;
+    }
+};
+
+// Places of the kept entries of such a list, in entry order: place(u) is the number of kept
+// entries before this thread's u-th, total their number.  One barrier; the caller puts another
+// between two uses.
+template <int E> struct Places {
+    unsigned long long m[E];
+    int base[E], total;
+    __device__ __forceinline__ Places(unsigned keep, SelShared& sh) {
+        int n = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            m[u] = __ballot((keep >> u) & 1u);
+            base[u] = n;
+            n += __popcll(m[u]);
+        }
+        if ((threadIdx.x & 63) == 0) sh.cnt[threadIdx.x >> 6] = n;
+        __syncthreads();
+        const int before = waves_before(sh.cnt, total);
+#pragma unroll
+        for (int u = 0; u < E; ++u) base[u] += before;
+    }
+    __device__ __forceinline__ int place(int u) const {
+        return base[u] + __builtin_amdgcn_mbcnt_hi((unsigned)(m[u] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m[u], 0u));
+    }
+};
+
+// entries per segment of a long list: whole tiles, so that a segment's bound comes from a full
+// tile whenever there is one
+__device__ __forceinline__ int seg_len(int count) {
+    const int tiles = (count + SEG_TILE - 1) / SEG_TILE;
+    return (tiles + SEG_MAX - 1) / SEG_MAX * SEG_TILE;
 }
 
-// The batch statistics of batch_stats_g<G> evaluated by ONE thread on the G slot values
-// (same pairing of additions, lane by lane, so the bits are those of the cross-lane form).
-__device__ __forceinline__ void lanes_sum(float (&v)[16], int G) {
-    float t[16];
-    if (G >= 16) {
-        for (int i = 0; i < 16; ++i) t[i] = v[i] + v[15 - i];
-        for (int i = 0; i < 16; ++i) v[i] = t[i];
-    }
-    if (G >= 8) {
-        for (int i = 0; i < 16; ++i) t[i] = v[i] + v[(i & 8) | (7 - (i & 7))];
-        for (int i = 0; i < 16; ++i) v[i] = t[i];
-    }
-    if (G >= 4) {
-        for (int i = 0; i < 16; ++i) t[i] = v[i] + v[i ^ 2];
-        for (int i = 0; i < 16; ++i) v[i] = t[i];
-    }
-    if (G >= 2) {
-        for (int i = 0; i < 16; ++i) t[i] = v[i] + v[i ^ 1];
-        for (int i = 0; i < 16; ++i) v[i] = t[i];
-    }
+// The 16 slot values of a reveal batch, summed in the order of the cross-lane form
+// (batch_stats_g): zero slots past nb make the order of every group size a case of this one.
+__device__ __forceinline__ float slot_sum(const float (&v)[16]) {
+    const float u0 = (v[0] + v[15]) + (v[7] + v[8]), u1 = (v[1] + v[14]) + (v[6] + v[9]);
+    const float u2 = (v[2] + v[13]) + (v[5] + v[10]), u3 = (v[3] + v[12]) + (v[4] + v[11]);
+    return (u0 + u2) + (u1 + u3);
 }
-__device__ __forceinline__ void batch_stats_thread(const float (&c)[16], int nb, int G, float& s,
-                                                   float& m2) {
-    float v[16];
-    for (int i = 0; i < 16; ++i) v[i] = (i < nb) ? c[i] : 0.f;
-    lanes_sum(v, G);
-    s = v[0];
-    float dv[16];
+// The batch statistics of batch_stats_g evaluated by ONE thread (same additions, same bits).
+// cell(i): the batch's i-th cell.
+template <class CellFn>
+__device__ __forceinline__ void batch_stats_thread(CellFn cell, int nb, float& s, float& m2) {
+    if (nb <= 4) {                                  // uniform
+        float c[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = i < nb ? cell(i) : 0.f;
+        s = (c[0] + c[2]) + (c[1] + c[3]);
+        const float mean = div_count(s, nb);
+        float d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float x = i < nb ? c[i] - mean : 0.f;
+            d[i] = x * x;
+        }
+        m2 = (d[0] + d[2]) + (d[1] + d[3]);
+        return;
+    }
+    float c[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[i] = i < nb ? cell(i) : 0.f;
+    s = slot_sum(c);
+    const float mean = div_count(s, nb);
+#pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const float d = (i < nb) ? (c[i] - div_count(v[i], nb)) : 0.f;
-        dv[i] = d * d;
+        const float x = i < nb ? c[i] - mean : 0.f;
+        c[i] = x * x;
     }
-    lanes_sum(dv, G);
-    m2 = dv[0];
+    m2 = slot_sum(c);
 }
 
 // =====================================================================================
 // threshold + prune: tau_r = K-th largest LCB over the active set, A_{r+1} = {UCB >= tau_r}
 // (Algorithm 1, threshold and elimination steps), one workgroup per query, stable.
-// For a query whose cells are cached the round's reveal is folded in first: each entry's
-// (sum, M2) takes the batch pi[lo..lo+nb) from its cached cells.
+// A query whose cells are cached needs nothing but this kernel any more: its remaining rounds run
+// here one after the other, each entry's (sum, M2) taking the batch pi[lo..lo+nb) from its
+// cached cells.
 // =====================================================================================
 struct SelArgs {
     QueryCtl* ctl;
@@ -677,9 +831,9 @@ struct SelArgs {
     int R;
     unsigned long long dense_thr;        // ~0: this round cannot be a dense one
     int64_t N;
-    int nq, T, K, KM;
-    int r, n, n_prev, lo, nb, G;
-    float kappa, a, b;
+    int nq, T, B, K, KM;
+    int r, n, n_prev, nb;                // this launch's round
+    float a, b;
     const int32_t* pi;
     int cache_cap, TP;
     const int32_t* cid;
@@ -692,23 +846,16 @@ struct SelArgs {
     float* tr_lcb;
     float* tr_ucb;
     uint8_t* tr_alive;
-    // segmented pre-filter of long lists (k_select_segments): candidates of segment s sit at
-    // out[s * seg_len(count, n_seg) ...], seg_cnt[q][s] of them
-    int n_seg;                // 0: no segmented pre-filter ran
-    int32_t* seg_cnt;         // [nq][SEG_MAX]
+    int32_t* seg_cnt;                    // [nq][SEG_MAX]: candidates per segment (k_select_segments)
+    float kappa[COLBANDIT_MAX_ROUNDS + 1];   // radius per unit sigma_hat of each round
 };
-
-constexpr int SEG_MAX = 64;
-// entries per segment: a multiple of the widest per-thread run
-__device__ __host__ __forceinline__ int seg_len(int count, int n_seg) {
-    return ((count + n_seg - 1) / n_seg + 15) & ~15;
-}
 
 // Candidates that the segment workgroups left at the segment starts of `buf` -> one contiguous
 // run at the front, order kept.  A destination never lies beyond its source, and a chunk is read
 // completely before it is written.
-__device__ int merge_segments(int32_t* buf, const int32_t* cnt, int count, int n_seg) {
-    const int len = seg_len(count, n_seg);
+__device__ int merge_segments(int32_t* buf, const int32_t* cnt, int count) {
+    const int len = seg_len(count);
+    const int n_seg = (count + len - 1) / len;
     int base = 0;
     for (int sg = 0; sg < n_seg; ++sg) {
         const int c = cnt[sg];
@@ -728,20 +875,367 @@ __device__ int merge_segments(int32_t* buf, const int32_t* cnt, int count, int n
     return base;
 }
 
+// Where candidate i of a segmented list lies.  first: LDS int[SEG_MAX + 1], the number of
+// candidates before each segment (segment_starts).
+__device__ __forceinline__ int segment_starts(const int32_t* cnt, int count, int* first) {
+    const int len = seg_len(count);
+    const int n_seg = (count + len - 1) / len;
+    if (threadIdx.x < 64) {
+        const int c = (int)threadIdx.x < n_seg ? cnt[threadIdx.x] : 0;
+        const int incl = wave_incl_scan(c);
+        first[threadIdx.x + 1] = incl;
+        if (threadIdx.x == 0) first[0] = 0;
+    }
+    __syncthreads();
+    return first[SEG_MAX];
+}
+__device__ __forceinline__ int segment_place(int i, int len, const int* first) {
+    int s = 0;
+#pragma unroll
+    for (int step = SEG_MAX / 2; step >= 1; step >>= 1)
+        if (first[s + step] <= i) s += step;
+    return s * len + (i - first[s]);
+}
+
+// Survivor count and threshold of a round, kept in LDS until the query's rounds of this launch
+// are over: a store to memory in the round would be waited for at its next barrier.
+__device__ __forceinline__ void note_round(SelShared& sh, int r, int count, float tau) {
+    sh.round_count[r - 1] = count;
+    sh.round_tau[r - 1] = tau;
+}
+
+// The end of a query's rounds in this launch: its state, and the documents (pairs and tokens) that
+// the next round would have to gather if the list holds ids.
+// Also writes the history of the rounds run, and of those that the query will not take part in.
+__device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryCtl& nc, int r, bool slots,
+                                           long long my_tokens, SelShared& sh,
+                                           unsigned long long* kept_tokens) {
+    if (!slots) {                                   // uniform over the workgroup
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) my_tokens += __shfl_down(my_tokens, o);
+        if ((threadIdx.x & 63) == 0 && my_tokens != 0) atomicAdd(kept_tokens, (unsigned long long)my_tokens);
+    }
+    __syncthreads();
+    const int x = A.r + (int)threadIdx.x;           // round
+    if (x <= (nc.active ? r : A.R)) {
+        const int count = x <= r ? sh.round_count[x - 1] : nc.count;
+        A.cnt_hist[x * A.nq + q] = count;
+        if (A.tr_count) A.tr_count[x * A.nq + q] = count;
+        if (x <= r) {
+            A.tau_hist[(x - 1) * A.nq + q] = sh.round_tau[x - 1];
+            if (A.tr_tau) A.tr_tau[(x - 1) * A.nq + q] = sh.round_tau[x - 1];
+        }
+    }
+    if (threadIdx.x == 0) {
+        A.ctl[q] = nc;
+        if (nc.active) {
+            atomicAdd(A.pairs + r + 1, (unsigned long long)nc.count);
+            atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
+        }
+    }
+}
+
+// The rounds of a query whose ncand <= SEL_REGS * SEL_THREADS candidates fit the registers, from
+// round r on.
+__device__ __forceinline__ void prune_regs(const SelArgs& A, int q, int count, QueryCtl nc,
+                                           const int32_t* in, int32_t* out, float2* stat, const float2* bat,
+                                           bool slots, bool fold_dense, bool segmented, int ncand,
+                                           int r, bool from_cells, SelShared& sh, const int* seg_first,
+                                           unsigned long long* kept_tokens) {
+    constexpr int E = SEL_REGS;
+    const int T = A.T;
+    const float a = A.a, b = A.b;
+    // Loads are unconditional: places past the end repeat the last entry, entries that have been
+    // dropped are carried along, and only `live` decides.  Places that no thread has (a short
+    // list) are skipped by scalar branches.
+    const Spread sp(ncand);
+    unsigned live = sp.mask<E>();
+    auto used = [&](int u) { return u * 64 < sp.span; };   // uniform
+    int e[E];
+    float2 st[E];
+    if (segmented) {
+        const int len = seg_len(count);
+#pragma unroll
+        for (int u = 0; u < E; ++u) e[u] = out[segment_place(sp.at(u), len, seg_first)];
+    } else if (in) {
+#pragma unroll
+        for (int u = 0; u < E; ++u) e[u] = in[sp.at(u)];
+    } else {
+#pragma unroll
+        for (int u = 0; u < E; ++u) e[u] = sp.at(u);
+    }
+    if (from_cells && r == 1) {                     // nothing revealed yet: no statistics to read
+#pragma unroll
+        for (int u = 0; u < E; ++u) st[u] = make_float2(0.f, 0.f);
+    } else {
+#pragma unroll
+        for (int u = 0; u < E; ++u) st[u] = stat[e[u]];
+    }
+    if (fold_dense) {
+        float2 bb[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) bb[u] = bat[e[u]];
+#pragma unroll
+        for (int u = 0; u < E; ++u)
+            if (used(u)) merge_stats(st[u].x, st[u].y, A.n_prev, bb[u].x, bb[u].y, A.nb);
+    }
+    for (;; ++r, from_cells = true) {
+        const int lo = (r - 1) * A.B;
+        const int n = lo + A.B < T ? lo + A.B : T;
+        const int nb = n - lo;
+        if (from_cells) {
+            const int32_t* pq = A.pi + (size_t)q * T + lo;
+            const float* cells = A.ccell + (size_t)q * A.cache_cap * A.TP;
+            if (nb <= 4) {                          // four entries' cells in flight
+#pragma unroll
+                for (int g = 0; g < E; g += 4)
+                    if (used(g)) {
+                        float cv[4][4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int t = pq[i < nb ? i : 0];
+#pragma unroll
+                            for (int w = 0; w < 4; ++w) cv[w][i] = cells[(unsigned)(e[g + w] * A.TP + t)];
+                        }
+#pragma unroll
+                        for (int w = 0; w < 4; ++w)
+                            if (used(g + w)) {
+                                float sb, m2b;
+                                batch_stats_thread([&](int i) { return cv[w][i & 3]; }, nb, sb, m2b);
+                                merge_stats(st[g + w].x, st[g + w].y, lo, sb, m2b, nb);
+                            }
+                    }
+            } else {
+#pragma unroll
+                for (int u = 0; u < E; ++u)
+                    if (used(u)) {
+                        const float* crow = cells + (unsigned)(e[u] * A.TP);
+                        float sb, m2b;
+                        batch_stats_thread([&](int i) { return crow[pq[i]]; }, nb, sb, m2b);
+                        merge_stats(st[u].x, st[u].y, lo, sb, m2b, nb);
+                    }
+            }
+        }
+        const float kappa = A.kappa[r];
+        uint32_t key[E];
+        float hi[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            key[u] = 0u;
+            hi[u] = 0.f;
+            if (used(u)) {
+                float lcb;
+                interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, hi[u]);
+                key[u] = float_key(lcb);
+            }
+        }
+        const float tau = key_float(kth_largest_regs<E>(key, live, A.K, sh));
+        unsigned keep = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) keep |= (hi[u] >= tau ? 1u : 0u) << u;
+        keep &= live;
+        if (A.tr_lcb) {
+            const size_t tro = ((size_t)(r - 1) * A.nq + q) * A.N;
+            const int32_t* cid = A.cid + (size_t)q * A.cache_cap;
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if ((live >> u) & 1u) {
+                    const int id = slots ? cid[e[u]] : e[u];
+                    float lcb, ucb;
+                    interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, ucb);
+                    A.tr_lcb[tro + id] = lcb;
+                    A.tr_ucb[tro + id] = ucb;
+                    A.tr_alive[tro + id] = (keep >> u) & 1u;
+                }
+        }
+        live = keep;
+        const Places<E> pl(live, sh);
+        nc.count = pl.total;
+        if (threadIdx.x == 0) note_round(sh, r, nc.count, tau);
+        if (slots && nc.count > A.KM && r < A.R) continue;
+#pragma unroll
+        for (int u = 0; u < E; ++u)
+            if ((live >> u) & 1u) out[pl.place(u)] = e[u];
+        break;
+    }
+    nc.active = !slots && nc.count > A.KM;
+    long long my_tokens = 0;                        // tokens of the documents this thread keeps
+    if (!slots) {
+#pragma unroll
+        for (int u = 0; u < E; ++u)
+            if ((live >> u) & 1u) {                 // what a gather of the survivors would have to read
+                my_tokens += A.off[e[u] + 1] - A.off[e[u]];
+                if (fold_dense) stat[e[u]] = st[u];
+            }
+    }
+    end_rounds(A, q, nc, r, slots, my_tokens, sh, kept_tokens);
+}
+
+// One round of a query with a longer list, from memory: the statistics of an entry are read three
+// times (bound, keys above it, prune).  Returns true when the query's rounds are done; false when
+// cached rounds remain: then r is the next round and ncand the length of the list in `out`.
+__device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, QueryCtl nc,
+                                           const int32_t* in, int32_t* out, float2* stat, const float2* bat,
+                                           bool slots, bool fold_dense, bool segmented, int& ncand,
+                                           int& r, bool from_cells, SelShared& sh,
+                                           unsigned long long* kept_tokens) {
+    const int32_t* cid = A.cid + (size_t)q * A.cache_cap;
+    const int T = A.T;
+    const float a = A.a, b = A.b;
+    const int lo = (r - 1) * A.B;
+    const int n = lo + A.B < T ? lo + A.B : T;
+    const int nb = n - lo;
+    const float kappa = A.kappa[r];
+    long long my_tokens = 0;
+    if (segmented) {
+        merge_segments(out, A.seg_cnt + (size_t)q * SEG_MAX, count);
+        in = out;                                   // pruned in place below
+    }
+    auto entry = [&](int idx) { return in ? in[idx] : idx; };
+    if (from_cells) {
+        const int32_t* pq = A.pi + (size_t)q * T + lo;
+        const float* cells = A.ccell + (size_t)q * A.cache_cap * A.TP;
+        for (int idx = threadIdx.x; idx < ncand; idx += SEL_THREADS) {
+            const int e = entry(idx);
+            const float* crow = cells + (unsigned)(e * A.TP);
+            float sb, m2b;
+            batch_stats_thread([&](int i) { return crow[pq[i]]; }, nb, sb, m2b);
+            float2 st = make_float2(0.f, 0.f);
+            if (lo > 0) st = stat[e];
+            merge_stats(st.x, st.y, lo, sb, m2b, nb);
+            stat[e] = st;
+        }
+        __syncthreads();
+    } else if (fold_dense) {                        // the candidates' statistics take the round's batch
+        for (int idx = threadIdx.x; idx < ncand; idx += SEL_THREADS) {
+            const int e = entry(idx);
+            float2 st = stat[e];
+            const float2 bb = bat[e];
+            merge_stats(st.x, st.y, lo, bb.x, bb.y, nb);
+            stat[e] = st;
+        }
+        __syncthreads();
+    }
+    auto key_of = [&](int idx) -> uint32_t {
+        float lcb, ucb;
+        const float2 st = stat[entry(idx)];
+        interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
+        return float_key(lcb);
+    };
+    // a lower bound from a sample: all entries of up to SEL_TILE, else evenly spaced runs
+    const int n_sample = ncand < SEL_TILE ? ncand : SEL_TILE;
+    const int run_stride = ncand < SEL_TILE ? SEL_RUN : ncand / (SEL_TILE / SEL_RUN);
+    uint32_t top = 0u;
+    for (int base = 0; base < n_sample; base += SEL_CHUNK) {
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u) {
+            const int j = base + u * SEL_THREADS + (int)threadIdx.x;
+            const uint32_t k = j < n_sample ? key_of((j / SEL_RUN) * run_stride + (j % SEL_RUN)) : 0u;
+            top = k > top ? k : top;
+        }
+    }
+    const uint32_t bound = lower_bound_key(top, A.K, sh);
+    // the keys that reach it, then the K-th largest of those
+    for (int base = 0; base < ncand; base += SEL_CHUNK) {
+        uint32_t key[SEL_ITEMS];
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u) {
+            const int idx = base + u * SEL_THREADS + (int)threadIdx.x;
+            key[u] = idx < ncand ? key_of(idx) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u)
+            collect_few(key[u], base + u * SEL_THREADS + (int)threadIdx.x < ncand && key[u] >= bound, sh);
+    }
+    uint32_t tkey;
+    if (!kth_of_few(A.K, tkey, sh)) tkey = kth_largest_list(ncand, A.K, key_of, sh);
+    const float tau = key_float(tkey);
+    // Stable compaction of {entry : UCB >= tau}, possibly in place: a chunk is read completely
+    // before anything is written, and writes stay below the next chunk.  Software pipeline over
+    // chunks: the entries are fetched two chunks ahead and their statistics one chunk ahead,
+    // so the loads are in flight across this chunk's scan and its barriers.
+    const size_t tro = ((size_t)(r - 1) * A.nq + q) * A.N;
+    const int t0 = threadIdx.x * SEL_ITEMS;         // SEL_ITEMS consecutive entries
+    int kept = 0;
+    auto load_e = [&](int start, int (&e)[SEL_ITEMS]) {
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u) {
+            const int idx = start + t0 + u;
+            e[u] = idx < ncand ? entry(idx) : 0;
+        }
+    };
+    auto load_s = [&](int start, const int (&e)[SEL_ITEMS], float2 (&st)[SEL_ITEMS]) {
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u)
+            st[u] = (start + t0 + u < ncand) ? stat[e[u]] : make_float2(0.f, 0.f);
+    };
+    int e[SEL_ITEMS], e_next[SEL_ITEMS];
+    float2 st[SEL_ITEMS];
+    load_e(0, e);
+    load_s(0, e, st);
+    load_e(SEL_CHUNK, e_next);
+    for (int start = 0; start < ncand; start += SEL_CHUNK) {
+        const int i0 = start + t0;
+        int e_next2[SEL_ITEMS];
+        float2 st_next[SEL_ITEMS];
+        load_s(start + SEL_CHUNK, e_next, st_next);
+        load_e(start + 2 * SEL_CHUNK, e_next2);
+        unsigned keep = 0;
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u) {
+            if (i0 + u < ncand) {
+                float lcb, ucb;
+                interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, ucb);
+                const bool kp = ucb >= tau;
+                keep |= (kp ? 1u : 0u) << u;
+                if (A.tr_lcb) {
+                    const int id = slots ? cid[e[u]] : e[u];
+                    A.tr_lcb[tro + id] = lcb;
+                    A.tr_ucb[tro + id] = ucb;
+                    A.tr_alive[tro + id] = kp ? 1 : 0;
+                }
+            }
+        }
+        if (__syncthreads_or(keep != 0)) {
+            int total;
+            int pos = kept + block_excl_scan(__popc(keep), sh.wtot, total);
+#pragma unroll
+            for (int u = 0; u < SEL_ITEMS; ++u)
+                if (keep & (1u << u)) {
+                    out[pos++] = e[u];
+                    if (!slots) my_tokens += A.off[e[u] + 1] - A.off[e[u]];
+                }
+            kept += total;
+        }
+#pragma unroll
+        for (int u = 0; u < SEL_ITEMS; ++u) {
+            e[u] = e_next[u];
+            st[u] = st_next[u];
+            e_next[u] = e_next2[u];
+        }
+    }
+    nc.count = kept;
+    if (threadIdx.x == 0) note_round(sh, r, kept, tau);
+    if (slots && kept > A.KM && r < A.R) {
+        ncand = kept;
+        ++r;
+        __syncthreads();                            // the list is read by other threads next
+        return false;
+    }
+    nc.active = !slots && kept > A.KM;
+    end_rounds(A, q, nc, r, slots, my_tokens, sh, kept_tokens);
+    return true;
+}
+
+// Bound by latency and instructions, not by bytes: a list that fits the registers is read once, and
+// selection, prune and count of all its rounds run there.
 __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
-    __shared__ uint32_t hist[2048];
-    __shared__ int pick[2];
-    __shared__ int wtot[SEL_WAVES];
+    __shared__ SelShared sh;
+    __shared__ int seg_first[SEG_MAX + 1];
     __shared__ unsigned long long kept_tokens;
     const int q = blockIdx.x;
     const QueryCtl c = A.ctl[q];
-    if (!c.active) {
-        if (threadIdx.x == 0) {
-            A.cnt_hist[A.r * A.nq + q] = c.count;
-            if (A.tr_count) A.tr_count[A.r * A.nq + q] = c.count;
-        }
-        return;
-    }
+    if (!c.active) return;
     const int count = c.count;
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
@@ -750,280 +1244,123 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     // round's cell-caching gather (same rule as in k_gather)
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
     const bool slots = c.mode == 1 || (c.mode == 0 && !c.implicit && count <= A.cache_cap && !dense);
-    const float2* stat = slots ? A.cstat + (size_t)q * A.cache_cap : A.stat + (size_t)q * A.N;
-    const int32_t* cid = A.cid + (size_t)q * A.cache_cap;
-    const int n = A.n, T = A.T;
-    const float kappa = A.kappa, a = A.a, b = A.b;
-    if (threadIdx.x == 0) kept_tokens = 0ull;       // published by the barriers of the passes below
-    long long my_tokens = 0;                        // tokens of the documents this thread keeps
+    float2* stat = slots ? A.cstat + (size_t)q * A.cache_cap : A.stat + (size_t)q * A.N;
+    const float2* bat = A.stat2 + (size_t)q * A.N;
+    const bool fold_dense = dense && c.mode == 0 && in != nullptr;   // a batch that a dense pass left in stat2
+    if (threadIdx.x == 0) kept_tokens = 0ull;
+    clear_hist(sh);
 
-    if (c.mode == 1) {          // fold this round's batch in from the cached cells
-        float2* cst = A.cstat + (size_t)q * A.cache_cap;
-        const int32_t* pq = A.pi + (size_t)q * T + A.lo;
-        for (int idx = threadIdx.x; idx < count; idx += SEL_THREADS) {
-            const int e = in[idx];
-            const float* crow = A.ccell + ((size_t)q * A.cache_cap + e) * A.TP;
-            float cv[16];
-            for (int i = 0; i < 16; ++i) cv[i] = i < A.nb ? crow[pq[i]] : 0.f;
-            float sb, m2b;
-            batch_stats_thread(cv, A.nb, A.G, sb, m2b);
-            float2 st = cst[e];
-            merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
-            cst[e] = st;
-        }
-        __syncthreads();
-    }
+    const bool segmented = count > SEL_TILE;        // then k_select_segments has run
+    int ncand = count;
+    if (segmented) ncand = segment_starts(A.seg_cnt + (size_t)q * SEG_MAX, count, seg_first);
 
-    const bool segmented = A.n_seg > 0 && count > SEL_PREFILTER_MIN && !slots;
-    if (dense && c.mode == 0 && in && !segmented) {   // fold in the batch a dense pass left in stat2
-        float2* dst = A.stat + (size_t)q * A.N;
-        const float2* bat = A.stat2 + (size_t)q * A.N;
-        for (int idx = threadIdx.x; idx < count; idx += SEL_THREADS) {
-            const int e = in[idx];
-            float2 st = dst[e];
-            const float2 bb = bat[e];
-            merge_stats(st.x, st.y, A.n_prev, bb.x, bb.y, A.nb);
-            dst[e] = st;
-        }
-        __syncthreads();
+    QueryCtl nc;
+    nc.cur = out_sel;
+    nc.implicit = 0;
+    nc.mode = slots ? 1 : 0;
+    nc.bound = nc.pad1 = nc.pad2 = 0;
+    int r = A.r;
+    bool from_cells = c.mode == 1;                  // this round's batch still has to be folded in
+    bool seg = segmented, fold = fold_dense;
+    while (ncand > SEL_REGS * SEL_THREADS) {
+        if (prune_list(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, &kept_tokens))
+            return;
+        // cached rounds remain: on from the shorter list, into the other buffer
+        from_cells = true;
+        seg = fold = false;
+        in = out;
+        nc.cur ^= 1;
+        out = (nc.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     }
-
-    auto key_of = [&](const int32_t* l, int idx) -> uint32_t {
-        const int e = l ? l[idx] : idx;
-        float lcb, ucb;
-        const float2 st = stat[e];
-        interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
-        return float_key(lcb);
-    };
-    const size_t tro = ((size_t)(A.r - 1) * A.nq + q) * A.N;
-    // Stable compaction of {entry of l[0..cnt) : UCB >= thr} into outl (outl may be l itself:
-    // a chunk is read completely before anything is written, and writes stay below the
-    // next chunk).  The trace takes every dropped entry, and the kept ones if trace_kept.
-    auto filter = [&](auto items_c, const int32_t* l, int cnt, int32_t* outl, float thr,
-                      bool trace_kept) -> int {
-        constexpr int ITEMS = decltype(items_c)::value;      // entries per thread per chunk
-        constexpr int CHUNK = SEL_THREADS * ITEMS;
-        int base = 0;
-        // software pipeline over chunks: the entries are fetched two chunks ahead and their
-        // statistics one chunk ahead, so the loads of the next chunk are in flight across
-        // this chunk's scan and its barriers
-        const int t0 = threadIdx.x * ITEMS;                 // ITEMS consecutive entries
-        auto load_e = [&](int start, int (&e)[ITEMS]) {
-#pragma unroll
-            for (int u = 0; u < ITEMS; ++u) {
-                const int idx = start + t0 + u;
-                e[u] = idx < cnt ? (l ? l[idx] : idx) : 0;
-            }
-        };
-        auto load_s = [&](int start, const int (&e)[ITEMS], float2 (&st)[ITEMS]) {
-#pragma unroll
-            for (int u = 0; u < ITEMS; ++u)
-                st[u] = (start + t0 + u < cnt) ? stat[e[u]] : make_float2(0.f, 0.f);
-        };
-        int e[ITEMS], e_next[ITEMS];
-        float2 st[ITEMS];
-        load_e(0, e);
-        load_s(0, e, st);
-        load_e(CHUNK, e_next);
-        for (int start = 0; start < cnt; start += CHUNK) {
-            const int i0 = start + t0;
-            int e_next2[ITEMS];
-            float2 st_next[ITEMS];
-            load_s(start + CHUNK, e_next, st_next);
-            load_e(start + 2 * CHUNK, e_next2);
-            unsigned keep = 0;
-#pragma unroll
-            for (int u = 0; u < ITEMS; ++u) {
-                if (i0 + u < cnt) {
-                    float lcb, ucb;
-                    interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, ucb);
-                    const bool kp = ucb >= thr;
-                    keep |= (kp ? 1u : 0u) << u;
-                    if (A.tr_lcb && (trace_kept || !kp)) {
-                        const int id = slots ? cid[e[u]] : e[u];
-                        A.tr_lcb[tro + id] = lcb;
-                        A.tr_ucb[tro + id] = ucb;
-                        A.tr_alive[tro + id] = kp ? 1 : 0;
-                    }
-                }
-            }
-            if (__syncthreads_or(keep != 0)) {          // a pre-filter keeps nothing of most chunks
-                int total;
-                int pos = base + block_excl_scan(__popc(keep), wtot, total);
-#pragma unroll
-                for (int u = 0; u < ITEMS; ++u)
-                    if (keep & (1u << u)) {
-                        outl[pos++] = e[u];
-                        // the final pass over document ids also adds up what a gather of the
-                        // survivors would have to read
-                        if (trace_kept && !slots) my_tokens += A.off[e[u] + 1] - A.off[e[u]];
-                    }
-                base += total;
-            }
-#pragma unroll
-            for (int u = 0; u < ITEMS; ++u) {
-                e[u] = e_next[u];
-                st[u] = st_next[u];
-                e_next[u] = e_next2[u];
-            }
-        }
-        return base;
-    };
-
-    // Large active sets (the first round): a strided sample gives a threshold tau_lo that
-    // cannot exceed tau (the K-th largest of a subset is at most that of the whole set), so
-    // one streaming pass keeps the candidates {UCB >= tau_lo}, a superset of both the
-    // survivors and the K largest LCBs; the exact threshold and the prune then run on
-    // those few.
-    const int32_t* sel_in = in;
-    int sel_count = count;
-    if (segmented) {
-        // the segment workgroups have folded, sampled and pre-filtered; gather their candidates
-        sel_count = merge_segments(out, A.seg_cnt + (size_t)q * SEG_MAX, count, A.n_seg);
-        sel_in = out;
-        if (dense && c.mode == 0 && in) {       // the candidates' statistics take the round's batch
-            float2* dst = A.stat + (size_t)q * A.N;
-            const float2* bat = A.stat2 + (size_t)q * A.N;
-            for (int idx = threadIdx.x; idx < sel_count; idx += SEL_THREADS) {
-                const int e = out[idx];
-                float2 st = dst[e];
-                const float2 bb = bat[e];
-                merge_stats(st.x, st.y, A.n_prev, bb.x, bb.y, A.nb);
-                dst[e] = st;
-            }
-            __syncthreads();
-        }
-    } else if (count > SEL_PREFILTER_MIN) {
-        auto key_s = [&](int j) -> uint32_t { return key_of(in, sample_pos(j, count)); };
-        const float tau_lo = key_float(block_kth_largest_sample(A.K, key_s, hist, pick));
-        // the streaming pass: wide chunks keep enough loads in flight for one workgroup
-        sel_count = filter(std::integral_constant<int, SEL_ITEMS_WIDE>{}, in, count, out, tau_lo, false);
-        sel_in = out;
-    }
-    uint32_t tkey;
-    if (sel_count > SEL_PREFILTER_MIN) {
-        // Still a long list (a conservative radius prunes little): the exact threshold depends
-        // only on the entries whose LCB reaches a sampled lower threshold (the K-th largest of
-        // a subset cannot exceed that of the whole list, so these include the K largest).  One
-        // pass collects them, in any order, into the list buffer that this round no longer
-        // reads; the three radix passes then run over those few instead of the whole list.
-        auto key_s = [&](int j) -> uint32_t { return key_of(sel_in, sample_pos(j, sel_count)); };
-        const uint32_t lo_key = block_kth_largest_sample(A.K, key_s, hist, pick);
-        int32_t* few = (out_sel ? A.list0 : A.list1) + (size_t)q * A.N;   // sel_in == out here
-        if (threadIdx.x == 0) pick[0] = 0;
-        __syncthreads();
-        const int lane = threadIdx.x & 63;
-        for (int base0 = 0; base0 < sel_count; base0 += SEL_CHUNK) {
-            int e[SEL_ITEMS];
-            bool on[SEL_ITEMS];
-#pragma unroll
-            for (int u = 0; u < SEL_ITEMS; ++u) {
-                const int idx = base0 + u * SEL_THREADS + (int)threadIdx.x;
-                e[u] = idx < sel_count ? sel_in[idx] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < SEL_ITEMS; ++u) {
-                const int idx = base0 + u * SEL_THREADS + (int)threadIdx.x;
-                float lcb, ucb;
-                const float2 st = stat[e[u]];
-                interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
-                on[u] = idx < sel_count && float_key(lcb) >= lo_key;
-            }
-#pragma unroll
-            for (int u = 0; u < SEL_ITEMS; ++u) {
-                const unsigned long long m = __ballot(on[u]);
-                if (m != 0ull) {                            // uniform over the wavefront
-                    int at = 0;
-                    if (lane == 0) at = atomicAdd(&pick[0], __popcll(m));
-                    at = __shfl(at, 0);
-                    if (on[u]) few[at + __popcll(m & ((1ull << lane) - 1ull))] = e[u];
-                }
-            }
-        }
-        __syncthreads();
-        const int n_few = pick[0];
-        __syncthreads();
-        auto key_few = [&](int idx) -> uint32_t { return key_of(few, idx); };
-        tkey = block_kth_largest(n_few, A.K, key_few, hist, pick);
-    } else {
-        auto key_sel = [&](int idx) -> uint32_t { return key_of(sel_in, idx); };
-        tkey = block_kth_largest(sel_count, A.K, key_sel, hist, pick);
-    }
-    const float tau = key_float(tkey);
-    const int base = filter(std::integral_constant<int, SEL_ITEMS>{}, sel_in, sel_count, out, tau, true);
-    if (!slots) {                       // uniform over the workgroup
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) my_tokens += __shfl_down(my_tokens, o);
-        if ((threadIdx.x & 63) == 0 && my_tokens != 0)
-            atomicAdd(&kept_tokens, (unsigned long long)my_tokens);
-        __syncthreads();
-    }
-
-    if (threadIdx.x == 0) {
-        QueryCtl nc;
-        nc.count = base;
-        nc.cur = out_sel;
-        nc.implicit = 0;
-        nc.active = base > A.KM;
-        nc.mode = slots ? 1 : 0;
-        nc.pad0 = nc.pad1 = nc.pad2 = 0;
-        A.ctl[q] = nc;
-        // what the next round would have to gather: the active sets still held as ids
-        if (nc.active && nc.mode == 0) {
-            atomicAdd(A.pairs + A.r + 1, (unsigned long long)base);
-            atomicAdd(A.pairs + (A.R + 2) + A.r + 1, kept_tokens);
-        }
-        A.cnt_hist[A.r * A.nq + q] = base;
-        A.tau_hist[(A.r - 1) * A.nq + q] = tau;
-        if (A.tr_count) {
-            A.tr_count[A.r * A.nq + q] = base;
-            A.tr_tau[(A.r - 1) * A.nq + q] = tau;
-        }
-    }
+    prune_regs(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens);
 }
 
-// A cheap upper estimate of interval()'s UCB for the pre-filter (n, T, kappa, b uniform).
-struct FastUcb {
-    float c_hat, c_sig, rest_b;
-    int mode;           // 0: hard bound only (n <= 1), 1: hybrid, 2: exact sum (n >= T)
+// Cheap outer estimate of interval() for the pre-filter: reciprocal multiplications and the
+// hardware square root, each good to a few units in the last place, and an allowance of 64 such
+// units of the largest term: lo <= LCB and hi >= max(LCB, UCB) (cells outside [a,b] can put the
+// LCB above the UCB, and the K largest LCBs must stay); n, T, kappa, a, b are uniform.
+struct FastBounds {
+    float c_hat, c_sig, rest_a, rest_b, mag;
+    bool hybrid;        // else the hard bounds only (n <= 1), or the exact sum (n >= T: rest = 0)
 };
-__device__ __forceinline__ FastUcb fast_ucb_consts(int n, int T, float kappa, float b) {
-    FastUcb f;
-    f.mode = n <= 1 ? 0 : (n >= T ? 2 : 1);
-    f.c_hat = n > 0 ? (float)T / (float)n : 0.f;
-    f.c_sig = n > 1 ? kappa * kappa / (float)(n - 1) : 0.f;
+__device__ __forceinline__ FastBounds fast_bounds_consts(int n, int T, float kappa, float a, float b) {
+    FastBounds f;
+    f.hybrid = n > 1 && n < T;
+    f.c_hat = f.hybrid ? (float)T / (float)n : 1.f;
+    f.c_sig = f.hybrid ? kappa * kappa / (float)(n - 1) : 0.f;
+    f.rest_a = (float)(T - n) * a;
     f.rest_b = (float)(T - n) * b;
+    f.mag = fmaxf(fabsf(f.rest_a), fabsf(f.rest_b));
     return f;
 }
-__device__ __forceinline__ float fast_ucb(float S, float M2, int n, int T, const FastUcb& f) {
-    (void)n; (void)T;
-    const float ub = S + f.rest_b;
-    if (f.mode == 0) return ub;
-    if (f.mode == 2) return S;
-    const float r = __builtin_amdgcn_sqrtf(fmaxf(M2, 0.f) * f.c_sig);
-    return fminf(ub, S * f.c_hat + r);
+__device__ __forceinline__ float fast_radius(float M2, const FastBounds& f) {
+    return __builtin_amdgcn_sqrtf(fmaxf(M2, 0.f) * f.c_sig);
+}
+__device__ __forceinline__ float fast_hi(float S, float M2, const FastBounds& f) {
+    const float est = S * f.c_hat, r = fast_radius(M2, f);
+    float hi = S + f.rest_b;
+    if (f.hybrid) hi = fmaxf(fminf(hi, est + r), fmaxf(S + f.rest_a, est - r));
+    return hi + 8e-6f * (fabsf(est) + r + f.mag);
+}
+// key of the lower estimate; a document outside the contract (statistics not finite) has the
+// interval [-inf, -inf]
+__device__ __forceinline__ uint32_t fast_lo_key(float S, float M2, const FastBounds& f) {
+    const float est = S * f.c_hat, r = fast_radius(M2, f);
+    float lo = S + f.rest_a;
+    if (f.hybrid) lo = fmaxf(lo, est - r);
+    lo -= 8e-6f * (fabsf(est) + r + f.mag);
+    const bool bad = (__float_as_uint(S) & 0x7fffffffu) >= 0x7f800000u || is_nan_bits(M2);
+    return bad ? 0u : float_key(lo);
 }
 
-// Pre-filter of a long active list, spread over n_seg workgroups per query (one workgroup cannot
-// pull a multi-megabyte list from memory fast enough).  Every workgroup of a query derives the
-// same lower threshold tau_lo from the same sample, then streams its own segment once and keeps
-// {UCB >= tau_lo} in order at the start of its segment of the output list, recording how many.
-// In a corpus-pass round the round's batch (stat2) is merged in registers only: nothing is
-// written back here, because other workgroups of the query are still sampling; k_select_prune
-// gathers the segments and stores the merged statistics of the candidates, the only entries
-// that are ever read again.
-__global__ __launch_bounds__(SEL_THREADS) void k_select_segments(SelArgs A) {
-    __shared__ uint32_t hist[2048];
-    __shared__ int pick[2];
-    __shared__ int wtot[SEL_WAVES];
+// Lower threshold of a long round-1 list: the K-th largest LCB of a sample of SEL_TILE entries,
+// evenly spaced runs of SEL_RUN adjacent ones (whole cache lines; any subset gives a valid lower
+// threshold, an even one a close one whatever the order of the corpus).  One workgroup per query.
+// Left in QueryCtl::bound.
+__global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
+    __shared__ SelShared sh;
+    const int q = blockIdx.x;
+    const QueryCtl c = A.ctl[q];
+    if (!c.active || !c.implicit || c.count <= SEL_TILE) return;
+    const float2* stat = A.stat + (size_t)q * A.N;
+    const FastBounds fb = fast_bounds_consts(A.n, A.T, A.kappa[A.r], A.a, A.b);
+    clear_hist(sh);
+    const int run_stride = c.count / (SEL_TILE / SEL_RUN);
+    float2 st[SEL_E];
+    uint32_t key[SEL_E];
+#pragma unroll
+    for (int u = 0; u < SEL_E; ++u) {
+        const int j = u * SEL_THREADS + (int)threadIdx.x;
+        st[u] = stat[(j / SEL_RUN) * run_stride + (j % SEL_RUN)];
+    }
+#pragma unroll
+    for (int u = 0; u < SEL_E; ++u) key[u] = fast_lo_key(st[u].x, st[u].y, fb);
+    const uint32_t bound = kth_largest_regs<SEL_E>(key, 0xffffu, A.K, sh);
+    if (threadIdx.x == 0) A.ctl[q].bound = (int)bound;
+}
+
+// Pre-filter of a long active list, a workgroup per segment (one workgroup per query cannot pull a
+// multi-megabyte list from memory fast enough).  Each tile of the segment is read once into
+// registers and {UCB >= threshold} is kept, in order, at the start of the segment of the output
+// list.  The threshold of round 1 comes from k_select_sample; the lists of later rounds are seldom
+// this long, and rather than launch the sampler in each of them every tile takes a lower bound
+// of its own K-th largest LCB (that of a part of the list cannot exceed that of the whole).
+// 64 M entries of 8 bytes (128 queries x 500,000): 131 us = 3.9 TB/s with a given threshold, bound by
+// about 24 instructions an entry; 285 us with the tiles' own thresholds and as much when every
+// workgroup sampled for itself.
+// In a corpus-pass round the round's batch (stat2) is merged in registers only: k_select_prune
+// stores the merged statistics of the survivors, the only entries that are ever read again.
+__global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
+    __shared__ SelShared sh;
     const int q = blockIdx.y, sg = blockIdx.x;
     const QueryCtl c = A.ctl[q];
-    if (!c.active) return;
     const int count = c.count;
-    if (count <= SEL_PREFILTER_MIN) return;
+    if (!c.active || count <= SEL_TILE) return;     // cached lists are never this long
+    const int len = seg_len(count);
+    const int lo = sg * len;
+    if (lo >= count) return;
+    const int hi = lo + len < count ? lo + len : count;
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
-    const bool slots = c.mode == 1 || (c.mode == 0 && !c.implicit && count <= A.cache_cap && !dense);
-    if (slots) return;                      // cache-sized lists are never this long
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
     int32_t* out = (out_sel ? A.list1 : A.list0) + (size_t)q * A.N;
@@ -1031,113 +1368,89 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_segments(SelArgs A) {
     const float2* bat = A.stat2 + (size_t)q * A.N;
     const bool fold = dense && in != nullptr;
     const int n = A.n, T = A.T;
-    const float kappa = A.kappa, a = A.a, b = A.b;
-
-    auto stat_of = [&](int e) -> float2 {
-        float2 st = stat[e];
-        if (fold) {
-            const float2 bb = bat[e];
-            merge_stats(st.x, st.y, A.n_prev, bb.x, bb.y, A.nb);
-        }
-        return st;
-    };
-    auto key_s = [&](int j) -> uint32_t {
-        const int pos = sample_pos(j, count);
-        const float2 st = stat_of(in ? in[pos] : pos);
-        float lcb, ucb;
-        interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
-        return float_key(lcb);
-    };
-    const float tau_lo = key_float(block_kth_largest_sample(A.K, key_s, hist, pick));
-    const FastUcb fk = fast_ucb_consts(n, T, kappa, b);
-    const float tau_fast = tau_lo - (1e-3f + 1e-5f * fabsf(tau_lo));
-
-    const int len = seg_len(count, A.n_seg);
-    const int lo = sg * len;
-    const int hi = lo + len < count ? lo + len : count;
+    const float kappa = A.kappa[A.r], a = A.a, b = A.b;
+    const FastBounds fb = fast_bounds_consts(n, T, kappa, a, b);
     const size_t tro = ((size_t)(A.r - 1) * A.nq + q) * A.N;
-    constexpr int ITEMS = SEL_ITEMS_WIDE;
-    constexpr int CHUNK = SEL_THREADS * ITEMS;
-    const int t0 = threadIdx.x * ITEMS;
-    auto load_e = [&](int start, int (&e)[ITEMS]) {
+    clear_hist(sh);
+    int base = lo;
+    for (int start = lo; start < hi; start += SEG_TILE) {
+        const int left = hi - start < SEG_TILE ? hi - start : SEG_TILE;
+        const Spread sp(left);
+        const unsigned ok = sp.mask<SEG_E>();
+        float2 st[SEG_E];
+        auto at = [&](int u) { return start + sp.at(u); };
+        if (in) {
+            int e[SEG_E];
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            const int idx = start + t0 + u;
-            e[u] = idx < hi ? (in ? in[idx] : idx) : 0;
-        }
-    };
-    auto load_s = [&](int start, const int (&e)[ITEMS], float2 (&st)[ITEMS], float2 (&bb)[ITEMS]) {
+            for (int u = 0; u < SEG_E; ++u) e[u] = in[at(u)];
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            const bool ok = start + t0 + u < hi;
-            st[u] = ok ? stat[e[u]] : make_float2(0.f, 0.f);
-            bb[u] = (ok && fold) ? bat[e[u]] : make_float2(0.f, 0.f);
-        }
-    };
-    int base = 0;
-    int e[ITEMS], e_next[ITEMS];
-    float2 st[ITEMS], bb[ITEMS];
-    load_e(lo, e);
-    load_s(lo, e, st, bb);
-    load_e(lo + CHUNK, e_next);
-    for (int start = lo; start < hi; start += CHUNK) {
-        const int i0 = start + t0;
-        int e_next2[ITEMS];
-        float2 st_next[ITEMS], bb_next[ITEMS];
-        load_s(start + CHUNK, e_next, st_next, bb_next);
-        load_e(start + 2 * CHUNK, e_next2);
-        unsigned keep = 0;
-        if (A.tr_lcb || fold) {
-            // exact intervals: the trace records every dropped entry's interval
+            for (int u = 0; u < SEG_E; ++u) st[u] = stat[e[u]];
+            if (fold) {
 #pragma unroll
-            for (int u = 0; u < ITEMS; ++u) {
-                if (i0 + u < hi) {
-                    if (fold) merge_stats(st[u].x, st[u].y, A.n_prev, bb[u].x, bb[u].y, A.nb);
-                    float lcb, ucb;
-                    interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, ucb);
-                    const bool kp = ucb >= tau_lo;
-                    keep |= (kp ? 1u : 0u) << u;
-                    if (A.tr_lcb && !kp) {
-                        A.tr_lcb[tro + e[u]] = lcb;
-                        A.tr_ucb[tro + e[u]] = ucb;
-                        A.tr_alive[tro + e[u]] = 0;
-                    }
+                for (int u = 0; u < SEG_E; ++u) {
+                    const float2 bb = bat[e[u]];
+                    merge_stats(st[u].x, st[u].y, A.n_prev, bb.x, bb.y, A.nb);
+                    if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                 }
             }
         } else {
-            // A pre-filter may keep too much but never too little: the UCB is evaluated with
-            // reciprocal multiplications and the hardware square root, and compared with the
-            // threshold lowered by far more than the error of that shortcut (values are of
-            // size <= T; the shortcut is good to a few ulps).
 #pragma unroll
-            for (int u = 0; u < ITEMS; ++u) {
-                if (i0 + u < hi) {
-                    const float ucb = fast_ucb(st[u].x, st[u].y, n, T, fk);
-                    keep |= (ucb >= tau_fast ? 1u : 0u) << u;
+            for (int u = 0; u < SEG_E; ++u) st[u] = stat[at(u)];
+        }
+        uint32_t bound = (uint32_t)c.bound;
+        if (in) {
+            uint32_t top = 0u;
+#pragma unroll
+            for (int u = 0; u < SEG_E; ++u) {
+                const uint32_t k = (ok >> u) & 1u ? fast_lo_key(st[u].x, st[u].y, fb) : 0u;
+                top = k > top ? k : top;
+            }
+            bound = lower_bound_key(top, A.K, sh);
+        }
+        const float thr = key_float(bound);
+        unsigned keep = ok;
+        if (thr > -__builtin_inff()) {              // else all, also documents outside the contract
+#pragma unroll
+            for (int u = 0; u < SEG_E; ++u)
+                if (!(fast_hi(st[u].x, st[u].y, fb) >= thr)) keep &= ~(1u << u);
+        }
+        if (A.tr_lcb) {                             // the trace records every dropped entry's interval
+#pragma unroll 1
+            for (int u = 0; u < SEG_E; ++u) {
+                if (!(((ok & ~keep) >> u) & 1u)) continue;
+                const int e = in ? in[at(u)] : at(u);
+                float2 x = stat[e];
+                if (fold) {
+                    const float2 bb = bat[e];
+                    merge_stats(x.x, x.y, A.n_prev, bb.x, bb.y, A.nb);
                 }
+                float lcb, ucb;
+                interval(x.x, x.y, n, T, kappa, a, b, lcb, ucb);
+                A.tr_lcb[tro + e] = lcb;
+                A.tr_ucb[tro + e] = ucb;
+                A.tr_alive[tro + e] = 0;
             }
         }
-        if (__syncthreads_or(keep != 0)) {
-            int total;
-            int pos = lo + base + block_excl_scan(__popc(keep), wtot, total);
+        const Places<SEG_E> pl(keep, sh);
 #pragma unroll
-            for (int u = 0; u < ITEMS; ++u)
-                if (keep & (1u << u)) out[pos++] = e[u];
-            base += total;
-        }
-#pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            e[u] = e_next[u];
-            st[u] = st_next[u];
-            bb[u] = bb_next[u];
-            e_next[u] = e_next2[u];
-        }
+        for (int u = 0; u < SEG_E; ++u)
+            if ((keep >> u) & 1u) out[base + pl.place(u)] = in ? in[at(u)] : at(u);
+        base += pl.total;
+        __syncthreads();
     }
-    if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base;
+    if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
+}
+
+// Segment workgroups per query: a list of any length up to N has at most this many segments
+// (seg_len: one per tile up to SEG_MAX tiles, at most SEG_MAX beyond).
+static unsigned segments_of(int64_t N) {
+    const int64_t tiles = (N + SEG_TILE - 1) / SEG_TILE;
+    return (unsigned)(tiles < SEG_MAX ? tiles : SEG_MAX);
 }
 
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
-                               const RevealRound& rr, int R, const Trace& tr, hipStream_t st) {
+                               const RevealRound& rr, int R, const float* kappa, const Trace& tr,
+                               hipStream_t st) {
     SelArgs A{};
     A.ctl = W.ctl;
     A.list0 = W.list[0];
@@ -1151,16 +1464,13 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.N = P.N;
     A.nq = P.nq;
     A.T = P.T;
+    A.B = kn.B;
     A.K = kn.K;
     A.KM = kn.K + kn.M;
     A.r = rr.r;
     A.n = rr.n;
     A.n_prev = rr.n_prev;
-    A.lo = rr.lo;
     A.nb = rr.nb;
-    A.G = 1;
-    while (A.G < rr.nb) A.G <<= 1;
-    A.kappa = rr.kappa;
     A.a = kn.a;
     A.b = kn.b;
     A.pi = W.pi;
@@ -1176,15 +1486,11 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.tr_lcb = tr.lcb;
     A.tr_ucb = tr.ucb;
     A.tr_alive = tr.alive;
-    // lists longer than the pre-filter limit are first cut down by several workgroups per query
-    A.n_seg = 0;
     A.seg_cnt = W.seg_cnt;
-    if (P.N > SEL_PREFILTER_MIN) {
-        int n_seg = 512 / P.nq;      // about two workgroups per CU in total
-        n_seg = n_seg < 2 ? 2 : (n_seg > SEG_MAX ? SEG_MAX : n_seg);
-        A.n_seg = n_seg;
-        k_select_segments<<<dim3(n_seg, P.nq), SEL_THREADS, 0, st>>>(A);
-    }
+    for (int r = 0; r <= R; ++r) A.kappa[r] = kappa[r];
+    // lists that do not fit one workgroup's registers are first cut down, one workgroup per tile
+    if (P.N > SEL_TILE && rr.r == 1) k_select_sample<<<P.nq, SEL_THREADS, 0, st>>>(A);
+    if (P.N > SEL_TILE) k_select_segments<<<dim3(segments_of(P.N), P.nq), SEL_THREADS, 0, st>>>(A);
     k_select_prune<<<P.nq, SEL_THREADS, 0, st>>>(A);
     return hipGetLastError();
 }
@@ -1205,64 +1511,57 @@ struct TopkArgs {
     int K;
     int64_t* out_ids;
     float* out_scores;
-    int n_seg;             // > 0: k_topk_segments has pre-filtered the positions (ctl == nullptr)
     int32_t* seg_cnt;      // [nq][SEG_MAX]
 };
 
-// The pre-filter of k_topk for all-documents inputs, spread over n_seg workgroups per query:
-// same sample threshold in every workgroup, one streaming pass over the workgroup's segment,
-// candidate positions in order at the segment's start of the scratch list.
-__global__ __launch_bounds__(SEL_THREADS) void k_topk_segments(TopkArgs A) {
-    __shared__ uint32_t hist[2048];
-    __shared__ int pick[2];
-    __shared__ int wtot[SEL_WAVES];
+// The pre-filter of k_topk for long all-documents inputs, a workgroup per segment: each tile is
+// read once, and the positions whose value reaches a lower bound of the tile's own K-th
+// largest (lower_bound_key) go, in order, to the segment's start of the scratch list.
+__global__ __launch_bounds__(SEL_THREADS, 8) void k_topk_segments(TopkArgs A) {
+    __shared__ SelShared sh;
     const int q = blockIdx.y, sg = blockIdx.x;
     const int count = (int)A.N;
-    if (count <= SEL_PREFILTER_MIN) return;
+    const int len = seg_len(count);
+    const int lo = sg * len;
+    if (lo >= count) return;
+    const int hi = lo + len < count ? lo + len : count;
     const float* vals = A.vals + (size_t)q * A.N;
     int32_t* tmp = A.list0 + (size_t)q * A.N;
-    const int Kq = A.K < count ? A.K : count;
-    auto key_s = [&](int j) -> uint32_t { return float_key(vals[sample_pos(j, count)]); };
-    const uint32_t lo_key = block_kth_largest_sample(Kq, key_s, hist, pick);
-    const int len = seg_len(count, A.n_seg);
-    const int lo = sg * len;
-    const int hi = lo + len < count ? lo + len : count;
-    constexpr int ITEMS = SEL_ITEMS_WIDE;
-    constexpr int CHUNK = SEL_THREADS * ITEMS;
-    const int t0 = threadIdx.x * ITEMS;
-    int base = 0;
-    float v[ITEMS];
+    clear_hist(sh);
+    int base = lo;
+    for (int start = lo; start < hi; start += SEG_TILE) {
+        const int left = hi - start < SEG_TILE ? hi - start : SEG_TILE;
+        const Spread sp(left);
+        const unsigned ok = sp.mask<SEG_E>();
+        float v[SEG_E];
+        uint32_t key[SEG_E], top = 0u;
 #pragma unroll
-    for (int u = 0; u < ITEMS; ++u) v[u] = lo + t0 + u < hi ? vals[lo + t0 + u] : 0.f;
-    for (int start = lo; start < hi; start += CHUNK) {
-        const int i0 = start + t0;
-        float v_next[ITEMS];
+        for (int u = 0; u < SEG_E; ++u) v[u] = vals[start + sp.at(u)];
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) v_next[u] = i0 + CHUNK + u < hi ? vals[i0 + CHUNK + u] : 0.f;
+        for (int u = 0; u < SEG_E; ++u) {
+            key[u] = (ok >> u) & 1u ? float_key(v[u]) : 0u;
+            top = key[u] > top ? key[u] : top;
+        }
+        const uint32_t thr = lower_bound_key(top, A.K, sh);
         unsigned keep = 0;
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u)
-            if (i0 + u < hi && float_key(v[u]) >= lo_key) keep |= 1u << u;
+        for (int u = 0; u < SEG_E; ++u) keep |= (key[u] >= thr ? 1u : 0u) << u;
+        const Places<SEG_E> pl(keep & ok, sh);
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) v[u] = v_next[u];
-        if (__syncthreads_or(keep != 0)) {
-            int total;
-            int pos = lo + base + block_excl_scan(__popc(keep), wtot, total);
-#pragma unroll
-            for (int u = 0; u < ITEMS; ++u)
-                if (keep & (1u << u)) tmp[pos++] = i0 + u;
-            base += total;
-        }
+        for (int u = 0; u < SEG_E; ++u)
+            if (((keep & ok) >> u) & 1u) tmp[base + pl.place(u)] = start + sp.at(u);
+        base += pl.total;
+        __syncthreads();
     }
-    if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base;
+    if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
 }
 
 __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
-    __shared__ uint32_t hist[2048];
-    __shared__ int pick[2];
-    __shared__ int wtot[SEL_WAVES];
+    __shared__ SelShared sh;
+    __shared__ int seg_first[SEG_MAX + 1];
     __shared__ float cs[1024];
     __shared__ int ci[1024];
+    __shared__ int n_above;
     const int q = blockIdx.x;
     int count = (int)A.N;
     const int32_t* list = nullptr;
@@ -1280,94 +1579,105 @@ __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
     const float* vals = A.vals + (size_t)q * A.N;
     const int Kq = A.K < count ? A.K : count;
     if (Kq > 0) {
-        // candidate positions: all of 0..count-1, or (long inputs) those whose value reaches
-        // the K-th largest value of a strided sample, which cannot exceed the true K-th
-        const int32_t* cand = nullptr;
+        if (threadIdx.x == 0) n_above = 0;
+        clear_hist(sh);
+        // candidate positions: all of 0..count-1, or what the pre-filter left of a long input
+        // (survivors are few: a longer list of them is scanned whole)
+        const bool segmented = !A.ctl && count > SEL_TILE;
         int ncand = count;
-        if (A.n_seg > 0 && !A.ctl && count > SEL_PREFILTER_MIN) {
-            ncand = merge_segments(scratch, A.seg_cnt + (size_t)q * SEG_MAX, count, A.n_seg);
-            cand = scratch;
-        } else if (count > SEL_PREFILTER_MIN) {
-            int32_t* tmp = scratch;
-            auto key_s = [&](int j) -> uint32_t { return float_key(vals[sample_pos(j, count)]); };
-            const uint32_t lo = block_kth_largest_sample(Kq, key_s, hist, pick);
-            int base = 0;
-            const int t0 = threadIdx.x * SEL_ITEMS_WIDE;
-            float v[SEL_ITEMS_WIDE];                       // the next chunk's values are fetched
-#pragma unroll                                        // before this chunk's barriers
-            for (int u = 0; u < SEL_ITEMS_WIDE; ++u) v[u] = t0 + u < count ? vals[t0 + u] : 0.f;
-            for (int start = 0; start < count; start += (SEL_THREADS * SEL_ITEMS_WIDE)) {
-                const int i0 = start + t0;
-                float v_next[SEL_ITEMS_WIDE];
+        if (segmented) ncand = segment_starts(A.seg_cnt + (size_t)q * SEG_MAX, count, seg_first);
+        if (ncand <= SEL_TILE) {
+            const Spread sp(ncand);
+            const unsigned on = sp.mask<SEL_E>();
+            int p[SEL_E];
+            float v[SEL_E];
+            uint32_t key[SEL_E];
+            if (segmented) {
+                const int len = seg_len(count);
 #pragma unroll
-                for (int u = 0; u < SEL_ITEMS_WIDE; ++u)
-                    v_next[u] = i0 + (SEL_THREADS * SEL_ITEMS_WIDE) + u < count ? vals[i0 + (SEL_THREADS * SEL_ITEMS_WIDE) + u] : 0.f;
-                unsigned keep = 0;
+                for (int u = 0; u < SEL_E; ++u) p[u] = scratch[segment_place(sp.at(u), len, seg_first)];
+            } else {
 #pragma unroll
-                for (int u = 0; u < SEL_ITEMS_WIDE; ++u)
-                    if (i0 + u < count && float_key(v[u]) >= lo) keep |= 1u << u;
+                for (int u = 0; u < SEL_E; ++u) p[u] = sp.at(u);
+            }
 #pragma unroll
-                for (int u = 0; u < SEL_ITEMS_WIDE; ++u) v[u] = v_next[u];
-                if (__syncthreads_or(keep != 0)) {
-                    int total;
-                    int pos = base + block_excl_scan(__popc(keep), wtot, total);
+            for (int u = 0; u < SEL_E; ++u) v[u] = vals[p[u]];
 #pragma unroll
-                    for (int u = 0; u < SEL_ITEMS_WIDE; ++u)
-                        if (keep & (1u << u)) tmp[pos++] = i0 + u;
-                    base += total;
+            for (int u = 0; u < SEL_E; ++u) key[u] = float_key(v[u]);
+            const uint32_t tkey = kth_largest_regs<SEL_E>(key, on, Kq, sh);
+            // winners above the K-th value in any order (they are ranked below), those equal to
+            // it in index order as far as there is room
+            unsigned eq = 0;
+            auto put = [&](int slot, int u) {
+                const int e = list ? list[p[u]] : p[u];
+                cs[slot] = v[u];
+                ci[slot] = cid ? cid[e] : e;
+            };
+#pragma unroll
+            for (int u = 0; u < SEL_E; ++u)
+                if ((on >> u) & 1u) {
+                    if (key[u] > tkey) put(atomicAdd(&n_above, 1), u);
+                    else if (key[u] == tkey) eq |= 1u << u;
                 }
-            }
-            __syncthreads();
-            cand = tmp;
-            ncand = base;
-        }
-        auto key_of = [&](int j) -> uint32_t { return float_key(vals[cand ? cand[j] : j]); };
-        const uint32_t tkey = block_kth_largest(ncand, Kq, key_of, hist, pick);
-        // how many are strictly above the K-th value
-        int gt_local = 0;
-        for (int j = threadIdx.x; j < ncand; j += SEL_THREADS) gt_local += key_of(j) > tkey;
-        int n_gt;
-        block_excl_scan(gt_local, wtot, n_gt);
-        const int need_eq = Kq - n_gt;
-        int base_gt = 0, base_eq = 0;
-        for (int start = 0; start < ncand; start += SEL_CHUNK) {
-            const int i0 = start + threadIdx.x * SEL_ITEMS;
-            float v[SEL_ITEMS];
-            int p[SEL_ITEMS];
-            unsigned gt = 0, eq = 0;
+            const Places<SEL_E> pl(eq, sh);         // its barrier completes n_above
+            const int n_gt = n_above;
 #pragma unroll
-            for (int u = 0; u < SEL_ITEMS; ++u) {
-                p[u] = (i0 + u < ncand) ? (cand ? cand[i0 + u] : i0 + u) : 0;
-                v[u] = (i0 + u < ncand) ? vals[p[u]] : 0.f;
+            for (int u = 0; u < SEL_E; ++u)
+                if (((eq >> u) & 1u) && n_gt + pl.place(u) < Kq) put(n_gt + pl.place(u), u);
+        } else {
+            const int32_t* cand = nullptr;
+            if (segmented) {
+                ncand = merge_segments(scratch, A.seg_cnt + (size_t)q * SEG_MAX, count);
+                cand = scratch;
             }
-#pragma unroll
-            for (int u = 0; u < SEL_ITEMS; ++u) {
-                if (i0 + u < ncand) {
-                    const uint32_t key = float_key(v[u]);
-                    gt |= (key > tkey ? 1u : 0u) << u;
-                    eq |= (key == tkey ? 1u : 0u) << u;
-                }
-            }
-            if (__syncthreads_or((gt | eq) != 0)) {      // most chunks hold no winner
-                int tot;
-                const int pos = block_excl_scan(__popc(gt) | (__popc(eq) << 16), wtot, tot);
-                int pg = base_gt + (pos & 0xffff), pe = base_eq + (pos >> 16);
+            auto key_of = [&](int j) -> uint32_t { return float_key(vals[cand ? cand[j] : j]); };
+            const uint32_t tkey = kth_largest_list(ncand, Kq, key_of, sh);
+            // how many are strictly above the K-th value
+            int gt_local = 0;
+            for (int j = threadIdx.x; j < ncand; j += SEL_THREADS) gt_local += key_of(j) > tkey;
+            int n_gt;
+            block_excl_scan(gt_local, sh.wtot, n_gt);
+            const int need_eq = Kq - n_gt;
+            int base_gt = 0, base_eq = 0;
+            for (int start = 0; start < ncand; start += SEL_CHUNK) {
+                const int i0 = start + threadIdx.x * SEL_ITEMS;
+                float v[SEL_ITEMS];
+                int p[SEL_ITEMS];
+                unsigned gt = 0, eq = 0;
 #pragma unroll
                 for (int u = 0; u < SEL_ITEMS; ++u) {
-                    int slot = -1;
-                    if (gt & (1u << u)) slot = pg++;
-                    else if (eq & (1u << u)) {
-                        if (pe < need_eq) slot = n_gt + pe;
-                        ++pe;
-                    }
-                    if (slot >= 0) {
-                        const int e = list ? list[p[u]] : p[u];
-                        cs[slot] = v[u];
-                        ci[slot] = cid ? cid[e] : e;
+                    p[u] = (i0 + u < ncand) ? (cand ? cand[i0 + u] : i0 + u) : 0;
+                    v[u] = (i0 + u < ncand) ? vals[p[u]] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < SEL_ITEMS; ++u) {
+                    if (i0 + u < ncand) {
+                        const uint32_t key = float_key(v[u]);
+                        gt |= (key > tkey ? 1u : 0u) << u;
+                        eq |= (key == tkey ? 1u : 0u) << u;
                     }
                 }
-                base_gt += tot & 0xffff;
-                base_eq += tot >> 16;
+                if (__syncthreads_or((gt | eq) != 0)) {      // most chunks hold no winner
+                    int tot;
+                    const int pos = block_excl_scan(__popc(gt) | (__popc(eq) << 16), sh.wtot, tot);
+                    int pg = base_gt + (pos & 0xffff), pe = base_eq + (pos >> 16);
+#pragma unroll
+                    for (int u = 0; u < SEL_ITEMS; ++u) {
+                        int slot = -1;
+                        if (gt & (1u << u)) slot = pg++;
+                        else if (eq & (1u << u)) {
+                            if (pe < need_eq) slot = n_gt + pe;
+                            ++pe;
+                        }
+                        if (slot >= 0) {
+                            const int e = list ? list[p[u]] : p[u];
+                            cs[slot] = v[u];
+                            ci[slot] = cid ? cid[e] : e;
+                        }
+                    }
+                    base_gt += tot & 0xffff;
+                    base_eq += tot >> 16;
+                }
             }
         }
         __syncthreads();
@@ -1402,14 +1712,9 @@ hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, const floa
     A.K = K;
     A.out_ids = out_ids;
     A.out_scores = out_scores;
-    A.n_seg = 0;
     A.seg_cnt = W.seg_cnt;
-    if (!use_ctl && P.N > SEL_PREFILTER_MIN) {
-        int n_seg = 512 / P.nq;
-        n_seg = n_seg < 2 ? 2 : (n_seg > SEG_MAX ? SEG_MAX : n_seg);
-        A.n_seg = n_seg;
-        k_topk_segments<<<dim3(n_seg, P.nq), SEL_THREADS, 0, st>>>(A);
-    }
+    if (!use_ctl && P.N > SEL_TILE)
+        k_topk_segments<<<dim3(segments_of(P.N), P.nq), SEL_THREADS, 0, st>>>(A);
     k_topk<<<P.nq, SEL_THREADS, 0, st>>>(A);
     return hipGetLastError();
 }

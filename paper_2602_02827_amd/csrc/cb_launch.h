@@ -66,7 +66,6 @@ struct RevealRound {
     int r;                // 1-based round
     int lo, nb;           // batch = pi[lo .. lo+nb)
     int n_prev, n;        // cells revealed before / after the round
-    float kappa;          // radius per unit sigma_hat at n
     // Rounds >= 2 pick their reveal path on the device: the corpus-streaming pass if
     // pairs[r] > dense_thr, else the per-pair gather.  Every kernel of the round evaluates the
     // same test.  ~0: always gather (also round 1, whose path the host fixes).
@@ -115,9 +114,12 @@ hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int chunk_
                                      hipStream_t st);
 bool dense_supported(const Problem& P, const Coarse* co);
 
-// R: number of rounds of the call (layout of W.pairs).
+// Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
+// this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
+// per unit sigma_hat of round r.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
-                               const RevealRound& rr, int R, const Trace& tr, hipStream_t st);
+                               const RevealRound& rr, int R, const float* kappa, const Trace& tr,
+                               hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
 // list position); else all N documents (vals indexed by id).

@@ -508,6 +508,21 @@ def test_long_lists_stay_long_under_a_conservative_radius(B, S, oracle_mod, nq):
     _run_colbandit_case(B, oracle_mod, w, 5, 5, 4, 1.0, seed=6, later_rounds=1)
 
 
+@pytest.mark.parametrize("N,K,alpha", [(1024, 5, 0.2), (1025, 32, 1.0), (4097, 33, 1.0), (8192, 5, 1.0),
+                                       (8193, 1, 1.0), (16384, 300, 1.0), (16385, 5, 1.0), (24577, 1000, 1.0)])
+def test_selection_at_the_edges_of_its_tiles(B, S, oracle_mod, N, K, alpha):
+    """Lists around what the selection kernels hold in registers (1,024 entries per place of a
+    thread, 8,192 in all), around the tile beyond which a list is pre-filtered (16,384), and K around
+    the number of group maxima (32); cached lists longer than the registers run their first
+    rounds from memory.  A tenth of the documents are copies of one document."""
+    rng = np.random.default_rng(N + K)
+    w = _custom(S, rng.integers(1, 3, N).tolist(), 2, 32, 128, "bf16", 91 + N)
+    off = w.offsets.cpu().numpy()
+    for i in rng.choice(N, N // 10, replace=False):
+        w.docs[off[i]] = w.docs[0]
+    _run_colbandit_case(B, oracle_mod, w, K, 5, 4, alpha, seed=N)
+
+
 def test_long_lists_with_massive_ties(B, S):
     """150,000 documents that are copies of 40 distinct ones: the K-th score is shared by
     thousands; ties resolve to the lowest indices."""
