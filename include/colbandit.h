@@ -60,9 +60,8 @@ enum {
 };
 
 /* Limits of this build (requests beyond them return COLBANDIT_ERR_UNSUPPORTED).
- * Embedding width d: 32, 64, 96 or 128.  The corpus-streaming kernels and the int8 codes
- * cover 64 and 128; at 32 and 96 every pass runs on the per-pair gather kernels (same
- * results, lower throughput) and opts.docs_i8 / colbandit_coarse_maxsim are refused.
+ * Embedding width d: 32, 64, 96 or 128.  The int8 codes cover 64 and 128; at 32 and 96
+ * opts.docs_i8 / colbandit_coarse_maxsim are refused.
  * Query tokens T: up to COLBANDIT_MAX_T for bf16, up to 64 for fp32. */
 #define COLBANDIT_MAX_T 128          /* query tokens                                  */
 #define COLBANDIT_MAX_K 1024         /* size of the returned top-K                    */
@@ -83,7 +82,7 @@ typedef struct {
                            test aid, layout below                                       */
     size_t trace_bytes;
     int force_gather;   /* nonzero: reveal round 1 with the gather kernel as well
-                           (test aid; the default picks the dense kernel for bf16)      */
+                           (test aid; the default picks the dense kernel)               */
     int no_cell_cache;  /* nonzero: re-gather the documents in every round instead of
                            caching a small active set's cells at its first gather
                            (test aid; the decisions are the same either way)            */
@@ -99,7 +98,7 @@ typedef struct {
     const float *docs_scale;  /* DEVICE [1]: decode scale of docs_i8 (required with it)  */
     int coarse_permille;      /* percentile, in 1/1000, of |Q| at which a query is clipped
                                  before coding; 0 -> 999 (the paper's 99.9th)            */
-    int later_rounds;   /* reveal path of rounds >= 2 for bf16 inputs.  0: chosen on the
+    int later_rounds;   /* reveal path of rounds >= 2.  0: chosen on the
                            device each round - one corpus-streaming pass shared by all
                            queries when the active sets are so large that gathering
                            every (query, document) pair would move more bytes, else the

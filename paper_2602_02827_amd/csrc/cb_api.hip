@@ -15,8 +15,13 @@ namespace {
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
-// Token chunk owned by one workgroup of the dense kernel.
+// Token chunk owned by one workgroup of the dense kernel and one group of its query columns: 4,096,
+// or for a small corpus the power of two (at least 128) that gives up to 2,048 workgroups, eight
+// per CU.  (6,007 documents, 0.9 M tokens, one column group: 224 chunks of 4,096 left CUs idle,
+// 84 us for a pass; 1,770 of 512 take 31 us.  Several column groups fill the chip with longer chunks,
+// over which a workgroup's query rows are loaded less often.)
 constexpr int kChunkTokens = 4096;
+constexpr int64_t kBlocksWanted = 2048;
 
 struct Layout {
     size_t ctl, list0, list1, stat, stat2, pairs, seg_cnt, rescored, scores, cnt_hist, tau_hist, pi,
@@ -97,6 +102,35 @@ Work carve(void* ws, const Layout& L) {
     return W;
 }
 
+// Sets the chunk length for passes over `tiles` column tiles, and the place of the chunk table.
+void choose_chunks(Work& W, const Problem& P, int64_t tiles) {
+    const int64_t per_group = P.dt == DT_F32 ? 16 : 32;
+    const int64_t groups = (tiles + per_group - 1) / per_group;
+    const int64_t wanted = kBlocksWanted / groups > 1 ? kBlocksWanted / groups : 1;
+    int c = kChunkTokens;
+    while (c > 128 && P.total <= wanted * (c / 2)) c /= 2;
+    W.chunk_tokens = c;
+    // The table of short chunks (at most kBlocksWanted + 1 entries) lies over the quantiser's
+    // scratch, which the coding of queries (one workgroup per query) does not use.
+    static_assert((kBlocksWanted + 1) * 4 <= 16384, "quantize_scratch_bytes holds 16 KB per segment");
+    if (c < kChunkTokens) W.chunk_doc = (int32_t*)W.qscratch;
+}
+
+// column tiles of the exhaustive kernel: 16 query tokens each, 1, 2, 4 or 8 per query
+int64_t score_tiles(const Problem& P) {
+    const int tq = (P.T + 15) / 16;
+    return (int64_t)P.nq * (tq <= 1 ? 1 : tq <= 2 ? 2 : tq <= 4 ? 4 : 8);
+}
+
+// Scoring or revealing every pair by gathering, a wavefront or workgroup each, beats the corpus pass
+// for the smallest calls: it needs one launch less and spreads a thousand documents better than
+// chunks do (1 query x 1,000 documents of 48 fp32 tokens: 9 us against 19), until the bytes of
+// every query's own reading, 5 TB/s, cost as much.
+bool small_call(const Problem& P) {
+    const double bytes = (double)P.nq * (double)P.total * P.d * (P.dt == DT_BF16 ? 2.0 : 4.0);
+    return bytes <= 40e6;
+}
+
 int check_shapes(const void* Q, int nq, int T, int d, int dt, const void* docs,
                  const int64_t* off, int64_t N, int64_t total) {
     if (!Q || !docs || !off) return COLBANDIT_ERR_NULL;
@@ -158,20 +192,25 @@ struct PhaseTimer {
     }
 };
 
-// Number of (query, document) pairs above which a later round is cheaper as one corpus pass
+// Number of (query, document) pairs above which round r of R is cheaper as one corpus pass
 // shared by all queries than as per-pair gathers.  Time model (seconds), with the rates these
 // kernels reach on an MI355X: a corpus pass costs the larger of streaming the tokens once
 // (~3.5 TB/s) and the matrix work of all query rows against them (~1.15 PFLOP/s); a gathered
 // pair streams its document once (~4.5 TB/s) and nothing is shared between queries.  A
 // gathered visit also caches the document's cells for the remaining rounds when the query fits
-// the cache, so the gather is preferred up to twice the cost of the pass.
-unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes) {
-    const double row_bytes = (codes ? 1.0 : 2.0) * P.d;   // int8 codes: half the bytes, twice the rate
+// the cache, so the gather is preferred up to twice the cost of the pass and of a round's other
+// launches (~18 us); and where every list fits, a gathered round is the last one to launch, which
+// saves those of all rounds after it.
+unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, int r, int R, bool lists_fit) {
+    // int8 codes: half the bytes of bf16 and twice the rate; fp32: twice the bytes, a tenth of the rate
+    const double row_bytes = (codes ? 1.0 : P.dt == DT_BF16 ? 2.0 : 4.0) * P.d;
+    const double rate = codes ? 2.3e15 : P.dt == DT_BF16 ? 1.15e15 : 0.11e15;
     const double rows = (double)(((int64_t)P.nq * G + 15) / 16 * 16);
-    const double per_token = fmax(row_bytes / 3.5e12, 2.0 * rows * P.d / (codes ? 2.3e15 : 1.15e15));
+    const double per_token = fmax(row_bytes / 3.5e12, 2.0 * rows * P.d / rate);
+    const double t_round = 18e-6;
     const double t_pass = (double)P.total * per_token;
     const double t_pair = ((double)P.total / (double)P.N) * row_bytes / 4.5e12;
-    const double thr = 2.0 * t_pass / t_pair;
+    const double thr = (2.0 * (t_pass + t_round) + (lists_fit ? (R - r) * t_round : 0.0)) / t_pair;
     return thr >= 1.8e19 ? ~0ull - 1 : (unsigned long long)thr;
 }
 
@@ -319,16 +358,17 @@ int colbandit_coarse_maxsim(const void* Q, int n_queries, int T, int d, colbandi
     const Layout L = make_layout(n_queries, T, d, N, total_tokens);
     rc = check_workspace(workspace, workspace_bytes, L.total);
     if (rc) return rc;
-    const Work W = carve(workspace, L);
+    Work W = carve(workspace, L);
     const Problem P{Q, n_queries, T, d, (int)dt, docs_i8, doc_offsets, N, total_tokens};
+    choose_chunks(W, P, score_tiles(P));
     hipStream_t st = (hipStream_t)stream;
     Coarse co{docs_i8, docs_scale, W.q8, W.qscale};
     if (!dense_supported(P, &co)) return COLBANDIT_ERR_UNSUPPORTED;
     hipError_t e = launch_quantize_i8(Q, (int)dt, n_queries, (int64_t)T * d, permille, W.q8,
                                       W.qscale, W.qscratch, st);
     int n_chunks = 0;
-    if (e == hipSuccess) e = launch_dense_prepare(P, W, kChunkTokens, &n_chunks, st);
-    if (e == hipSuccess) e = launch_dense_score(P, W, kChunkTokens, n_chunks, scores, cells, &co, st);
+    if (e == hipSuccess) e = launch_dense_prepare(P, W, &n_chunks, st);
+    if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, scores, cells, &co, st);
     if (e == hipSuccess && q_codes)
         e = hipMemcpyAsync(q_codes, W.q8, (size_t)n_queries * T * d, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess && q_scales)
@@ -402,24 +442,19 @@ int colbandit_doc_uniform(const void* Q, int n_queries, int T, int d, colbandit_
     const UniformLayout U = uniform_layout(n_queries, T, d, N, total_tokens);
     rc = check_workspace(workspace, workspace_bytes, U.total);
     if (rc) return rc;
-    const Work W = carve(workspace, make_layout(n_queries, T, d, N, total_tokens));
+    Work W = carve(workspace, make_layout(n_queries, T, d, N, total_tokens));
     const Problem P{Q, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
+    choose_chunks(W, P, score_tiles(P));
     hipStream_t st = (hipStream_t)stream;
     float* cells = (float*)((char*)workspace + U.cells);
     float* out = scores ? scores : W.scores;
     // the whole MaxSim matrix (exhaustive row sums go to a scratch array), then the subset sums
-    hipError_t e = hipSuccess;
-    if (dense_supported(P, nullptr)) {
-        int n_chunks = 0;
-        e = launch_dense_prepare(P, W, kChunkTokens, &n_chunks, st);
-        if (e == hipSuccess)
-            e = launch_dense_score(P, W, kChunkTokens, n_chunks, W.rescored, cells, nullptr, st);
-    } else {
-        e = launch_gather_score(P, W, false, W.rescored, cells, false, st);
-    }
+    int n_chunks = 0;
+    hipError_t e = launch_dense_prepare(P, W, &n_chunks, st);
+    if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, W.rescored, cells, nullptr, st);
     if (e == hipSuccess)
         e = launch_uniform_score(cells, n_queries, N, T, cells_per_doc, seed, out, masks, st);
-    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, out, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
     return e == hipSuccess ? COLBANDIT_OK : COLBANDIT_ERR_HIP;
 }
 
@@ -448,7 +483,7 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
     const BallLayout B = ball_layout(n_queries, T, d, (int)dt, N, total_tokens);
     rc = check_workspace(workspace, workspace_bytes, B.total);
     if (rc) return rc;
-    const Work W = carve(workspace, make_layout(n_queries, T, d, N, total_tokens));
+    Work W = carve(workspace, make_layout(n_queries, T, d, N, total_tokens));
     const Problem P{Q, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
     hipStream_t st = (hipStream_t)stream;
     char* b = (char*)workspace;
@@ -460,7 +495,7 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
     const size_t elem = dt == COLBANDIT_BF16 ? 2 : 4;
 
     hipError_t e = launch_ball_carve(P, tau, Cz, lab, kq, st);
-    if (e == hipSuccess && dt == COLBANDIT_BF16 && dense_supported(P, nullptr)) {
+    if (e == hipSuccess && dt == COLBANDIT_BF16 && (d == 64 || d == 128)) {
         // centroids of the batch, four to a group, through the corpus-streaming reveal kernel:
         // its work follows the number of query columns, i.e. the number of centroids
         void* Qg = b + B.Qg;
@@ -474,7 +509,8 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
         if (e == hipSuccess && (ng < n_queries || (int64_t)ng > (int64_t)n_queries * B.TG))
             e = hipErrorUnknown;
         int n_chunks = 0;
-        if (e == hipSuccess) e = launch_dense_prepare(P, W, kChunkTokens, &n_chunks, st);
+        choose_chunks(W, P, ((int64_t)ng * 4 + 15) / 16);
+        if (e == hipSuccess) e = launch_dense_prepare(P, W, &n_chunks, st);
         if (e == hipSuccess) {
             const Problem P2{Qg, ng, 4, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
             Work W2 = W;
@@ -486,13 +522,14 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
             rr.nb = 4;
             rr.n = 4;
             rr.dense_thr = ~0ull;
-            e = launch_dense_reveal(P2, W2, kChunkTokens, n_chunks, rr, 4, nullptr, st);
+            e = launch_dense_reveal(P2, W2, n_chunks, rr, 4, nullptr, st);
         }
         if (e == hipSuccess) e = launch_ball_reduce((const float*)part, 2, goff, n_queries, N, out, st);
     } else if (e == hipSuccess) {
-        // fp32: exhaustive scoring of the zero-padded centroid matrix (a zero row's cell is 0)
+        // fp32, and widths without a group pass: exhaustive scoring of the zero-padded centroid
+        // matrix (a zero row's cell is 0)
         const Problem P3{Cz, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
-        e = launch_gather_score(P3, W, false, out, nullptr, false, st);
+        e = launch_gather_all(P3, W, out, nullptr, st);
     }
     if (e == hipSuccess && n_clusters)
         e = hipMemcpyAsync(n_clusters, kq, 4 * (size_t)n_queries, hipMemcpyDeviceToDevice, st);
@@ -500,7 +537,7 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
         e = hipMemcpyAsync(labels, lab, 4 * (size_t)n_queries * T, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess && centroids)
         e = hipMemcpyAsync(centroids, Cz, elem * (size_t)n_queries * T * d, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, out, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
     return e == hipSuccess ? COLBANDIT_OK : COLBANDIT_ERR_HIP;
 }
 
@@ -522,7 +559,7 @@ int colbandit_full_maxsim(const void* Q, int n_queries, int T, int d, colbandit_
     rc = check_workspace(workspace, workspace_bytes, L.total);
     if (rc) return rc;
 
-    const Work W = carve(workspace, L);
+    Work W = carve(workspace, L);
     const Problem P{Q, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
     hipStream_t st = (hipStream_t)stream;
     float* out = scores ? scores : W.scores;
@@ -535,18 +572,22 @@ int colbandit_full_maxsim(const void* Q, int n_queries, int T, int d, colbandit_
     };
     hipError_t e = hipSuccess;
     mark();
-    if (dense_supported(P, nullptr)) {
-        int n_chunks = 0;
-        e = launch_dense_prepare(P, W, kChunkTokens, &n_chunks, st);
+    // One or two fp32 queries of more than 16 tokens are bound by the matrix pipes, and there the
+    // corpus kernel's wavefronts, which split the documents, all multiply the blocks in which one
+    // ends.  15.9 M tokens, gathering against the corpus pass: 4.5 and 5.9 ms for one query of 42
+    // tokens, 6.8 and 7.6 for two, 3.30 and 3.38 for one of 32.
+    if (small_call(P) || (dt == COLBANDIT_F32 && T > 16 && n_queries <= 2)) {
         mark();
-        if (e == hipSuccess)
-            e = launch_dense_score(P, W, kChunkTokens, n_chunks, out, cells, nullptr, st);
+        e = launch_gather_all(P, W, out, cells, st);
     } else {
+        int n_chunks = 0;
+        choose_chunks(W, P, score_tiles(P));
+        e = launch_dense_prepare(P, W, &n_chunks, st);
         mark();
-        e = launch_gather_score(P, W, false, out, cells, false, st);
+        if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, out, cells, nullptr, st);
     }
     mark();
-    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, out, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
     mark();
     if (phase_ms) {
         phase_ms[0] = phase_ms[1] = 0.f;
@@ -643,6 +684,10 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     if (builtin_scratch && static_scratch(&workspace) != hipSuccess) return COLBANDIT_ERR_HIP;
     Work W = carve(workspace, L);
     if (no_cache) W.cache_cap = 0;
+    // The work items lie over rows of tau_hist that no round of this call writes (rows R and up; two
+    // rows of nq floats, at an even number of floats).
+    static_assert(COLBANDIT_MAX_ROUNDS % 2 == 0, "the last pair of spare rows starts at an even one");
+    W.work = (unsigned long long*)(W.tau_hist + (size_t)(R + ((R & 1) && (n_queries & 1) ? 1 : 0)) * n_queries);
     const Problem P{Q, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
     hipStream_t st = (hipStream_t)stream;
 
@@ -661,9 +706,12 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
             e = launch_quantize_i8(Q, (int)dt, n_queries, (int64_t)T * d, q_permille, W.q8,
                                    W.qscale, W.qscratch, st);
     }
-    const bool dense = dense_supported(P, co) && !force_gather;
+    const bool dense = dense_supported(P, co) && !force_gather && !(small_call(P) && later_rounds != 1);
+    int G_max = 1;                                   // columns of a full batch
+    while (G_max < kn.B) G_max <<= 1;
+    choose_chunks(W, P, ((int64_t)n_queries * G_max + 15) / 16);
     int n_chunks = 0;
-    if (e == hipSuccess && loop && dense) e = launch_dense_prepare(P, W, kChunkTokens, &n_chunks, st);
+    if (e == hipSuccess && loop && dense) e = launch_dense_prepare(P, W, &n_chunks, st);
     float kappa[COLBANDIT_MAX_ROUNDS + 1] = {};      // radius per unit sigma_hat of each round
     for (int r = 1; r <= R; ++r) {
         const double kap = colbandit_radius_prefactor(alpha_ef, delta, T, N, r * kn.B < T ? r * kn.B : T);
@@ -682,23 +730,27 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         while (G < rr.nb) G <<= 1;
         rr.dense_thr = ~0ull;
         if (r == 1 && dense) {
-            e = launch_dense_reveal(P, W, kChunkTokens, n_chunks, rr, G, co, st);
+            e = launch_dense_reveal(P, W, n_chunks, rr, G, co, st);
         } else {
-            if (r >= 2 && dense && later_rounds != 2)
-                rr.dense_thr = later_rounds == 1 ? 0ull : dense_pairs_threshold(P, G, co != nullptr);
+            if (r >= 2 && dense && later_rounds != 2) {
+                rr.dense_thr = later_rounds == 1 ? 0ull
+                                                 : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap);
+                if (rr.dense_thr >= (unsigned long long)n_queries * (unsigned long long)N) rr.dense_thr = ~0ull;
+            }
             round_thr[r] = rr.dense_thr;
-            e = launch_dense_reveal_later(P, W, kChunkTokens, n_chunks, rr, G, co, st);
-            if (e == hipSuccess) e = launch_gather_reveal(P, W, rr, co, st);
-            if (e == hipSuccess && r >= 2) e = launch_gather_cells(P, W, rr, co, st);
+            e = launch_dense_reveal_later(P, W, n_chunks, rr, G, co, st);
+            if (e == hipSuccess) e = launch_gather_round(P, W, rr, co, st);
         }
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
         if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, tr, st);
         pt.mark(PH_SELECT);
+        // A gathered round in which every list fits the cell cache is the last one to launch:
+        // k_select_prune runs all rounds of a cached query.
+        if (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
-    if (e == hipSuccess) e = launch_gather_score(P, W, true, W.rescored, nullptr, co != nullptr, st);
-    if (e == hipSuccess && !co) e = launch_cached_score(P, W, W.rescored, st);
-    if (e == hipSuccess) e = launch_topk(P, W, true, W.rescored, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
+    if (e == hipSuccess) e = launch_topk(P, W, true, !co, W.rescored, K, topk_ids, topk_scores, st);
     pt.mark(PH_RESCORE);
     if (e != hipSuccess) {
         pt.destroy();
@@ -719,7 +771,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     // the rounds whose device-side test took the corpus pass (the same test as the kernels')
     uint64_t corpus_rounds = 0;
     for (int r = 2; ce == hipSuccess && loop && r <= R; ++r)
-        if (round_thr[r] != ~0ull && pairs_h[r] > round_thr[r]) corpus_rounds |= 1ull << (r - 1);
+        if (round_thr[r] != ~0ull && pair_count(pairs_h[r]) > round_thr[r]) corpus_rounds |= 1ull << (r - 1);
     float ms = 0.f, phase_ms[PH_COUNT] = {0.f, 0.f, 0.f, 0.f, 0.f};
     if (ce == hipSuccess) pt.collect(phase_ms, ms);
     pt.destroy();
@@ -761,7 +813,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         s.ms_select_prune = phase_ms[PH_SELECT];
         s.ms_rescore_topk = phase_ms[PH_RESCORE];
         s.corpus_pass_rounds = corpus_rounds;
-        s.pairs_round2 = R >= 2 ? pairs_h[2] : 0ull;
+        s.pairs_round2 = R >= 2 ? pair_count(pairs_h[2]) : 0ull;
         s.tokens_round2 = R >= 2 ? pairs_h[(R + 2) + 2] : 0ull;
     }
     free(hist);

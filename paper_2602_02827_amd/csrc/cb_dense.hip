@@ -1,6 +1,6 @@
-// Dense corpus-streaming MaxSim kernel for bf16 embeddings and int8 codes (gfx950).
+// Dense corpus-streaming MaxSim kernel for bf16 and fp32 embeddings and int8 codes (gfx950).
 //
-// Shape of the work: a [tokens x d] corpus against a few thousand query rows, d = 64/128.
+// Shape of the work: a [tokens x d] corpus against a few thousand query rows, d = 32/64/96/128.
 // The result matrix is never written; each 16x16 MFMA tile is folded at once into a
 // running per-(document, query row) maximum, and a document's maxima are summed when
 // its last token has passed (paper Eq. (1)-(2), (4)-(5)).
@@ -9,12 +9,14 @@
 //   * A workgroup (4 wavefronts) owns one token chunk (whole documents whose first token
 //     falls into a fixed-size token range) and one group of 64*NT query columns.
 //   * Query rows are the B operand and stay in registers for the whole kernel: each
-//     wavefront holds NT column tiles of 16 rows, full depth (NT*d/8 VGPRs).
+//     wavefront holds NT column tiles of 16 rows, full depth (NT*d/8 VGPRs; fp32 NT*d/4, hence
+//     NT <= 4).
 //   * Document tokens are the A operand.  They stream through a four-slot LDS ring of
 //     64-token stages (direct global -> LDS copies issued two stages ahead of the reader), so
 //     a token is read from memory once per workgroup and from LDS once per wavefront.
 //     Rows are stored with their 16-byte pieces XOR-swizzled by the row index, which
-//     spreads the 16 rows of an operand block over all banks.
+//     spreads the 16 rows of an operand block over all banks; a row whose length is not a power
+//     of two (d = 96) is padded to one in LDS.
 //   * The chunk's tokens form one stream of aligned 16-token blocks, whatever the document
 //     boundaries, so no token is multiplied twice.  A block inside one document folds into
 //     the running maxima directly; where a document ends inside a block the fold is split
@@ -32,12 +34,23 @@ constexpr int DENSE_THREADS = 256;
 // Ring geometry: four stages.  Kernels with few column tiles per wavefront (small query
 // batches: bound by memory, little register use) take 32-row stages, so that four workgroups fit
 // a CU instead of two and more wavefronts hide the latencies; the others take 64-row stages.
-template <int NT, int ROWB> struct RingShape {
-    static constexpr int ROWS_PER_LOAD = 64 / (ROWB / 16);
+// A_REGS: registers of one operand block (the query rows take NT of them, two token blocks are in
+// flight); four, three or two workgroups per CU by what that leaves.
+template <int NT, int PITCH, int A_REGS> struct RingShape {
+    static constexpr int ROWS_PER_LOAD = 64 / (PITCH / 16);
     static constexpr bool SMALL = NT <= 4 && 32 / ROWS_PER_LOAD / 4 >= 1;
     static constexpr int STAGE_ROWS = SMALL ? 32 : 64;
     static constexpr int RING_ROWS = 4 * STAGE_ROWS;
-    static constexpr int MIN_BLOCKS = SMALL ? (NT <= 2 ? 4 : 3) : 2;
+    static constexpr int REGS = (NT + 2) * A_REGS + 40;
+    static constexpr int BY_REGS = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : 2);
+    static constexpr int BY_SHAPE = SMALL ? (NT <= 2 ? 4 : 3) : 2;
+    static constexpr int MIN_BLOCKS = BY_REGS < BY_SHAPE ? BY_REGS : BY_SHAPE;
+};
+// bytes of a token row, and of its place in the ring (a power of two)
+template <class F, int D> struct RowShape {
+    static constexpr int BYTES = D * F::ELEM_BYTES;
+    static constexpr int PITCH = BYTES <= 64 ? 64 : BYTES <= 128 ? 128 : BYTES <= 256 ? 256 : 512;
+    static constexpr int A_REGS = BYTES / 16;
 };
 
 struct DenseArgs {
@@ -66,25 +79,32 @@ struct DenseArgs {
 };
 
 template <typename Tag, int D, int NT, int TQ, bool REVEAL, int SPLIT_DOCS = 0>
-__global__ __launch_bounds__(DENSE_THREADS, (RingShape<NT, D * Frag<Tag, D>::ELEM_BYTES>::MIN_BLOCKS))
+__global__ __launch_bounds__(DENSE_THREADS, (RingShape<NT, RowShape<Frag<Tag, D>, D>::PITCH,
+                                                       RowShape<Frag<Tag, D>, D>::A_REGS>::MIN_BLOCKS))
 void k_dense(DenseArgs A) {
     using F = Frag<Tag, D>;
-    using RS = RingShape<NT, D * F::ELEM_BYTES>;
+    using RS = RingShape<NT, RowShape<F, D>::PITCH, RowShape<F, D>::A_REGS>;
     constexpr int STAGE_ROWS = RS::STAGE_ROWS;
     constexpr int RING_ROWS = RS::RING_ROWS;
     using V = typename F::val_t;           // float, or int for int8 codes
     constexpr bool CODES = !__is_same(V, float);
-    constexpr int ROWB = D * F::ELEM_BYTES;   // bytes per token row
-    constexpr int NCH = ROWB / 16;         // 16-byte pieces per row
+    constexpr int ROWB = RowShape<F, D>::BYTES;    // bytes per token row in memory
+    constexpr int PITCH = RowShape<F, D>::PITCH;   // ... and in the ring
+    constexpr int NCH = PITCH / 16;                // 16-byte pieces per ring row
+    constexpr bool F32 = __is_same(Tag, f32_tag);
     // Cache policy of the token copies.  The reveal pass normally has one column group, and the
-    // score kernels with at most four column tiles per wavefront always have: a token row is read
-    // once and should not push other lines out of L2 - above all those of the (sum, M2) array,
-    // which fill up over several documents; such copies carry the non-temporal hint (bit 1).
-    constexpr int LOAD_POLICY = (REVEAL || NT <= 4) ? 2 : 0;
-    // Swizzle key of a ring row: rows whose 16-byte pieces would fall on the same banks
-    // (row stride ROWB against the 256-byte bank window) get different keys.
+    // score kernels with at most four column tiles per wavefront always have (fp32: at most two):
+    // a token row is read once and should not push other lines out of L2 - above all those of the
+    // (sum, M2) array, which fill up over several documents; such copies carry the non-temporal
+    // hint (bit 1).
+    constexpr int LOAD_POLICY = F32 ? (NT <= 2 ? 2 : 0) : (REVEAL || NT <= 4) ? 2 : 0;
+    // Swizzle key of a ring row: rows whose 16-byte pieces would fall on the same banks (row
+    // stride PITCH against the 256-byte bank window) get different keys.  The key's period must
+    // divide the rows of one load of all wavefronts; that is 8 rows at 512 bytes, which leaves
+    // two rows to a bank: nothing beside fp32's matrix time (8 of 1,024 cycles a column tile).
     constexpr int KEY_SHIFT = NCH >= 16 ? 0 : (NCH == 8 ? 1 : 2);
-    __shared__ __attribute__((aligned(16))) char ring[RING_ROWS * ROWB];
+    constexpr int KEY_MASK = NCH == 32 ? 7 : NCH - 1;
+    __shared__ __attribute__((aligned(16))) char ring[RING_ROWS * PITCH];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in an SGPR
@@ -122,9 +142,10 @@ void k_dense(DenseArgs A) {
     // multiplies the blocks inside its own documents (every fourth, or every second) and every
     // block in which a document ends, and writes the scores of its own documents only.  All four
     // still walk the same block stream, so the stage barriers match up.  (SPLIT_DOCS: the launch
-    // has one column group.)
-    static_assert(SPLIT_DOCS == 0 || ((SPLIT_DOCS == 2 || SPLIT_DOCS == 4) && !REVEAL && NT <= 2),
-                  "document splitting is for the smallest score kernels");
+    // has one column group.)  15.9 M tokens, bf16: 1.03 -> 0.77 ms for one query of 42 tokens, 1.03 ->
+    // 0.88 for two, 1.63 -> 1.29 and 1.64 -> 1.40 with 100 tokens.
+    static_assert(SPLIT_DOCS == 0 || ((SPLIT_DOCS == 2 || SPLIT_DOCS == 4) && !REVEAL),
+                  "document splitting is for small batches of the score kernels");
     constexpr int TILE_WAVES = SPLIT_DOCS ? 4 / SPLIT_DOCS : 4;      // wavefronts with tiles of their own
     const int tile0 = SPLIT_DOCS ? (wave % TILE_WAVES) * NT : (group * 4 + wave) * NT;
     auto mine = [&](int doc) {
@@ -162,8 +183,12 @@ void k_dense(DenseArgs A) {
     // load group, piece (lane % NCH) ^ key(row).  A complete stage therefore needs no per-lane
     // address arithmetic at all: uniform base + this constant offset.
     const int lrow0 = wave * ROWS_PER_LOAD + lane / NCH;
-    const unsigned fetch_off =
-        (unsigned)(lrow0 * ROWB + (((lane & (NCH - 1)) ^ ((lrow0 >> KEY_SHIFT) & (NCH - 1))) * 16));
+    // the piece that belongs at a lane's place; the padding's places repeat others
+    auto piece_of = [&](int row) {
+        const int c = (lane & (NCH - 1)) ^ ((row >> KEY_SHIFT) & KEY_MASK);
+        return c < ROWB / 16 ? c : c - (NCH - ROWB / 16);
+    };
+    const unsigned fetch_off = (unsigned)(lrow0 * ROWB + piece_of(lrow0) * 16);
     auto stage_fetch = [&](int s) {
         if ((s + 1) * STAGE_ROWS <= ntok) {
 #pragma unroll
@@ -171,7 +196,7 @@ void k_dense(DenseArgs A) {
                 const int r0 = s * STAGE_ROWS + i * 4 * ROWS_PER_LOAD;               // uniform
                 __builtin_amdgcn_global_load_lds(
                     (const __attribute__((address_space(1))) void*)(src + (size_t)r0 * ROWB + fetch_off),
-                    (__attribute__((address_space(3))) void*)(ring + ((r0 + wave * ROWS_PER_LOAD) & (RING_ROWS - 1)) * ROWB),
+                    (__attribute__((address_space(3))) void*)(ring + ((r0 + wave * ROWS_PER_LOAD) & (RING_ROWS - 1)) * PITCH),
                     16, 0, LOAD_POLICY);
             }
             return;
@@ -183,10 +208,9 @@ void k_dense(DenseArgs A) {
             if (rbase < ntok) {
                 const int lrow = rbase + lane / NCH;                  // the LDS row this lane fills
                 const int grow = lrow < ntok ? lrow : ntok - 1;
-                const int c = (lane & (NCH - 1)) ^ ((lrow >> KEY_SHIFT) & (NCH - 1));
                 __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(src + (size_t)grow * ROWB + c * 16),
-                    (__attribute__((address_space(3))) void*)(ring + (rbase & (RING_ROWS - 1)) * ROWB),
+                    (const __attribute__((address_space(1))) void*)(src + (size_t)grow * ROWB + piece_of(lrow) * 16),
+                    (__attribute__((address_space(3))) void*)(ring + (rbase & (RING_ROWS - 1)) * PITCH),
                     16, 0, LOAD_POLICY);
             }
         }
@@ -346,11 +370,11 @@ void k_dense(DenseArgs A) {
     unsigned blk_off[F::KS];
 #pragma unroll
     for (int ks = 0; ks < F::KS; ++ks)
-        blk_off[ks] = (unsigned)(col * ROWB + (((ks * 4 + kg) ^ ((col >> KEY_SHIFT) & (NCH - 1))) * 16));
+        blk_off[ks] = (unsigned)(col * PITCH + (((ks * 4 + kg) ^ ((col >> KEY_SHIFT) & KEY_MASK)) * 16));
     // a complete block (bs + 16 <= ntok) of a visible stage
     auto load_aligned = [&](F& a, int bs) {
         using piece_t = __remove_reference_t(decltype(a.v[0]));
-        const char* rp = ring + (bs & (RING_ROWS - 1)) * ROWB;       // uniform
+        const char* rp = ring + (bs & (RING_ROWS - 1)) * PITCH;      // uniform
 #pragma unroll
         for (int ks = 0; ks < F::KS; ++ks) a.v[ks] = *(const piece_t*)(rp + blk_off[ks]);
     };
@@ -363,8 +387,8 @@ void k_dense(DenseArgs A) {
         }
         int row = bs + col;
         row = row < ntok ? row : ntok - 1;
-        const char* rp = ring + (row & (RING_ROWS - 1)) * ROWB;
-        const int sw = (row >> KEY_SHIFT) & (NCH - 1);
+        const char* rp = ring + (row & (RING_ROWS - 1)) * PITCH;
+        const int sw = (row >> KEY_SHIFT) & KEY_MASK;
 #pragma unroll
         for (int ks = 0; ks < F::KS; ++ks) a.v[ks] = *(const piece_t*)(rp + (((ks * 4 + kg) ^ sw) * 16));
     };
@@ -420,7 +444,7 @@ void k_dense(DenseArgs A) {
     // document ends, and the chunk's last stages, take the general path.  Kernels with fewer
     // than eight column tiles per wavefront are bound by memory, not by the matrix pipes, and run
     // at a higher occupancy with fewer registers: they keep to the general path.
-    constexpr bool TIGHT_RUNS = NT >= 8;
+    constexpr bool TIGHT_RUNS = NT >= 8 && SPLIT_DOCS == 0;
     const int tight_end = TIGHT_RUNS ? (nfull - 2) * STAGE_ROWS : 0;
     auto stage_enter_full = [&](int bs) {        // bs < tight_end is a stage boundary
         wait_copies();
@@ -430,7 +454,7 @@ void k_dense(DenseArgs A) {
             const int r0 = bs + 2 * STAGE_ROWS + i * 4 * ROWS_PER_LOAD;               // uniform
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void*)(src + (size_t)r0 * ROWB + fetch_off),
-                (__attribute__((address_space(3))) void*)(ring + ((r0 + wave * ROWS_PER_LOAD) & (RING_ROWS - 1)) * ROWB),
+                (__attribute__((address_space(3))) void*)(ring + ((r0 + wave * ROWS_PER_LOAD) & (RING_ROWS - 1)) * PITCH),
                 16, 0, LOAD_POLICY);
         }
     };
@@ -495,13 +519,13 @@ __global__ void k_chunk_docs(const int64_t* off, int64_t N, int C, int n_chunks,
 }
 
 bool dense_supported(const Problem& P, const Coarse* co) {
-    // the streaming kernel reads bf16 embeddings or int8 codes
-    return (P.dt == DT_BF16 || co != nullptr) && (P.d == 64 || P.d == 128) &&
+    // int8 codes: the instruction contracts 64 elements at a time
+    return (co ? P.d == 64 || P.d == 128 : P.d == 32 || P.d == 64 || P.d == 96 || P.d == 128) &&
            P.total / 4096 < 0x7fffff00;
 }
 
-hipError_t launch_dense_prepare(const Problem& P, const Work& W, int C, int* n_chunks,
-                                hipStream_t st) {
+hipError_t launch_dense_prepare(const Problem& P, const Work& W, int* n_chunks, hipStream_t st) {
+    const int C = W.chunk_tokens;
     const int nc = (int)((P.total + C - 1) / C);
     *n_chunks = nc;
     const int64_t n = P.N + 1;
@@ -537,17 +561,24 @@ template <typename Tag, int D, int TQ>
 static hipError_t dense_score_nt(DenseArgs& A, int tiles, hipStream_t st) {
     // one or two queries (twice as many of at most 16 tokens): the tiles fit one or two
     // wavefronts, and four or two wavefronts split the documents
+    if constexpr (TQ == 4) {
+        if (tiles <= 4) return dense_go<Tag, D, 4, TQ, false, 4>(A, tiles, st);
+        if (tiles <= 8) return dense_go<Tag, D, 4, TQ, false, 2>(A, tiles, st);
+    }
+    if constexpr (TQ == 8 && Tag::wide) {
+        if (tiles <= 8) return dense_go<Tag, D, 8, TQ, false, 4>(A, tiles, st);
+        if (tiles <= 16) return dense_go<Tag, D, 8, TQ, false, 2>(A, tiles, st);
+    }
     if constexpr (TQ <= 2) {
         if (tiles <= 2) return dense_go<Tag, D, 2, TQ, false, 4>(A, tiles, st);
         if (tiles <= 4) return dense_go<Tag, D, 2, TQ, false, 2>(A, tiles, st);
-    }
-    if constexpr (TQ <= 2) {
         if (tiles <= 8) return dense_go<Tag, D, 2, TQ, false>(A, tiles, st);
     }
     if constexpr (TQ <= 4) {
-        if (tiles <= 16) return dense_go<Tag, D, 4, TQ, false>(A, tiles, st);
+        if (!Tag::wide || tiles <= 16) return dense_go<Tag, D, 4, TQ, false>(A, tiles, st);
     }
-    return dense_go<Tag, D, 8, TQ, false>(A, tiles, st);
+    if constexpr (Tag::wide) return dense_go<Tag, D, 8, TQ, false>(A, tiles, st);
+    else return hipErrorInvalidValue;
 }
 
 template <typename Tag, int D>
@@ -556,7 +587,17 @@ static hipError_t dense_score_d(DenseArgs& A, hipStream_t st) {
     if (tq <= 1) return dense_score_nt<Tag, D, 1>(A, A.nq * 1, st);
     if (tq <= 2) return dense_score_nt<Tag, D, 2>(A, A.nq * 2, st);
     if (tq <= 4) return dense_score_nt<Tag, D, 4>(A, A.nq * 4, st);
-    return dense_score_nt<Tag, D, 8>(A, A.nq * 8, st);
+    if constexpr (Tag::wide) return dense_score_nt<Tag, D, 8>(A, A.nq * 8, st);
+    else return hipErrorInvalidValue;
+}
+
+template <typename Tag> static hipError_t dense_score_any_d(DenseArgs& A, int d, hipStream_t st) {
+    switch (d) {
+        case 128: return dense_score_d<Tag, 128>(A, st);
+        case 96: return dense_score_d<Tag, 96>(A, st);
+        case 64: return dense_score_d<Tag, 64>(A, st);
+        default: return dense_score_d<Tag, 32>(A, st);
+    }
 }
 
 // int8 codes instead of the stored embeddings
@@ -567,9 +608,8 @@ static void use_codes(DenseArgs& A, const Coarse* co) {
     A.dscale = co->dscale;
 }
 
-hipError_t launch_dense_score(const Problem& P, const Work& W, int C, int n_chunks, float* out,
+hipError_t launch_dense_score(const Problem& P, const Work& W, int n_chunks, float* out,
                               float* cells, const Coarse* co, hipStream_t st) {
-    (void)C;
     DenseArgs A{};
     fill_dense(A, P, W, n_chunks);
     A.out = out;
@@ -578,7 +618,7 @@ hipError_t launch_dense_score(const Problem& P, const Work& W, int C, int n_chun
         use_codes(A, co);
         return P.d == 128 ? dense_score_d<i8_tag, 128>(A, st) : dense_score_d<i8_tag, 64>(A, st);
     }
-    return P.d == 128 ? dense_score_d<bf16_tag, 128>(A, st) : dense_score_d<bf16_tag, 64>(A, st);
+    return P.dt == DT_BF16 ? dense_score_any_d<bf16_tag>(A, P.d, st) : dense_score_any_d<f32_tag>(A, P.d, st);
 }
 
 template <typename Tag, int D>
@@ -586,8 +626,17 @@ static hipError_t dense_reveal_d(DenseArgs& A, hipStream_t st) {
     const int tiles = (A.nq * A.G + 15) / 16;
     if (tiles <= 4) return dense_go<Tag, D, 1, 1, true>(A, tiles, st);
     if (tiles <= 8) return dense_go<Tag, D, 2, 1, true>(A, tiles, st);
-    if (tiles <= 16) return dense_go<Tag, D, 4, 1, true>(A, tiles, st);
-    return dense_go<Tag, D, 8, 1, true>(A, tiles, st);
+    if (!Tag::wide || tiles <= 16) return dense_go<Tag, D, 4, 1, true>(A, tiles, st);
+    if constexpr (Tag::wide) return dense_go<Tag, D, 8, 1, true>(A, tiles, st);
+    else return hipErrorInvalidValue;
+}
+template <typename Tag> static hipError_t dense_reveal_any_d(DenseArgs& A, int d, hipStream_t st) {
+    switch (d) {
+        case 128: return dense_reveal_d<Tag, 128>(A, st);
+        case 96: return dense_reveal_d<Tag, 96>(A, st);
+        case 64: return dense_reveal_d<Tag, 64>(A, st);
+        default: return dense_reveal_d<Tag, 32>(A, st);
+    }
 }
 
 static hipError_t dense_reveal_any(DenseArgs& A, const Problem& P, const Coarse* co, hipStream_t st) {
@@ -595,12 +644,11 @@ static hipError_t dense_reveal_any(DenseArgs& A, const Problem& P, const Coarse*
         use_codes(A, co);
         return P.d == 128 ? dense_reveal_d<i8_tag, 128>(A, st) : dense_reveal_d<i8_tag, 64>(A, st);
     }
-    return P.d == 128 ? dense_reveal_d<bf16_tag, 128>(A, st) : dense_reveal_d<bf16_tag, 64>(A, st);
+    return P.dt == DT_BF16 ? dense_reveal_any_d<bf16_tag>(A, P.d, st) : dense_reveal_any_d<f32_tag>(A, P.d, st);
 }
 
-hipError_t launch_dense_reveal(const Problem& P, const Work& W, int C, int n_chunks,
+hipError_t launch_dense_reveal(const Problem& P, const Work& W, int n_chunks,
                                const RevealRound& rr, int G, const Coarse* co, hipStream_t st) {
-    (void)C;
     DenseArgs A{};
     fill_dense(A, P, W, n_chunks);
     A.lo = rr.lo;
@@ -609,10 +657,9 @@ hipError_t launch_dense_reveal(const Problem& P, const Work& W, int C, int n_chu
     return dense_reveal_any(A, P, co, st);
 }
 
-hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int C, int n_chunks,
+hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chunks,
                                      const RevealRound& rr, int G, const Coarse* co,
                                      hipStream_t st) {
-    (void)C;
     if (rr.dense_thr == ~0ull) return hipSuccess;
     DenseArgs A{};
     fill_dense(A, P, W, n_chunks);

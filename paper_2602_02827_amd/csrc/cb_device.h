@@ -35,13 +35,24 @@ struct QueryCtl {
     int pad1, pad2;
 };
 
+// A round's pairs that are still held as document ids: their number, and the queries that hold
+// them, counted together (one 64-bit atomic) so that the work items, appended in the order of the
+// atomics, have ascending first pairs.
+constexpr unsigned long long PAIR_MASK = (1ull << 40) - 1ull;
+__device__ __host__ __forceinline__ unsigned long long pair_count(unsigned long long head) { return head & PAIR_MASK; }
+__device__ __forceinline__ unsigned long long work_count(unsigned long long head) { return head >> 40; }
+__device__ __forceinline__ unsigned long long work_add(int pairs) { return (1ull << 40) | (unsigned long long)pairs; }
+// one query's item: number of its first pair, and the query (at most 65,535)
+__device__ __forceinline__ unsigned long long work_item(int q, unsigned long long start) { return start << 16 | (unsigned)q; }
+__device__ __forceinline__ unsigned long long work_start(unsigned long long item) { return item >> 16; }
+__device__ __forceinline__ int work_query(unsigned long long item) { return (int)(item & 0xffffu); }
+
 // Device-side choice of a later round's reveal path (uniform over the launch): true = the
 // corpus-streaming pass serves every active ids-mode query, false = per-pair gather.
 __device__ __forceinline__ bool dense_round(const unsigned long long* pairs_r,
                                             unsigned long long thr) {
-    return pairs_r != nullptr && *pairs_r > thr;
+    return pairs_r != nullptr && pair_count(*pairs_r) > thr;
 }
-
 
 // ---------------------------------------------------------------------------------
 // Operand fragments for the 16x16 MFMA family.  One fragment holds, for the lane's row

@@ -87,43 +87,33 @@ hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, 
 }
 
 // =====================================================================================
-// gather kernel: one wavefront per (query, document) pair.
+// gather kernels: (query, document) pairs, each document read from memory for its own query.
 //
-// The wavefront keeps the query rows it needs as B operands in registers, streams the
-// document's tokens from global memory in blocks of 16 rows (A operand, rows past the
-// end of the document repeat its last token, which cannot change a max), runs the MFMA
-// chain over d and folds the 16x16 result into a running per-column maximum.
-//   GM_REVEAL: one 16-column tile, column c < nb is query token pi[lo+c]; the epilogue
-//              merges the batch into the pair's (sum, M2).     [Algorithm 1, reveal step]
-//   GM_SCORE : TQ tiles = all T tokens; the epilogue is the row sum. [Eq. (2); rescore]
-//   GM_CELLS : TQ tiles = all T tokens; the epilogue stores the pair's T cells in the
-//              query's cell cache, merges this round's batch from them and turns the
-//              list entry into a cache slot.  A gathered reveal is bound by the bytes of
-//              the document, not by the cells computed from them, so a document is
-//              visited once and the later rounds (and the rescore) read its cells back;
-//              the order in which cells are REVEALED to the bounds is unchanged.
-// Which queries a launch serves (uniform per query, from QueryCtl):
-//   GM_REVEAL: active, ids mode, and (implicit or count > cache_cap)
-//   GM_CELLS : active, ids mode, not implicit, count <= cache_cap
-//   GM_SCORE : ctl == nullptr (all documents) or ids mode
+// A wavefront keeps the query rows it needs as B operands in registers, streams document tokens
+// from global memory in blocks of 16 rows (A operand, rows past the end of the document repeat its
+// last token, which cannot change a max), runs the MFMA chain over d and folds the 16x16 result
+// into a running per-column maximum.
+//   k_gather_round     the reveal of one round (Algorithm 1, reveal step), see there
+//   k_gather_survivors exact scores of the survivors (Eq. (2); rescore)
+//   k_gather_all       all documents of all queries (fp32, and widths that only gather)
 // =====================================================================================
-enum { GM_REVEAL = 0, GM_SCORE = 1, GM_CELLS = 2 };
-
 struct GatherArgs {
     const void* Q;
     const void* docs;
     const int64_t* off;
     int64_t N, total;
-    int T;
-    const QueryCtl* ctl;      // nullptr: every query scores all N documents
+    int nq, T;
+    const QueryCtl* ctl;
     int32_t* list0;
     int32_t* list1;
     // reveal
     const int32_t* pi;
     int lo, nb, n_prev, G;
     float2* stat;
-    const unsigned long long* pairs_r;   // see dense_round(); nullptr: always gather
-    unsigned long long dense_thr;
+    const unsigned long long* pairs_r;   // pairs of the round (pair_count); nullptr: all N documents of
+                                         // every query
+    const unsigned long long* work;      // its queries (work_item)
+    unsigned long long dense_thr;        // ~0: this round cannot be a corpus pass
     // cell cache
     int cache_cap, TP;
     int32_t* cid;
@@ -132,190 +122,376 @@ struct GatherArgs {
     // score
     float* out;
     float* cells;
-    int score_slots;          // GM_SCORE: also serve queries whose list holds cache slots
+    int score_slots;          // also serve queries whose list holds cache slots
     // int8 codes: a cell is the integer maximum times qscale[q] * dscale[0]
     const float* qscale;
     const float* dscale;
 };
 
-template <typename Tag, int D, int TQ, int MODE>
-__global__ __launch_bounds__(256) void k_gather(GatherArgs A) {
-    using F = Frag<Tag, D>;
-    using V = typename F::val_t;
-    constexpr bool CODES = !__is_same(V, float);
-    const int q = blockIdx.y;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int col = lane & 15;
-    const int kg = lane >> 4;
-    const size_t row_bytes = (size_t)D * F::ELEM_BYTES;
-
-    int count = (int)A.N;
-    int32_t* list = nullptr;
-    const int32_t* slot_ids = nullptr;      // list entries are cache slots: slot -> document id
-    if (MODE != GM_SCORE && dense_round(A.pairs_r, A.dense_thr)) return;   // the dense pass serves it
-    if (A.ctl) {
-        const QueryCtl c = A.ctl[q];
-        if (c.mode != 0 && !(MODE == GM_SCORE && A.score_slots)) return;
-        if (c.mode != 0) slot_ids = A.cid + (size_t)q * A.cache_cap;
-        if (MODE != GM_SCORE && !c.active) return;
-        const bool cacheable = !c.implicit && c.count <= A.cache_cap;
-        if (MODE == GM_REVEAL && cacheable) return;
-        if (MODE == GM_CELLS && !cacheable) return;
-        count = c.count;
-        if (!c.implicit) list = (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+// Folds the blocks first, first + stride, ... of the document [o0, o1) into h.
+template <int ROWB, int NT, class F>
+__device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o1, int first, int stride,
+                                         int col, int kg, const F (&bq)[NT], typename F::val_t (&h)[NT]) {
+    int64_t r0 = o0 + 16 * first;
+    if (r0 >= o1) return;
+    auto load = [&](F& a, int64_t r) {
+        int64_t row = r + col;
+        row = row < o1 ? row : o1 - 1;
+        a.load(docs + (size_t)row * ROWB, kg);
+    };
+    // A second block in flight where its registers do not cost a wavefront per SIMD.
+    constexpr int A_REGS = (int)sizeof(F) / 4;
+    constexpr bool AHEAD = (NT + 2) * A_REGS + 8 * NT <= 112;
+    F a;
+    load(a, r0);
+    for (;;) {
+        const int64_t r1 = r0 + 16 * stride;
+        const bool more = r1 < o1;
+        F next;
+        if (AHEAD && more) load(next, r1);
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) {
+            typename F::acc_t acc = {0, 0, 0, 0};
+            F::mma(acc, a, bq[tt]);
+            h[tt] = fold_max(h[tt], acc);
+        }
+        if (!more) return;
+        if (AHEAD) a = next;
+        else load(a, r1);
+        r0 = r1;
     }
-    const int first = blockIdx.x * 4 + wave;
-    if (first >= count) return;
+}
 
-    // query rows -> B fragments
-    F bq[TQ];
-    const char* Qq = (const char*)A.Q + (size_t)q * A.T * row_bytes;
+// Cross-lane column maxima of one document, decoded to float cells.  parts > 1: the four
+// wavefronts of the workgroup hold maxima of different blocks of it, which are combined through
+// `ex`; then only wavefront 0's result counts.  Two barriers (parts > 1 is uniform).
+constexpr int EX_FLOATS = 3 * 2 * 64;
+template <int NT, class V>
+__device__ __forceinline__ void doc_cells(const V (&h)[NT], int parts, float scale, int* ex,
+                                          float (&w)[Pack<NT>::NW]) {
+    using P = Pack<NT>;
+    V wi[P::NW];
+    P::colmax(h, wi);
+    if (parts > 1) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        if (wave > 0) {
+#pragma unroll
+            for (int j = 0; j < P::NW; ++j) ex[((wave - 1) * P::NW + j) * 64 + lane] = __builtin_bit_cast(int, wi[j]);
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int j = 0; j < P::NW; ++j)
+                    wi[j] = vmax(wi[j], __builtin_bit_cast(V, ex[(s * P::NW + j) * 64 + lane]));
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < P::NW; ++j) {
+        if constexpr (__is_same(V, float)) w[j] = wi[j];
+        else w[j] = (float)wi[j] * scale;
+    }
+}
+
+__device__ __forceinline__ void doc_range(const GatherArgs& A, int id, int64_t& o0, int64_t& o1) {
+    o0 = A.off[id];
+    o1 = A.off[id + 1];
+    o0 = o0 < 0 ? 0 : (o0 > A.total ? A.total : o0);
+    o1 = o1 < o0 ? o0 : (o1 > A.total ? A.total : o1);
+}
+
+// the T rows of a query as the B operands of TQ column tiles
+template <class F, int ROWB, int TQ>
+__device__ __forceinline__ void load_query(const GatherArgs& A, int q, int col, int kg, F (&bq)[TQ]) {
+    const char* Qq = (const char*)A.Q + (size_t)q * A.T * ROWB;
 #pragma unroll
     for (int tt = 0; tt < TQ; ++tt) {
-        int trow;
-        if (MODE == GM_REVEAL) {
-            trow = A.pi[(size_t)q * A.T + A.lo + (col < A.nb ? col : 0)];
-        } else {
-            const int t = tt * 16 + col;
-            trow = t < A.T ? t : 0;
+        const int t = tt * 16 + col;
+        bq[tt].load(Qq + (size_t)(t < A.T ? t : 0) * ROWB, kg);
+    }
+}
+
+constexpr int64_t ALL_DOCS = 64;
+
+// One round's reveal.  The round's pairs (over all queries that hold ids) are spread evenly over
+// the grid whatever the lengths of the lists: worker w of W takes pairs [w * per, (w + 1) * per).  Up
+// to one pair per workgroup, the four wavefronts share the pair's blocks (few pairs: the
+// time is the latency of one document: 64 queries x 9 pairs of 106 tokens 30 -> 9 us); beyond, each
+// wavefront takes pairs of its own.  What happens to a pair depends on its query:
+//   list longer than the cell cache   one 16-column tile, column c < nb is query token pi[lo+c]; the
+//                  epilogue merges the batch into the pair's (sum, M2).
+//   list that fits the cell cache     TQ tiles = all T tokens; the epilogue stores the pair's T
+//                  cells in the query's cell cache, merges this round's batch from them and turns the
+//                  list entry into a cache slot.  A gathered reveal is bound by the bytes of the
+//                  document, not by the cells computed from them, so a document is visited once
+//                  and the later rounds (and the rescore) read its cells back; the order in which
+//                  cells are REVEALED to the bounds is unchanged.
+template <typename Tag, int D, int TQ>
+__global__ __launch_bounds__(256) void k_gather_round(GatherArgs A) {
+    using F = Frag<Tag, D>;
+    using V = typename F::val_t;
+    constexpr int ROWB = D * F::ELEM_BYTES;
+    __shared__ int ex[EX_FLOATS];
+    if (A.dense_thr != ~0ull && dense_round(A.pairs_r, A.dense_thr)) return;   // the corpus pass serves it
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int col = lane & 15;
+    const int kg = lane >> 4;
+
+    const unsigned long long head = A.pairs_r ? *A.pairs_r : (unsigned long long)A.nq * (unsigned long long)A.N;
+    const long long total = (long long)(A.pairs_r ? pair_count(head) : head);
+    const int n_work = A.pairs_r ? (int)work_count(head) : A.nq;
+    const bool coop = total <= (long long)gridDim.x;
+    const int parts = coop ? 4 : 1;
+    const long long workers = coop ? gridDim.x : 4ll * gridDim.x;
+    const long long me = coop ? (long long)blockIdx.x : (long long)blockIdx.x * 4 + wave;
+    const long long per = (total + workers - 1) / workers;
+    long long x = me * per;
+    const long long x_end = x + per < total ? x + per : total;
+    if (x >= x_end) return;                         // in shared mode the same for the whole workgroup
+
+    // the last query whose first pair is not beyond x: 64 probes at a time
+    int item = 0;
+    if (A.pairs_r) {
+        int n = n_work;
+        while (n > 1) {
+            const int step = (n + 63) / 64;
+            const bool in = lane * step < n;
+            const long long s = in ? (long long)work_start(A.work[item + lane * step]) : 0;
+            const int hit = __popcll(__ballot(in && s <= x));       // >= 1: the item at hand starts at or before x
+            item += (hit - 1) * step;
+            n -= (hit - 1) * step;
+            n = n < step ? n : step;
         }
-        bq[tt].load(Qq + (size_t)trow * row_bytes, kg);
+    }
+    // round 1: all documents of all queries, ALL_DOCS of them for every query in turn, so that the
+    // queries that read a document do so at about the same time
+    int64_t block = 0, block_docs = 0;
+    auto at_block = [&](int64_t b) {
+        block = b;
+        block_docs = A.N - b * ALL_DOCS < ALL_DOCS ? A.N - b * ALL_DOCS : ALL_DOCS;
+    };
+    if (!A.pairs_r) {
+        at_block(x / (ALL_DOCS * A.nq));
+        item = (int)((x - block * ALL_DOCS * A.nq) / block_docs);
     }
 
-    const int stride = gridDim.x * 4;
-    for (int k = first; k < count; k += stride) {
-        int id = list ? list[k] : k;
-        if (slot_ids) id = slot_ids[id];
-        int64_t o0 = A.off[id], o1 = A.off[id + 1];
-        o0 = o0 < 0 ? 0 : (o0 > A.total ? A.total : o0);
-        o1 = o1 < o0 ? o0 : (o1 > A.total ? A.total : o1);
-
-        V h[TQ];
-#pragma unroll
-        for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-
-        // One block of 16 rows in flight per wavefront: the many wavefronts a CU holds already
-        // fill the memory system (a deeper per-wavefront pipeline - two blocks and the next
-        // pair's offsets in flight - was measured and changed neither the time nor the traffic).
-        for (int64_t r0 = o0; r0 < o1; r0 += 16) {
-            int64_t row = r0 + col;
-            row = row < o1 ? row : o1 - 1;
-            F a;
-            a.load((const char*)A.docs + (size_t)row * row_bytes, kg);
-#pragma unroll
-            for (int tt = 0; tt < TQ; ++tt) {
-                typename F::acc_t acc = {0, 0, 0, 0};
-                F::mma(acc, a, bq[tt]);
-                h[tt] = fold_max(h[tt], acc);
-            }
-        }
-
-        // cross-lane column maxima, decoded to float cells
-        constexpr int NWQ = Pack<MODE == GM_REVEAL ? 1 : TQ>::NW;
-        float w[NWQ];
-        if constexpr (CODES) {
-            V wi[NWQ];
-            Pack<MODE == GM_REVEAL ? 1 : TQ>::colmax(h, wi);
-            const float scale = A.qscale[q] * A.dscale[0];
-#pragma unroll
-            for (int j = 0; j < NWQ; ++j) w[j] = (float)wi[j] * scale;
+    for (; x < x_end; ++item) {
+        int q, k, k_end;
+        if (A.pairs_r) {
+            const unsigned long long it = A.work[item];
+            q = work_query(it);
+            const long long first = (long long)work_start(it);
+            const int n = A.ctl[q].count;
+            k = (int)(x - first);
+            k_end = x_end - first < n ? (int)(x_end - first) : n;
         } else {
-            Pack<MODE == GM_REVEAL ? 1 : TQ>::colmax(h, w);
-        }
-
-        if constexpr (MODE == GM_REVEAL) {
-            float sb, m2b;
-            batch_stats(w[0], col % A.G, A.nb, A.G, sb, m2b);
-            if (lane == 0) {
-                const size_t x = (size_t)q * A.N + id;
-                float2 st = make_float2(0.f, 0.f);
-                if (A.n_prev > 0) st = A.stat[x];
-                merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
-                A.stat[x] = st;
+            if (item == A.nq) {
+                at_block(block + 1);
+                item = 0;
             }
-        } else if constexpr (MODE == GM_CELLS) {
+            q = item;
+            const long long first = block * ALL_DOCS * A.nq + item * block_docs;   // pair of the block's first document
+            const int64_t d0 = block * ALL_DOCS;
+            k = (int)(d0 + (x - first));
+            k_end = (int)(d0 + (x_end - first < block_docs ? x_end - first : block_docs));
+        }
+        x += k_end - k;
+        const QueryCtl c = A.ctl[q];
+        const int count = c.count;
+        int32_t* list = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+        const float scale = A.qscale ? A.qscale[q] * A.dscale[0] : 1.f;
+        if (!list || count > A.cache_cap) {
+            F bq[1];
+            const int trow = A.pi[(size_t)q * A.T + A.lo + (col < A.nb ? col : 0)];
+            bq[0].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg);
+            for (; k < k_end; ++k) {
+                const int id = list ? list[k] : k;
+                int64_t o0, o1;
+                doc_range(A, id, o0, o1);
+                V h[1] = {lowest_val<V>()};
+                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, h);
+                float w[1];
+                doc_cells(h, parts, scale, ex, w);
+                float sb, m2b;
+                batch_stats(w[0], col % A.G, A.nb, A.G, sb, m2b);
+                if (lane == 0 && (!coop || wave == 0)) {
+                    const size_t at = (size_t)q * A.N + id;
+                    float2 st = make_float2(0.f, 0.f);
+                    if (A.n_prev > 0) st = A.stat[at];
+                    merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
+                    A.stat[at] = st;
+                }
+            }
+        } else {
             using P = Pack<TQ>;
+            F bq[TQ];
+            load_query<F, ROWB, TQ>(A, q, col, kg, bq);
             const int row = lane >> 4;
-            const size_t slot = (size_t)q * A.cache_cap + k;
-            float* crow = A.ccell + slot * A.TP;
-#pragma unroll
-            for (int j = 0; j < P::NW; ++j)
-                if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
             // this round's batch: slot s (lane s of row 0) fetches cell pi[lo+s] from its owner
-            const int sl = lane < A.nb ? lane : 0;
-            const int t = A.pi[(size_t)q * A.T + A.lo + sl];
+            const int t = A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
             const int tile = t >> 4;
             const int src = P::row_of_tile(tile) * 16 + (t & 15);
-            float v = __shfl(w[0], src);
-            if constexpr (P::NW > 1) {
-                const float v1 = __shfl(w[1], src);
-                v = tile >= 4 ? v1 : v;
-            }
-            float sb, m2b;
-            batch_stats(v, col % A.G, A.nb, A.G, sb, m2b);
-            if (lane == 0) {
-                float2 st = A.stat[(size_t)q * A.N + id];
-                merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
-                A.cstat[slot] = st;
-                A.cid[slot] = id;
-                list[k] = k;          // the entry now names its cache slot
-            }
-        } else {
-            using SC = Score<TQ, TQ>;
-            float sc[SC::NS];
-            SC::finish(w, A.T, col, sc);
-            if (lane == 0) A.out[(size_t)q * A.N + (A.ctl ? k : id)] = sc[0];
-            if (A.cells) {
-                const int row = lane >> 4;
+            for (; k < k_end; ++k) {
+                const int id = list[k];
+                int64_t o0, o1;
+                doc_range(A, id, o0, o1);
+                V h[TQ];
 #pragma unroll
-                for (int j = 0; j < SC::NW; ++j) {
-                    const int t = Pack<TQ>::tile_of_row(j, row) * 16 + col;
-                    if (Pack<TQ>::row_is_primary(row) && t < A.T)
-                        A.cells[((size_t)q * A.N + id) * A.T + t] = w[j];
+                for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
+                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, h);
+                float w[P::NW];
+                doc_cells(h, parts, scale, ex, w);
+                if (coop && wave > 0) continue;
+                const size_t slot = (size_t)q * A.cache_cap + k;
+                float* crow = A.ccell + slot * A.TP;
+#pragma unroll
+                for (int j = 0; j < P::NW; ++j)
+                    if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
+                float v = __shfl(w[0], src);
+                if constexpr (P::NW > 1) {
+                    const float v1 = __shfl(w[1], src);
+                    v = tile >= 4 ? v1 : v;
+                }
+                float sb, m2b;
+                batch_stats(v, col % A.G, A.nb, A.G, sb, m2b);
+                if (lane == 0) {
+                    float2 st = A.stat[(size_t)q * A.N + id];
+                    merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
+                    A.cstat[slot] = st;
+                    A.cid[slot] = id;
+                    list[k] = k;          // the entry now names its cache slot
                 }
             }
         }
     }
 }
 
-template <typename Tag, int D, int MODE>
-static hipError_t gather_tq(const GatherArgs& A, dim3 grid, hipStream_t st) {
+// Exact scores of the survivors of the queries whose list holds ids (score_slots: of all), by
+// list position; a workgroup per pair, its wavefronts share the document's blocks (survivors are
+// few: latency).  128 queries x 10 pairs of 106 tokens that no cache holds: 87 us with a
+// wavefront per pair and one block in flight, 12 us so; 64 queries x 10 pages of 1,030 tokens 81 -> 18.
+template <typename Tag, int D, int TQ>
+__global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
+    using F = Frag<Tag, D>;
+    using V = typename F::val_t;
+    constexpr int ROWB = D * F::ELEM_BYTES;
+    __shared__ int ex[EX_FLOATS];
+    const int q = blockIdx.y;
+    const QueryCtl c = A.ctl[q];
+    if (c.mode != 0 && !A.score_slots) return;
+    if ((int)blockIdx.x >= c.count) return;
+    const int32_t* slot_ids = c.mode != 0 ? A.cid + (size_t)q * A.cache_cap : nullptr;
+    const int32_t* list = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int col = lane & 15;
+    const int kg = lane >> 4;
+    F bq[TQ];
+    load_query<F, ROWB, TQ>(A, q, col, kg, bq);
+    for (int k = blockIdx.x; k < c.count; k += gridDim.x) {
+        int id = list ? list[k] : k;
+        if (slot_ids) id = slot_ids[id];
+        int64_t o0, o1;
+        doc_range(A, id, o0, o1);
+        V h[TQ];
+#pragma unroll
+        for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
+        fold_doc<ROWB>((const char*)A.docs, o0, o1, wave, 4, col, kg, bq, h);
+        float w[Pack<TQ>::NW];
+        doc_cells(h, 4, 1.f, ex, w);
+        using SC = Score<TQ, TQ>;
+        float sc[SC::NS];
+        SC::finish(w, A.T, col, sc);
+        if (lane == 0 && wave == 0) A.out[(size_t)q * A.N + k] = sc[0];
+    }
+}
+
+// All documents of all queries, a wavefront per pair.
+template <typename Tag, int D, int TQ>
+__global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
+    using F = Frag<Tag, D>;
+    using V = typename F::val_t;
+    constexpr int ROWB = D * F::ELEM_BYTES;
+    const int q = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int col = lane & 15;
+    const int kg = lane >> 4;
+    const int first = blockIdx.x * 4 + wave;
+    if (first >= (int)A.N) return;
+    F bq[TQ];
+    load_query<F, ROWB, TQ>(A, q, col, kg, bq);
+    for (int id = first; id < (int)A.N; id += gridDim.x * 4) {
+        int64_t o0, o1;
+        doc_range(A, id, o0, o1);
+        V h[TQ];
+#pragma unroll
+        for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
+        fold_doc<ROWB>((const char*)A.docs, o0, o1, 0, 1, col, kg, bq, h);
+        float w[Pack<TQ>::NW];
+        doc_cells(h, 1, 1.f, nullptr, w);
+        using SC = Score<TQ, TQ>;
+        float sc[SC::NS];
+        SC::finish(w, A.T, col, sc);
+        if (lane == 0) A.out[(size_t)q * A.N + id] = sc[0];
+        if (A.cells) {
+            const int row = lane >> 4;
+#pragma unroll
+            for (int j = 0; j < SC::NW; ++j) {
+                const int t = Pack<TQ>::tile_of_row(j, row) * 16 + col;
+                if (Pack<TQ>::row_is_primary(row) && t < A.T) A.cells[((size_t)q * A.N + id) * A.T + t] = w[j];
+            }
+        }
+    }
+}
+
+enum { GM_ROUND = 0, GM_SURVIVORS = 1, GM_ALL = 2 };
+
+template <typename Tag, int D, int TQ>
+static hipError_t gather_mode(const GatherArgs& A, int mode, dim3 grid, hipStream_t st) {
     const dim3 block(256);
-    const int tq = (A.T + 15) / 16;
-    if (tq <= 1) k_gather<Tag, D, 1, MODE><<<grid, block, 0, st>>>(A);
-    else if (tq <= 2) k_gather<Tag, D, 2, MODE><<<grid, block, 0, st>>>(A);
-    else if (tq <= 4) k_gather<Tag, D, 4, MODE><<<grid, block, 0, st>>>(A);
-    else if constexpr (Tag::wide) k_gather<Tag, D, 8, MODE><<<grid, block, 0, st>>>(A);
-    else return hipErrorInvalidValue;
+    if (mode == GM_ROUND) k_gather_round<Tag, D, TQ><<<grid, block, 0, st>>>(A);
+    else if constexpr (!__is_same(Tag, i8_tag)) {   // scores come from the stored embeddings
+        if (mode == GM_SURVIVORS) k_gather_survivors<Tag, D, TQ><<<grid, block, 0, st>>>(A);
+        else k_gather_all<Tag, D, TQ><<<grid, block, 0, st>>>(A);
+    } else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 template <typename Tag, int D>
-static hipError_t gather_dispatch(const GatherArgs& A, int mode, int nq, int64_t max_count,
-                                  hipStream_t st) {
-    // Workgroups per query: enough for every pair of a short list to have its own wavefront, at
-    // most 256.  (Capping the total over all queries makes the many launches that find nothing
-    // to do end sooner, but starves the few queries with long lists when the list lengths are
-    // uneven: 256 queries at alpha_ef = 0.5, K = 1 went from 5.5 to 7.6 ms.)
-    int gx = (int)((max_count + 3) / 4);
-    if (gx > 256) gx = 256;
-    if (gx < 1) gx = 1;
-    const dim3 grid(gx, nq);
-    if (mode == GM_REVEAL) {
-        k_gather<Tag, D, 1, GM_REVEAL><<<grid, dim3(256), 0, st>>>(A);
-        return hipGetLastError();
-    }
-    if (mode == GM_CELLS) return gather_tq<Tag, D, GM_CELLS>(A, grid, st);
-    return gather_tq<Tag, D, GM_SCORE>(A, grid, st);
+static hipError_t gather_tq(const GatherArgs& A, int mode, dim3 grid, hipStream_t st) {
+    const int tq = (A.T + 15) / 16;
+    if (tq <= 1) return gather_mode<Tag, D, 1>(A, mode, grid, st);
+    if (tq <= 2) return gather_mode<Tag, D, 2>(A, mode, grid, st);
+    if (tq <= 4) return gather_mode<Tag, D, 4>(A, mode, grid, st);
+    if constexpr (Tag::wide) return gather_mode<Tag, D, 8>(A, mode, grid, st);
+    return hipErrorInvalidValue;
 }
 
-static void fill_gather_common(GatherArgs& A, const Problem& P, const Work& W) {
+template <typename Tag>
+static hipError_t gather_by_d(const GatherArgs& A, int mode, int d, dim3 grid, hipStream_t st) {
+    if (d == 128) return gather_tq<Tag, 128>(A, mode, grid, st);
+    if (d == 64) return gather_tq<Tag, 64>(A, mode, grid, st);
+    // widths that only the gather kernels cover (the int8 MFMA contracts 64 elements at a time)
+    if constexpr (!__is_same(Tag, i8_tag)) {
+        if (d == 96) return gather_tq<Tag, 96>(A, mode, grid, st);
+        if (d == 32) return gather_tq<Tag, 32>(A, mode, grid, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+// co != nullptr: the reveal reads the int8 codes instead of the stored embeddings
+static hipError_t gather_any(GatherArgs& A, int mode, const Problem& P, const Work& W, dim3 grid,
+                             const Coarse* co, hipStream_t st) {
     A.Q = P.Q;
     A.docs = P.docs;
     A.off = P.off;
     A.N = P.N;
     A.total = P.total;
+    A.nq = P.nq;
     A.T = P.T;
     A.list0 = W.list[0];
     A.list1 = W.list[1];
@@ -326,115 +502,68 @@ static void fill_gather_common(GatherArgs& A, const Problem& P, const Work& W) {
     A.cid = W.cid;
     A.cstat = W.cstat;
     A.ccell = W.ccell;
-}
-
-template <typename Tag>
-static hipError_t gather_by_d(const GatherArgs& A, int mode, const Problem& P, int64_t max_count,
-                              hipStream_t st) {
-    if (P.d == 128) return gather_dispatch<Tag, 128>(A, mode, P.nq, max_count, st);
-    if (P.d == 64) return gather_dispatch<Tag, 64>(A, mode, P.nq, max_count, st);
-    // widths that only the gather kernels cover (the int8 MFMA contracts 64 elements at a time)
-    if constexpr (!__is_same(Tag, i8_tag)) {
-        if (P.d == 96) return gather_dispatch<Tag, 96>(A, mode, P.nq, max_count, st);
-        if (P.d == 32) return gather_dispatch<Tag, 32>(A, mode, P.nq, max_count, st);
-    }
-    return hipErrorInvalidValue;
-}
-
-static void fill_round(GatherArgs& A, const Work& W, const RevealRound& rr) {
-    A.pairs_r = rr.dense_thr == ~0ull ? nullptr : W.pairs + rr.r;
-    A.dense_thr = rr.dense_thr;
-    A.lo = rr.lo;
-    A.nb = rr.nb;
-    A.n_prev = rr.n_prev;
-    A.G = 1;
-    while (A.G < rr.nb) A.G <<= 1;
-}
-
-// co != nullptr: the reveal reads the int8 codes instead of the stored embeddings
-static hipError_t gather_any(GatherArgs& A, int mode, const Problem& P, int64_t max_count,
-                             const Coarse* co, hipStream_t st) {
     if (co) {
         A.Q = co->Q8;
         A.docs = co->docs8;
         A.qscale = co->qscale;
         A.dscale = co->dscale;
-        return gather_by_d<i8_tag>(A, mode, P, max_count, st);
+        return gather_by_d<i8_tag>(A, mode, P.d, grid, st);
     }
-    return P.dt == DT_BF16 ? gather_by_d<bf16_tag>(A, mode, P, max_count, st)
-                           : gather_by_d<f32_tag>(A, mode, P, max_count, st);
+    return P.dt == DT_BF16 ? gather_by_d<bf16_tag>(A, mode, P.d, grid, st)
+                           : gather_by_d<f32_tag>(A, mode, P.d, grid, st);
 }
 
-hipError_t launch_gather_reveal(const Problem& P, const Work& W, const RevealRound& rr,
-                                const Coarse* co, hipStream_t st) {
+// Workgroups of a round's gather: enough that the hardware's dispatch evens out documents of
+// different lengths (eight or more per CU and several turns of them), few enough that a round
+// without pairs ends at once (8,192: 4.7 us; 256 per query at 128 queries: 9 us).
+constexpr long long GATHER_BLOCKS = 8192;
+
+hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, const Coarse* co,
+                               hipStream_t st) {
     GatherArgs A{};
-    fill_gather_common(A, P, W);
     A.ctl = W.ctl;
-    fill_round(A, W, rr);
-    return gather_any(A, GM_REVEAL, P, P.N, co, st);
+    A.lo = rr.lo;
+    A.nb = rr.nb;
+    A.n_prev = rr.n_prev;
+    A.G = 1;
+    while (A.G < rr.nb) A.G <<= 1;
+    A.pairs_r = rr.r == 1 ? nullptr : W.pairs + rr.r;
+    A.work = W.work;
+    A.dense_thr = rr.dense_thr;
+    const long long most = (long long)P.nq * P.N;
+    return gather_any(A, GM_ROUND, P, W, dim3((unsigned)(most < GATHER_BLOCKS ? most : GATHER_BLOCKS)), co, st);
 }
 
-hipError_t launch_gather_cells(const Problem& P, const Work& W, const RevealRound& rr,
-                               const Coarse* co, hipStream_t st) {
-    if (W.cache_cap <= 0) return hipSuccess;
+hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,
+                                   bool score_slots, hipStream_t st) {
     GatherArgs A{};
-    fill_gather_common(A, P, W);
     A.ctl = W.ctl;
-    fill_round(A, W, rr);
-    return gather_any(A, GM_CELLS, P, W.cache_cap, co, st);
+    A.out = out;
+    A.score_slots = score_slots ? 1 : 0;
+    // most queries end with at most K + M survivors
+    const int64_t want = (int64_t)kn.K + kn.M < 256 ? (int64_t)kn.K + kn.M : 256;
+    return gather_any(A, GM_SURVIVORS, P, W, dim3((unsigned)(P.N < want ? P.N : want), P.nq), nullptr, st);
 }
 
-hipError_t launch_gather_score(const Problem& P, const Work& W, bool use_ctl, float* out,
-                               float* cells, bool score_slots, hipStream_t st) {
+hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float* cells, hipStream_t st) {
     GatherArgs A{};
-    fill_gather_common(A, P, W);
-    A.ctl = use_ctl ? W.ctl : nullptr;
     A.out = out;
     A.cells = cells;
-    A.score_slots = score_slots ? 1 : 0;
-    return gather_any(A, GM_SCORE, P, P.N, nullptr, st);
+    const int64_t gx = (P.N + 3) / 4;
+    return gather_any(A, GM_ALL, P, W, dim3((unsigned)(gx < 256 ? gx : 256), P.nq), nullptr, st);
 }
 
-// Exact scores of cached survivors: the T cells of a slot are laid out as the column
-// maxima of TQ tiles and summed by the same routine as everywhere else (same bits).
-struct CachedScoreArgs {
-    const QueryCtl* ctl;
-    const int32_t* list0;
-    const int32_t* list1;
-    const float* ccell;
-    int64_t N;
-    int T, TP, cache_cap;
-    float* out;
-};
-
+// Exact score of a survivor from its cached cells: the T cells of a slot are laid out as the
+// column maxima of TQ tiles and summed by the same routine as everywhere else (same bits).
 template <int TQ>
-__global__ __launch_bounds__(256) void k_cached_score(CachedScoreArgs A) {
-    const int q = blockIdx.y;
-    const QueryCtl c = A.ctl[q];
-    if (c.mode != 1) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15;
-    const int32_t* list = (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+__device__ __forceinline__ float cached_score(const float* crow, int T) {
+    const int col = threadIdx.x & 15;
     using SC = Score<TQ, TQ>;
-    for (int k = blockIdx.x * 4 + wave; k < c.count; k += gridDim.x * 4) {
-        const float* crow = A.ccell + ((size_t)q * A.cache_cap + list[k]) * A.TP;
-        float h[TQ], w[SC::NW], sc[SC::NS];
+    float h[TQ], w[SC::NW], sc[SC::NS];
 #pragma unroll
-        for (int tt = 0; tt < TQ; ++tt) h[tt] = crow[tt * 16 + col];
-        SC::run(h, A.T, col, w, sc);
-        if (lane == 0) A.out[(size_t)q * A.N + k] = sc[0];
-    }
-}
-
-hipError_t launch_cached_score(const Problem& P, const Work& W, float* out, hipStream_t st) {
-    if (W.cache_cap <= 0) return hipSuccess;
-    CachedScoreArgs A{W.ctl, W.list[0], W.list[1], W.ccell, P.N, P.T, W.TP, W.cache_cap, out};
-    const dim3 grid(16, P.nq), block(256);
-    const int tq = (P.T + 15) / 16;
-    if (tq <= 1) k_cached_score<1><<<grid, block, 0, st>>>(A);
-    else if (tq <= 2) k_cached_score<2><<<grid, block, 0, st>>>(A);
-    else if (tq <= 4) k_cached_score<4><<<grid, block, 0, st>>>(A);
-    else k_cached_score<8><<<grid, block, 0, st>>>(A);
-    return hipGetLastError();
+    for (int tt = 0; tt < TQ; ++tt) h[tt] = crow[tt * 16 + col];
+    SC::run(h, T, col, w, sc);
+    return sc[0];
 }
 
 // =====================================================================================
@@ -827,6 +956,7 @@ struct SelArgs {
     float2* stat;
     const float2* stat2;
     unsigned long long* pairs;           // [R+2] pairs, then [R+2] document tokens of those pairs
+    unsigned long long* work;            // [nq] queries of the next round
     const int64_t* off;                  // document offsets (token counts of the kept pairs)
     int R;
     unsigned long long dense_thr;        // ~0: this round cannot be a dense one
@@ -928,19 +1058,22 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
     }
     if (threadIdx.x == 0) {
         A.ctl[q] = nc;
-        if (nc.active) {
-            atomicAdd(A.pairs + r + 1, (unsigned long long)nc.count);
+        if (nc.active) {                            // pairs and work item in one step: starts ascend with the items
+            const unsigned long long at = atomicAdd(A.pairs + r + 1, work_add(nc.count));
+            A.work[work_count(at)] = work_item(q, pair_count(at));
             atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
         }
     }
 }
 
 // The rounds of a query whose ncand <= SEL_REGS * SEL_THREADS candidates fit the registers, from
-// round r on.
-__device__ __forceinline__ void prune_regs(const SelArgs& A, int q, int count, QueryCtl nc,
+// round r on.  Returns true when they are done; false when cached rounds remain and at most half of the
+// places that the list takes in each thread are still needed: then r is the next round, ncand the
+// length of the list in `out`, and the statistics are stored.
+__device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, QueryCtl nc,
                                            const int32_t* in, int32_t* out, float2* stat, const float2* bat,
-                                           bool slots, bool fold_dense, bool segmented, int ncand,
-                                           int r, bool from_cells, SelShared& sh, const int* seg_first,
+                                           bool slots, bool fold_dense, bool segmented, int& ncand,
+                                           int& r, bool from_cells, SelShared& sh, const int* seg_first,
                                            unsigned long long* kept_tokens) {
     constexpr int E = SEL_REGS;
     const int T = A.T;
@@ -1052,10 +1185,20 @@ __device__ __forceinline__ void prune_regs(const SelArgs& A, int q, int count, Q
         const Places<E> pl(live, sh);
         nc.count = pl.total;
         if (threadIdx.x == 0) note_round(sh, r, nc.count, tau);
-        if (slots && nc.count > A.KM && r < A.R) continue;
+        const bool more = slots && nc.count > A.KM && r < A.R;
+        if (more && Spread(nc.count).span * 2 > sp.span) continue;
 #pragma unroll
         for (int u = 0; u < E; ++u)
-            if ((live >> u) & 1u) out[pl.place(u)] = e[u];
+            if ((live >> u) & 1u) {
+                out[pl.place(u)] = e[u];
+                if (more) stat[e[u]] = st[u];
+            }
+        if (more) {
+            ncand = nc.count;
+            ++r;
+            __syncthreads();                        // list and statistics are read by other threads next
+            return false;
+        }
         break;
     }
     nc.active = !slots && nc.count > A.KM;
@@ -1069,17 +1212,119 @@ __device__ __forceinline__ void prune_regs(const SelArgs& A, int q, int count, Q
             }
     }
     end_rounds(A, q, nc, r, slots, my_tokens, sh, kept_tokens);
+    return true;
 }
 
-// One round of a query with a longer list, from memory: the statistics of an entry are read three
-// times (bound, keys above it, prune).  Returns true when the query's rounds are done; false when
-// cached rounds remain: then r is the next round and ncand the length of the list in `out`.
-__device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, QueryCtl nc,
+// One round of a query whose list fits a tile but not, with its statistics, the registers: keys
+// and upper bounds are held there, entries and statistics are read again.  Returns true when the
+// query's rounds are done; false when cached rounds remain: then r is the next round and ncand the
+// length of the list in `out`.
+__device__ __forceinline__ bool prune_tile(const SelArgs& A, int q, int count, QueryCtl nc,
                                            const int32_t* in, int32_t* out, float2* stat, const float2* bat,
                                            bool slots, bool fold_dense, bool segmented, int& ncand,
-                                           int& r, bool from_cells, SelShared& sh,
+                                           int& r, bool from_cells, SelShared& sh, const int* seg_first,
                                            unsigned long long* kept_tokens) {
-    const int32_t* cid = A.cid + (size_t)q * A.cache_cap;
+    constexpr int E = SEL_E;
+    const int T = A.T;
+    const float a = A.a, b = A.b;
+    const int lo = (r - 1) * A.B;
+    const int n = lo + A.B < T ? lo + A.B : T;
+    const int nb = n - lo;
+    const float kappa = A.kappa[r];
+    const int32_t* pq = A.pi + (size_t)q * T + lo;
+    const float* cells = A.ccell + (size_t)q * A.cache_cap * A.TP;
+    const int len = seg_len(count);
+    const Spread sp(ncand);
+    const unsigned live = sp.mask<E>();
+    auto entry = [&](int u) {
+        const int i = sp.at(u);
+        return segmented ? out[segment_place(i, len, seg_first)] : (in ? in[i] : i);
+    };
+    // statistics after this round's batch; `store`: for the rounds after it
+    auto stat_of = [&](int e, bool store) {
+        float2 st = make_float2(0.f, 0.f);
+        if (!from_cells || lo > 0) st = stat[e];
+        if (from_cells) {
+            const float* crow = cells + (unsigned)(e * A.TP);
+            float sb, m2b;
+            batch_stats_thread([&](int i) { return crow[pq[i]]; }, nb, sb, m2b);
+            merge_stats(st.x, st.y, lo, sb, m2b, nb);
+        } else if (fold_dense) {
+            const float2 bb = bat[e];
+            merge_stats(st.x, st.y, lo, bb.x, bb.y, nb);
+        }
+        if (store && (from_cells || fold_dense)) stat[e] = st;
+        return st;
+    };
+    uint32_t key[E];
+    float hi[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        key[u] = 0u;
+        hi[u] = 0.f;
+        if (u * 64 < sp.span) {                     // uniform
+            const float2 st = stat_of(entry(u), (live >> u) & 1u);
+            float lcb;
+            interval(st.x, st.y, n, T, kappa, a, b, lcb, hi[u]);
+            key[u] = float_key(lcb);
+        }
+        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    const float tau = key_float(kth_largest_regs<E>(key, live, A.K, sh));
+    unsigned keep = 0;
+#pragma unroll
+    for (int u = 0; u < E; ++u) keep |= (hi[u] >= tau ? 1u : 0u) << u;
+    keep &= live;
+    const Places<E> pl(keep, sh);
+    nc.count = pl.total;
+    if (threadIdx.x == 0) note_round(sh, r, nc.count, tau);
+    if (A.tr_lcb) {
+        const size_t tro = ((size_t)(r - 1) * A.nq + q) * A.N;
+        const int32_t* cid = A.cid + (size_t)q * A.cache_cap;
+#pragma unroll 1
+        for (int u = 0; u < E; ++u)
+            if ((live >> u) & 1u) {
+                const int e = entry(u);
+                const int id = slots ? cid[e] : e;
+                const float2 st = stat[e];          // stored above
+                float lcb, ucb;
+                interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
+                A.tr_lcb[tro + id] = lcb;
+                A.tr_ucb[tro + id] = ucb;
+                A.tr_alive[tro + id] = (keep >> u) & 1u;
+            }
+    }
+    int mine[E];                                    // read before anything is written: the list may be in `out`
+#pragma unroll
+    for (int u = 0; u < E; ++u) mine[u] = entry(u);
+    __syncthreads();
+    long long my_tokens = 0;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if ((keep >> u) & 1u) {
+            out[pl.place(u)] = mine[u];
+            if (!slots) my_tokens += A.off[mine[u] + 1] - A.off[mine[u]];
+        }
+        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    if (slots && nc.count > A.KM && r < A.R) {
+        ncand = nc.count;
+        ++r;
+        __syncthreads();                            // the list is read by other threads next
+        return false;
+    }
+    nc.active = !slots && nc.count > A.KM;
+    end_rounds(A, q, nc, r, slots, my_tokens, sh, kept_tokens);
+    return true;
+}
+
+constexpr int LIST_ITEMS = 8;                      // entries per thread and trip: loads in flight
+constexpr int LIST_CHUNK = SEL_THREADS * LIST_ITEMS;
+// A round of a longer list (document ids: cached lists fit a tile; cut down by k_select_segments),
+// from memory: the statistics of an entry are read three times (bound, keys above it, prune).
+__device__ __forceinline__ void prune_list(const SelArgs& A, int q, int count, QueryCtl nc,
+                                           int32_t* out, float2* stat, const float2* bat, bool fold_dense,
+                                           int ncand, int r, SelShared& sh, unsigned long long* kept_tokens) {
     const int T = A.T;
     const float a = A.a, b = A.b;
     const int lo = (r - 1) * A.B;
@@ -1087,28 +1332,11 @@ __device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, Q
     const int nb = n - lo;
     const float kappa = A.kappa[r];
     long long my_tokens = 0;
-    if (segmented) {
-        merge_segments(out, A.seg_cnt + (size_t)q * SEG_MAX, count);
-        in = out;                                   // pruned in place below
-    }
-    auto entry = [&](int idx) { return in ? in[idx] : idx; };
-    if (from_cells) {
-        const int32_t* pq = A.pi + (size_t)q * T + lo;
-        const float* cells = A.ccell + (size_t)q * A.cache_cap * A.TP;
+    merge_segments(out, A.seg_cnt + (size_t)q * SEG_MAX, count);
+    if (fold_dense) {                        // the candidates' statistics take the round's batch
+#pragma unroll 4
         for (int idx = threadIdx.x; idx < ncand; idx += SEL_THREADS) {
-            const int e = entry(idx);
-            const float* crow = cells + (unsigned)(e * A.TP);
-            float sb, m2b;
-            batch_stats_thread([&](int i) { return crow[pq[i]]; }, nb, sb, m2b);
-            float2 st = make_float2(0.f, 0.f);
-            if (lo > 0) st = stat[e];
-            merge_stats(st.x, st.y, lo, sb, m2b, nb);
-            stat[e] = st;
-        }
-        __syncthreads();
-    } else if (fold_dense) {                        // the candidates' statistics take the round's batch
-        for (int idx = threadIdx.x; idx < ncand; idx += SEL_THREADS) {
-            const int e = entry(idx);
+            const int e = out[idx];
             float2 st = stat[e];
             const float2 bb = bat[e];
             merge_stats(st.x, st.y, lo, bb.x, bb.y, nb);
@@ -1118,7 +1346,7 @@ __device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, Q
     }
     auto key_of = [&](int idx) -> uint32_t {
         float lcb, ucb;
-        const float2 st = stat[entry(idx)];
+        const float2 st = stat[out[idx]];
         interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
         return float_key(lcb);
     };
@@ -1126,9 +1354,9 @@ __device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, Q
     const int n_sample = ncand < SEL_TILE ? ncand : SEL_TILE;
     const int run_stride = ncand < SEL_TILE ? SEL_RUN : ncand / (SEL_TILE / SEL_RUN);
     uint32_t top = 0u;
-    for (int base = 0; base < n_sample; base += SEL_CHUNK) {
+    for (int base = 0; base < n_sample; base += LIST_CHUNK) {
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u) {
+        for (int u = 0; u < LIST_ITEMS; ++u) {
             const int j = base + u * SEL_THREADS + (int)threadIdx.x;
             const uint32_t k = j < n_sample ? key_of((j / SEL_RUN) * run_stride + (j % SEL_RUN)) : 0u;
             top = k > top ? k : top;
@@ -1136,63 +1364,62 @@ __device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, Q
     }
     const uint32_t bound = lower_bound_key(top, A.K, sh);
     // the keys that reach it, then the K-th largest of those
-    for (int base = 0; base < ncand; base += SEL_CHUNK) {
-        uint32_t key[SEL_ITEMS];
+    for (int base = 0; base < ncand; base += LIST_CHUNK) {
+        uint32_t key[LIST_ITEMS];
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u) {
+        for (int u = 0; u < LIST_ITEMS; ++u) {
             const int idx = base + u * SEL_THREADS + (int)threadIdx.x;
             key[u] = idx < ncand ? key_of(idx) : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u)
+        for (int u = 0; u < LIST_ITEMS; ++u)
             collect_few(key[u], base + u * SEL_THREADS + (int)threadIdx.x < ncand && key[u] >= bound, sh);
     }
     uint32_t tkey;
     if (!kth_of_few(A.K, tkey, sh)) tkey = kth_largest_list(ncand, A.K, key_of, sh);
     const float tau = key_float(tkey);
-    // Stable compaction of {entry : UCB >= tau}, possibly in place: a chunk is read completely
+    // Stable compaction of {entry : UCB >= tau} in place: a chunk is read completely
     // before anything is written, and writes stay below the next chunk.  Software pipeline over
     // chunks: the entries are fetched two chunks ahead and their statistics one chunk ahead,
     // so the loads are in flight across this chunk's scan and its barriers.
     const size_t tro = ((size_t)(r - 1) * A.nq + q) * A.N;
-    const int t0 = threadIdx.x * SEL_ITEMS;         // SEL_ITEMS consecutive entries
+    const int t0 = threadIdx.x * LIST_ITEMS;         // LIST_ITEMS consecutive entries
     int kept = 0;
-    auto load_e = [&](int start, int (&e)[SEL_ITEMS]) {
+    auto load_e = [&](int start, int (&e)[LIST_ITEMS]) {
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u) {
+        for (int u = 0; u < LIST_ITEMS; ++u) {
             const int idx = start + t0 + u;
-            e[u] = idx < ncand ? entry(idx) : 0;
+            e[u] = idx < ncand ? out[idx] : 0;
         }
     };
-    auto load_s = [&](int start, const int (&e)[SEL_ITEMS], float2 (&st)[SEL_ITEMS]) {
+    auto load_s = [&](int start, const int (&e)[LIST_ITEMS], float2 (&st)[LIST_ITEMS]) {
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u)
+        for (int u = 0; u < LIST_ITEMS; ++u)
             st[u] = (start + t0 + u < ncand) ? stat[e[u]] : make_float2(0.f, 0.f);
     };
-    int e[SEL_ITEMS], e_next[SEL_ITEMS];
-    float2 st[SEL_ITEMS];
+    int e[LIST_ITEMS], e_next[LIST_ITEMS];
+    float2 st[LIST_ITEMS];
     load_e(0, e);
     load_s(0, e, st);
-    load_e(SEL_CHUNK, e_next);
-    for (int start = 0; start < ncand; start += SEL_CHUNK) {
+    load_e(LIST_CHUNK, e_next);
+    for (int start = 0; start < ncand; start += LIST_CHUNK) {
         const int i0 = start + t0;
-        int e_next2[SEL_ITEMS];
-        float2 st_next[SEL_ITEMS];
-        load_s(start + SEL_CHUNK, e_next, st_next);
-        load_e(start + 2 * SEL_CHUNK, e_next2);
+        int e_next2[LIST_ITEMS];
+        float2 st_next[LIST_ITEMS];
+        load_s(start + LIST_CHUNK, e_next, st_next);
+        load_e(start + 2 * LIST_CHUNK, e_next2);
         unsigned keep = 0;
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u) {
+        for (int u = 0; u < LIST_ITEMS; ++u) {
             if (i0 + u < ncand) {
                 float lcb, ucb;
                 interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, ucb);
                 const bool kp = ucb >= tau;
                 keep |= (kp ? 1u : 0u) << u;
                 if (A.tr_lcb) {
-                    const int id = slots ? cid[e[u]] : e[u];
-                    A.tr_lcb[tro + id] = lcb;
-                    A.tr_ucb[tro + id] = ucb;
-                    A.tr_alive[tro + id] = kp ? 1 : 0;
+                    A.tr_lcb[tro + e[u]] = lcb;
+                    A.tr_ucb[tro + e[u]] = ucb;
+                    A.tr_alive[tro + e[u]] = kp ? 1 : 0;
                 }
             }
         }
@@ -1200,15 +1427,15 @@ __device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, Q
             int total;
             int pos = kept + block_excl_scan(__popc(keep), sh.wtot, total);
 #pragma unroll
-            for (int u = 0; u < SEL_ITEMS; ++u)
+            for (int u = 0; u < LIST_ITEMS; ++u)
                 if (keep & (1u << u)) {
                     out[pos++] = e[u];
-                    if (!slots) my_tokens += A.off[e[u] + 1] - A.off[e[u]];
+                    my_tokens += A.off[e[u] + 1] - A.off[e[u]];
                 }
             kept += total;
         }
 #pragma unroll
-        for (int u = 0; u < SEL_ITEMS; ++u) {
+        for (int u = 0; u < LIST_ITEMS; ++u) {
             e[u] = e_next[u];
             st[u] = st_next[u];
             e_next[u] = e_next2[u];
@@ -1216,15 +1443,8 @@ __device__ __forceinline__ bool prune_list(const SelArgs& A, int q, int count, Q
     }
     nc.count = kept;
     if (threadIdx.x == 0) note_round(sh, r, kept, tau);
-    if (slots && kept > A.KM && r < A.R) {
-        ncand = kept;
-        ++r;
-        __syncthreads();                            // the list is read by other threads next
-        return false;
-    }
-    nc.active = !slots && kept > A.KM;
-    end_rounds(A, q, nc, r, slots, my_tokens, sh, kept_tokens);
-    return true;
+    nc.active = kept > A.KM;
+    end_rounds(A, q, nc, r, false, my_tokens, sh, kept_tokens);
 }
 
 // Bound by latency and instructions, not by bytes: a list that fits the registers is read once, and
@@ -1241,7 +1461,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
     int32_t* out = (out_sel ? A.list1 : A.list0) + (size_t)q * A.N;
     // entries are cache slots if the query was switched earlier (mode 1) or by this
-    // round's cell-caching gather (same rule as in k_gather)
+    // round's cell-caching gather (same rule as in k_gather_round)
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
     const bool slots = c.mode == 1 || (c.mode == 0 && !c.implicit && count <= A.cache_cap && !dense);
     float2* stat = slots ? A.cstat + (size_t)q * A.cache_cap : A.stat + (size_t)q * A.N;
@@ -1262,9 +1482,16 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     int r = A.r;
     bool from_cells = c.mode == 1;                  // this round's batch still has to be folded in
     bool seg = segmented, fold = fold_dense;
-    while (ncand > SEL_REGS * SEL_THREADS) {
-        if (prune_list(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, &kept_tokens))
-            return;
+    if (ncand > SEL_TILE) {
+        prune_list(A, q, count, nc, out, stat, bat, fold, ncand, r, sh, &kept_tokens);
+        return;
+    }
+    for (;;) {
+        const bool done =
+            ncand <= SEL_REGS * SEL_THREADS
+                ? prune_regs(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens)
+                : prune_tile(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens);
+        if (done) return;
         // cached rounds remain: on from the shorter list, into the other buffer
         from_cells = true;
         seg = fold = false;
@@ -1272,7 +1499,6 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
         nc.cur ^= 1;
         out = (nc.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     }
-    prune_regs(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens);
 }
 
 // Cheap outer estimate of interval() for the pre-filter: reciprocal multiplications and the
@@ -1352,14 +1578,13 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
 // stores the merged statistics of the survivors, the only entries that are ever read again.
 __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     __shared__ SelShared sh;
-    const int q = blockIdx.y, sg = blockIdx.x;
+    const int q = blockIdx.y;
     const QueryCtl c = A.ctl[q];
     const int count = c.count;
     if (!c.active || count <= SEL_TILE) return;     // cached lists are never this long
     const int len = seg_len(count);
-    const int lo = sg * len;
-    if (lo >= count) return;
-    const int hi = lo + len < count ? lo + len : count;
+    const int n_seg = (count + len - 1) / len;
+    if ((int)blockIdx.x >= n_seg) return;
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
@@ -1372,73 +1597,77 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     const FastBounds fb = fast_bounds_consts(n, T, kappa, a, b);
     const size_t tro = ((size_t)(A.r - 1) * A.nq + q) * A.N;
     clear_hist(sh);
-    int base = lo;
-    for (int start = lo; start < hi; start += SEG_TILE) {
-        const int left = hi - start < SEG_TILE ? hi - start : SEG_TILE;
-        const Spread sp(left);
-        const unsigned ok = sp.mask<SEG_E>();
-        float2 st[SEG_E];
-        auto at = [&](int u) { return start + sp.at(u); };
-        if (in) {
-            int e[SEG_E];
+    for (int sg = blockIdx.x; sg < n_seg; sg += gridDim.x) {
+        const int lo = sg * len;
+        const int hi = lo + len < count ? lo + len : count;
+        int base = lo;
+        for (int start = lo; start < hi; start += SEG_TILE) {
+            const int left = hi - start < SEG_TILE ? hi - start : SEG_TILE;
+            const Spread sp(left);
+            const unsigned ok = sp.mask<SEG_E>();
+            float2 st[SEG_E];
+            auto at = [&](int u) { return start + sp.at(u); };
+            if (in) {
+                int e[SEG_E];
 #pragma unroll
-            for (int u = 0; u < SEG_E; ++u) e[u] = in[at(u)];
+                for (int u = 0; u < SEG_E; ++u) e[u] = in[at(u)];
 #pragma unroll
-            for (int u = 0; u < SEG_E; ++u) st[u] = stat[e[u]];
-            if (fold) {
+                for (int u = 0; u < SEG_E; ++u) st[u] = stat[e[u]];
+                if (fold) {
+#pragma unroll
+                    for (int u = 0; u < SEG_E; ++u) {
+                        const float2 bb = bat[e[u]];
+                        merge_stats(st[u].x, st[u].y, A.n_prev, bb.x, bb.y, A.nb);
+                        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < SEG_E; ++u) st[u] = stat[at(u)];
+            }
+            uint32_t bound = (uint32_t)c.bound;
+            if (in) {
+                uint32_t top = 0u;
 #pragma unroll
                 for (int u = 0; u < SEG_E; ++u) {
-                    const float2 bb = bat[e[u]];
-                    merge_stats(st[u].x, st[u].y, A.n_prev, bb.x, bb.y, A.nb);
-                    if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    const uint32_t k = (ok >> u) & 1u ? fast_lo_key(st[u].x, st[u].y, fb) : 0u;
+                    top = k > top ? k : top;
+                }
+                bound = lower_bound_key(top, A.K, sh);
+            }
+            const float thr = key_float(bound);
+            unsigned keep = ok;
+            if (thr > -__builtin_inff()) {              // else all, also documents outside the contract
+#pragma unroll
+                for (int u = 0; u < SEG_E; ++u)
+                    if (!(fast_hi(st[u].x, st[u].y, fb) >= thr)) keep &= ~(1u << u);
+            }
+            if (A.tr_lcb) {                             // the trace records every dropped entry's interval
+#pragma unroll 1
+                for (int u = 0; u < SEG_E; ++u) {
+                    if (!(((ok & ~keep) >> u) & 1u)) continue;
+                    const int e = in ? in[at(u)] : at(u);
+                    float2 x = stat[e];
+                    if (fold) {
+                        const float2 bb = bat[e];
+                        merge_stats(x.x, x.y, A.n_prev, bb.x, bb.y, A.nb);
+                    }
+                    float lcb, ucb;
+                    interval(x.x, x.y, n, T, kappa, a, b, lcb, ucb);
+                    A.tr_lcb[tro + e] = lcb;
+                    A.tr_ucb[tro + e] = ucb;
+                    A.tr_alive[tro + e] = 0;
                 }
             }
-        } else {
-#pragma unroll
-            for (int u = 0; u < SEG_E; ++u) st[u] = stat[at(u)];
-        }
-        uint32_t bound = (uint32_t)c.bound;
-        if (in) {
-            uint32_t top = 0u;
-#pragma unroll
-            for (int u = 0; u < SEG_E; ++u) {
-                const uint32_t k = (ok >> u) & 1u ? fast_lo_key(st[u].x, st[u].y, fb) : 0u;
-                top = k > top ? k : top;
-            }
-            bound = lower_bound_key(top, A.K, sh);
-        }
-        const float thr = key_float(bound);
-        unsigned keep = ok;
-        if (thr > -__builtin_inff()) {              // else all, also documents outside the contract
+            const Places<SEG_E> pl(keep, sh);
 #pragma unroll
             for (int u = 0; u < SEG_E; ++u)
-                if (!(fast_hi(st[u].x, st[u].y, fb) >= thr)) keep &= ~(1u << u);
+                if ((keep >> u) & 1u) out[base + pl.place(u)] = in ? in[at(u)] : at(u);
+            base += pl.total;
+            __syncthreads();
         }
-        if (A.tr_lcb) {                             // the trace records every dropped entry's interval
-#pragma unroll 1
-            for (int u = 0; u < SEG_E; ++u) {
-                if (!(((ok & ~keep) >> u) & 1u)) continue;
-                const int e = in ? in[at(u)] : at(u);
-                float2 x = stat[e];
-                if (fold) {
-                    const float2 bb = bat[e];
-                    merge_stats(x.x, x.y, A.n_prev, bb.x, bb.y, A.nb);
-                }
-                float lcb, ucb;
-                interval(x.x, x.y, n, T, kappa, a, b, lcb, ucb);
-                A.tr_lcb[tro + e] = lcb;
-                A.tr_ucb[tro + e] = ucb;
-                A.tr_alive[tro + e] = 0;
-            }
-        }
-        const Places<SEG_E> pl(keep, sh);
-#pragma unroll
-        for (int u = 0; u < SEG_E; ++u)
-            if ((keep >> u) & 1u) out[base + pl.place(u)] = in ? in[at(u)] : at(u);
-        base += pl.total;
-        __syncthreads();
+        if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
     }
-    if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
 }
 
 // Segment workgroups per query: a list of any length up to N has at most this many segments
@@ -1458,6 +1687,7 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.stat = W.stat;
     A.stat2 = W.stat2;
     A.pairs = W.pairs;
+    A.work = W.work;
     A.off = P.off;
     A.R = R;
     A.dense_thr = rr.dense_thr;
@@ -1489,8 +1719,17 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.seg_cnt = W.seg_cnt;
     for (int r = 0; r <= R; ++r) A.kappa[r] = kappa[r];
     // lists that do not fit one workgroup's registers are first cut down, one workgroup per tile
-    if (P.N > SEL_TILE && rr.r == 1) k_select_sample<<<P.nq, SEL_THREADS, 0, st>>>(A);
-    if (P.N > SEL_TILE) k_select_segments<<<dim3(segments_of(P.N), P.nq), SEL_THREADS, 0, st>>>(A);
+    if (P.N > SEL_TILE) {
+        unsigned gx = segments_of(P.N);
+        if (rr.r == 1) {
+            k_select_sample<<<P.nq, SEL_THREADS, 0, st>>>(A);
+        } else {
+            // later lists are seldom long: no more workgroups than end quickly with nothing to do
+            const unsigned few = (unsigned)(2048 / P.nq > 1 ? 2048 / P.nq : 1);
+            gx = gx < few ? gx : few;
+        }
+        k_select_segments<<<dim3(gx, P.nq), SEL_THREADS, 0, st>>>(A);
+    }
     k_select_prune<<<P.nq, SEL_THREADS, 0, st>>>(A);
     return hipGetLastError();
 }
@@ -1506,7 +1745,9 @@ struct TopkArgs {
     int32_t* list1;        // for candidate positions of long inputs
     const int32_t* cid;
     int cache_cap;
-    const float* vals;     // [nq][N]
+    float* vals;           // [nq][N]; written here for survivors with exact cached cells
+    const float* ccell;    // nullptr: every value is there already
+    int T, TP;
     int64_t N;
     int K;
     int64_t* out_ids;
@@ -1575,6 +1816,18 @@ __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
             scratch = (c.cur ? A.list0 : A.list1) + (size_t)q * A.N;
         }
         if (c.mode == 1) cid = A.cid + (size_t)q * A.cache_cap;
+        if (c.mode == 1 && A.ccell) {               // a wavefront per survivor
+            float* v = A.vals + (size_t)q * A.N;
+            const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
+            for (int k = my_wave(); k < count; k += SEL_WAVES) {
+                const float* crow = rows + (size_t)list[k] * A.TP;
+                const float x = A.TP == 16 ? cached_score<1>(crow, A.T)
+                              : A.TP == 32 ? cached_score<2>(crow, A.T)
+                              : A.TP == 64 ? cached_score<4>(crow, A.T) : cached_score<8>(crow, A.T);
+                if ((threadIdx.x & 63) == 0) v[k] = x;
+            }
+            __syncthreads();
+        }
     }
     const float* vals = A.vals + (size_t)q * A.N;
     const int Kq = A.K < count ? A.K : count;
@@ -1699,7 +1952,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
     }
 }
 
-hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, const float* vals, int K,
+hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, bool cached, float* vals, int K,
                        int64_t* out_ids, float* out_scores, hipStream_t st) {
     TopkArgs A{};
     A.ctl = use_ctl ? W.ctl : nullptr;
@@ -1708,6 +1961,9 @@ hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, const floa
     A.cid = W.cid;
     A.cache_cap = W.cache_cap;
     A.vals = vals;
+    A.ccell = cached ? W.ccell : nullptr;
+    A.T = P.T;
+    A.TP = W.TP;
     A.N = P.N;
     A.K = K;
     A.out_ids = out_ids;

@@ -23,15 +23,18 @@ struct Work {
     int32_t* list[2];     // [nq][N] each: ids of the active set, ascending
     float2* stat;         // [nq][N] per (query, doc): revealed sum, centred sum of squares
     float2* stat2;        // [nq][N] batch (sum, centred squares) of a later round's dense pass
-    unsigned long long* pairs;   // [R+2] pairs[r]: (query, doc) pairs round r would have to gather;
+    unsigned long long* pairs;   // [R+2] pairs[r]: (query, doc) pairs round r would have to gather
+                                 // and the queries that hold them (pair_count, work_count);
                                  // then [R+2]: the document tokens of those pairs
+    unsigned long long* work;    // [nq] the queries of the next round (work_item)
     int32_t* seg_cnt;     // [nq][64] candidates per segment of a segmented pre-filter
     float* rescored;      // [nq][N] exact score of the k-th survivor
     float* scores;        // [nq][N] Full-MaxSim scores when the caller keeps none
     int32_t* cnt_hist;    // [(R+1)][nq]
     float* tau_hist;      // [R][nq]
     int32_t* pi;          // [nq][T]
-    int32_t* chunk_doc;   // [nchunks+1] first document of each token chunk (dense kernel)
+    int chunk_tokens;     // tokens per chunk of the dense kernel
+    int32_t* chunk_doc;   // [nchunks+1] first document of each token chunk
     int* flag;            // [64] error / scratch flags
     // cell cache of queries whose active set has shrunk to <= cache_cap documents
     int cache_cap;        // slots per query (0: caching off)
@@ -80,37 +83,33 @@ struct Knobs {
 hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
                        const int32_t* user_pi, const Trace& tr, hipStream_t st);
 
-// Reveal one batch for every active (query, doc) pair by gathering the documents.
-hipError_t launch_gather_reveal(const Problem& P, const Work& W, const RevealRound& rr,
-                                const Coarse* co, hipStream_t st);
-
-// The reveal of round rr for queries that fit the cell cache: all T cells of every active
-// document are computed once and cached; later rounds and the rescore read them back.
-hipError_t launch_gather_cells(const Problem& P, const Work& W, const RevealRound& rr,
+// Reveal round rr by gathering the documents of every active (query, document) pair.  Queries whose
+// list fits the cell cache get all T cells of their documents computed once and cached;
+// k_select_prune and the rescore read them back.
+hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr,
                                const Coarse* co, hipStream_t st);
-hipError_t launch_cached_score(const Problem& P, const Work& W, float* out, hipStream_t st);
 
-// Exact scores from the stored embeddings.  ctl == nullptr: all documents of every query,
-// written by doc id into `out` ([nq][N]); otherwise the current active set, written by list
-// position (score_slots: including the queries whose list holds cache slots, whose cached
-// cells are coarse and cannot give the exact score).
-hipError_t launch_gather_score(const Problem& P, const Work& W, bool use_ctl, float* out,
-                               float* cells, bool score_slots, hipStream_t st);
+// Exact scores from the stored embeddings.  Survivors: of the current active sets, written by
+// list position (score_slots: including the queries whose list holds cache slots, whose cached
+// cells are coarse and cannot give the exact score).  All: every document of every query, written
+// by doc id into `out` ([nq][N]).
+hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,
+                                   bool score_slots, hipStream_t st);
+hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float* cells, hipStream_t st);
 
-// Dense (corpus-streaming) kernel for bf16: Full-MaxSim scores or the first reveal batch.
-hipError_t launch_dense_prepare(const Problem& P, const Work& W, int chunk_tokens, int* n_chunks,
+// Dense (corpus-streaming) kernel: Full-MaxSim scores or the first reveal batch.
+hipError_t launch_dense_prepare(const Problem& P, const Work& W, int* n_chunks,
                                 hipStream_t st);
 // co != nullptr: the pass runs on the int8 codes (integer matrix instructions, exact int32
 // maxima decoded by the two scales) instead of the stored embeddings.
-hipError_t launch_dense_score(const Problem& P, const Work& W, int chunk_tokens, int n_chunks,
+hipError_t launch_dense_score(const Problem& P, const Work& W, int n_chunks,
                               float* out, float* cells, const Coarse* co, hipStream_t st);
-hipError_t launch_dense_reveal(const Problem& P, const Work& W, int chunk_tokens, int n_chunks,
+hipError_t launch_dense_reveal(const Problem& P, const Work& W, int n_chunks,
                                const RevealRound& rr, int G, const Coarse* co, hipStream_t st);
 // The same pass for a round >= 2: runs only if the round's device-side test picks it, writes the
 // batch statistics of every (active ids-mode query, document) to stat2; k_select_prune merges
 // them into the running statistics of the documents still active.
-hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int chunk_tokens,
-                                     int n_chunks, const RevealRound& rr, int G, const Coarse* co,
+hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chunks, const RevealRound& rr, int G, const Coarse* co,
                                      hipStream_t st);
 bool dense_supported(const Problem& P, const Coarse* co);
 
@@ -122,8 +121,9 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
-// list position); else all N documents (vals indexed by id).
-hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, const float* vals, int K,
+// list position); else all N documents (vals indexed by id).  cached: the queries whose list holds
+// cache slots take their survivors' scores from the cached cells (and store them in vals).
+hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, bool cached, float* vals, int K,
                        int64_t* out_ids, float* out_scores, hipStream_t st);
 
 // int8 codes of x ([n_segments][seg_elems] values of dtype dt): per segment, clip = the

@@ -101,6 +101,35 @@ def test_full_maxsim_bf16_dense_ragged(B, S, oracle_mod, nq, T, d):
                     TOL["bf16"])
 
 
+@pytest.mark.parametrize("dtype,nq,T,d", [("bf16", 1, 32, 128), ("bf16", 2, 42, 128), ("bf16", 1, 100, 64),
+                                          ("bf16", 2, 70, 96), ("bf16", 3, 32, 96), ("bf16", 40, 16, 32),
+                                          ("f32", 3, 32, 128), ("f32", 9, 30, 128), ("f32", 4, 24, 96),
+                                          ("f32", 5, 50, 32), ("f32", 1, 16, 64), ("f32", 3, 64, 64)])
+def test_corpus_pass_of_every_width_and_type(B, S, oracle_mod, dtype, nq, T, d):
+    """Exhaustive scores beyond the calls small enough to gather: every width (96: rows padded in
+    LDS), fp32, the batches whose wavefronts split the documents, and token chunks of 256 to 1,024
+    with documents longer than a chunk; the same corpus through Col-Bandit's reveal pass."""
+    rng = np.random.default_rng(nq * 1000 + T + d)
+    unit = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257, 700, 1030, 1] + \
+        rng.integers(1, 200, 150).tolist()
+    row = d * (2 if dtype == "bf16" else 4)
+    lengths = unit * (int(4.2e7 / (nq * row * sum(unit))) + 1)
+    w = _custom(S, lengths, nq, T, d, dtype, 7)
+    some = range(min(nq, 3))
+    H, Sor = _oracle_scores(oracle_mod, w, some)
+    r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=7, want_cells=True)
+    torch.cuda.synchronize()
+    for q in some:
+        np.testing.assert_allclose(r["cells"][q].cpu().numpy(), H[q], rtol=TOL[dtype], atol=1e-5)
+        np.testing.assert_allclose(r["scores"][q].cpu().numpy(), Sor[q], rtol=TOL[dtype], atol=1e-4)
+        _check_topk(r["topk_ids"][q].cpu().numpy(), r["topk_scores"][q].cpu().numpy(), Sor[q], 7, TOL[dtype])
+    dense = B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.5, 0.01, 5, 3, trace=True)
+    gathered = B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.5, 0.01, 5, 3, trace=True, force_gather=True)
+    torch.cuda.synchronize()
+    _same_run(dense, gathered)
+    assert torch.equal(dense["topk_scores"], torch.gather(r["scores"], 1, dense["topk_ids"]))
+
+
 def test_documents_much_longer_than_a_token_chunk(B, S, oracle_mod):
     """Documents of several chunks leave runs of empty chunks behind them (a chunk belongs to the
     document that starts in it); every workgroup with an empty chunk must exit and the others
