@@ -537,11 +537,11 @@ def test_long_lists_stay_long_under_a_conservative_radius(B, S, oracle_mod, nq):
     _run_colbandit_case(B, oracle_mod, w, 5, 5, 4, 1.0, seed=6, later_rounds=1)
 
 
-@pytest.mark.parametrize("N,K,alpha", [(1024, 5, 0.2), (1025, 32, 1.0), (4097, 33, 1.0), (8192, 5, 1.0),
+@pytest.mark.parametrize("N,K,alpha", [(1024, 5, 0.2), (1025, 32, 1.0), (4096, 5, 1.0), (4097, 33, 1.0), (8192, 5, 1.0),
                                        (8193, 1, 1.0), (16384, 300, 1.0), (16385, 5, 1.0), (24577, 1000, 1.0)])
 def test_selection_at_the_edges_of_its_tiles(B, S, oracle_mod, N, K, alpha):
     """Lists around what the selection kernels hold in registers (1,024 entries per place of a
-    thread, 8,192 in all), around the tile beyond which a list is pre-filtered (16,384), and K around
+    thread, 4,096 in all), around the tile beyond which a list is pre-filtered (16,384), and K around
     the number of group maxima (32); cached lists longer than the registers run their first
     rounds from memory.  A tenth of the documents are copies of one document."""
     rng = np.random.default_rng(N + K)
@@ -729,6 +729,39 @@ def test_quantize_i8_codes_and_scales_match_oracle(B, oracle_mod, dtype, rows, d
     z = torch.zeros((4, d), dtype=x.dtype, device="cuda")
     cz, sz = B.colbandit_quantize_i8(z)
     assert int(cz.abs().max()) == 0 and float(sz[0]) == 0.0
+
+
+@pytest.mark.parametrize("kind,permille", [("normal", 999), ("normal", 1000), ("normal", 986), ("normal", 900),
+                                           ("constant", 999), ("rare", 999), ("wide", 999), ("sorted", 999)])
+def test_quantize_long_bf16_segment_by_its_tail(B, kind, permille):
+    """Segments of 2^26 values and more count only what lies above a sampled bound; a bound that the
+    values defeat (all equal, nearly all zero, a tail wider than the bins, large values that the sample
+    misses) falls back on the full passes.  The clip is the exact order statistic either way."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(permille)
+    rows = (1 << 19) + 3
+    x = torch.randn((rows, 128), generator=g, device="cuda")
+    if kind == "constant":
+        x = torch.full_like(x, -0.75)
+    elif kind == "rare":
+        x = torch.where(torch.rand(x.shape, generator=g, device="cuda") < 0.0005, x, torch.zeros_like(x))
+    elif kind == "wide":
+        x = torch.exp(20 * x)
+    elif kind == "sorted":
+        x = x.abs().reshape(-1).sort().values.reshape(x.shape)
+    x = x.to(torch.bfloat16)
+    codes, scale = B.colbandit_quantize_i8(x, permille=permille)
+    n = x.numel()
+    counts = torch.bincount((x.view(torch.int16).reshape(-1) & 0x7fff).to(torch.int32), minlength=32768)
+    rank = (n * permille + 999) // 1000
+    key = int(torch.searchsorted(torch.cumsum(counts, 0), torch.tensor([rank], device="cuda"))[0])
+    clip = torch.tensor([key], dtype=torch.int16, device="cuda").view(torch.bfloat16).float()
+    clip = clip.cpu().numpy()[0]                       # single-precision divisions on the host
+    assert scale.cpu().numpy()[0] == clip / np.float32(127)
+    inv = float(np.float32(127) / clip) if clip > 0 else 0.0
+    for lo in range(0, rows, 1 << 18):
+        want = torch.clamp(torch.round(x[lo:lo + (1 << 18)].float() * inv), -127, 127).to(torch.int8)
+        assert torch.equal(codes[lo:lo + (1 << 18)], want)
 
 
 @pytest.mark.parametrize("nq,T,d", [(1, 32, 128), (5, 32, 128), (20, 24, 128), (3, 40, 128), (2, 100, 128),
