@@ -455,9 +455,10 @@ template <int G> __device__ __forceinline__ float sum_group(float v) {
 // into registers whose ROWS are tiles: after pack_colmax every lane of row r of w[j]
 // holds the maximum over all 16 accumulator rows of column col of tile tile_of_row(j, r).
 template <int NT> struct Pack {
-    static constexpr int NW = NT >= 4 ? NT / 4 : 1;
+    static constexpr int NW = (NT + 3) / 4;
     // which tile sits in row `row` of packed register j
     __device__ __forceinline__ static int tile_of_row(int j, int row) {
+        if (NT % 4 == 2 && j == NW - 1) return NT - 2 + (row >> 1);
         if (NT >= 4) return 4 * j + (((row & 1) << 1) | (row >> 1));
         if (NT == 2) return row >> 1;
         return 0;
@@ -485,10 +486,14 @@ template <int NT> struct Pack {
             w[0] = maxpack16(m, m);
         } else {
 #pragma unroll
-            for (int j = 0; j < NW; ++j) {
+            for (int j = 0; j < NT / 4; ++j) {
                 const V m0 = maxpack32(h[4 * j], h[4 * j + 1]);
                 const V m1 = maxpack32(h[4 * j + 2], h[4 * j + 3]);
                 w[j] = maxpack16(m0, m1);
+            }
+            if constexpr (NT % 4 == 2) {            // the last two tiles, each in two rows
+                const V m = maxpack32(h[NT - 2], h[NT - 1]);
+                w[NW - 1] = maxpack16(m, m);
             }
         }
     }

@@ -130,6 +130,36 @@ def test_corpus_pass_of_every_width_and_type(B, S, oracle_mod, dtype, nq, T, d):
     assert torch.equal(dense["topk_scores"], torch.gather(r["scores"], 1, dense["topk_ids"]))
 
 
+@pytest.mark.parametrize("T,d", [(1, 128), (8, 64), (9, 128), (17, 128), (24, 96), (25, 64), (33, 128), (48, 64),
+                                 (49, 128), (65, 64), (96, 128), (97, 64)])
+def test_packed_query_tiles_give_the_bits_of_whole_tiles(B, S, oracle_mod, T, d):
+    """Batches whose query lengths leave column tiles partly empty share tiles between queries (T up to
+    8, 17..24, 33..48, 65..96; the neighbours of those lengths do not); scores and cells carry the same
+    bits as the small-batch kernels give, on the embeddings and on int8 codes, and agree with the oracle."""
+    rng = np.random.default_rng(T)
+    lengths = ([1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257, 700, 1] + rng.integers(1, 120, 60).tolist()) * 3
+    per = 1 if T <= 16 else 2 if T <= 32 else 4 if T <= 64 else 8
+    nq = 37 // per + 16                                    # more than 16 tiles, an incomplete last wavefront
+    w = _custom(S, lengths, nq, T, d, "bf16", 70 + T)
+    r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)
+    H, Sor = _oracle_scores(oracle_mod, w, [nq - 1])
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(r["cells"][nq - 1].cpu().numpy(), H[0], rtol=TOL["bf16"], atol=1e-5)
+    np.testing.assert_allclose(r["scores"][nq - 1].cpu().numpy(), Sor[0], rtol=TOL["bf16"], atol=1e-4)
+    step = 2
+    for q in range(0, nq, step):
+        few = B.colbandit_full_maxsim(w.Q[q:q + step], w.docs, w.offsets, K=0, want_cells=True)
+        assert torch.equal(few["scores"], r["scores"][q:q + step])
+        assert torch.equal(few["cells"], r["cells"][q:q + step])
+    if d % 64 == 0:
+        codes, scale = B.colbandit_quantize_i8(w.docs)
+        c = B.colbandit_coarse_maxsim(w.Q, codes, scale, w.offsets, want_cells=True)
+        for q in range(0, nq, step):
+            few = B.colbandit_coarse_maxsim(w.Q[q:q + step], codes, scale, w.offsets, want_cells=True)
+            assert torch.equal(few["scores"], c["scores"][q:q + step])
+            assert torch.equal(few["cells"], c["cells"][q:q + step])
+
+
 def test_documents_much_longer_than_a_token_chunk(B, S, oracle_mod):
     """Documents of several chunks leave runs of empty chunks behind them (a chunk belongs to the
     document that starts in it); every workgroup with an empty chunk must exit and the others
