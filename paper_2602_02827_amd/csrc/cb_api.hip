@@ -209,8 +209,18 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
     const double per_token = fmax(row_bytes / 3.5e12, 2.0 * rows * P.d / rate);
     const double t_round = 18e-6;
     const double t_pass = (double)P.total * per_token;
-    const double t_pair = ((double)P.total / (double)P.N) * row_bytes / 4.5e12;
-    const double thr = (2.0 * (t_pass + t_round) + (lists_fit ? (R - r) * t_round : 0.0)) / t_pair;
+    double t_pair = ((double)P.total / (double)P.N) * row_bytes / 4.5e12;
+    double passes = 2.0;
+    if (!codes && P.dt == DT_F32) {
+        // matrix work bounds both: all T tokens of a pair at once against a batch in each pass, so
+        // where the lists fit the cache the one visit is weighed against a pass in every round left
+        // (33 queries x 57 tokens over 1,154 pages of 647, d = 96, 9 rounds of passes: 4.7 ms, gathered 4.4)
+        const int tq = (P.T + 15) / 16;
+        const double tile_rows = 16.0 * (tq <= 1 ? 1 : tq <= 2 ? 2 : 4);
+        t_pair = fmax(t_pair, ((double)P.total / (double)P.N) * 2.0 * tile_rows * P.d / 0.1e15);
+        if (lists_fit) passes = R - r + 1;
+    }
+    const double thr = (passes * (t_pass + t_round) + (lists_fit ? (R - r) * t_round : 0.0)) / t_pair;
     return thr >= 1.8e19 ? ~0ull - 1 : (unsigned long long)thr;
 }
 
@@ -694,7 +704,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     PhaseTimer pt;
     if (stats && !pt.start(st)) return COLBANDIT_ERR_HIP;
 
-    hipError_t e = launch_init(P, W, kn, R, seed, user_pi, tr, st);
+    hipError_t e = hipSuccess;
     const bool loop = N > (int64_t)K + M;    // |A_1| > K + M, else the loop body never runs
     // coarse pass: code the queries (per query) and reveal from the int8 codes
     const Coarse* co = nullptr;
@@ -710,8 +720,11 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     int G_max = 1;                                   // columns of a full batch
     while (G_max < kn.B) G_max <<= 1;
     choose_chunks(W, P, ((int64_t)n_queries * G_max + 15) / 16);
-    int n_chunks = 0;
-    if (e == hipSuccess && loop && dense) e = launch_dense_prepare(P, W, &n_chunks, st);
+    const int n_chunks = loop && dense ? dense_chunks(P, W) : 0;
+    // the smallest calls visit every document once: round 1 caches all cells of all documents
+    const bool cache_all = loop && !dense && !force_gather && later_rounds == 0 && small_call(P) &&
+                           N <= (int64_t)W.cache_cap;
+    if (e == hipSuccess) e = launch_init(P, W, kn, R, seed, user_pi, tr, n_chunks, st);
     float kappa[COLBANDIT_MAX_ROUNDS + 1] = {};      // radius per unit sigma_hat of each round
     for (int r = 1; r <= R; ++r) {
         const double kap = colbandit_radius_prefactor(alpha_ef, delta, T, N, r * kn.B < T ? r * kn.B : T);
@@ -739,14 +752,14 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
             }
             round_thr[r] = rr.dense_thr;
             e = launch_dense_reveal_later(P, W, n_chunks, rr, G, co, st);
-            if (e == hipSuccess) e = launch_gather_round(P, W, rr, co, st);
+            if (e == hipSuccess) e = launch_gather_round(P, W, rr, cache_all, co, st);
         }
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
-        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, tr, st);
+        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, tr, st);
         pt.mark(PH_SELECT);
         // A gathered round in which every list fits the cell cache is the last one to launch:
         // k_select_prune runs all rounds of a cached query.
-        if (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap) break;
+        if (cache_all || (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap)) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
     if (e == hipSuccess) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
@@ -791,7 +804,10 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
             // the cache computes all T cells of its documents once, later rounds read them back
             const bool pass = r == 0 || ((corpus_rounds >> r) & 1ull);
             if (!cached) {
-                if (pass) s.cells_computed += (int64_t)(hi - lo) * N;
+                if (cache_all) {                      // round 1 computed all cells of all documents
+                    s.cells_computed += (int64_t)T * N;
+                    cached = true;
+                } else if (pass) s.cells_computed += (int64_t)(hi - lo) * N;
                 else if (W.cache_cap > 0 && count <= W.cache_cap) {
                     s.cells_computed += (int64_t)T * count;
                     cached = true;

@@ -576,18 +576,13 @@ void k_dense(DenseArgs A) {
     while (doc < i1) finalize(doc++);           // documents without tokens at the chunk's end
 }
 
-// ---- first document of every token chunk: chunk_doc[c] = min{ i : off[i] >= c*C }
+// ---- first document of every token chunk
 __global__ void k_chunk_docs(const int64_t* off, int64_t N, int C, int n_chunks, int32_t* chunk_doc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > N) return;
-    int64_t lo = (i == 0) ? 0 : off[i - 1] / C + 1;
-    int64_t hi = off[i] / C;
-    if (off[i] < 0) hi = -1;
-    if (i > 0 && off[i - 1] < 0) lo = 0;
-    if (i == N) hi = n_chunks;       // everything past the last offset is empty
-    lo = lo < 0 ? 0 : lo;
-    hi = hi > n_chunks ? n_chunks : hi;
-    for (int64_t c = lo; c <= hi; ++c) chunk_doc[c] = (int32_t)i;
+    chunk_docs((int64_t)blockIdx.x * blockDim.x + threadIdx.x, off, N, C, n_chunks, chunk_doc);
+}
+
+int dense_chunks(const Problem& P, const Work& W) {
+    return (int)((P.total + W.chunk_tokens - 1) / W.chunk_tokens);
 }
 
 bool dense_supported(const Problem& P, const Coarse* co) {
@@ -598,7 +593,7 @@ bool dense_supported(const Problem& P, const Coarse* co) {
 
 hipError_t launch_dense_prepare(const Problem& P, const Work& W, int* n_chunks, hipStream_t st) {
     const int C = W.chunk_tokens;
-    const int nc = (int)((P.total + C - 1) / C);
+    const int nc = dense_chunks(P, W);
     *n_chunks = nc;
     const int64_t n = P.N + 1;
     k_chunk_docs<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(P.off, P.N, C, nc, W.chunk_doc);

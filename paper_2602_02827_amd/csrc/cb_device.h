@@ -47,6 +47,21 @@ __device__ __forceinline__ unsigned long long work_item(int q, unsigned long lon
 __device__ __forceinline__ unsigned long long work_start(unsigned long long item) { return item >> 16; }
 __device__ __forceinline__ int work_query(unsigned long long item) { return (int)(item & 0xffffu); }
 
+// Chunk table of the corpus pass, chunk_doc[c] = min{ i : off[i] >= c*C }: entry i of N + 1 writes the
+// chunks that begin between its predecessor's first token and its own.
+__device__ __forceinline__ void chunk_docs(int64_t i, const int64_t* off, int64_t N, int C, int n_chunks,
+                                           int32_t* chunk_doc) {
+    if (i > N) return;
+    int64_t lo = (i == 0) ? 0 : off[i - 1] / C + 1;
+    int64_t hi = off[i] / C;
+    if (off[i] < 0) hi = -1;
+    if (i > 0 && off[i - 1] < 0) lo = 0;
+    if (i == N) hi = n_chunks;       // everything past the last offset is empty
+    lo = lo < 0 ? 0 : lo;
+    hi = hi > n_chunks ? n_chunks : hi;
+    for (int64_t c = lo; c <= hi; ++c) chunk_doc[c] = (int32_t)i;
+}
+
 // Device-side choice of a later round's reveal path (uniform over the launch): true = the
 // corpus-streaming pass serves every active ids-mode query, false = per-pair gather.
 __device__ __forceinline__ bool dense_round(const unsigned long long* pairs_r,

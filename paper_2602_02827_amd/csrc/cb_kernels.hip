@@ -18,46 +18,87 @@ __device__ __forceinline__ uint64_t splitmix64_next(uint64_t& s) {
     return z ^ (z >> 31);
 }
 
-__global__ void k_init(QueryCtl* ctl, int32_t* pi, const int32_t* user_pi, int32_t* cnt_hist,
-                       float* tau_hist, int nq, int T, int R, int64_t N, int KM, uint64_t seed,
-                       int32_t* tr_count, float* tr_tau, unsigned long long* pairs) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q == 0)
-        for (int r = 0; r < 2 * (R + 2); ++r) pairs[r] = 0ull;   // pair counts, then their token counts
-    if (q >= nq) return;
-    QueryCtl c;
-    c.count = (int)N;
-    c.cur = 0;
-    c.implicit = 1;
-    c.active = N > (int64_t)KM;
-    c.mode = 0;
-    c.bound = c.pad1 = c.pad2 = 0;
-    ctl[q] = c;
-    for (int r = 0; r <= R; ++r) {
-        cnt_hist[r * nq + q] = (int)N;
-        if (tr_count) tr_count[r * nq + q] = (int)N;
+struct InitArgs {
+    QueryCtl* ctl;
+    int32_t* pi;
+    const int32_t* user_pi;
+    int32_t* cnt_hist;
+    float* tau_hist;
+    int nq, T, R, KM;
+    int64_t N;
+    uint64_t seed;
+    int32_t* tr_count;
+    float* tr_tau;
+    unsigned long long* pairs;
+    int init_blocks;          // workgroups of four queries; those after them fill the chunk table
+    const int64_t* off;
+    int chunk_tokens, n_chunks;
+    int32_t* chunk_doc;
+};
+
+// A wavefront per query.  The permutation is a Fisher-Yates shuffle driven by SplitMix64 (Sec. 4.2:
+// one seeded uniform permutation per query); the generator's state after s steps is known in closed
+// form, so the lanes draw the T - 1 positions side by side (64-bit remainders, the costly part) and
+// only the exchanges run one after the other, between lanes' registers.  One thread per query drawing
+// them in turn took 14 us and the chunk table of the corpus pass 5 in a launch of its own, both together
+// take 7 here (T = 32).
+__global__ __launch_bounds__(256) void k_init(InitArgs A) {
+    if ((int)blockIdx.x >= A.init_blocks) {
+        chunk_docs((int64_t)((int)blockIdx.x - A.init_blocks) * 256 + threadIdx.x, A.off, A.N, A.chunk_tokens,
+                   A.n_chunks, A.chunk_doc);
+        return;
     }
-    for (int r = 0; r < R; ++r) {
-        tau_hist[r * nq + q] = __uint_as_float(0x7fc00000u);   // quiet NaN: "round not run"
-        if (tr_tau) tr_tau[r * nq + q] = __uint_as_float(0x7fc00000u);
+    const int lane = threadIdx.x & 63;
+    const int q = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (q == 0)                                     // pair counts, then their token counts
+        for (int r = lane; r < 2 * (A.R + 2); r += 64) A.pairs[r] = 0ull;
+    if (q >= A.nq) return;
+    const int T = A.T;
+    if (lane == 0) {
+        QueryCtl c;
+        c.count = (int)A.N;
+        c.cur = 0;
+        c.implicit = 1;
+        c.active = A.N > (int64_t)A.KM;
+        c.mode = 0;
+        c.bound = c.pad1 = c.pad2 = 0;
+        A.ctl[q] = c;
     }
-    int32_t* p = pi + (size_t)q * T;
-    if (user_pi) {
-        for (int t = 0; t < T; ++t) {   // clamped: a bad table must not steer a read out of Q
-            const int32_t v = user_pi[(size_t)q * T + t];
+    for (int r = lane; r <= A.R; r += 64) {
+        A.cnt_hist[r * A.nq + q] = (int)A.N;
+        if (A.tr_count) A.tr_count[r * A.nq + q] = (int)A.N;
+        if (r < A.R) {
+            A.tau_hist[r * A.nq + q] = __uint_as_float(0x7fc00000u);   // quiet NaN: "round not run"
+            if (A.tr_tau) A.tr_tau[r * A.nq + q] = __uint_as_float(0x7fc00000u);
+        }
+    }
+    int32_t* p = A.pi + (size_t)q * T;
+    if (A.user_pi) {
+        for (int t = lane; t < T; t += 64) {        // clamped: a bad table must not steer a read out of Q
+            const int32_t v = A.user_pi[(size_t)q * T + t];
             p[t] = v < 0 ? 0 : (v >= T ? T - 1 : v);
         }
-    } else {
-        // Fisher-Yates driven by SplitMix64 (Sec. 4.2: one seeded uniform permutation per query)
-        uint64_t s = seed + ((uint64_t)q + 1ull) * 0x9E3779B97F4A7C15ull;
-        for (int t = 0; t < T; ++t) p[t] = t;
-        for (int i = T - 1; i >= 1; --i) {
-            const int j = (int)(splitmix64_next(s) % (uint64_t)(i + 1));
-            const int32_t tmp = p[i];
-            p[i] = p[j];
-            p[j] = tmp;
-        }
+        return;
     }
+    const uint64_t s0 = A.seed + ((uint64_t)q + 1ull) * 0x9E3779B97F4A7C15ull;
+    auto draw = [&](int i) -> int {                 // the position that i is exchanged with: step T - i
+        uint64_t s = s0 + (uint64_t)(T - 1 - i) * 0x9E3779B97F4A7C15ull;
+        return (int)(splitmix64_next(s) % (uint64_t)(i + 1));
+    };
+    int j0 = 0, j1 = 0, p0 = lane, p1 = lane + 64;
+    if (lane >= 1 && lane < T) j0 = draw(lane);
+    if (lane + 64 < T) j1 = draw(lane + 64);
+    for (int i = T - 1; i >= 1; --i) {
+        const int j = i < 64 ? __builtin_amdgcn_readlane(j0, i) : __builtin_amdgcn_readlane(j1, i - 64);
+        const int a = i < 64 ? __builtin_amdgcn_readlane(p0, i) : __builtin_amdgcn_readlane(p1, i - 64);
+        const int b = j < 64 ? __builtin_amdgcn_readlane(p0, j) : __builtin_amdgcn_readlane(p1, j - 64);
+        if (i < 64) p0 = lane == i ? b : p0;
+        else p1 = lane + 64 == i ? b : p1;
+        if (j < 64) p0 = lane == j ? a : p0;
+        else p1 = lane + 64 == j ? a : p1;
+    }
+    if (lane < T) p[lane] = p0;
+    if (lane + 64 < T) p[lane + 64] = p1;
 }
 
 __global__ void k_fill_f32(float* p, size_t n, float v) {
@@ -72,10 +113,29 @@ __global__ void k_fill_u8(uint8_t* p, size_t n, uint8_t v) {
 }
 
 hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
-                       const int32_t* user_pi, const Trace& tr, hipStream_t st) {
-    k_init<<<(P.nq + 63) / 64, 64, 0, st>>>(W.ctl, W.pi, user_pi, W.cnt_hist, W.tau_hist, P.nq,
-                                            P.T, R, P.N, kn.K + kn.M, seed, tr.count, tr.tau,
-                                            W.pairs);
+                       const int32_t* user_pi, const Trace& tr, int n_chunks, hipStream_t st) {
+    InitArgs A{};
+    A.ctl = W.ctl;
+    A.pi = W.pi;
+    A.user_pi = user_pi;
+    A.cnt_hist = W.cnt_hist;
+    A.tau_hist = W.tau_hist;
+    A.nq = P.nq;
+    A.T = P.T;
+    A.R = R;
+    A.KM = kn.K + kn.M;
+    A.N = P.N;
+    A.seed = seed;
+    A.tr_count = tr.count;
+    A.tr_tau = tr.tau;
+    A.pairs = W.pairs;
+    A.init_blocks = (P.nq + 3) / 4;
+    A.off = P.off;
+    A.chunk_tokens = W.chunk_tokens;
+    A.n_chunks = n_chunks;
+    A.chunk_doc = W.chunk_doc;
+    const unsigned chunk_blocks = n_chunks > 0 ? (unsigned)((P.N + 1 + 255) / 256) : 0u;
+    k_init<<<(unsigned)A.init_blocks + chunk_blocks, 256, 0, st>>>(A);
     if (tr.lcb) {
         const size_t n = (size_t)R * P.nq * P.N;
         const int g = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
@@ -115,6 +175,7 @@ struct GatherArgs {
     const unsigned long long* work;      // its queries (work_item)
     unsigned long long dense_thr;        // ~0: this round cannot be a corpus pass
     // cell cache
+    int cache_all;            // round 1 caches the cells of all N documents (slot = document)
     int cache_cap, TP;
     int32_t* cid;
     float2* cstat;
@@ -227,7 +288,9 @@ constexpr int64_t ALL_DOCS = 64;
 //                  list entry into a cache slot.  A gathered reveal is bound by the bytes of the
 //                  document, not by the cells computed from them, so a document is visited once
 //                  and the later rounds (and the rescore) read its cells back; the order in which
-//                  cells are REVEALED to the bounds is unchanged.
+//                  cells are REVEALED to the bounds is unchanged.  cache_all: so does round 1 of the
+//                  smallest calls, which then needs no second visit and no launch of a later round (1
+//                  query x 1,000 documents of 48 fp32 tokens: 63 -> 55 us a call).
 template <typename Tag, int D, int TQ>
 __global__ __launch_bounds__(256) void k_gather_round(GatherArgs A) {
     using F = Frag<Tag, D>;
@@ -303,7 +366,7 @@ __global__ __launch_bounds__(256) void k_gather_round(GatherArgs A) {
         const int count = c.count;
         int32_t* list = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
         const float scale = A.qscale ? A.qscale[q] * A.dscale[0] : 1.f;
-        if (!list || count > A.cache_cap) {
+        if (!A.cache_all && (!list || count > A.cache_cap)) {
             F bq[1];
             const int trow = A.pi[(size_t)q * A.T + A.lo + (col < A.nb ? col : 0)];
             bq[0].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg);
@@ -335,7 +398,7 @@ __global__ __launch_bounds__(256) void k_gather_round(GatherArgs A) {
             const int tile = t >> 4;
             const int src = P::row_of_tile(tile) * 16 + (t & 15);
             for (; k < k_end; ++k) {
-                const int id = list[k];
+                const int id = list ? list[k] : k;
                 int64_t o0, o1;
                 doc_range(A, id, o0, o1);
                 V h[TQ];
@@ -358,11 +421,12 @@ __global__ __launch_bounds__(256) void k_gather_round(GatherArgs A) {
                 float sb, m2b;
                 batch_stats(v, col % A.G, A.nb, A.G, sb, m2b);
                 if (lane == 0) {
-                    float2 st = A.stat[(size_t)q * A.N + id];
+                    float2 st = make_float2(0.f, 0.f);
+                    if (A.n_prev > 0) st = A.stat[(size_t)q * A.N + id];
                     merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
                     A.cstat[slot] = st;
                     A.cid[slot] = id;
-                    list[k] = k;          // the entry now names its cache slot
+                    if (list) list[k] = k;          // the entry now names its cache slot
                 }
             }
         }
@@ -518,10 +582,11 @@ static hipError_t gather_any(GatherArgs& A, int mode, const Problem& P, const Wo
 // without pairs ends at once (8,192: 4.7 us; 256 per query at 128 queries: 9 us).
 constexpr long long GATHER_BLOCKS = 8192;
 
-hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, const Coarse* co,
-                               hipStream_t st) {
+hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, bool cache_all,
+                               const Coarse* co, hipStream_t st) {
     GatherArgs A{};
     A.ctl = W.ctl;
+    A.cache_all = cache_all ? 1 : 0;
     A.lo = rr.lo;
     A.nb = rr.nb;
     A.n_prev = rr.n_prev;
@@ -965,6 +1030,8 @@ struct SelArgs {
     int r, n, n_prev, nb;                // this launch's round
     float a, b;
     const int32_t* pi;
+    int cache_all;                       // round 1 has cached the cells of all documents
+    int note_pairs;                      // ... then the pairs going on to round 2 are counted for the statistics
     int cache_cap, TP;
     const int32_t* cid;
     float2* cstat;
@@ -1064,6 +1131,23 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
             atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
         }
     }
+}
+
+// Round 1 of a query all of whose cells are cached: the pairs that go on, and their tokens, for the
+// statistics (no kernel reads them).  entry(u): the thread's u-th entry, a document id here.
+template <int E, class EntryFn>
+__device__ __forceinline__ void note_pairs(const SelArgs& A, int count, unsigned keep, EntryFn entry) {
+    long long tokens = 0;
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+        if ((keep >> u) & 1u) {
+            const int e = entry(u);
+            tokens += A.off[e + 1] - A.off[e];
+        }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) tokens += __shfl_down(tokens, o);
+    if ((threadIdx.x & 63) == 0 && tokens != 0) atomicAdd(A.pairs + (A.R + 2) + 2, (unsigned long long)tokens);
+    if (threadIdx.x == 0) atomicAdd(A.pairs + 2, (unsigned long long)count);
 }
 
 // The rounds of a query whose ncand <= SEL_REGS * SEL_THREADS candidates fit the registers, from
@@ -1186,6 +1270,7 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
         nc.count = pl.total;
         if (threadIdx.x == 0) note_round(sh, r, nc.count, tau);
         const bool more = slots && nc.count > A.KM && r < A.R;
+        if (more && r == 1 && A.note_pairs) note_pairs<E>(A, nc.count, live, [&](int u) { return e[u]; });
         if (more && Spread(nc.count).span * 2 > sp.span) continue;
 #pragma unroll
         for (int u = 0; u < E; ++u)
@@ -1308,6 +1393,7 @@ __device__ __forceinline__ bool prune_tile(const SelArgs& A, int q, int count, Q
         if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     if (slots && nc.count > A.KM && r < A.R) {
+        if (r == 1 && A.note_pairs) note_pairs<E>(A, nc.count, keep, [&](int u) { return mine[u]; });
         ncand = nc.count;
         ++r;
         __syncthreads();                            // the list is read by other threads next
@@ -1463,7 +1549,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     // entries are cache slots if the query was switched earlier (mode 1) or by this
     // round's cell-caching gather (same rule as in k_gather_round)
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
-    const bool slots = c.mode == 1 || (c.mode == 0 && !c.implicit && count <= A.cache_cap && !dense);
+    const bool slots = c.mode == 1 || A.cache_all || (c.mode == 0 && !c.implicit && count <= A.cache_cap && !dense);
     float2* stat = slots ? A.cstat + (size_t)q * A.cache_cap : A.stat + (size_t)q * A.N;
     const float2* bat = A.stat2 + (size_t)q * A.N;
     const bool fold_dense = dense && c.mode == 0 && in != nullptr;   // a batch that a dense pass left in stat2
@@ -1678,9 +1764,11 @@ static unsigned segments_of(int64_t N) {
 }
 
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
-                               const RevealRound& rr, int R, const float* kappa, const Trace& tr,
-                               hipStream_t st) {
+                               const RevealRound& rr, int R, const float* kappa, bool cache_all,
+                               bool note_pairs, const Trace& tr, hipStream_t st) {
     SelArgs A{};
+    A.cache_all = cache_all ? 1 : 0;
+    A.note_pairs = cache_all && note_pairs ? 1 : 0;
     A.ctl = W.ctl;
     A.list0 = W.list[0];
     A.list1 = W.list[1];
@@ -1797,6 +1885,50 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_topk_segments(TopkArgs A) {
     if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
 }
 
+// The winners of at most E * SEL_THREADS candidates, held in registers: into cs / ci, in no order.
+template <int E>
+__device__ __forceinline__ void topk_regs(const float* vals, const int32_t* list, const int32_t* cid,
+                                          const int32_t* scratch, bool segmented, int count, int ncand, int Kq,
+                                          float* cs, int* ci, int* n_above, const int* seg_first, SelShared& sh) {
+    const Spread sp(ncand);
+    const unsigned on = sp.mask<E>();
+    int p[E];
+    float v[E];
+    uint32_t key[E];
+    if (segmented) {
+        const int len = seg_len(count);
+#pragma unroll
+        for (int u = 0; u < E; ++u) p[u] = scratch[segment_place(sp.at(u), len, seg_first)];
+    } else {
+#pragma unroll
+        for (int u = 0; u < E; ++u) p[u] = sp.at(u);
+    }
+#pragma unroll
+    for (int u = 0; u < E; ++u) v[u] = vals[p[u]];
+#pragma unroll
+    for (int u = 0; u < E; ++u) key[u] = float_key(v[u]);
+    const uint32_t tkey = kth_largest_regs<E>(key, on, Kq, sh);
+    // winners above the K-th value in any order (they are ranked below), those equal to
+    // it in index order as far as there is room
+    unsigned eq = 0;
+    auto put = [&](int slot, int u) {
+        const int e = list ? list[p[u]] : p[u];
+        cs[slot] = v[u];
+        ci[slot] = cid ? cid[e] : e;
+    };
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+        if ((on >> u) & 1u) {
+            if (key[u] > tkey) put(atomicAdd(n_above, 1), u);
+            else if (key[u] == tkey) eq |= 1u << u;
+        }
+    const Places<E> pl(eq, sh);         // its barrier completes n_above
+    const int n_gt = *n_above;
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+        if (((eq >> u) & 1u) && n_gt + pl.place(u) < Kq) put(n_gt + pl.place(u), u);
+}
+
 __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
     __shared__ SelShared sh;
     __shared__ int seg_first[SEG_MAX + 1];
@@ -1839,44 +1971,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
         const bool segmented = !A.ctl && count > SEL_TILE;
         int ncand = count;
         if (segmented) ncand = segment_starts(A.seg_cnt + (size_t)q * SEG_MAX, count, seg_first);
-        if (ncand <= SEL_TILE) {
-            const Spread sp(ncand);
-            const unsigned on = sp.mask<SEL_E>();
-            int p[SEL_E];
-            float v[SEL_E];
-            uint32_t key[SEL_E];
-            if (segmented) {
-                const int len = seg_len(count);
-#pragma unroll
-                for (int u = 0; u < SEL_E; ++u) p[u] = scratch[segment_place(sp.at(u), len, seg_first)];
-            } else {
-#pragma unroll
-                for (int u = 0; u < SEL_E; ++u) p[u] = sp.at(u);
-            }
-#pragma unroll
-            for (int u = 0; u < SEL_E; ++u) v[u] = vals[p[u]];
-#pragma unroll
-            for (int u = 0; u < SEL_E; ++u) key[u] = float_key(v[u]);
-            const uint32_t tkey = kth_largest_regs<SEL_E>(key, on, Kq, sh);
-            // winners above the K-th value in any order (they are ranked below), those equal to
-            // it in index order as far as there is room
-            unsigned eq = 0;
-            auto put = [&](int slot, int u) {
-                const int e = list ? list[p[u]] : p[u];
-                cs[slot] = v[u];
-                ci[slot] = cid ? cid[e] : e;
-            };
-#pragma unroll
-            for (int u = 0; u < SEL_E; ++u)
-                if ((on >> u) & 1u) {
-                    if (key[u] > tkey) put(atomicAdd(&n_above, 1), u);
-                    else if (key[u] == tkey) eq |= 1u << u;
-                }
-            const Places<SEL_E> pl(eq, sh);         // its barrier completes n_above
-            const int n_gt = n_above;
-#pragma unroll
-            for (int u = 0; u < SEL_E; ++u)
-                if (((eq >> u) & 1u) && n_gt + pl.place(u) < Kq) put(n_gt + pl.place(u), u);
+        if (ncand <= 4 * SEL_THREADS) {
+            topk_regs<4>(vals, list, cid, scratch, segmented, count, ncand, Kq, cs, ci, &n_above, seg_first, sh);
+        } else if (ncand <= SEL_TILE) {
+            topk_regs<SEL_E>(vals, list, cid, scratch, segmented, count, ncand, Kq, cs, ci, &n_above, seg_first, sh);
         } else {
             const int32_t* cand = nullptr;
             if (segmented) {

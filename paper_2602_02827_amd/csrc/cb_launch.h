@@ -80,13 +80,14 @@ struct Knobs {
     float a, b;
 };
 
+// n_chunks > 0: also fills the chunk table of the corpus passes (launch_dense_prepare).
 hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
-                       const int32_t* user_pi, const Trace& tr, hipStream_t st);
+                       const int32_t* user_pi, const Trace& tr, int n_chunks, hipStream_t st);
 
 // Reveal round rr by gathering the documents of every active (query, document) pair.  Queries whose
 // list fits the cell cache get all T cells of their documents computed once and cached;
-// k_select_prune and the rescore read them back.
-hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr,
+// k_select_prune and the rescore read them back.  cache_all (round 1): so do all queries at once.
+hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, bool cache_all,
                                const Coarse* co, hipStream_t st);
 
 // Exact scores from the stored embeddings.  Survivors: of the current active sets, written by
@@ -112,13 +113,14 @@ hipError_t launch_dense_reveal(const Problem& P, const Work& W, int n_chunks,
 hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chunks, const RevealRound& rr, int G, const Coarse* co,
                                      hipStream_t st);
 bool dense_supported(const Problem& P, const Coarse* co);
+int dense_chunks(const Problem& P, const Work& W);
 
 // Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
 // this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
 // per unit sigma_hat of round r.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
-                               const RevealRound& rr, int R, const float* kappa, const Trace& tr,
-                               hipStream_t st);
+                               const RevealRound& rr, int R, const float* kappa, bool cache_all,
+                               bool note_pairs, const Trace& tr, hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
 // list position); else all N documents (vals indexed by id).  cached: the queries whose list holds

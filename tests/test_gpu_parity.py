@@ -450,6 +450,33 @@ def test_cell_cache_and_regather_give_identical_runs(B, S, alpha, Bsz, T):
     _same_run(r1, r2)
 
 
+@pytest.mark.parametrize("dtype,N,nq,T,d,Bsz,alpha,coarse",
+                         [("bf16", 11, 1, 1, 128, 1, 1.0, None), ("bf16", 1000, 3, 32, 128, 4, 0.2, None),
+                          ("bf16", 1025, 4, 128, 96, 7, 1.0, None), ("bf16", 4097, 1, 65, 32, 16, 1.0, None),
+                          ("f32", 1000, 1, 32, 128, 4, 0.5, None), ("f32", 5000, 1, 17, 64, 3, 1.0, None),
+                          ("bf16", 900, 3, 32, 128, 4, 0.5, "int8"), ("bf16", 16384, 1, 24, 64, 4, 1.0, None)])
+def test_smallest_calls_that_visit_every_document_once(B, S, oracle_mod, dtype, N, nq, T, d, Bsz, alpha, coarse):
+    """Small corpora have all cells computed and cached in round 1: the decisions, bounds and bits
+    of the rounds that gather anew, and the oracle's answer; lists around the sizes that the prune
+    kernel holds in registers, the longest list that the cache holds, T up to its limit."""
+    rng = np.random.default_rng(N + T)
+    w = _custom(S, rng.integers(1, 4 if N > 5000 else 16, N).tolist(), nq, T, d, dtype, 6 + N)
+    kw = dict(B=Bsz, trace=True)
+    if coarse:
+        kw["docs_i8"], kw["docs_scale"] = B.colbandit_quantize_i8(w.docs)
+    runs = [B.colbandit_topk(w.Q, w.docs, w.offsets, 5, alpha, 0.01, 5, 3, **kw, **o)
+            for o in ({}, {"no_cell_cache": True}, {"force_gather": True}, {"later_rounds": 2})]
+    torch.cuda.synchronize()
+    for r in runs[1:]:
+        _same_run(runs[0], r)
+    st = runs[0]["stats"]
+    # on int8 codes the exact rescore computes the survivors' cells once more
+    assert all(s["cells_computed"] == T * N + (s["cells_rescore"] if coarse else 0) for s in st)
+    assert all(s["corpus_pass_rounds"] == [] for s in st)
+    if not coarse:
+        _run_colbandit_case(B, oracle_mod, w, 5, 5, Bsz, alpha, seed=3)
+
+
 @pytest.mark.parametrize("alpha,Bsz,T,nq", [(1.0, 4, 32, 4), (0.5, 3, 24, 9), (1.0, 16, 100, 2), (0.2, 4, 32, 40)])
 def test_later_rounds_by_corpus_pass_or_by_gather_are_identical(B, S, oracle_mod, alpha, Bsz, T, nq):
     """Rounds >= 2 revealed by the corpus-streaming pass (merged into the running statistics by
