@@ -16,12 +16,16 @@ namespace {
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // Token chunk owned by one workgroup of the dense kernel and one group of its query columns: 4,096,
-// or for a small corpus the power of two (at least 128) that gives up to 2,048 workgroups, eight
-// per CU.  (6,007 documents, 0.9 M tokens, one column group: 224 chunks of 4,096 left CUs idle,
-// 84 us for a pass; 1,770 of 512 take 31 us.  Several column groups fill the chip with longer chunks,
-// over which a workgroup's query rows are loaded less often.)
+// or for a small corpus the power of two (at least 128) that gives up to 4,095 workgroups, eight or
+// more turns of those that the chip holds: the last turn, often nearly empty, then weighs little.
+// (6,007 documents, 0.9 M tokens, one column group: 224 chunks of 4,096 left CUs idle, 84 us for a
+// pass; 1,770 of 512 take 31 us.  100 queries x 6,000 documents of 106 tokens 464 -> 426 us
+// against 2,047 workgroups; with 8,190 430, 50,000 x 64 unchanged.  fp32, 16 x 20,000: 2,505 us with
+// 2,047, 2,256 with 4,095, 2,140 with 8,190 and with 16,380.)
+// Several column groups fill the chip with longer chunks, over which a workgroup's query rows are
+// loaded less often.
 constexpr int kChunkTokens = 4096;
-constexpr int64_t kBlocksWanted = 2048;
+constexpr int64_t kBlocksWanted = 4095;
 
 struct Layout {
     size_t ctl, list0, list1, stat, stat2, pairs, seg_cnt, rescored, scores, cnt_hist, tau_hist, pi,
@@ -103,15 +107,20 @@ Work carve(void* ws, const Layout& L) {
 }
 
 // Sets the chunk length for passes over `tiles` column tiles, and the place of the chunk table.
-void choose_chunks(Work& W, const Problem& P, int64_t tiles) {
-    const int64_t per_group = P.dt == DT_F32 ? 16 : 32;
+// fp32 chunks are shorter: a token costs ten times the matrix time, so a workgroup's start weighs
+// less and an uneven last turn of workgroups more (kBlocksWanted).
+void choose_chunks(Work& W, const Problem& P, int64_t tiles, bool codes = false) {
+    const bool f32 = P.dt == DT_F32 && !codes;
+    const int64_t per_group = f32 ? 16 : 32;
     const int64_t groups = (tiles + per_group - 1) / per_group;
-    const int64_t wanted = kBlocksWanted / groups > 1 ? kBlocksWanted / groups : 1;
+    int64_t most = f32 ? 2 * kBlocksWanted : kBlocksWanted;
+    if (most > kBlocksWanted * P.nq) most = kBlocksWanted * P.nq;
+    const int64_t wanted = most / groups > 1 ? most / groups : 1;
     int c = kChunkTokens;
     while (c > 128 && P.total <= wanted * (c / 2)) c /= 2;
     W.chunk_tokens = c;
-    // The table of short chunks (at most kBlocksWanted + 1 entries) lies over the quantiser's
-    // scratch, which the coding of queries (one workgroup per query) does not use.
+    // The table of short chunks (at most kBlocksWanted entries per query, and one) lies over the
+    // quantiser's scratch, which the coding of queries (one workgroup per query) does not use.
     static_assert((kBlocksWanted + 1) * 4 <= 16384, "quantize_scratch_bytes holds 16 KB per segment");
     if (c < kChunkTokens) W.chunk_doc = (int32_t*)W.qscratch;
 }
@@ -370,7 +379,7 @@ int colbandit_coarse_maxsim(const void* Q, int n_queries, int T, int d, colbandi
     if (rc) return rc;
     Work W = carve(workspace, L);
     const Problem P{Q, n_queries, T, d, (int)dt, docs_i8, doc_offsets, N, total_tokens};
-    choose_chunks(W, P, score_tiles(P));
+    choose_chunks(W, P, score_tiles(P), true);
     hipStream_t st = (hipStream_t)stream;
     Coarse co{docs_i8, docs_scale, W.q8, W.qscale};
     if (!dense_supported(P, &co)) return COLBANDIT_ERR_UNSUPPORTED;
@@ -719,7 +728,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     const bool dense = dense_supported(P, co) && !force_gather && !(small_call(P) && later_rounds != 1);
     int G_max = 1;                                   // columns of a full batch
     while (G_max < kn.B) G_max <<= 1;
-    choose_chunks(W, P, ((int64_t)n_queries * G_max + 15) / 16);
+    choose_chunks(W, P, ((int64_t)n_queries * G_max + 15) / 16, co != nullptr);
     const int n_chunks = loop && dense ? dense_chunks(P, W) : 0;
     // the smallest calls visit every document once: round 1 caches all cells of all documents
     const bool cache_all = loop && !dense && !force_gather && later_rounds == 0 && small_call(P) &&
