@@ -595,7 +595,12 @@ int colbandit_full_maxsim(const void* Q, int n_queries, int T, int d, colbandit_
     // corpus kernel's wavefronts, which split the documents, all multiply the blocks in which one
     // ends.  15.9 M tokens, gathering against the corpus pass: 4.5 and 5.9 ms for one query of 42
     // tokens, 6.8 and 7.6 for two, 3.30 and 3.38 for one of 32.
-    if (small_call(P) || (dt == COLBANDIT_F32 && T > 16 && n_queries <= 2)) {
+    // Five queries of two tiles fill ten of the sixteen tiles that the corpus kernel multiplies; as long
+    // as the last-level cache (256 MB) serves most of the five readings of the corpus, gathering wins:
+    // 0.19 M tokens of d = 64 66 and 84 us, 2.1 M of d = 32 272 and 317; 2.1 M of d = 128 (1.1 GB) 1,269
+    // and 1,124.  Six: 76 and 84 for the first, 1,422 and 1,124 for the last.
+    const bool few_tiles = n_queries == 5 && T > 16 && T <= 32 && (double)total_tokens * d * 4.0 <= 330e6;
+    if (small_call(P) || (dt == COLBANDIT_F32 && ((T > 16 && n_queries <= 2) || few_tiles))) {
         mark();
         e = launch_gather_all(P, W, out, cells, st);
     } else {
@@ -771,7 +776,8 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         if (cache_all || (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap)) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
-    if (e == hipSuccess) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
+    // (after cache_all every query's survivors have them: no launch, 4 us of a call of 50)
+    if (e == hipSuccess && !(cache_all && !co)) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
     if (e == hipSuccess) e = launch_topk(P, W, true, !co, W.rescored, K, topk_ids, topk_scores, st);
     pt.mark(PH_RESCORE);
     if (e != hipSuccess) {

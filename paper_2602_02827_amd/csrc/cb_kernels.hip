@@ -595,8 +595,13 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
     A.pairs_r = rr.r == 1 ? nullptr : W.pairs + rr.r;
     A.work = W.work;
     A.dense_thr = rr.dense_thr;
-    const long long most = (long long)P.nq * P.N;
-    return gather_any(A, GM_ROUND, P, W, dim3((unsigned)(most < GATHER_BLOCKS ? most : GATHER_BLOCKS)), co, st);
+    long long blocks = (long long)P.nq * P.N;
+    // The smallest calls' whole matrix: a document shared by four wavefronts loads the query four times.
+    // From some three pairs a CU a wavefront per pair is faster (us a call: 1,000 pairs of 48 fp32
+    // tokens 112 -> 104, 2,000 of bf16 56 -> 50), below shared documents are (250 pairs 35 and 38, 250
+    // of 500 tokens 38 and 51).
+    if (cache_all && blocks >= 768) blocks = (blocks + 3) / 4;
+    return gather_any(A, GM_ROUND, P, W, dim3((unsigned)(blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS)), co, st);
 }
 
 hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,

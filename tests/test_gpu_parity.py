@@ -104,7 +104,8 @@ def test_full_maxsim_bf16_dense_ragged(B, S, oracle_mod, nq, T, d):
 @pytest.mark.parametrize("dtype,nq,T,d", [("bf16", 1, 32, 128), ("bf16", 2, 42, 128), ("bf16", 1, 100, 64),
                                           ("bf16", 2, 70, 96), ("bf16", 3, 32, 96), ("bf16", 40, 16, 32),
                                           ("f32", 3, 32, 128), ("f32", 9, 30, 128), ("f32", 4, 24, 96),
-                                          ("f32", 5, 50, 32), ("f32", 1, 16, 64), ("f32", 3, 64, 64)])
+                                          ("f32", 5, 50, 32), ("f32", 1, 16, 64), ("f32", 3, 64, 64),
+                                          ("f32", 9, 24, 64), ("f32", 17, 16, 32), ("f32", 5, 32, 64)])
 def test_corpus_pass_of_every_width_and_type(B, S, oracle_mod, dtype, nq, T, d):
     """Exhaustive scores beyond the calls small enough to gather: every width (96: rows padded in
     LDS), fp32, the batches whose wavefronts split the documents, and token chunks of 256 to 1,024
