@@ -528,8 +528,10 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
         if (e == hipSuccess && (ng < n_queries || (int64_t)ng > (int64_t)n_queries * B.TG))
             e = hipErrorUnknown;
         int n_chunks = 0;
-        choose_chunks(W, P, ((int64_t)ng * 4 + 15) / 16);
-        if (e == hipSuccess) e = launch_dense_prepare(P, W, &n_chunks, st);
+        if (e == hipSuccess) {                       // else ng has not arrived
+            choose_chunks(W, P, ((int64_t)ng * 4 + 15) / 16);
+            e = launch_dense_prepare(P, W, &n_chunks, st);
+        }
         if (e == hipSuccess) {
             const Problem P2{Qg, ng, 4, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
             Work W2 = W;

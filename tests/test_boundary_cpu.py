@@ -199,6 +199,31 @@ def test_baseline_argument_errors(B):
     assert L.colbandit_ball_carving_workspace_bytes(2, 32, 128, 5, 1000, 48000) == 0
 
 
+def test_ball_carving_reports_a_failure_after_its_first_launch(B, tmp_path):
+    """A launch or wait that fails half way (a stream under capture cannot be waited for) is an error
+    code, not a signal: the group count that the rest of the call is sized by has not arrived.  The two
+    launches before it are replaced by a success and a failure."""
+    import subprocess
+    import sys
+    src, so = tmp_path / "stub.cpp", tmp_path / "stub.so"
+    src.write_text(
+        "#include <hip/hip_runtime_api.h>\n#include <stdint.h>\n"
+        "namespace cb {\nstruct Problem;\n"
+        "hipError_t launch_ball_carve(const Problem&, float, void*, int32_t*, int32_t*, hipStream_t)\n"
+        "{ return hipSuccess; }\n"
+        "hipError_t launch_ball_groups(const Problem&, const void*, const int32_t*, int32_t*, void*, int32_t*,\n"
+        "                              hipStream_t) { return hipErrorUnknown; }\n}\n")
+    subprocess.run(["g++", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", str(src), "-o",
+                    str(so)], check=True)
+    prog = (f"import ctypes, sys; sys.path.insert(0, {ROOT!r}); ctypes.CDLL({str(so)!r}, mode=ctypes.RTLD_GLOBAL)\n"
+            "from paper_2602_02827_amd import binding\n"
+            "rc = binding.lib().colbandit_ball_carving(0x1000, 3, 32, 128, 1, 0x2000, 0x3000, 100, 4000, 5, 0.7,\n"
+            "    None, None, None, 0x4000, 0x5000, 0x6000, 0x10000, 1 << 40, None)\n"
+            "sys.exit(100 - rc)\n")
+    r = subprocess.run([sys.executable, "-c", prog], capture_output=True, text=True)
+    assert r.returncode == 107, (r.returncode, r.stderr)       # COLBANDIT_ERR_HIP
+
+
 def test_cells_per_doc_of_doc_uniform(B, oracle_mod):
     """colbandit_cells_per_doc against exact rational arithmetic on the paper's gamma sweep and
     against the oracle's separately written counterpart; error codes."""
