@@ -145,7 +145,7 @@ int check_shapes(const void* Q, int nq, int T, int d, int dt, const void* docs,
     if (!Q || !docs || !off) return COLBANDIT_ERR_NULL;
     if (nq < 1 || T < 1 || d < 1 || N < 1 || total < N) return COLBANDIT_ERR_SHAPE;
     if (dt != COLBANDIT_F32 && dt != COLBANDIT_BF16) return COLBANDIT_ERR_SHAPE;
-    // the selection kernels index a list a few chunks (of up to 16,384 entries) past its end
+    // the selection kernels form indexes up to three chunks of 8,192 entries past a list's end
     if (N > 0x7fffffff - (1 << 17) || nq > 65535) return COLBANDIT_ERR_UNSUPPORTED;
     if (d != 32 && d != 64 && d != 96 && d != 128) return COLBANDIT_ERR_UNSUPPORTED;
     if (T > (dt == COLBANDIT_BF16 ? COLBANDIT_MAX_T : 64)) return COLBANDIT_ERR_UNSUPPORTED;

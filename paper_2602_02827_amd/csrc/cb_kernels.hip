@@ -4,6 +4,7 @@
 
 #include "../../include/colbandit.h"
 #include "cb_launch.h"
+#include "cb_segments.h"
 
 namespace cb {
 
@@ -650,10 +651,7 @@ constexpr int SEL_RUN = 16;                        // samples are taken in runs 
 constexpr int SEL_E = 16;
 constexpr int SEL_TILE = SEL_E * SEL_THREADS;
 static_assert(SEL_TILE == 16384, "the cell cache's slots per query must fit one tile");
-// Tile of the pre-filter kernels: half as many registers, so that two workgroups share a CU.
-constexpr int SEG_E = 8;
-constexpr int SEG_TILE = SEG_E * SEL_THREADS;
-constexpr int SEG_MAX = 64;                        // segments of a long list
+constexpr int SEG_E = SEG_TILE / SEL_THREADS;      // pre-filter kernels: entries per thread and tile
 constexpr int SEL_REGS = 4;                        // 8 spills (topk 1,000 x 1: 62 -> 70 us)
 constexpr int SEL_BINS = 2048;
 constexpr int SEL_FEW = 1024;
@@ -966,13 +964,6 @@ template <int E> struct Places {
     }
 };
 
-// entries per segment of a long list: whole tiles, so that a segment's bound comes from a full
-// tile whenever there is one
-__device__ __forceinline__ int seg_len(int count) {
-    const int tiles = (count + SEG_TILE - 1) / SEG_TILE;
-    return (tiles + SEG_MAX - 1) / SEG_MAX * SEG_TILE;
-}
-
 // The 16 slot values of a reveal batch, summed in the order of the cross-lane form
 // (batch_stats_g): zero slots past nb make the order of every group size a case of this one.
 __device__ __forceinline__ float slot_sum(const float (&v)[16]) {
@@ -1057,7 +1048,7 @@ struct SelArgs {
 // completely before it is written.
 __device__ int merge_segments(int32_t* buf, const int32_t* cnt, int count) {
     const int len = seg_len(count);
-    const int n_seg = (count + len - 1) / len;
+    const int n_seg = seg_count(count);
     int base = 0;
     for (int sg = 0; sg < n_seg; ++sg) {
         const int c = cnt[sg];
@@ -1080,8 +1071,7 @@ __device__ int merge_segments(int32_t* buf, const int32_t* cnt, int count) {
 // Where candidate i of a segmented list lies.  first: LDS int[SEG_MAX + 1], the number of
 // candidates before each segment (segment_starts).
 __device__ __forceinline__ int segment_starts(const int32_t* cnt, int count, int* first) {
-    const int len = seg_len(count);
-    const int n_seg = (count + len - 1) / len;
+    const int n_seg = seg_count(count);
     if (threadIdx.x < 64) {
         const int c = (int)threadIdx.x < n_seg ? cnt[threadIdx.x] : 0;
         const int incl = wave_incl_scan(c);
@@ -1674,7 +1664,7 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     const int count = c.count;
     if (!c.active || count <= SEL_TILE) return;     // cached lists are never this long
     const int len = seg_len(count);
-    const int n_seg = (count + len - 1) / len;
+    const int n_seg = seg_count(count);
     if ((int)blockIdx.x >= n_seg) return;
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
@@ -1690,7 +1680,7 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     clear_hist(sh);
     for (int sg = blockIdx.x; sg < n_seg; sg += gridDim.x) {
         const int lo = sg * len;
-        const int hi = lo + len < count ? lo + len : count;
+        const int hi = seg_end(lo, len, count);
         int base = lo;
         for (int start = lo; start < hi; start += SEG_TILE) {
             const int left = hi - start < SEG_TILE ? hi - start : SEG_TILE;
@@ -1856,9 +1846,9 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_topk_segments(TopkArgs A) {
     const int q = blockIdx.y, sg = blockIdx.x;
     const int count = (int)A.N;
     const int len = seg_len(count);
+    if (sg >= seg_count(count)) return;
     const int lo = sg * len;
-    if (lo >= count) return;
-    const int hi = lo + len < count ? lo + len : count;
+    const int hi = seg_end(lo, len, count);
     const float* vals = A.vals + (size_t)q * A.N;
     int32_t* tmp = A.list0 + (size_t)q * A.N;
     clear_hist(sh);

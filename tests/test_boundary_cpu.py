@@ -264,6 +264,47 @@ def test_topk_static_argument_errors_need_no_device(B):
     assert B.colbandit_workspace_bytes(8, 32, 128, 6000, 640000) <= B.STATIC_SCRATCH_BYTES
 
 
+def test_segments_of_a_list_cover_it_up_to_the_largest_size(tmp_path):
+    """The pre-filter's segments (cb_segments.h, the kernels' own arithmetic) against 64-bit sums: at
+    most 64 of them, whole tiles, together the list, from one entry to the largest N accepted."""
+    import subprocess
+    src, exe = tmp_path / "seg.cpp", tmp_path / "seg"
+    src.write_text("""
+#include <cstdio>
+#include "cb_segments.h"
+using namespace cb;
+int check(long long n) {
+    const int count = (int)n;
+    const long long len = seg_len(count), n_seg = seg_count(count);
+    if (len < SEG_TILE || len % SEG_TILE || n_seg < 1 || n_seg > SEG_MAX || (n_seg - 1) * len >= n || n_seg * len < n) return 1;
+    long long at = 0;
+    for (int s = 0; s < n_seg; ++s) {
+        if (s * len != at) return 1;
+        const int lo = s * (int)len, hi = seg_end(lo, (int)len, count);
+        if (lo != at || hi <= lo || hi - lo > len) return 1;
+        at = hi;
+    }
+    return at != n;
+}
+int main() {
+    const long long top = 0x7fffffffLL - (1 << 17);
+    int bad = 0;
+    for (long long tiles = 1; tiles * SEG_TILE <= top; tiles = tiles < 300 ? tiles + 1 : tiles + tiles / 97)
+        for (long long d = -2; d <= 2; ++d)
+            if (tiles * SEG_TILE + d >= 1 && tiles * SEG_TILE + d <= top) bad += check(tiles * SEG_TILE + d);
+    for (long long n = top - (1 << 25) - 3 * SEG_TILE; n <= top; n += n < top - 70000 ? 4093 : 1) bad += check(n);
+    std::printf("%d\\n", bad);
+    return bad != 0;
+}
+""")
+    inc = os.path.join(ROOT, "paper_2602_02827_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-fwrapv", "-std=c++17", "-I", inc, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    api = open(os.path.join(inc, "cb_api.hip")).read()
+    assert "N > 0x7fffffff - (1 << 17)" in api          # the limit that this test goes up to
+
+
 def test_workspace_and_trace_sizes(B):
     assert B.colbandit_workspace_bytes(0, 32, 128, 10, 100) == 0
     assert B.colbandit_workspace_bytes(1, 32, 128, 10, 5) == 0
