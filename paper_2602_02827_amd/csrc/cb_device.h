@@ -47,8 +47,9 @@ __device__ __forceinline__ unsigned long long work_item(int q, unsigned long lon
 __device__ __forceinline__ unsigned long long work_start(unsigned long long item) { return item >> 16; }
 __device__ __forceinline__ int work_query(unsigned long long item) { return (int)(item & 0xffffu); }
 
-// Chunk table of the corpus pass, chunk_doc[c] = min{ i : off[i] >= c*C }: entry i of N + 1 writes the
-// chunks that begin between its predecessor's first token and its own.
+// Chunk table of the corpus pass, chunk_doc[c] = min{ i : off[i] >= c*C } for c < n_chunks, and N at
+// the end (documents without tokens behind the last token belong to the last chunk): entry i of N + 1
+// writes the chunks that begin between its predecessor's first token and its own.
 __device__ __forceinline__ void chunk_docs(int64_t i, const int64_t* off, int64_t N, int C, int n_chunks,
                                            int32_t* chunk_doc) {
     if (i > N) return;
@@ -56,9 +57,13 @@ __device__ __forceinline__ void chunk_docs(int64_t i, const int64_t* off, int64_
     int64_t hi = off[i] / C;
     if (off[i] < 0) hi = -1;
     if (i > 0 && off[i - 1] < 0) lo = 0;
-    if (i == N) hi = n_chunks;       // everything past the last offset is empty
+    if (i == N) {                    // everything past the last offset is empty
+        hi = n_chunks;
+        lo = lo > n_chunks ? n_chunks : lo;
+    } else {
+        hi = hi > n_chunks - 1 ? n_chunks - 1 : hi;
+    }
     lo = lo < 0 ? 0 : lo;
-    hi = hi > n_chunks ? n_chunks : hi;
     for (int64_t c = lo; c <= hi; ++c) chunk_doc[c] = (int32_t)i;
 }
 

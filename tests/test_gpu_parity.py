@@ -212,6 +212,26 @@ def test_documents_without_tokens_get_minus_infinity_and_disturb_nothing(B, S, o
             assert np.all(np.isneginf(got[q][[i for i, n in enumerate(lengths) if n == 0]]))
 
 
+@pytest.mark.parametrize("dtype,nq,d,last", [("f32", 3, 128, 1024), ("f32", 3, 128, 1025), ("bf16", 1, 128, 1024),
+                                             ("bf16", 20, 64, 1025), ("bf16", 3, 96, 1024), ("f32", 40, 32, 1025)])
+def test_documents_without_tokens_behind_the_last_token_are_written(B, S, dtype, nq, d, last):
+    """The corpus pass: such documents begin where no chunk does (1,024: the tokens end with a chunk)
+    or are alone in theirs (1,025), and score -inf; no output keeps what was in the buffer before."""
+    row = d * (2 if dtype == "bf16" else 4)
+    lengths = [1024] * (int(4.2e7 / (nq * row * 1024)) + 1) + [last, 0, 0, 0]
+    w = _custom(S, lengths, nq, 32, d, dtype, 47)
+    assert nq * w.total_tokens * row > 40e6                      # not a call small enough to gather
+    out = {"scores": torch.full((nq, w.N), 7.0, device="cuda")}
+    full = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=4, out=out)
+    torch.cuda.synchronize()
+    assert torch.isneginf(full["scores"][:, -3:]).all() and (full["scores"][:, :-3].abs() < 32).all()
+    assert (full["topk_ids"] < w.N - 3).all()
+    res = [B.colbandit_topk(w.Q, w.docs, w.offsets, 4, 0.5, 0.01, 5, 3, trace=True, **o)
+           for o in ({"later_rounds": 1}, {"force_gather": True})]
+    torch.cuda.synchronize()
+    _same_run(*res)
+
+
 def test_nan_rows_and_token_less_documents_do_not_damage_other_documents(B, S, oracle_mod):
     """Inputs outside the contract: one document whose embeddings are NaN, one without tokens.
     Their own scores are meaningless, but they must neither enter a top-K nor wipe out a query's
