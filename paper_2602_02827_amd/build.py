@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcolbandit.so")
 SOURCES = ["cb_api.hip", "cb_kernels.hip", "cb_dense.hip", "cb_quant.hip", "cb_baselines.hip"]
-HEADERS = ["cb_device.h", "cb_launch.h", "cb_segments.h", os.path.join("..", "..", "include", "colbandit.h")]
+HEADERS = ["cb_device.h", "cb_launch.h", "cb_segments.h", "cb_sample.h", os.path.join("..", "..", "include", "colbandit.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-Xarch_device", "-fno-honor-nans", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed fp32 VALU forms are kept off for the device code of this library
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -305,6 +305,43 @@ int main() {
     assert "N > 0x7fffffff - (1 << 17)" in api          # the limit that this test goes up to
 
 
+@pytest.mark.parametrize("pieces", [4, 8, 12, 16])
+def test_the_quantisers_sample_sees_every_column(tmp_path, pieces):
+    """cb_sample.h, the kernel's own arithmetic: one piece in every run of `step`, ascending and in range,
+    and over rows of `pieces` pieces (d = 32 to 128 of bf16) every column about equally often, whatever
+    factors the step shares with the row: a share of 16384 / pieces within six standard deviations."""
+    import subprocess
+    src, exe = tmp_path / "sample.cpp", tmp_path / "sample"
+    src.write_text("""
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <initializer_list>
+#include "cb_sample.h"
+int main(int, char** v) {
+    const int pieces = std::atoi(v[1]);
+    int bad = 0;
+    for (long long step : {512LL, 513LL, 976LL, 977LL, 1024LL, 7812LL, 8192LL, 1LL << 20, (1LL << 30) + 16}) {
+        int seen[16] = {};
+        for (int i = 0; i < 16384; ++i) {
+            const long long p = cb::sample_piece((uint32_t)i, step);
+            if (p < i * step || p >= (i + 1) * step) ++bad;
+            ++seen[p % pieces];
+        }
+        const double mean = 16384.0 / pieces;
+        for (int c = 0; c < pieces; ++c)
+            if (std::fabs(seen[c] - mean) > 6 * std::sqrt(mean)) ++bad;
+    }
+    std::printf("%d\\n", bad);
+    return bad != 0;
+}
+""")
+    inc = os.path.join(ROOT, "paper_2602_02827_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", inc, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe), str(pieces)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
 def test_workspace_and_trace_sizes(B):
     assert B.colbandit_workspace_bytes(0, 32, 128, 10, 100) == 0
     assert B.colbandit_workspace_bytes(1, 32, 128, 10, 5) == 0

@@ -809,6 +809,28 @@ def test_quantize_i8_codes_and_scales_match_oracle(B, oracle_mod, dtype, rows, d
     assert int(cz.abs().max()) == 0 and float(sz[0]) == 0.0
 
 
+@pytest.mark.parametrize("rows,d", [(1 << 20, 128), (1000000, 128), (1 << 20, 64), (1 << 20, 96)])
+def test_one_counting_pass_finds_the_clip_of_columns_of_unequal_scale(B, rows, d):
+    """The sampled bound of a long segment serves columns whose scales differ a hundredfold, also where
+    the distance of the samples shares factors with the rows: the clip is known after the counting
+    pass (the state at the head of the workspace says so) and is the exact order statistic."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + d)
+    for scale in (torch.logspace(0, -2, d), torch.logspace(-2, 0, d)):
+        x = (torch.randn((rows, d), generator=g, device="cuda") * scale.cuda()).to(torch.bfloat16)
+        codes = torch.empty(x.shape, dtype=torch.int8, device="cuda")
+        scales = torch.empty(1, device="cuda")
+        ws = torch.zeros(B.lib().colbandit_quantize_workspace_bytes(1), dtype=torch.uint8, device="cuda")
+        rc = B.lib().colbandit_quantize_i8(x.data_ptr(), 1, 1, rows, d, 999, codes.data_ptr(), scales.data_ptr(),
+                                           ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0
+        assert ws[:24].view(torch.int32)[5].item() == 1           # rank (two words), prefix, mask, bound, done
+        drop = x.numel() - (x.numel() * 999 + 999) // 1000
+        clip = x.abs().reshape(-1).topk(drop + 1).values[drop].float().cpu().numpy()
+        assert scales.cpu().numpy()[0] == clip / np.float32(127)
+
+
 @pytest.mark.parametrize("kind,permille", [("normal", 999), ("normal", 1000), ("normal", 986), ("normal", 900),
                                            ("constant", 999), ("rare", 999), ("wide", 999), ("sorted", 999)])
 def test_quantize_long_bf16_segment_by_its_tail(B, kind, permille):
