@@ -35,7 +35,7 @@ constexpr int DENSE_THREADS = 256;
 // batches: bound by memory, little register use) take 32-row stages, so that four workgroups fit
 // a CU instead of two and more wavefronts hide the latencies; the others take 64-row stages.
 // A_REGS: registers of one operand block (the query rows take NT of them, two token blocks are in
-// flight); four, three or two workgroups per CU by what that leaves.
+// flight); four, three or two workgroups per CU by what that and the rings' LDS leave.
 template <int NT, int PITCH, int A_REGS> struct RingShape {
     static constexpr int ROWS_PER_LOAD = 64 / (PITCH / 16);
     static constexpr bool SMALL = NT <= 4 && 32 / ROWS_PER_LOAD / 4 >= 1;
@@ -44,7 +44,10 @@ template <int NT, int PITCH, int A_REGS> struct RingShape {
     static constexpr int REGS = (NT + 2) * A_REGS + 40;
     static constexpr int BY_REGS = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : 2);
     static constexpr int BY_SHAPE = SMALL ? (NT <= 2 ? 4 : 3) : 2;
-    static constexpr int MIN_BLOCKS = BY_REGS < BY_SHAPE ? BY_REGS : BY_SHAPE;
+    static constexpr int BY_LDS = 160 * 1024 / (RING_ROWS * PITCH);   // fp32 at d = 96 and 128: two
+    static constexpr int FIT = BY_REGS < BY_SHAPE ? BY_REGS : BY_SHAPE;
+    static constexpr int MIN_BLOCKS = FIT < BY_LDS ? FIT : BY_LDS;
+    static_assert(MIN_BLOCKS >= 1 && MIN_BLOCKS * RING_ROWS * PITCH <= 160 * 1024, "the rings of a CU's workgroups");
 };
 // bytes of a token row, and of its place in the ring (a power of two)
 template <class F, int D> struct RowShape {
