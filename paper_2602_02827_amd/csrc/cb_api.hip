@@ -108,7 +108,9 @@ Work carve(void* ws, const Layout& L) {
 
 // Sets the chunk length for passes over `tiles` column tiles, and the place of the chunk table.
 // fp32 chunks are shorter: a token costs ten times the matrix time, so a workgroup's start weighs
-// less and an uneven last turn of workgroups more (kBlocksWanted).
+// less and an uneven last turn of workgroups more (kBlocksWanted).  Groups are counted by the work of a
+// whole one: fp32 batches that go in groups of half as many tiles get twice the workgroups, of the same
+// work each (9 queries, 6.4 M tokens of d = 32: 1,355 us; 1,399 with the groups that are launched).
 void choose_chunks(Work& W, const Problem& P, int64_t tiles, bool codes = false) {
     const bool f32 = P.dt == DT_F32 && !codes;
     const int64_t per_group = f32 ? 16 : 32;
@@ -123,12 +125,6 @@ void choose_chunks(Work& W, const Problem& P, int64_t tiles, bool codes = false)
     // quantiser's scratch, which the coding of queries (one workgroup per query) does not use.
     static_assert((kBlocksWanted + 1) * 4 <= 16384, "quantize_scratch_bytes holds 16 KB per segment");
     if (c < kChunkTokens) W.chunk_doc = (int32_t*)W.qscratch;
-}
-
-// column tiles of the exhaustive kernel: 16 query tokens each, 1, 2, 4 or 8 per query
-int64_t score_tiles(const Problem& P) {
-    const int tq = (P.T + 15) / 16;
-    return (int64_t)P.nq * (tq <= 1 ? 1 : tq <= 2 ? 2 : tq <= 4 ? 4 : 8);
 }
 
 // Scoring or revealing every pair by gathering, a wavefront or workgroup each, beats the corpus pass
@@ -379,7 +375,7 @@ int colbandit_coarse_maxsim(const void* Q, int n_queries, int T, int d, colbandi
     if (rc) return rc;
     Work W = carve(workspace, L);
     const Problem P{Q, n_queries, T, d, (int)dt, docs_i8, doc_offsets, N, total_tokens};
-    choose_chunks(W, P, score_tiles(P), true);
+    choose_chunks(W, P, score_shape(P, true).tiles, true);
     hipStream_t st = (hipStream_t)stream;
     Coarse co{docs_i8, docs_scale, W.q8, W.qscale};
     if (!dense_supported(P, &co)) return COLBANDIT_ERR_UNSUPPORTED;
@@ -463,7 +459,7 @@ int colbandit_doc_uniform(const void* Q, int n_queries, int T, int d, colbandit_
     if (rc) return rc;
     Work W = carve(workspace, make_layout(n_queries, T, d, N, total_tokens));
     const Problem P{Q, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
-    choose_chunks(W, P, score_tiles(P));
+    choose_chunks(W, P, score_shape(P, false).tiles);
     hipStream_t st = (hipStream_t)stream;
     float* cells = (float*)((char*)workspace + U.cells);
     float* out = scores ? scores : W.scores;
@@ -607,7 +603,7 @@ int colbandit_full_maxsim(const void* Q, int n_queries, int T, int d, colbandit_
         e = launch_gather_all(P, W, out, cells, st);
     } else {
         int n_chunks = 0;
-        choose_chunks(W, P, score_tiles(P));
+        choose_chunks(W, P, score_shape(P, false).tiles);
         e = launch_dense_prepare(P, W, &n_chunks, st);
         mark();
         if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, out, cells, nullptr, st);

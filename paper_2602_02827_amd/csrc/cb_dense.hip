@@ -103,10 +103,12 @@ void k_dense(DenseArgs A) {
     constexpr int NCH = PITCH / 16;                // 16-byte pieces per ring row
     constexpr bool F32 = __is_same(Tag, f32_tag);
     // Cache policy of the token copies.  The reveal pass normally has one column group, and the
-    // score kernels with at most four column tiles per wavefront always have (fp32: at most two):
-    // a token row is read once and should not push other lines out of L2 - above all those of the
-    // (sum, M2) array, which fill up over several documents; such copies carry the non-temporal
-    // hint (bit 1).
+    // score kernels with at most four column tiles per wavefront always have (fp32: normally with
+    // two): a token row is read once and should not push other lines out of L2 - above all those of
+    // the (sum, M2) array, which fill up over several documents; such copies carry the non-temporal
+    // hint (bit 1).  Several fp32 groups of two tiles read a row again; they are bound by the matrix
+    // pipes and as fast with the hint as without (9 queries 1,740 and 1,738 us), one group is not (4
+    // queries 623 and 628).
     constexpr int LOAD_POLICY = F32 ? (NT <= 2 ? 2 : 0) : (REVEAL || NT <= 4) ? 2 : 0;
     // Swizzle key of a ring row: rows whose 16-byte pieces would fall on the same banks (row
     // stride PITCH against the 256-byte bank window) get different keys.  The key's period must
@@ -618,9 +620,8 @@ static void fill_dense(DenseArgs& A, const Problem& P, const Work& W, int n_chun
 }
 
 template <typename Tag, int D, int NT, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
-static hipError_t dense_go(DenseArgs& A, int tiles, hipStream_t st) {
-    constexpr int PER_WAVE = PACKED ? 8 : NT;       // whole tiles' worth of queries
-    A.n_groups = SPLIT_DOCS ? 1 : (tiles + 4 * PER_WAVE - 1) / (4 * PER_WAVE);
+static hipError_t dense_go(DenseArgs& A, int groups, hipStream_t st) {
+    A.n_groups = groups;
     const int chunks8 = (A.n_chunks + 7) / 8 * 8;
     const long long blocks = (long long)chunks8 * A.n_groups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -628,56 +629,73 @@ static hipError_t dense_go(DenseArgs& A, int tiles, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename Tag, int D, int TQ>
-static hipError_t dense_score_nt(DenseArgs& A, int tiles, hipStream_t st) {
+ScoreShape score_shape(const Problem& P, bool codes) {
+    const bool f32 = P.dt == DT_F32 && !codes;
+    const int tq = (P.T + 15) / 16;
+    ScoreShape s{};
+    s.tq = tq <= 1 ? 1 : tq <= 2 ? 2 : tq <= 4 ? 4 : 8;
+    s.tiles = (int64_t)P.nq * s.tq;
     // one or two queries (twice as many of at most 16 tokens): the tiles fit one or two
     // wavefronts, and four or two wavefronts split the documents
-    if constexpr (TQ == 4) {
-        if (tiles <= 4) return dense_go<Tag, D, 4, TQ, false, 4>(A, tiles, st);
-        if (tiles <= 8) return dense_go<Tag, D, 4, TQ, false, 2>(A, tiles, st);
+    const int few = s.tq <= 2 ? 2 : s.tq;
+    if (s.tiles <= 2 * few) {
+        s.nt = few;
+        s.split = s.tiles <= few ? 4 : 2;
+        s.groups = 1;
+        return s;
     }
-    if constexpr (TQ == 8 && Tag::wide) {
-        if (tiles <= 8) return dense_go<Tag, D, 8, TQ, false, 4>(A, tiles, st);
-        if (tiles <= 16) return dense_go<Tag, D, 8, TQ, false, 2>(A, tiles, st);
-    }
-    if constexpr (TQ <= 2) {
-        if (tiles <= 2) return dense_go<Tag, D, 2, TQ, false, 4>(A, tiles, st);
-        if (tiles <= 4) return dense_go<Tag, D, 2, TQ, false, 2>(A, tiles, st);
-        if (tiles <= 8) return dense_go<Tag, D, 2, TQ, false>(A, tiles, st);
-    }
+    if (s.tq <= 2 && s.tiles <= 8) s.nt = 2;
     // fp32 is bound by the matrix pipes: half as many tiles per wavefront where that leaves clearly
     // fewer of them empty (9 queries of two tiles, 24 instead of 32 multiplied: 10,000 documents of
     // d = 128 1,119 -> 914 us, 1,827 of d = 64 146 -> 115; 27 queries 2,146 -> 2,035)
-    if constexpr (!Tag::wide && TQ <= 2) {
-        if ((tiles + 7) / 8 * 8 * 9 < (tiles + 15) / 16 * 16 * 8) return dense_go<Tag, D, 2, TQ, false>(A, tiles, st);
+    else if (f32 && s.tq <= 2 && (s.tiles + 7) / 8 * 8 * 9 < (s.tiles + 15) / 16 * 16 * 8) s.nt = 2;
+    else if (f32 || (s.tq <= 4 && s.tiles <= 16)) s.nt = 4;
+    else s.nt = 8;
+    s.groups = (int)((s.tiles + 4 * s.nt - 1) / (4 * s.nt));
+    return s;
+}
+
+template <typename Tag, int D, int TQ>
+static hipError_t dense_score_nt(DenseArgs& A, const ScoreShape& s, hipStream_t st) {
+    if constexpr (TQ <= 2) {
+        if (s.split == 4) return dense_go<Tag, D, 2, TQ, false, 4>(A, 1, st);
+        if (s.split == 2) return dense_go<Tag, D, 2, TQ, false, 2>(A, 1, st);
+        if (s.nt == 2) return dense_go<Tag, D, 2, TQ, false>(A, s.groups, st);
+    }
+    if constexpr (TQ == 4) {
+        if (s.split == 4) return dense_go<Tag, D, 4, TQ, false, 4>(A, 1, st);
+        if (s.split == 2) return dense_go<Tag, D, 4, TQ, false, 2>(A, 1, st);
+    }
+    if constexpr (TQ == 8 && Tag::wide) {
+        if (s.split == 4) return dense_go<Tag, D, 8, TQ, false, 4>(A, 1, st);
+        if (s.split == 2) return dense_go<Tag, D, 8, TQ, false, 2>(A, 1, st);
     }
     if constexpr (TQ <= 4) {
-        if (!Tag::wide || tiles <= 16) return dense_go<Tag, D, 4, TQ, false>(A, tiles, st);
+        if (s.nt == 4) return dense_go<Tag, D, 4, TQ, false>(A, s.groups, st);
     }
     if constexpr (Tag::wide && D >= 64) {
-        A.hq = (A.T + 7) / 8;
-        if (A.hq * (8 / TQ) <= 2 * PACKED_NT) return dense_go<Tag, D, PACKED_NT, TQ, false, 0, true>(A, tiles, st);
+        A.hq = (A.T + 7) / 8;                       // a wavefront's queries are those of eight whole tiles
+        if (A.hq * (8 / TQ) <= 2 * PACKED_NT) return dense_go<Tag, D, PACKED_NT, TQ, false, 0, true>(A, s.groups, st);
     }
-    if constexpr (Tag::wide) return dense_go<Tag, D, 8, TQ, false>(A, tiles, st);
+    if constexpr (Tag::wide) return dense_go<Tag, D, 8, TQ, false>(A, s.groups, st);
     else return hipErrorInvalidValue;
 }
 
 template <typename Tag, int D>
-static hipError_t dense_score_d(DenseArgs& A, hipStream_t st) {
-    const int tq = (A.T + 15) / 16;
-    if (tq <= 1) return dense_score_nt<Tag, D, 1>(A, A.nq * 1, st);
-    if (tq <= 2) return dense_score_nt<Tag, D, 2>(A, A.nq * 2, st);
-    if (tq <= 4) return dense_score_nt<Tag, D, 4>(A, A.nq * 4, st);
-    if constexpr (Tag::wide) return dense_score_nt<Tag, D, 8>(A, A.nq * 8, st);
+static hipError_t dense_score_d(DenseArgs& A, const ScoreShape& s, hipStream_t st) {
+    if (s.tq == 1) return dense_score_nt<Tag, D, 1>(A, s, st);
+    if (s.tq == 2) return dense_score_nt<Tag, D, 2>(A, s, st);
+    if (s.tq == 4) return dense_score_nt<Tag, D, 4>(A, s, st);
+    if constexpr (Tag::wide) return dense_score_nt<Tag, D, 8>(A, s, st);
     else return hipErrorInvalidValue;
 }
 
-template <typename Tag> static hipError_t dense_score_any_d(DenseArgs& A, int d, hipStream_t st) {
+template <typename Tag> static hipError_t dense_score_any_d(DenseArgs& A, const ScoreShape& s, int d, hipStream_t st) {
     switch (d) {
-        case 128: return dense_score_d<Tag, 128>(A, st);
-        case 96: return dense_score_d<Tag, 96>(A, st);
-        case 64: return dense_score_d<Tag, 64>(A, st);
-        default: return dense_score_d<Tag, 32>(A, st);
+        case 128: return dense_score_d<Tag, 128>(A, s, st);
+        case 96: return dense_score_d<Tag, 96>(A, s, st);
+        case 64: return dense_score_d<Tag, 64>(A, s, st);
+        default: return dense_score_d<Tag, 32>(A, s, st);
     }
 }
 
@@ -695,20 +713,21 @@ hipError_t launch_dense_score(const Problem& P, const Work& W, int n_chunks, flo
     fill_dense(A, P, W, n_chunks);
     A.out = out;
     A.cells = cells;
+    const ScoreShape s = score_shape(P, co != nullptr);
     if (co) {
         use_codes(A, co);
-        return P.d == 128 ? dense_score_d<i8_tag, 128>(A, st) : dense_score_d<i8_tag, 64>(A, st);
+        return P.d == 128 ? dense_score_d<i8_tag, 128>(A, s, st) : dense_score_d<i8_tag, 64>(A, s, st);
     }
-    return P.dt == DT_BF16 ? dense_score_any_d<bf16_tag>(A, P.d, st) : dense_score_any_d<f32_tag>(A, P.d, st);
+    return P.dt == DT_BF16 ? dense_score_any_d<bf16_tag>(A, s, P.d, st) : dense_score_any_d<f32_tag>(A, s, P.d, st);
 }
 
 template <typename Tag, int D>
 static hipError_t dense_reveal_d(DenseArgs& A, hipStream_t st) {
     const int tiles = (A.nq * A.G + 15) / 16;
-    if (tiles <= 4) return dense_go<Tag, D, 1, 1, true>(A, tiles, st);
-    if (tiles <= 8) return dense_go<Tag, D, 2, 1, true>(A, tiles, st);
-    if (!Tag::wide || tiles <= 16) return dense_go<Tag, D, 4, 1, true>(A, tiles, st);
-    if constexpr (Tag::wide) return dense_go<Tag, D, 8, 1, true>(A, tiles, st);
+    if (tiles <= 4) return dense_go<Tag, D, 1, 1, true>(A, 1, st);
+    if (tiles <= 8) return dense_go<Tag, D, 2, 1, true>(A, 1, st);
+    if (!Tag::wide || tiles <= 16) return dense_go<Tag, D, 4, 1, true>(A, (tiles + 15) / 16, st);
+    if constexpr (Tag::wide) return dense_go<Tag, D, 8, 1, true>(A, (tiles + 31) / 32, st);
     else return hipErrorInvalidValue;
 }
 template <typename Tag> static hipError_t dense_reveal_any_d(DenseArgs& A, int d, hipStream_t st) {

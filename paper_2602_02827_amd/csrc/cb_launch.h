@@ -112,6 +112,15 @@ hipError_t launch_dense_reveal(const Problem& P, const Work& W, int n_chunks,
 // them into the running statistics of the documents still active.
 hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chunks, const RevealRound& rr, int G, const Coarse* co,
                                      hipStream_t st);
+// How an exhaustive pass covers P's queries with column tiles of 16 query tokens.  codes: on int8 codes.
+struct ScoreShape {
+    int tq;               // tiles per query: 1, 2, 4 or 8
+    int64_t tiles;        // of all queries
+    int nt;               // tiles per wavefront
+    int split;            // > 0: wavefronts that take the same tiles and split the documents
+    int groups;           // column groups (workgroups that stream the same tokens)
+};
+ScoreShape score_shape(const Problem& P, bool codes);
 bool dense_supported(const Problem& P, const Coarse* co);
 int dense_chunks(const Problem& P, const Work& W);
 
