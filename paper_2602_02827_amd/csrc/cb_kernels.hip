@@ -184,6 +184,7 @@ struct GatherArgs {
     // score
     float* out;
     float* cells;
+    int shared;               // k_gather_all: the wavefronts of a workgroup share a document (gather_shares)
     int score_slots;          // also serve queries whose list holds cache slots
     // int8 codes: a cell is the integer maximum times qscale[q] * dscale[0]
     const float* qscale;
@@ -474,30 +475,34 @@ __global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
     }
 }
 
-// All documents of all queries, a wavefront per pair.
+// All documents of all queries, a wavefront per pair, or (shared) a workgroup, whose wavefronts share
+// the document's blocks.
 template <typename Tag, int D, int TQ>
 __global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
+    __shared__ int ex[EX_FLOATS];
     const int q = blockIdx.y;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int col = lane & 15;
     const int kg = lane >> 4;
-    const int first = blockIdx.x * 4 + wave;
-    if (first >= (int)A.N) return;
+    const int parts = A.shared ? 4 : 1;
+    const int first = A.shared ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
+    if (first >= (int)A.N) return;                  // shared: the same for the whole workgroup
     F bq[TQ];
     load_query<F, ROWB, TQ>(A, q, col, kg, bq);
-    for (int id = first; id < (int)A.N; id += gridDim.x * 4) {
+    for (int id = first; id < (int)A.N; id += (int)gridDim.x * (4 / parts)) {
         int64_t o0, o1;
         doc_range(A, id, o0, o1);
         V h[TQ];
 #pragma unroll
         for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-        fold_doc<ROWB>((const char*)A.docs, o0, o1, 0, 1, col, kg, bq, h);
+        fold_doc<ROWB>((const char*)A.docs, o0, o1, A.shared ? wave : 0, parts, col, kg, bq, h);
         float w[Pack<TQ>::NW];
-        doc_cells(h, 1, 1.f, nullptr, w);
+        doc_cells(h, parts, 1.f, ex, w);
+        if (A.shared && wave > 0) continue;
         using SC = Score<TQ, TQ>;
         float sc[SC::NS];
         SC::finish(w, A.T, col, sc);
@@ -616,11 +621,21 @@ hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs&
     return gather_any(A, GM_SURVIVORS, P, W, dim3((unsigned)(P.N < want ? P.N : want), P.nq), nullptr, st);
 }
 
+// A workgroup per pair where wavefronts would be few, or where their last turn (1,024 SIMDs) would
+// be emptier and the documents are long enough for four: 10 documents of 15,000 tokens 459 us with a
+// wavefront each and 123 shared (bf16, one query), 200 of 1,030 x 6 fp32 queries 186 and 124; 1,000 pairs
+// of 1,030 196 and 207, 1,000 of 48 13 and 16.
+bool gather_shares(const Problem& P) {
+    const int64_t pairs = (int64_t)P.nq * P.N;
+    return pairs < 768 || (pairs < 4096 && P.total >= 512 * P.N && 4 * ((pairs + 1023) / 1024) > (pairs + 255) / 256);
+}
+
 hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float* cells, hipStream_t st) {
     GatherArgs A{};
     A.out = out;
     A.cells = cells;
-    const int64_t gx = (P.N + 3) / 4;
+    A.shared = gather_shares(P) ? 1 : 0;
+    const int64_t gx = A.shared ? P.N : (P.N + 3) / 4;
     return gather_any(A, GM_ALL, P, W, dim3((unsigned)(gx < 256 ? gx : 256), P.nq), nullptr, st);
 }
 

@@ -97,6 +97,7 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
 hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,
                                    bool score_slots, hipStream_t st);
 hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float* cells, hipStream_t st);
+bool gather_shares(const Problem& P);   // launch_gather_all gives a pair a workgroup
 
 // Dense (corpus-streaming) kernel: Full-MaxSim scores or the first reveal batch.
 hipError_t launch_dense_prepare(const Problem& P, const Work& W, int* n_chunks,

@@ -131,6 +131,43 @@ def test_corpus_pass_of_every_width_and_type(B, S, oracle_mod, dtype, nq, T, d):
     assert torch.equal(dense["topk_scores"], torch.gather(r["scores"], 1, dense["topk_ids"]))
 
 
+def _kernels(fn):
+    """The names of the kernels that fn launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    return " ".join(e.key for e in p.key_averages())
+
+
+@pytest.mark.parametrize("dtype,N,L,nq,T,d,kernel",
+                         [("bf16", 10, 3000, 1, 32, 128, "k_gather_all"), ("bf16", 1, 5000, 3, 100, 64, "k_gather_all"),
+                          ("bf16", 767, 40, 1, 24, 96, "k_gather_all"), ("bf16", 768, 40, 1, 8, 96, "k_gather_all"),
+                          ("bf16", 1000, 520, 1, 32, 32, "k_gather_all"), ("bf16", 3000, 100, 3, 32, 128, "k_dense"),
+                          ("f32", 30, 3000, 2, 32, 128, "k_gather_all"), ("f32", 600, 520, 2, 48, 64, "k_gather_all")])
+def test_paths_of_exhaustive_scoring(B, dtype, N, L, nq, T, d, kernel):
+    """Gathered calls whose documents a workgroup's wavefronts share (few long ones) and do not, and the
+    corpus pass: scores and cells against products in 64 bits."""
+    g = torch.Generator(device="cuda"); g.manual_seed(N + L + nq)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    docs = torch.nn.functional.normalize(torch.randn((N * L, d), generator=g, device="cuda"), dim=1).to(td)
+    Q = torch.nn.functional.normalize(torch.randn((nq, T, d), generator=g, device="cuda"), dim=2).to(td)
+    off = torch.arange(0, N * L + 1, L, device="cuda", dtype=torch.int64)
+    res = []
+    K = min(N, 3)
+    assert kernel in _kernels(lambda: res.append(B.colbandit_full_maxsim(Q, docs, off, K=K, want_cells=True)))
+    rows = Q.reshape(nq * T, d).double().t()
+    for lo in range(0, N, 500):
+        hi = min(N, lo + 500)
+        H = (docs[lo * L:hi * L].double() @ rows).view(hi - lo, L, nq, T).amax(1).permute(1, 0, 2)
+        for r in res:
+            assert (r["scores"][:, lo:hi] - H.sum(2)).abs().max() < 1e-6 * T      # 32-bit sums of T cells below 1
+        assert (res[0]["cells"][:, lo:hi] - H).abs().max() < 1e-6
+    order = torch.argsort(res[0]["scores"], dim=1, descending=True, stable=True)[:, :K]
+    assert torch.equal(order, res[0]["topk_ids"])
+
+
 @pytest.mark.parametrize("T,d", [(1, 128), (8, 64), (9, 128), (17, 128), (24, 96), (25, 64), (33, 128), (48, 64),
                                  (49, 128), (65, 64), (96, 128), (97, 64)])
 def test_packed_query_tiles_give_the_bits_of_whole_tiles(B, S, oracle_mod, T, d):
