@@ -136,6 +136,21 @@ bool small_call(const Problem& P) {
     return bytes <= 40e6;
 }
 
+// Scores of all pairs: by gathering, or by a corpus pass, for which the chunks are set.
+bool score_by_gather(Work& W, const Problem& P) {
+    choose_chunks(W, P, score_shape(P, false).tiles);
+    // One or two fp32 queries of more than 16 tokens are bound by the matrix pipes, and there the
+    // corpus kernel's wavefronts, which split the documents, all multiply the blocks in which one
+    // ends.  15.9 M tokens, gathering against the corpus pass: 4.5 and 5.9 ms for one query of 42
+    // tokens, 6.8 and 7.6 for two, 3.30 and 3.38 for one of 32.
+    // Five queries of two tiles fill ten of the sixteen tiles that the corpus kernel multiplies; as long
+    // as the last-level cache (256 MB) serves most of the five readings of the corpus, gathering wins:
+    // 0.19 M tokens of d = 64 66 and 84 us, 2.1 M of d = 32 272 and 317; 2.1 M of d = 128 (1.1 GB) 1,269
+    // and 1,124.  Six: 76 and 84 for the first, 1,422 and 1,124 for the last.
+    const bool few_tiles = P.nq == 5 && P.T > 16 && P.T <= 32 && (double)P.total * P.d * 4.0 <= 330e6;
+    return small_call(P) || (P.dt == DT_F32 && ((P.T > 16 && P.nq <= 2) || few_tiles));
+}
+
 int check_shapes(const void* Q, int nq, int T, int d, int dt, const void* docs,
                  const int64_t* off, int64_t N, int64_t total) {
     if (!Q || !docs || !off) return COLBANDIT_ERR_NULL;
@@ -459,14 +474,18 @@ int colbandit_doc_uniform(const void* Q, int n_queries, int T, int d, colbandit_
     if (rc) return rc;
     Work W = carve(workspace, make_layout(n_queries, T, d, N, total_tokens));
     const Problem P{Q, n_queries, T, d, (int)dt, doc_tokens, doc_offsets, N, total_tokens};
-    choose_chunks(W, P, score_shape(P, false).tiles);
     hipStream_t st = (hipStream_t)stream;
     float* cells = (float*)((char*)workspace + U.cells);
     float* out = scores ? scores : W.scores;
     // the whole MaxSim matrix (exhaustive row sums go to a scratch array), then the subset sums
-    int n_chunks = 0;
-    hipError_t e = launch_dense_prepare(P, W, &n_chunks, st);
-    if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, W.rescored, cells, nullptr, st);
+    hipError_t e = hipSuccess;
+    if (score_by_gather(W, P)) {
+        e = launch_gather_all(P, W, W.rescored, cells, st);
+    } else {
+        int n_chunks = 0;
+        e = launch_dense_prepare(P, W, &n_chunks, st);
+        if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, W.rescored, cells, nullptr, st);
+    }
     if (e == hipSuccess)
         e = launch_uniform_score(cells, n_queries, N, T, cells_per_doc, seed, out, masks, st);
     if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
@@ -589,21 +608,11 @@ int colbandit_full_maxsim(const void* Q, int n_queries, int T, int d, colbandit_
     };
     hipError_t e = hipSuccess;
     mark();
-    // One or two fp32 queries of more than 16 tokens are bound by the matrix pipes, and there the
-    // corpus kernel's wavefronts, which split the documents, all multiply the blocks in which one
-    // ends.  15.9 M tokens, gathering against the corpus pass: 4.5 and 5.9 ms for one query of 42
-    // tokens, 6.8 and 7.6 for two, 3.30 and 3.38 for one of 32.
-    // Five queries of two tiles fill ten of the sixteen tiles that the corpus kernel multiplies; as long
-    // as the last-level cache (256 MB) serves most of the five readings of the corpus, gathering wins:
-    // 0.19 M tokens of d = 64 66 and 84 us, 2.1 M of d = 32 272 and 317; 2.1 M of d = 128 (1.1 GB) 1,269
-    // and 1,124.  Six: 76 and 84 for the first, 1,422 and 1,124 for the last.
-    const bool few_tiles = n_queries == 5 && T > 16 && T <= 32 && (double)total_tokens * d * 4.0 <= 330e6;
-    if (small_call(P) || (dt == COLBANDIT_F32 && ((T > 16 && n_queries <= 2) || few_tiles))) {
+    if (score_by_gather(W, P)) {
         mark();
         e = launch_gather_all(P, W, out, cells, st);
     } else {
         int n_chunks = 0;
-        choose_chunks(W, P, score_shape(P, false).tiles);
         e = launch_dense_prepare(P, W, &n_chunks, st);
         mark();
         if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, out, cells, nullptr, st);

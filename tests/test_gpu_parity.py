@@ -148,7 +148,8 @@ def _kernels(fn):
                           ("f32", 30, 3000, 2, 32, 128, "k_gather_all"), ("f32", 600, 520, 2, 48, 64, "k_gather_all")])
 def test_paths_of_exhaustive_scoring(B, dtype, N, L, nq, T, d, kernel):
     """Gathered calls whose documents a workgroup's wavefronts share (few long ones) and do not, and the
-    corpus pass: scores and cells against products in 64 bits."""
+    corpus pass: scores and cells against products in 64 bits; Doc-Uniform takes its cells from the
+    same path."""
     g = torch.Generator(device="cuda"); g.manual_seed(N + L + nq)
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
     docs = torch.nn.functional.normalize(torch.randn((N * L, d), generator=g, device="cuda"), dim=1).to(td)
@@ -157,6 +158,8 @@ def test_paths_of_exhaustive_scoring(B, dtype, N, L, nq, T, d, kernel):
     res = []
     K = min(N, 3)
     assert kernel in _kernels(lambda: res.append(B.colbandit_full_maxsim(Q, docs, off, K=K, want_cells=True)))
+    if T <= 64:
+        assert kernel in _kernels(lambda: res.append(B.colbandit_doc_uniform(Q, docs, off, K, T)))
     rows = Q.reshape(nq * T, d).double().t()
     for lo in range(0, N, 500):
         hi = min(N, lo + 500)
