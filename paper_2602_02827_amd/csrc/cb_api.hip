@@ -136,19 +136,40 @@ bool small_call(const Problem& P) {
     return bytes <= 40e6;
 }
 
-// Scores of all pairs: by gathering, or by a corpus pass, for which the chunks are set.
+// Scores of all pairs: by gathering, or by a corpus pass, for which the chunks are set.  bf16: small_call.
+// fp32 is bound by the matrix pipes either way, so what decides is how many of the column tiles that a
+// pass multiplies are filled, and whether either fills the chip.  Time model (microseconds), from 900
+// shapes (4 to 20,000 documents of 48 to 20,000 tokens, 1 to 32 queries of 16 to 48, d = 32 to 128), on
+// which it picks the faster path or one within 8 % of it but for 19 (at most 1.34x):
+//   pass    a token costs 31 ps a tile multiplied, 35.5 at two a wavefront (d = 128; empty ones as well; short
+//           chunks more, and wavefronts that split the documents repeat blocks in which one ends);
+//           never less than a document's blocks one after the other in one workgroup
+//   gather  43 ps a tile filled, 51 with four tiles a query of d = 96 and 128; a document's last block
+//           counted whole; every query reads the corpus, at 7.4 TB/s, and reads again cost up to three
+//           tenths more beyond the last-level cache; never less than a document's blocks one after
+//           the other in a wavefront, or shared by four (gather_shares)
+// gather and pass, us: 5,000 documents of 100 tokens, d = 128, T = 32: 1 query 83 and 162, 3 160 and 189, 4
+// 206 and 188, 5 256 and 323, 8 386 and 322, 9 431 and 499, 16 745 and 607; T = 16: 5 190 and 190; 20,000
+// (1 GB): 2 478 and 550, 3 650 and 597, 5 1,102 and 1,064; 50 of 8,000: 8 363 and 1,812.
+// One query, and two of more than 16 tokens, fill a quarter to a half of a pass's tiles and gather at
+// all sizes (1 GB, T = 16: 198 and 453, T = 32: 412 and 453, T = 48 in d = 64: 323 and 508).
 bool score_by_gather(Work& W, const Problem& P) {
-    choose_chunks(W, P, score_shape(P, false).tiles);
-    // One or two fp32 queries of more than 16 tokens are bound by the matrix pipes, and there the
-    // corpus kernel's wavefronts, which split the documents, all multiply the blocks in which one
-    // ends.  15.9 M tokens, gathering against the corpus pass: 4.5 and 5.9 ms for one query of 42
-    // tokens, 6.8 and 7.6 for two, 3.30 and 3.38 for one of 32.
-    // Five queries of two tiles fill ten of the sixteen tiles that the corpus kernel multiplies; as long
-    // as the last-level cache (256 MB) serves most of the five readings of the corpus, gathering wins:
-    // 0.19 M tokens of d = 64 66 and 84 us, 2.1 M of d = 32 272 and 317; 2.1 M of d = 128 (1.1 GB) 1,269
-    // and 1,124.  Six: 76 and 84 for the first, 1,422 and 1,124 for the last.
-    const bool few_tiles = P.nq == 5 && P.T > 16 && P.T <= 32 && (double)P.total * P.d * 4.0 <= 330e6;
-    return small_call(P) || (P.dt == DT_F32 && ((P.T > 16 && P.nq <= 2) || few_tiles));
+    const ScoreShape s = score_shape(P, false);
+    choose_chunks(W, P, s.tiles);
+    if (P.dt != DT_F32) return small_call(P);
+    if (small_call(P) || always_gathers(s)) return true;
+    const double d = P.d, total = (double)P.total, blocks = total / (double)P.N / 16.0;
+    const double repeat = s.split ? 0.92 : 1.0;
+    const double tiles = 4.0 * s.nt * s.groups;
+    const double stream = total * tiles * (s.nt == 2 ? 35.5e-6 : 31e-6) * (1.0 + 32.0 / W.chunk_tokens) * d / 128.0;
+    const double one_doc = blocks * (s.nt == 2 ? 0.16 + 0.0146 * d : 0.3 + 0.026 * d);
+    const double t_pass = 14.0 + repeat * fmax(stream, one_doc);
+    const double corpus = total * d * 4.0;
+    double t_gather = fmax((double)P.nq * (total + 8.0 * (double)P.N) * s.tq * (s.tq * P.d >= 384 ? 51e-6 : 42.7e-6) * d / 128.0,
+                           (double)P.nq * corpus / 7.4e6);
+    if (corpus > 256e6) t_gather *= 1.0 + 0.1 * fmin(P.nq - 1.0, 3.0);
+    t_gather = fmax(t_gather, blocks * (0.3 + 0.0045 * d * s.tq) / (gather_shares(P) ? 4.0 : 1.0));
+    return 12.0 + t_gather < t_pass;
 }
 
 int check_shapes(const void* Q, int nq, int T, int d, int dt, const void* docs,

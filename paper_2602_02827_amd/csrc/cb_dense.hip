@@ -657,18 +657,17 @@ ScoreShape score_shape(const Problem& P, bool codes) {
 
 template <typename Tag, int D, int TQ>
 static hipError_t dense_score_nt(DenseArgs& A, const ScoreShape& s, hipStream_t st) {
+    constexpr int FEW = TQ <= 2 ? 2 : TQ;           // tiles of a wavefront that splits documents
+    if constexpr (Tag::wide) {
+        if (s.split == 4) return dense_go<Tag, D, FEW, TQ, false, 4>(A, 1, st);
+    } else {
+        if (always_gathers(s)) return hipErrorInvalidValue;
+    }
+    if constexpr (Tag::wide || TQ == 1) {
+        if (s.split == 2) return dense_go<Tag, D, FEW, TQ, false, 2>(A, 1, st);
+    }
     if constexpr (TQ <= 2) {
-        if (s.split == 4) return dense_go<Tag, D, 2, TQ, false, 4>(A, 1, st);
-        if (s.split == 2) return dense_go<Tag, D, 2, TQ, false, 2>(A, 1, st);
         if (s.nt == 2) return dense_go<Tag, D, 2, TQ, false>(A, s.groups, st);
-    }
-    if constexpr (TQ == 4) {
-        if (s.split == 4) return dense_go<Tag, D, 4, TQ, false, 4>(A, 1, st);
-        if (s.split == 2) return dense_go<Tag, D, 4, TQ, false, 2>(A, 1, st);
-    }
-    if constexpr (TQ == 8 && Tag::wide) {
-        if (s.split == 4) return dense_go<Tag, D, 8, TQ, false, 4>(A, 1, st);
-        if (s.split == 2) return dense_go<Tag, D, 8, TQ, false, 2>(A, 1, st);
     }
     if constexpr (TQ <= 4) {
         if (s.nt == 4) return dense_go<Tag, D, 4, TQ, false>(A, s.groups, st);

@@ -113,7 +113,7 @@ hipError_t launch_dense_reveal(const Problem& P, const Work& W, int n_chunks,
 // them into the running statistics of the documents still active.
 hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chunks, const RevealRound& rr, int G, const Coarse* co,
                                      hipStream_t st);
-// How an exhaustive pass covers P's queries with column tiles of 16 query tokens.  codes: on int8 codes.
+// How an exhaustive pass covers P's queries with column tiles of 16 query tokens.
 struct ScoreShape {
     int tq;               // tiles per query: 1, 2, 4 or 8
     int64_t tiles;        // of all queries
@@ -121,7 +121,10 @@ struct ScoreShape {
     int split;            // > 0: wavefronts that take the same tiles and split the documents
     int groups;           // column groups (workgroups that stream the same tokens)
 };
+// codes: a pass on int8 codes.
 ScoreShape score_shape(const Problem& P, bool codes);
+// fp32 batches that always gather: there is no corpus kernel for them
+inline bool always_gathers(const ScoreShape& s) { return s.split == 4 || (s.split == 2 && s.tq > 1); }
 bool dense_supported(const Problem& P, const Coarse* co);
 int dense_chunks(const Problem& P, const Work& W);
 

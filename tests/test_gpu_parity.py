@@ -142,14 +142,19 @@ def _kernels(fn):
 
 
 @pytest.mark.parametrize("dtype,N,L,nq,T,d,kernel",
-                         [("bf16", 10, 3000, 1, 32, 128, "k_gather_all"), ("bf16", 1, 5000, 3, 100, 64, "k_gather_all"),
-                          ("bf16", 767, 40, 1, 24, 96, "k_gather_all"), ("bf16", 768, 40, 1, 8, 96, "k_gather_all"),
-                          ("bf16", 1000, 520, 1, 32, 32, "k_gather_all"), ("bf16", 3000, 100, 3, 32, 128, "k_dense"),
-                          ("f32", 30, 3000, 2, 32, 128, "k_gather_all"), ("f32", 600, 520, 2, 48, 64, "k_gather_all")])
+                         [("f32", 5000, 100, 1, 16, 128, "k_gather_all"), ("f32", 5000, 100, 2, 33, 64, "k_gather_all"),
+                          ("f32", 5000, 100, 5, 32, 128, "k_gather_all"), ("f32", 5000, 100, 4, 32, 128, "k_dense"),
+                          ("f32", 5000, 100, 8, 16, 128, "k_dense"), ("f32", 1000, 48, 32, 32, 128, "k_dense"),
+                          ("f32", 50, 3000, 8, 32, 128, "k_gather_all"), ("f32", 3, 7001, 16, 48, 32, "k_gather_all"),
+                          ("f32", 200, 520, 6, 32, 96, "k_gather_all"), ("bf16", 10, 3000, 1, 32, 128, "k_gather_all"),
+                          ("bf16", 1, 5000, 3, 100, 64, "k_gather_all"), ("bf16", 767, 40, 1, 24, 96, "k_gather_all"),
+                          ("bf16", 768, 40, 1, 8, 96, "k_gather_all"), ("bf16", 1000, 520, 1, 32, 32, "k_gather_all"),
+                          ("bf16", 3000, 100, 3, 32, 128, "k_dense"), ("f32", 30, 3000, 2, 32, 128, "k_gather_all"),
+                          ("f32", 600, 520, 2, 48, 64, "k_gather_all")])
 def test_paths_of_exhaustive_scoring(B, dtype, N, L, nq, T, d, kernel):
-    """Gathered calls whose documents a workgroup's wavefronts share (few long ones) and do not, and the
-    corpus pass: scores and cells against products in 64 bits; Doc-Uniform takes its cells from the
-    same path."""
+    """Which path serves a call, on both sides of the rules (tiles filled against tiles multiplied, few
+    long documents, the smallest calls), with documents shared by a workgroup's wavefronts and not:
+    scores and cells against products in 64 bits; Doc-Uniform takes its cells from the same path."""
     g = torch.Generator(device="cuda"); g.manual_seed(N + L + nq)
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
     docs = torch.nn.functional.normalize(torch.randn((N * L, d), generator=g, device="cuda"), dim=1).to(td)
