@@ -144,7 +144,7 @@ void k_dense(DenseArgs A) {
     tok_begin = tok_begin < 0 ? 0 : (tok_begin > A.total ? A.total : tok_begin);
     tok_end = tok_end < tok_begin ? tok_begin : (tok_end > A.total ? A.total : tok_end);
     const int ntok = (int)(tok_end - tok_begin);
-    if (ntok <= 0 && i1 < (int)A.N) return;         // documents without tokens behind the last token are written
+    if (ntok <= 0) return;
 
     const int lgG = REVEAL ? 31 - __builtin_clz(A.G > 0 ? A.G : 1) : 0;   // G is a power of two
     // ---- query rows of this wavefront's column tiles -> B fragments (registers)

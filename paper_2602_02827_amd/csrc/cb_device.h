@@ -47,9 +47,10 @@ __device__ __forceinline__ unsigned long long work_item(int q, unsigned long lon
 __device__ __forceinline__ unsigned long long work_start(unsigned long long item) { return item >> 16; }
 __device__ __forceinline__ int work_query(unsigned long long item) { return (int)(item & 0xffffu); }
 
-// Chunk table of the corpus pass, chunk_doc[c] = min{ i : off[i] >= c*C } for c < n_chunks, and N at
-// the end (documents without tokens behind the last token belong to the last chunk): entry i of N + 1
-// writes the chunks that begin between its predecessor's first token and its own.
+// Chunk table of the corpus pass, chunk_doc[c] = min{ i : off[i] >= c*C }, and N for every chunk behind
+// the one in which the last document with tokens begins: documents without tokens behind it belong
+// to its chunk, so that no workgroup has only those.  Entry i of N + 1 writes the chunks that begin between
+// its predecessor's first token and its own.
 __device__ __forceinline__ void chunk_docs(int64_t i, const int64_t* off, int64_t N, int C, int n_chunks,
                                            int32_t* chunk_doc) {
     if (i > N) return;
@@ -57,14 +58,15 @@ __device__ __forceinline__ void chunk_docs(int64_t i, const int64_t* off, int64_
     int64_t hi = off[i] / C;
     if (off[i] < 0) hi = -1;
     if (i > 0 && off[i - 1] < 0) lo = 0;
-    if (i == N) {                    // everything past the last offset is empty
+    int32_t doc = (int32_t)i;
+    if (i == N || off[i] >= off[N]) {
+        if (i > 0 && off[i - 1] >= off[N]) return;   // an earlier entry has written the rest
         hi = n_chunks;
-        lo = lo > n_chunks ? n_chunks : lo;
-    } else {
-        hi = hi > n_chunks - 1 ? n_chunks - 1 : hi;
+        if (i > 0) doc = (int32_t)N;
     }
     lo = lo < 0 ? 0 : lo;
-    for (int64_t c = lo; c <= hi; ++c) chunk_doc[c] = (int32_t)i;
+    hi = hi > n_chunks ? n_chunks : hi;
+    for (int64_t c = lo; c <= hi; ++c) chunk_doc[c] = doc;
 }
 
 // Device-side choice of a later round's reveal path (uniform over the launch): true = the
