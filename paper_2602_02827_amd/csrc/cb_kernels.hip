@@ -191,6 +191,20 @@ struct GatherArgs {
     const float* dscale;
 };
 
+// Whether a second block of a document is in flight: where its registers do not cost a wavefront per
+// SIMD.
+template <int NT, class F> constexpr bool two_in_flight() {
+    return (NT + 2) * ((int)sizeof(F) / 4) + 8 * NT <= 112;
+}
+// Wavefronts per SIMD of k_gather_round, which serves two kinds of list and without a bound takes a few
+// registers too many for the four (or what the query rows leave) that a kernel with one block in
+// flight needs (T = 48, 50,000 documents x 16 queries 1,645 -> 1,546 us a call, T = 100 and d = 96, 20,000
+// x 16 1,005 -> 908).  fp32 at d = 128 and two tiles stays at three: four spill (3,847 -> 4,031).
+template <int TQ, class F> constexpr int round_waves() {
+    constexpr int FIT = 512 / ((TQ + 1) * ((int)sizeof(F) / 4) + 36);
+    return two_in_flight<TQ, F>() ? 1 : (FIT < 4 ? FIT : 4);
+}
+
 // Folds the blocks first, first + stride, ... of the document [o0, o1) into h.
 template <int ROWB, int NT, class F>
 __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o1, int first, int stride,
@@ -202,9 +216,7 @@ __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o
         row = row < o1 ? row : o1 - 1;
         a.load(docs + (size_t)row * ROWB, kg);
     };
-    // A second block in flight where its registers do not cost a wavefront per SIMD.
-    constexpr int A_REGS = (int)sizeof(F) / 4;
-    constexpr bool AHEAD = (NT + 2) * A_REGS + 8 * NT <= 112;
+    constexpr bool AHEAD = two_in_flight<NT, F>();
     F a;
     load(a, r0);
     for (;;) {
@@ -294,7 +306,7 @@ constexpr int64_t ALL_DOCS = 64;
 //                  smallest calls, which then needs no second visit and no launch of a later round (1
 //                  query x 1,000 documents of 48 fp32 tokens: 63 -> 55 us a call).
 template <typename Tag, int D, int TQ>
-__global__ __launch_bounds__(256) void k_gather_round(GatherArgs A) {
+__global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gather_round(GatherArgs A) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
