@@ -294,7 +294,11 @@ constexpr int64_t ALL_DOCS = 64;
 // the grid whatever the lengths of the lists: worker w of W takes pairs [w * per, (w + 1) * per).  Up
 // to one pair per workgroup, the four wavefronts share the pair's blocks (few pairs: the
 // time is the latency of one document: 64 queries x 9 pairs of 106 tokens 30 -> 9 us); beyond, each
-// wavefront takes pairs of its own.  What happens to a pair depends on its query:
+// wavefront takes pairs of its own.  Workers of more than one pair take their places in as many
+// streams as there are queries, so that lists that share documents, ascending all, read them at about
+// the same time: 8 queries x 100,000 documents of 106 tokens, alpha 0.5, 5,530 -> 5,090 us a call,
+// 4 x 16,048 of 1,000 3,450 -> 3,080; with a pair each the divisions would cost more (84 -> 86).
+// What happens to a pair depends on its query:
 //   list longer than the cell cache   one 16-column tile, column c < nb is query token pi[lo+c]; the
 //                  epilogue merges the batch into the pair's (sum, M2).
 //   list that fits the cell cache     TQ tiles = all T tokens; the epilogue stores the pair's T
@@ -323,8 +327,12 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
     const bool coop = total <= (long long)gridDim.x;
     const int parts = coop ? 4 : 1;
     const long long workers = coop ? gridDim.x : 4ll * gridDim.x;
-    const long long me = coop ? (long long)blockIdx.x : (long long)blockIdx.x * 4 + wave;
     const long long per = (total + workers - 1) / workers;
+    int me = coop ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
+    if (per > 1 && n_work > 1 && A.pairs_r) {
+        const int rows = (int)((total + per - 1) / per) / n_work;
+        if (me < rows * n_work) me = me % n_work * rows + me / n_work;
+    }
     long long x = me * per;
     const long long x_end = x + per < total ? x + per : total;
     if (x >= x_end) return;                         // in shared mode the same for the whole workgroup

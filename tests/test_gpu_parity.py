@@ -516,6 +516,21 @@ def test_cell_cache_and_regather_give_identical_runs(B, S, alpha, Bsz, T):
     _same_run(r1, r2)
 
 
+@pytest.mark.parametrize("N,nq,T,longest", [(20000, 5, 32, 3), (40000, 3, 48, 2), (9000, 9, 24, 5), (30000, 2, 100, 2)])
+def test_gathered_rounds_of_more_pairs_than_workers(B, S, N, nq, T, longest):
+    """Lists of unequal length whose pairs (beyond 32,768) are dealt out in streams, held as ids and in
+    the cell cache: the decisions, bounds and bits of the corpus passes and of gathers in every round."""
+    rng = np.random.default_rng(N)
+    w = _custom(S, rng.integers(1, longest + 1, N).tolist(), nq, T, 128, "bf16", N)
+    w.Q[0] *= 0.25                                           # close scores: a list that shrinks late
+    runs = [B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.9, 0.01, 5, 3, trace=True, **o)
+            for o in ({"later_rounds": 2}, {"later_rounds": 1}, {"later_rounds": 2, "no_cell_cache": True})]
+    torch.cuda.synchronize()
+    assert runs[0]["stats"][0]["pairs_round2"] > 32768
+    for r in runs[1:]:
+        _same_run(runs[0], r)
+
+
 @pytest.mark.parametrize("dtype,N,nq,T,d,Bsz,alpha,coarse",
                          [("bf16", 11, 1, 1, 128, 1, 1.0, None), ("bf16", 1000, 3, 32, 128, 4, 0.2, None),
                           ("bf16", 1025, 4, 128, 96, 7, 1.0, None), ("bf16", 4097, 1, 65, 32, 16, 1.0, None),
