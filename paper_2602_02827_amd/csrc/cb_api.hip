@@ -804,8 +804,11 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         if (cache_all || (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap)) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
-    // (after cache_all every query's survivors have them: no launch, 4 us of a call of 50)
-    if (e == hipSuccess && !(cache_all && !co)) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
+    // (after cache_all every query's survivors have them: no launch, 4 us of a call of 50).  Where no
+    // round ran, all documents survive: shared by wavefronts only if they are few (296 documents of 18
+    // tokens x 74 queries 86 -> 44 us a call)
+    if (e == hipSuccess && !loop) e = launch_gather_all(P, W, W.rescored, nullptr, st);    // no round: all documents
+    else if (e == hipSuccess && !(cache_all && !co)) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
     if (e == hipSuccess) e = launch_topk(P, W, true, !co, W.rescored, K, topk_ids, topk_scores, st);
     pt.mark(PH_RESCORE);
     if (e != hipSuccess) {

@@ -516,6 +516,22 @@ def test_cell_cache_and_regather_give_identical_runs(B, S, alpha, Bsz, T):
     _same_run(r1, r2)
 
 
+@pytest.mark.parametrize("dtype,coarse", [("bf16", False), ("f32", False), ("bf16", True)])
+def test_without_a_round_all_documents_are_scored_like_an_exhaustive_call(B, S, dtype, coarse):
+    """N <= K + M: the gather of whole matrices, not one workgroup per survivor; ids and bits of the
+    exhaustive call, also when codes were given."""
+    w = _custom(S, np.random.default_rng(8).integers(1, 32, 300).tolist(), 20, 24, 64, dtype, 8)
+    kw = {}
+    if coarse:
+        kw["docs_i8"], kw["docs_scale"] = B.colbandit_quantize_i8(w.docs)
+    res = []
+    names = _kernels(lambda: res.append(B.colbandit_topk(w.Q, w.docs, w.offsets, 7, 0.2, 0.01, 293, 3, want_stats=False, **kw)))
+    assert "k_gather_all" in names and "k_gather_survivors" not in names and "k_select_prune" not in names
+    full = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=7)
+    torch.cuda.synchronize()
+    assert torch.equal(res[0]["topk_ids"], full["topk_ids"]) and torch.equal(res[0]["topk_scores"], full["topk_scores"])
+
+
 @pytest.mark.parametrize("N,nq,T,longest", [(20000, 5, 32, 3), (40000, 3, 48, 2), (9000, 9, 24, 5), (30000, 2, 100, 2)])
 def test_gathered_rounds_of_more_pairs_than_workers(B, S, N, nq, T, longest):
     """Lists of unequal length whose pairs (beyond 32,768) are dealt out in streams, held as ids and in
