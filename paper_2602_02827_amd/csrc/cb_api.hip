@@ -239,9 +239,9 @@ struct PhaseTimer {
 // (~3.5 TB/s) and the matrix work of all query rows against them (~1.15 PFLOP/s); a gathered
 // pair streams its document once (~4.5 TB/s) and nothing is shared between queries.  A
 // gathered visit also caches the document's cells for the remaining rounds when the query fits
-// the cache, so the gather is preferred up to twice the cost of the pass and of a round's other
-// launches (~18 us); and where every list fits, a gathered round is the last one to launch, which
-// saves those of all rounds after it.
+// the cache, so the gather is preferred up to twice the cost of the pass and, where every list
+// fits, of a round's other launches (~18 us): there a gathered round is the last one to launch,
+// which also saves those of all rounds after it.
 unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, int r, int R, bool lists_fit) {
     // int8 codes: half the bytes of bf16 and twice the rate; fp32: twice the bytes, a tenth of the rate
     const double row_bytes = (codes ? 1.0 : P.dt == DT_BF16 ? 2.0 : 4.0) * P.d;
@@ -249,7 +249,7 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
     const double rows = (double)(((int64_t)P.nq * G + 15) / 16 * 16);
     const double per_token = fmax(row_bytes / 3.5e12, 2.0 * rows * P.d / rate);
     const double t_round = 18e-6;
-    const double t_pass = (double)P.total * per_token;
+    double t_pass = (double)P.total * per_token;
     double t_pair = ((double)P.total / (double)P.N) * row_bytes / 4.5e12;
     double passes = 2.0;
     if (!codes && P.dt == DT_F32) {
@@ -257,11 +257,17 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
         // where the lists fit the cache the one visit is weighed against a pass in every round left
         // (33 queries x 57 tokens over 1,154 pages of 647, d = 96, 9 rounds of passes: 4.7 ms, gathered 4.4)
         const int tq = (P.T + 15) / 16;
+        // (a pass takes no less than a mean document's blocks one after the other in a workgroup: 34
+        // queries x 131 documents of 2,380 tokens, d = 64, 290 us where the tokens' matrix work is 50;
+        // three such passes made a call of 2.1 ms out of 0.93)
+        const double tiles = rows / 16.0;
+        const double block = tiles <= 4 ? 0.1e-6 + 0.0075e-6 * P.d : tiles <= 8 ? 0.16e-6 + 0.0146e-6 * P.d : 0.3e-6 + 0.026e-6 * P.d;
+        t_pass = fmax(t_pass, (double)P.total / (double)P.N / 16.0 * block);
         const double tile_rows = 16.0 * (tq <= 1 ? 1 : tq <= 2 ? 2 : 4);
         t_pair = fmax(t_pair, ((double)P.total / (double)P.N) * 2.0 * tile_rows * P.d / 0.1e15);
         if (lists_fit) passes = R - r + 1;
     }
-    const double thr = (passes * (t_pass + t_round) + (lists_fit ? (R - r) * t_round : 0.0)) / t_pair;
+    const double thr = (passes * t_pass + (lists_fit ? (passes + R - r) * t_round : 0.0)) / t_pair;
     return thr >= 1.8e19 ? ~0ull - 1 : (unsigned long long)thr;
 }
 

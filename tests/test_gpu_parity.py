@@ -532,6 +532,16 @@ def test_without_a_round_all_documents_are_scored_like_an_exhaustive_call(B, S, 
     assert torch.equal(res[0]["topk_ids"], full["topk_ids"]) and torch.equal(res[0]["topk_scores"], full["topk_scores"])
 
 
+def test_few_long_fp32_documents_do_not_stream_round_after_round(B, S):
+    """A corpus pass takes as long as a document in one workgroup; where that outweighs the gather of the few
+    pairs there are, the rounds gather."""
+    w = _custom(S, np.random.default_rng(5).integers(800, 4000, 131).tolist(), 34, 16, 64, "f32", 5)
+    res = [B.colbandit_topk(w.Q, w.docs, w.offsets, 43, 0.3, 0.01, 0, 3, trace=True, **o) for o in ({}, {"later_rounds": 1})]
+    torch.cuda.synchronize()
+    assert all(s["corpus_pass_rounds"] == [] for s in res[0]["stats"])
+    _same_run(*res)
+
+
 @pytest.mark.parametrize("N,nq,T,longest", [(20000, 5, 32, 3), (40000, 3, 48, 2), (9000, 9, 24, 5), (30000, 2, 100, 2)])
 def test_gathered_rounds_of_more_pairs_than_workers(B, S, N, nq, T, longest):
     """Lists of unequal length whose pairs (beyond 32,768) are dealt out in streams, held as ids and in
