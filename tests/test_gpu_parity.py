@@ -702,12 +702,13 @@ def test_long_lists_stay_long_under_a_conservative_radius(B, S, oracle_mod, nq):
 
 
 @pytest.mark.parametrize("N,K,alpha", [(1024, 5, 0.2), (1025, 32, 1.0), (4096, 5, 1.0), (4097, 33, 1.0), (8192, 5, 1.0),
-                                       (8193, 1, 1.0), (16384, 300, 1.0), (16385, 5, 1.0), (24577, 1000, 1.0)])
+                                       (8193, 1, 1.0), (16384, 300, 1.0), (16385, 5, 1.0), (24577, 1000, 1.0),
+                                       (40961, 500, 0.9), (33000, 508, 1.0), (33100, 508, 1.0)])
 def test_selection_at_the_edges_of_its_tiles(B, S, oracle_mod, N, K, alpha):
     """Lists around what the selection kernels hold in registers (1,024 entries per place of a
     thread, 4,096 in all), around the tile beyond which a list is pre-filtered (16,384), and K around
     the number of group maxima (32); cached lists longer than the registers run their first
-    rounds from memory.  A tenth of the documents are copies of one document."""
+    rounds from memory; longer lists and K on both sides of what LDS holds of a sampled bound's entries.  A tenth of the documents are copies of one document."""
     rng = np.random.default_rng(N + K)
     w = _custom(S, rng.integers(1, 3, N).tolist(), 2, 32, 128, "bf16", 91 + N)
     off = w.offsets.cpu().numpy()
