@@ -495,7 +495,7 @@ void k_dense(DenseArgs A) {
             for (int tt = 0; tt < NT; ++tt) hB[tt] = lowest_val<V>();
             const int bb = b < lo ? lo : b;     // offsets that run backwards: an empty part
             // the usual case - one document end in the block - takes the fold specialised by the
-            // row of the end (the wide kernels only: it is 15 copies of the block's code)
+            // row of the end (six and eight tiles only: it is 15 copies of the block's code)
             if (NT >= PACKED_NT && lo == 0 && bb >= 1 && bb <= 15) block_mma_split_rows<NT>(a, bq, h, hB, bb);
             else block_mma_split<NT>(a, bq, h, hB, lo, bb, rowbase);
             finalize(doc);
@@ -518,8 +518,8 @@ void k_dense(DenseArgs A) {
     // that holds nothing but the operand reads and the MFMAs of two blocks (and, every fourth
     // block, the stage entry); it covers the rows below tight_end, where every block has a
     // complete successor and every stage entered requests a complete stage.  A block in which a
-    // document ends, and the chunk's last stages, take the general path.  Kernels with fewer
-    // than eight column tiles per wavefront are bound by memory, not by the matrix pipes, and run
+    // document ends, and the chunk's last stages, take the general path.  Kernels with at most
+    // four column tiles per wavefront are bound by memory more than by the matrix pipes, and run
     // at a higher occupancy with fewer registers: they keep to the general path.
     constexpr bool TIGHT_RUNS = NT >= PACKED_NT && SPLIT_DOCS == 0;
     const int tight_end = TIGHT_RUNS ? (nfull - 2) * STAGE_ROWS : 0;

@@ -156,7 +156,8 @@ hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, 
 // into a running per-column maximum.
 //   k_gather_round     the reveal of one round (Algorithm 1, reveal step), see there
 //   k_gather_survivors exact scores of the survivors (Eq. (2); rescore)
-//   k_gather_all       all documents of all queries (fp32, and widths that only gather)
+//   k_gather_all       all documents of all queries: the smallest calls, fp32 where it beats the corpus
+//                      pass, Ball-carving in fp32 and in the widths without a group pass
 // =====================================================================================
 struct GatherArgs {
     const void* Q;
@@ -565,7 +566,7 @@ template <typename Tag>
 static hipError_t gather_by_d(const GatherArgs& A, int mode, int d, dim3 grid, hipStream_t st) {
     if (d == 128) return gather_tq<Tag, 128>(A, mode, grid, st);
     if (d == 64) return gather_tq<Tag, 64>(A, mode, grid, st);
-    // widths that only the gather kernels cover (the int8 MFMA contracts 64 elements at a time)
+    // no codes in these widths: the int8 MFMA contracts 64 elements at a time
     if constexpr (!__is_same(Tag, i8_tag)) {
         if (d == 96) return gather_tq<Tag, 96>(A, mode, grid, st);
         if (d == 32) return gather_tq<Tag, 32>(A, mode, grid, st);
@@ -687,7 +688,9 @@ constexpr int SEL_E = 16;
 constexpr int SEL_TILE = SEL_E * SEL_THREADS;
 static_assert(SEL_TILE == 16384, "the cell cache's slots per query must fit one tile");
 constexpr int SEG_E = SEG_TILE / SEL_THREADS;      // pre-filter kernels: entries per thread and tile
-constexpr int SEL_REGS = 4;                        // 8 spills (topk 1,000 x 1: 62 -> 70 us)
+// (8: topk 1,000 x 1 62 -> 70 us.  k_select_prune holds three ways through a list and needs more than the
+// 128 registers that 1,024 threads leave: with 4, 13 of them and 56 bytes of scratch a lane spill.)
+constexpr int SEL_REGS = 4;
 constexpr int SEL_BINS = 2048;
 constexpr int SEL_FEW = 1024;
 
@@ -1211,13 +1214,8 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
 #pragma unroll
         for (int u = 0; u < E; ++u) e[u] = sp.at(u);
     }
-    if (from_cells && r == 1) {                     // nothing revealed yet: no statistics to read
 #pragma unroll
-        for (int u = 0; u < E; ++u) st[u] = make_float2(0.f, 0.f);
-    } else {
-#pragma unroll
-        for (int u = 0; u < E; ++u) st[u] = stat[e[u]];
-    }
+    for (int u = 0; u < E; ++u) st[u] = stat[e[u]];
     if (fold_dense) {
         float2 bb[E];
 #pragma unroll
@@ -1357,8 +1355,7 @@ __device__ __forceinline__ bool prune_tile(const SelArgs& A, int q, int count, Q
     };
     // statistics after this round's batch; `store`: for the rounds after it
     auto stat_of = [&](int e, bool store) {
-        float2 st = make_float2(0.f, 0.f);
-        if (!from_cells || lo > 0) st = stat[e];
+        float2 st = stat[e];
         if (from_cells) {
             const float* crow = cells + (unsigned)(e * A.TP);
             float sb, m2b;
@@ -1631,13 +1628,13 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
     int32_t* out = (out_sel ? A.list1 : A.list0) + (size_t)q * A.N;
-    // entries are cache slots if the query was switched earlier (mode 1) or by this
-    // round's cell-caching gather (same rule as in k_gather_round)
+    // entries are cache slots if this round's gather has cached the cells (same rule as in
+    // k_gather_round); an active query's list always came as ids, for cached rounds end here
     const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
-    const bool slots = c.mode == 1 || A.cache_all || (c.mode == 0 && !c.implicit && count <= A.cache_cap && !dense);
+    const bool slots = A.cache_all || (!c.implicit && count <= A.cache_cap && !dense);
     float2* stat = slots ? A.cstat + (size_t)q * A.cache_cap : A.stat + (size_t)q * A.N;
     const float2* bat = A.stat2 + (size_t)q * A.N;
-    const bool fold_dense = dense && c.mode == 0 && in != nullptr;   // a batch that a dense pass left in stat2
+    const bool fold_dense = dense && in != nullptr;   // a batch that a dense pass left in stat2
     if (threadIdx.x == 0) kept_tokens = 0ull;
     clear_hist(sh);
 
@@ -1651,7 +1648,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     nc.mode = slots ? 1 : 0;
     nc.bound = nc.pad1 = nc.pad2 = 0;
     int r = A.r;
-    bool from_cells = c.mode == 1;                  // this round's batch still has to be folded in
+    bool from_cells = false;                        // the round's batch still has to be folded in
     bool seg = segmented, fold = fold_dense;
     if (ncand > SEL_TILE) {
         prune_list(A, q, count, nc, out, stat, bat, fold, ncand, r, sh, &kept_tokens);
