@@ -23,6 +23,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0        # MI355X dense bf16 MFMA
+PEAK_F32_TFLOPS = 157.3          # fp32 MFMA
 PEAK_HBM_GBS = 8000.0
 
 # HBM bytes per launch of the dominant kernels come from hardware-counter runs of this very
@@ -321,13 +322,14 @@ def main():
     tflops_kernel = flops_full / (ms_dense * 1e-3) / 1e12
     traffic = measured_traffic("%s/nq%d/N%d/tok%d" % (w.name, nq, N, total))
     traffic_rs = measured_traffic("%s/nq%d/N%d/tok%d" % (w.name, nq, N, total), "by_request_size")
-    dense = w.dtype == "bf16"
-    elem = 2 if dense else 4
-    roofline = {"bound": "mfma" if dense else "alu",
-                "kernel": "k_dense (Full-MaxSim scoring kernel, bf16 16x16x32 MFMA)" if dense
-                          else "k_gather (fp32 inputs)",
-                "achieved": round(tflops_kernel, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(tflops_kernel / PEAK_BF16_TFLOPS, 4), "traffic": traffic.get("full_maxsim"),
+    bf16 = w.dtype == "bf16"
+    elem = 2 if bf16 else 4
+    peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_TFLOPS
+    roofline = {"bound": "mfma",
+                "kernel": "k_dense (Full-MaxSim scoring kernel, bf16 16x16x32 MFMA)" if bf16
+                          else "k_dense, or k_gather_all for few queries (fp32 16x16x4 MFMA)",
+                "achieved": round(tflops_kernel, 2), "peak": peak, "unit": "TFLOP/s",
+                "frac": round(tflops_kernel / peak, 4), "traffic": traffic.get("full_maxsim"),
                 "traffic_by_request_size": traffic_rs.get("full_maxsim"),
                 "ms_per_launch": round(ms_dense, 3),
                 "flops_per_launch": flops_full,
@@ -348,7 +350,7 @@ def main():
     nb1 = min(w.B, T)
     bytes_r1 = float(total) * d * elem + 8.0 * nq * N
     flops_r1 = 2.0 * nq * nb1 * d * total
-    t_hbm, t_mfma = bytes_r1 / (PEAK_HBM_GBS * 1e9), flops_r1 / (PEAK_BF16_TFLOPS * 1e12)
+    t_hbm, t_mfma = bytes_r1 / (PEAK_HBM_GBS * 1e9), flops_r1 / (peak * 1e12)
     reveal1 = {"kernel": "k_dense<..., REVEAL> (round-1 reveal, corpus-streaming)",
                "ms": round(ms_r1, 3),
                "bound": "mfma" if t_mfma >= t_hbm else "hbm",
@@ -359,12 +361,12 @@ def main():
                        "bytes": bytes_r1, "traffic": traffic.get("reveal_round1"),
                        "traffic_by_request_size": traffic_rs.get("reveal_round1")},
                "mfma": {"achieved": round(flops_r1 / (ms_r1 * 1e-3) / 1e12, 1) if ms_r1 > 0 else None,
-                        "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                        "peak": peak, "unit": "TFLOP/s",
                         "frac": round(t_mfma * 1e3 / ms_r1, 4) if ms_r1 > 0 else None,
                         "flops": flops_r1},
                "note": "ms = the whole first-reveal phase of the statistics call (k_init, chunk table "
                        "and the reveal kernel; events on the launch stream); frac = the larger of the "
-                       "two lower bounds on the time over the measured time"} if dense else None
+                       "two lower bounds on the time over the measured time"} if bf16 else None
 
     # round 2 against the HBM roofline: every (query, document) pair that survives round 1 is
     # streamed once (visit-once cell cache).  Bytes = the tokens of exactly those documents, added
@@ -377,7 +379,7 @@ def main():
     # much that most gathered bytes come from cache, HBM is not the bound
     gather_valid = ms_r2 > 0 and 2 not in st[0]["corpus_pass_rounds"] and gather_bytes <= 4.0 * total * d * elem
     gbs = lambda ms: round(gather_bytes / (ms * 1e-3) / 1e9, 1) if gather_valid and ms > 0 else None
-    gather = {"bound": "hbm", "kernel": "k_gather (round 2: reveal + cell cache fill)",
+    gather = {"bound": "hbm", "kernel": "k_gather_round (round 2: reveal + cell cache fill)",
               "achieved": gbs(ms_r2), "peak": PEAK_HBM_GBS, "unit": "GB/s",
               "frac": round(gbs(ms_r2) / PEAK_HBM_GBS, 4) if gather_valid else None,
               "traffic": traffic.get("gather_round2"),
