@@ -51,6 +51,23 @@ def _oracle_scores(oracle_mod, w, qs=None):
     return H, H.sum(axis=2)
 
 
+def _kernels(fn):
+    """The names of the kernels that fn launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    return " ".join(e.key for e in p.key_averages())
+
+
+def _past_small(lengths, nq, d, dtype):
+    """The lengths repeated until nq queries over them are no longer a call small enough to gather
+    (40 MB of reading)."""
+    row = d * (2 if dtype == "bf16" else 4)
+    return list(lengths) * (int(4.2e7 / (nq * row * sum(lengths))) + 1)
+
+
 def _check_topk(ids, scores, S_or, K, tol):
     """ids/scores: GPU top-K of one query; S_or: oracle scores of all docs."""
     order = np.lexsort((np.arange(len(S_or)), -S_or))
@@ -84,14 +101,16 @@ def test_full_maxsim_fp32_config1(B, S, oracle_mod):
                                      (40, 16, 64), (4, 32, 96), (3, 24, 32), (2, 100, 96)])
 def test_full_maxsim_bf16_dense_ragged(B, S, oracle_mod, nq, T, d):
     # lengths span 1 token, block edges (15/16/17), stage edges (63/64/65), ring wrap (>256)
-    # and documents longer than a workgroup's token chunk (4096)
+    # and documents longer than a workgroup's token chunk (at most 4096)
     rng = np.random.default_rng(nq * 1000 + T)
     lengths = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257, 700, 1030, 4500, 1] + \
         rng.integers(1, 200, 150).tolist() + [5000, 3] + rng.integers(30, 181, 100).tolist()
-    w = _custom(S, lengths, nq, T, d, "bf16", 7)
+    w = _custom(S, _past_small(lengths, nq, d, "bf16"), nq, T, d, "bf16", 7)
     H, Sor = _oracle_scores(oracle_mod, w)
-    r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=7, want_cells=True)
-    torch.cuda.synchronize()
+    res = []
+    assert "k_dense<cb::bf16_tag" in _kernels(
+        lambda: res.append(B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=7, want_cells=True)))
+    r = res[0]
     np.testing.assert_allclose(r["cells"].cpu().numpy(), H, rtol=TOL["bf16"], atol=1e-5)
     np.testing.assert_allclose(r["scores"].cpu().numpy(), Sor, rtol=TOL["bf16"], atol=1e-4)
     # fp32 accumulation of exact bf16 products is far tighter than the stated tolerance
@@ -101,44 +120,46 @@ def test_full_maxsim_bf16_dense_ragged(B, S, oracle_mod, nq, T, d):
                     TOL["bf16"])
 
 
-@pytest.mark.parametrize("dtype,nq,T,d", [("bf16", 1, 32, 128), ("bf16", 2, 42, 128), ("bf16", 1, 100, 64),
-                                          ("bf16", 2, 70, 96), ("bf16", 3, 32, 96), ("bf16", 40, 16, 32),
-                                          ("f32", 3, 32, 128), ("f32", 9, 30, 128), ("f32", 4, 24, 96),
-                                          ("f32", 5, 50, 32), ("f32", 1, 16, 64), ("f32", 3, 64, 64),
-                                          ("f32", 9, 24, 64), ("f32", 17, 16, 32), ("f32", 5, 32, 64)])
-def test_corpus_pass_of_every_width_and_type(B, S, oracle_mod, dtype, nq, T, d):
+@pytest.mark.parametrize("dtype,nq,T,d,tokens,kernel",
+                         [("bf16", 1, 32, 128, 0, "128, 2, 2, false, 4"), ("bf16", 2, 42, 128, 0, "128, 4, 4, false, 2"),
+                          ("bf16", 1, 100, 64, 0, "64, 8, 8, false, 4"), ("bf16", 2, 70, 96, 0, "96, 8, 8, false, 2"),
+                          ("bf16", 3, 32, 96, 0, "96, 2, 2, false, 0"), ("bf16", 40, 16, 32, 0, "32, 8, 1, false, 0"),
+                          ("f32", 3, 32, 128, 0, None), ("f32", 9, 30, 128, 0, None), ("f32", 4, 24, 96, 0, None),
+                          ("f32", 5, 50, 32, 0, None), ("f32", 1, 16, 64, 0, None), ("f32", 3, 64, 64, 0, None),
+                          ("f32", 9, 24, 64, 0, None), ("f32", 17, 16, 32, 0, None), ("f32", 5, 32, 64, 0, None),
+                          ("f32", 4, 32, 128, 260e3, "128, 2, 2, false, 0"), ("f32", 12, 30, 128, 150e3, "128, 2, 2, false, 0"),
+                          ("f32", 16, 32, 128, 40e3, "128, 4, 2, false, 0"), ("f32", 4, 16, 128, 560e3, "128, 2, 1, false, 2"),
+                          ("f32", 8, 32, 96, 80e3, "96, 4, 2, false, 0"), ("f32", 23, 16, 96, 30e3, "96, 2, 1, false, 0"),
+                          ("f32", 8, 50, 32, 90e3, "32, 4, 4, false, 0"), ("f32", 8, 16, 64, 70e3, "64, 2, 1, false, 0"),
+                          ("f32", 4, 64, 64, 90e3, "64, 4, 4, false, 0"), ("f32", 12, 24, 64, 300e3, "64, 2, 2, false, 0"),
+                          ("f32", 40, 32, 32, 30e3, "32, 4, 2, false, 0")])
+def test_corpus_pass_of_every_width_and_type(B, S, oracle_mod, dtype, nq, T, d, tokens, kernel):
     """Exhaustive scores beyond the calls small enough to gather: every width (96: rows padded in
-    LDS), fp32, the batches whose wavefronts split the documents, and token chunks of 256 to 1,024
-    with documents longer than a chunk; the same corpus through Col-Bandit's reveal pass."""
+    LDS), fp32, the batches whose wavefronts split the documents, and token chunks of 128 to 1,024
+    with documents longer than a chunk; the same corpus through Col-Bandit's reveal pass.  kernel: the
+    corpus kernel of the exhaustive call (fp32 batches that fill few of its column tiles gather)."""
     rng = np.random.default_rng(nq * 1000 + T + d)
     unit = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257, 700, 1030, 1] + \
         rng.integers(1, 200, 150).tolist()
-    row = d * (2 if dtype == "bf16" else 4)
-    lengths = unit * (int(4.2e7 / (nq * row * sum(unit))) + 1)
+    lengths = unit * (int(tokens / sum(unit)) + 1) if tokens else _past_small(unit, nq, d, dtype)
     w = _custom(S, lengths, nq, T, d, dtype, 7)
-    some = range(min(nq, 3))
+    some = range(min(nq, 3 if tokens < 1e5 else 1))
     H, Sor = _oracle_scores(oracle_mod, w, some)
-    r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=7, want_cells=True)
-    torch.cuda.synchronize()
+    res = []
+    names = _kernels(lambda: res.append(B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=7, want_cells=True)))
+    assert (f"k_dense<cb::{dtype}_tag, {kernel}" if kernel else "k_gather_all<cb::f32_tag") in names
+    r = res[0]
     for q in some:
         np.testing.assert_allclose(r["cells"][q].cpu().numpy(), H[q], rtol=TOL[dtype], atol=1e-5)
         np.testing.assert_allclose(r["scores"][q].cpu().numpy(), Sor[q], rtol=TOL[dtype], atol=1e-4)
         _check_topk(r["topk_ids"][q].cpu().numpy(), r["topk_scores"][q].cpu().numpy(), Sor[q], 7, TOL[dtype])
-    dense = B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.5, 0.01, 5, 3, trace=True)
+    assert f"k_dense<cb::{dtype}_tag, {d}, " in _kernels(
+        lambda: res.append(B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.5, 0.01, 5, 3, trace=True)))
+    dense = res[1]
     gathered = B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.5, 0.01, 5, 3, trace=True, force_gather=True)
     torch.cuda.synchronize()
     _same_run(dense, gathered)
     assert torch.equal(dense["topk_scores"], torch.gather(r["scores"], 1, dense["topk_ids"]))
-
-
-def _kernels(fn):
-    """The names of the kernels that fn launches."""
-    from torch.profiler import ProfilerActivity, profile
-    torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        fn()
-        torch.cuda.synchronize()
-    return " ".join(e.key for e in p.key_averages())
 
 
 @pytest.mark.parametrize("dtype,N,L,nq,T,d,kernel",
@@ -183,23 +204,31 @@ def test_packed_query_tiles_give_the_bits_of_whole_tiles(B, S, oracle_mod, T, d)
     8, 17..24, 33..48, 65..96; the neighbours of those lengths do not); scores and cells carry the same
     bits as the small-batch kernels give, on the embeddings and on int8 codes, and agree with the oracle."""
     rng = np.random.default_rng(T)
-    lengths = ([1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257, 700, 1] + rng.integers(1, 120, 60).tolist()) * 3
+    unit = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257, 700, 1] + rng.integers(1, 120, 60).tolist()
     per = 1 if T <= 16 else 2 if T <= 32 else 4 if T <= 64 else 8
     nq = 37 // per + 16                                    # more than 16 tiles, an incomplete last wavefront
-    w = _custom(S, lengths, nq, T, d, "bf16", 70 + T)
-    r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)
+    step = 2
+    w = _custom(S, _past_small(unit, step, d, "bf16"), nq, T, d, "bf16", 70 + T)
+    packed = T <= 8 or 17 <= T <= 24 or 33 <= T <= 48 or 65 <= T <= 96
+    kernel = f"{d}, 6, {per}, false, 0, true>" if packed else f"{d}, 8, {per}, false, 0, false>"
+    res = []
+    assert f"k_dense<cb::bf16_tag, {kernel}" in _kernels(
+        lambda: res.append(B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)))
+    r = res[0]
     H, Sor = _oracle_scores(oracle_mod, w, [nq - 1])
-    torch.cuda.synchronize()
     np.testing.assert_allclose(r["cells"][nq - 1].cpu().numpy(), H[0], rtol=TOL["bf16"], atol=1e-5)
     np.testing.assert_allclose(r["scores"][nq - 1].cpu().numpy(), Sor[0], rtol=TOL["bf16"], atol=1e-4)
-    step = 2
+    split = f"k_dense<cb::bf16_tag, {d}, {max(2, per)}, {per}, false, {4 if per == 1 else 2}"
+    assert split in _kernels(lambda: B.colbandit_full_maxsim(w.Q[:step], w.docs, w.offsets, K=0))
     for q in range(0, nq, step):
         few = B.colbandit_full_maxsim(w.Q[q:q + step], w.docs, w.offsets, K=0, want_cells=True)
         assert torch.equal(few["scores"], r["scores"][q:q + step])
         assert torch.equal(few["cells"], r["cells"][q:q + step])
     if d % 64 == 0:
         codes, scale = B.colbandit_quantize_i8(w.docs)
-        c = B.colbandit_coarse_maxsim(w.Q, codes, scale, w.offsets, want_cells=True)
+        assert f"k_dense<cb::i8_tag, {kernel}" in _kernels(
+            lambda: res.append(B.colbandit_coarse_maxsim(w.Q, codes, scale, w.offsets, want_cells=True)))
+        c = res[1]
         for q in range(0, nq, step):
             few = B.colbandit_coarse_maxsim(w.Q[q:q + step], codes, scale, w.offsets, want_cells=True)
             assert torch.equal(few["scores"], c["scores"][q:q + step])
@@ -211,16 +240,20 @@ def test_documents_much_longer_than_a_token_chunk(B, S, oracle_mod):
     document that starts in it); every workgroup with an empty chunk must exit and the others
     must cover the long rows - exhaustive cells for a wide and a narrow batch, and the reveal
     pass through Col-Bandit's first round."""
-    lengths = [20000, 3, 9000, 1, 1, 4096, 4097, 8192, 17, 12289, 40]
-    for nq in (1, 2, 20):       # one query: the wavefronts of a workgroup split the documents
-        w = _custom(S, lengths, nq, 32, 128, "bf16", 5 + nq)
+    unit = [20000, 3, 9000, 1, 1, 4096, 4097, 8192, 17, 12289, 40]
+    # one and two queries: the wavefronts of a workgroup split the documents
+    for nq, kernel in ((1, "2, 2, false, 4"), (2, "2, 2, false, 2"), (20, "8, 2, false, 0")):
+        w = _custom(S, _past_small(unit, nq, 128, "bf16"), nq, 32, 128, "bf16", 5 + nq)
         H, Sor = _oracle_scores(oracle_mod, w)
-        r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)
-        torch.cuda.synchronize()
+        res = []
+        assert f"k_dense<cb::bf16_tag, 128, {kernel}" in _kernels(
+            lambda: res.append(B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)))
+        r = res[0]
         np.testing.assert_allclose(r["cells"].cpu().numpy(), H, rtol=TOL["bf16"], atol=1e-5)
         np.testing.assert_allclose(r["scores"].cpu().numpy(), Sor, rtol=TOL["bf16"], atol=1e-4)
-    w = _custom(S, lengths, 3, 32, 128, "bf16", 9)
-    _run_colbandit_case(B, oracle_mod, w, 2, 1, 4, 0.5, seed=3)
+    w = _custom(S, _past_small(unit, 3, 128, "bf16"), 3, 32, 128, "bf16", 9)
+    assert "k_dense<cb::bf16_tag, 128, 1, 1, true" in _kernels(
+        lambda: _run_colbandit_case(B, oracle_mod, w, 2, 1, 4, 0.5, seed=3))
 
 
 def test_full_maxsim_fp32_ragged_and_d64(B, S, oracle_mod):
@@ -243,18 +276,22 @@ def test_documents_without_tokens_get_minus_infinity_and_disturb_nothing(B, S, o
     lengths = rng.integers(1, 40, 400).tolist()
     for i in (0, 1, 7, 8, 9, 100, 250, 251, 252, 399):
         lengths[i] = 0
-    for nq in (3, 1):
-        w = _custom(S, lengths, nq, 32, 128, "bf16", 43)
-        full = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=0)
-        torch.cuda.synchronize()
-        got = full["scores"].cpu().numpy()
+    unit = lengths
+    # gathered, then the corpus kernels: split documents, two tiles, six packed ones, eight
+    for nq, T, kernel in ((3, 32, "k_gather_all"), (1, 32, "128, 2, 2, false, 4"), (3, 32, "128, 2, 2, false, 0"),
+                          (40, 24, "128, 6, 2, false, 0, true>"), (20, 32, "128, 8, 2, false, 0, false>")):
+        lengths = unit if kernel == "k_gather_all" else _past_small(unit, nq, 128, "bf16")
+        w = _custom(S, lengths, nq, T, 128, "bf16", 43)
+        res = []
+        assert kernel in _kernels(lambda: res.append(B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=0)))
+        got = res[0]["scores"].cpu().numpy()
         keep = [i for i, n in enumerate(lengths) if n > 0]
         E, off = w.host_docs(keep)
         Qh = w.host_queries()
-        for q in range(w.nq):
+        for q in range(min(w.nq, 6)):
             want = oracle_mod.row_sums(oracle_mod.maxsim_cells(Qh[q], E, off))
             np.testing.assert_allclose(got[q][keep], want, rtol=TOL["bf16"], atol=1e-4)
-            assert np.all(np.isneginf(got[q][[i for i, n in enumerate(lengths) if n == 0]]))
+        assert np.all(np.isneginf(got[:, [i for i, n in enumerate(lengths) if n == 0]]))
 
 
 @pytest.mark.parametrize("dtype,nq,d,last", [("f32", 3, 128, 1024), ("f32", 3, 128, 1025), ("bf16", 1, 128, 1024),
@@ -994,10 +1031,13 @@ def test_every_position_of_a_document_end_inside_a_block(B, S, oracle_mod):
         lengths += [b, 32 - b]
     lengths += [3, 4, 9, 5, 5, 6, 16, 1, 1, 1, 13] + list(range(1, 40))
     nq, T, d = 20, 32, 128
+    lengths = _past_small(lengths, nq, d, "bf16")
     w = _custom(S, lengths, nq, T, d, "bf16", 77)
     H, Sor = _oracle_scores(oracle_mod, w)
-    r = B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)
-    torch.cuda.synchronize()
+    ran = []
+    assert "k_dense<cb::bf16_tag, 128, 8, 2, false, 0, false>" in _kernels(
+        lambda: ran.append(B.colbandit_full_maxsim(w.Q, w.docs, w.offsets, K=3, want_cells=True)))
+    r = ran[0]
     np.testing.assert_allclose(r["cells"].cpu().numpy(), H, rtol=TOL["bf16"], atol=1e-5)
     np.testing.assert_allclose(r["scores"].cpu().numpy(), Sor, rtol=TOL["bf16"], atol=1e-4)
     # int8 codes: exact integer maxima
@@ -1014,10 +1054,12 @@ def test_every_position_of_a_document_end_inside_a_block(B, S, oracle_mod):
     # the reveal pass with eight tiles per wavefront: 72 queries x 4 revealed tokens
     w2 = _custom(S, lengths, 72, T, d, "bf16", 78)
     full = B.colbandit_full_maxsim(w2.Q, w2.docs, w2.offsets, K=0, want_cells=True)
-    res = B.colbandit_topk(w2.Q, w2.docs, w2.offsets, 3, 1.0, 0.01, 2, 9, B=4, trace=True)
     e8, es = B.colbandit_quantize_i8(w2.docs)
-    res8 = B.colbandit_topk(w2.Q, w2.docs, w2.offsets, 3, 1.0, 0.01, 2, 9, B=4, trace=True,
-                            docs_i8=e8, docs_scale=es)
+    assert "k_dense<cb::bf16_tag, 128, 8, 1, true" in _kernels(lambda: ran.append(
+        B.colbandit_topk(w2.Q, w2.docs, w2.offsets, 3, 1.0, 0.01, 2, 9, B=4, trace=True)))
+    assert "k_dense<cb::i8_tag, 128, 8, 1, true" in _kernels(lambda: ran.append(
+        B.colbandit_topk(w2.Q, w2.docs, w2.offsets, 3, 1.0, 0.01, 2, 9, B=4, trace=True, docs_i8=e8, docs_scale=es)))
+    res, res8 = ran[1:]
     cm2 = B.colbandit_coarse_maxsim(w2.Q, e8, es, w2.offsets, want_cells=True)
     torch.cuda.synchronize()
     for q in (0, 35, 71):
