@@ -85,8 +85,9 @@ struct DenseArgs {
 // PACKED: query lengths that leave a quarter or more of their column tiles empty (T = 17..24,
 // 33..48, 65..96, up to 8).  A wavefront takes as many queries as eight whole tiles would hold, but at
 // half tiles each, in six tiles; the maxima of a document then pass through LDS into the layout
-// whose sum every other kernel takes.  A quarter of the matrix work less; 64 queries of 24 tokens
-// over 20,000 pages of 1,030 tokens 6.84 -> 5.49 ms, of 40 tokens over 6.4 M tokens 4.43 -> 3.49.
+// whose sum every other kernel takes.  A quarter of the matrix work less, and as much less to fold, in
+// every width; 64 queries of 24 tokens over 20,000 pages of 1,030 tokens 6.84 -> 5.49 ms (d = 32: 1.82 ->
+// 1.43), of 40 tokens over 6.4 M tokens 4.43 -> 3.49.
 constexpr int PACKED_NT = 6;
 template <typename Tag, int D, int NT, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
 __global__ __launch_bounds__(DENSE_THREADS, (RingShape<NT, RowShape<Frag<Tag, D>, D>::PITCH,
@@ -672,7 +673,7 @@ static hipError_t dense_score_nt(DenseArgs& A, const ScoreShape& s, hipStream_t 
     if constexpr (TQ <= 4) {
         if (s.nt == 4) return dense_go<Tag, D, 4, TQ, false>(A, s.groups, st);
     }
-    if constexpr (Tag::wide && D >= 64) {
+    if constexpr (Tag::wide) {
         A.hq = (A.T + 7) / 8;                       // a wavefront's queries are those of eight whole tiles
         if (A.hq * (8 / TQ) <= 2 * PACKED_NT) return dense_go<Tag, D, PACKED_NT, TQ, false, 0, true>(A, s.groups, st);
     }

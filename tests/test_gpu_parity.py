@@ -205,7 +205,7 @@ def test_paths_of_exhaustive_scoring(B, dtype, N, L, nq, T, d, kernel):
 
 
 @pytest.mark.parametrize("T,d", [(1, 128), (8, 64), (9, 128), (17, 128), (24, 96), (25, 64), (33, 128), (48, 64),
-                                 (49, 128), (65, 64), (96, 128), (97, 64)])
+                                 (49, 128), (65, 64), (96, 128), (97, 64), (7, 32), (20, 32), (47, 32), (90, 32)])
 def test_packed_query_tiles_give_the_bits_of_whole_tiles(B, S, oracle_mod, T, d):
     """Batches whose query lengths leave column tiles partly empty share tiles between queries (T up to
     8, 17..24, 33..48, 65..96; the neighbours of those lengths do not); scores and cells carry the same
