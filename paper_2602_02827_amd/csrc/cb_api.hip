@@ -241,7 +241,10 @@ struct PhaseTimer {
 // gathered visit also caches the document's cells for the remaining rounds when the query fits
 // the cache, so the gather is preferred up to twice the cost of the pass and, where every list
 // fits, of a round's other launches (~18 us): there a gathered round is the last one to launch,
-// which also saves those of all rounds after it.
+// which also saves those of all rounds after it.  Lists beyond the cache are launched round after round
+// either way, and where even full ones are gathered for no more than twice a pass and a round's
+// launches the pass is left out (~0): its empty launch is 4 us in every round (3 queries x 19,583 documents of
+// 48 tokens, T = 53 in rounds of 2, d = 32, a full gather 40 us and a pass 17: 762 us with it, 732 without).
 unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, int r, int R, bool lists_fit) {
     // int8 codes: half the bytes of bf16 and twice the rate; fp32: twice the bytes, a tenth of the rate
     const double row_bytes = (codes ? 1.0 : P.dt == DT_BF16 ? 2.0 : 4.0) * P.d;
@@ -267,6 +270,7 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
         t_pair = fmax(t_pair, ((double)P.total / (double)P.N) * 2.0 * tile_rows * P.d / 0.1e15);
         if (lists_fit) passes = R - r + 1;
     }
+    if (!lists_fit && (double)P.nq * (double)P.N * t_pair < passes * (t_pass + t_round)) return ~0ull;
     const double thr = (passes * t_pass + (lists_fit ? (passes + R - r) * t_round : 0.0)) / t_pair;
     return thr >= 1.8e19 ? ~0ull - 1 : (unsigned long long)thr;
 }

@@ -52,7 +52,7 @@ def _oracle_scores(oracle_mod, w, qs=None):
 
 
 def _kernels(fn, into=None):
-    """The names of the kernels that fn launches; its result is appended to `into`.  A profile now and
+    """The names of the kernels that fn launches, one for each launch; its result is appended to `into`.  A profile now and
     then comes back without any kernel record (API records only): then fn runs again."""
     from torch.profiler import ProfilerActivity, profile
     for _ in range(5):
@@ -60,7 +60,7 @@ def _kernels(fn, into=None):
         with profile(activities=[ProfilerActivity.CUDA]) as p:
             result = fn()
             torch.cuda.synchronize()
-        names = " ".join(e.key for e in p.key_averages())
+        names = " ".join(e.key for e in p.events())
         if "cb::" in names:
             break
     if into is not None:
@@ -585,6 +585,16 @@ def test_few_long_fp32_documents_do_not_stream_round_after_round(B, S):
     torch.cuda.synchronize()
     assert all(s["corpus_pass_rounds"] == [] for s in res[0]["stats"])
     _same_run(*res)
+
+
+def test_rounds_that_a_pass_could_not_shorten_launch_none(B, S):
+    """Lists beyond the cell cache that are gathered in less than two passes and a round's launches: the
+    corpus kernel runs in round 1 only, and the decisions are those of passes in every round."""
+    w = _custom(S, np.random.default_rng(7).integers(32, 65, 17000).tolist(), 3, 53, 32, "bf16", 7)
+    call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 100, 0.1, 0.01, 0, 2, B=2, **o)
+    call()
+    assert [_kernels(lambda: call(**o)).count("k_dense<") for o in ({}, {"later_rounds": 1})] == [1, 27]
+    _same_run(call(trace=True), call(trace=True, later_rounds=1))
 
 
 @pytest.mark.parametrize("N,nq,T,longest", [(20000, 5, 32, 3), (40000, 3, 48, 2), (9000, 9, 24, 5), (30000, 2, 100, 2)])
