@@ -82,7 +82,7 @@ typedef struct {
                            test aid, layout below                                       */
     size_t trace_bytes;
     int force_gather;   /* nonzero: reveal round 1 with the gather kernel as well
-                           (test aid; the default picks the dense kernel)               */
+                           (test aid; the default gathers only in the smallest calls)   */
     int no_cell_cache;  /* nonzero: re-gather the documents in every round instead of
                            caching a small active set's cells at its first gather
                            (test aid; the decisions are the same either way)            */

@@ -1744,7 +1744,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
 // list.  The threshold of round 1 comes from k_select_sample; the lists of later rounds are seldom
 // this long, and rather than launch the sampler in each of them every tile takes a lower bound
 // of its own K-th largest LCB (that of a part of the list cannot exceed that of the whole).
-// 64 M entries of 8 bytes (128 queries x 500,000): 131 us = 3.9 TB/s with a given threshold, bound by
+// 64 M entries of 8 bytes (128 queries x 500,000): 145 us = 3.5 TB/s with a given threshold, bound by
 // about 24 instructions an entry; 285 us with the tiles' own thresholds and as much when every
 // workgroup sampled for itself.
 // In a corpus-pass round the round's batch (stat2) is merged in registers only: k_select_prune
