@@ -23,7 +23,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0        # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3          # fp32 MFMA
+PEAK_F32_TFLOPS = 2500.0 / 6     # six bf16 products of the pieces of two fp32 values
 PEAK_HBM_GBS = 8000.0
 
 # HBM bytes per launch of the dominant kernels come from hardware-counter runs of this very
@@ -327,7 +327,7 @@ def main():
     peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_TFLOPS
     roofline = {"bound": "mfma",
                 "kernel": "k_dense (Full-MaxSim scoring kernel, bf16 16x16x32 MFMA)" if bf16
-                          else "k_dense, or k_gather_all for few queries (fp32 16x16x4 MFMA)",
+                          else "k_dense, or k_gather_all for few queries (fp32 as six bf16 16x16x32 MFMA)",
                 "achieved": round(tflops_kernel, 2), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(tflops_kernel / peak, 4), "traffic": traffic.get("full_maxsim"),
                 "traffic_by_request_size": traffic_rs.get("full_maxsim"),

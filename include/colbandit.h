@@ -227,7 +227,8 @@ int colbandit_coarse_maxsim(const void *Q, int n_queries, int T, int d, colbandi
  *                                on `stream`
  *   workspace                    DEVICE, 256-byte aligned, >= colbandit_workspace_bytes
  * bf16 inputs are multiplied on the matrix cores with fp32 accumulation; fp32 inputs
- * use fp32 matrix instructions.  Fully asynchronous unless phase_ms is given.
+ * are cut into three bf16 pieces each, exactly, whose products are summed in fp32 (the precision of
+ * an fp32 sum).  Fully asynchronous unless phase_ms is given.
  */
 int colbandit_full_maxsim(const void *Q, int n_queries, int T, int d, colbandit_dtype dt,
                           const void *doc_tokens, const int64_t *doc_offsets, int64_t N,

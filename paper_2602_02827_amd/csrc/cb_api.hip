@@ -20,8 +20,9 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 // more turns of those that the chip holds: the last turn, often nearly empty, then weighs little.
 // (6,007 documents, 0.9 M tokens, one column group: 224 chunks of 4,096 left CUs idle, 84 us for a
 // pass; 1,770 of 512 take 31 us.  100 queries x 6,000 documents of 106 tokens 464 -> 426 us
-// against 2,047 workgroups; with 8,190 430, 50,000 x 64 unchanged.  fp32, 16 x 20,000: 2,505 us with
-// 2,047, 2,256 with 4,095, 2,140 with 8,190 and with 16,380.)
+// against 2,047 workgroups; with 8,190 430, 50,000 x 64 unchanged.  fp32, 16 x 20,000: 1,300 us in
+// chunks of 4,096 tokens, 1,258 of 1,024, 1,309 of 512, 1,546 of 128; 16 x 5,000 of 100 tokens 361 us against
+// 482 with 8,190 workgroups.)
 // Several column groups fill the chip with longer chunks, over which a workgroup's query rows are
 // loaded less often.
 constexpr int kChunkTokens = 4096;
@@ -107,17 +108,12 @@ Work carve(void* ws, const Layout& L) {
 }
 
 // Sets the chunk length for passes over `tiles` column tiles, and the place of the chunk table.
-// fp32 chunks are shorter: a token costs ten times the matrix time, so a workgroup's start weighs
-// less and an uneven last turn of workgroups more (kBlocksWanted).  Groups are counted by the work of a
-// whole one: fp32 batches that go in groups of half as many tiles get twice the workgroups, of the same
-// work each (9 queries, 6.4 M tokens of d = 32: 1,355 us; 1,399 with the groups that are launched).
+// A group of fp32 tiles has half as many.
 void choose_chunks(Work& W, const Problem& P, int64_t tiles, bool codes = false) {
     const bool f32 = P.dt == DT_F32 && !codes;
     const int64_t per_group = f32 ? 16 : 32;
     const int64_t groups = (tiles + per_group - 1) / per_group;
-    int64_t most = f32 ? 2 * kBlocksWanted : kBlocksWanted;
-    if (most > kBlocksWanted * P.nq) most = kBlocksWanted * P.nq;
-    const int64_t wanted = most / groups > 1 ? most / groups : 1;
+    const int64_t wanted = kBlocksWanted / groups > 1 ? kBlocksWanted / groups : 1;
     int c = kChunkTokens;
     while (c > 128 && P.total <= wanted * (c / 2)) c /= 2;
     W.chunk_tokens = c;
@@ -137,39 +133,39 @@ bool small_call(const Problem& P) {
 }
 
 // Scores of all pairs: by gathering, or by a corpus pass, for which the chunks are set.  bf16: small_call.
-// fp32 is bound by the matrix pipes either way, so what decides is how many of the column tiles that a
-// pass multiplies are filled, and whether either fills the chip.  Time model (microseconds), from 900
-// shapes (4 to 20,000 documents of 48 to 20,000 tokens, 1 to 32 queries of 16 to 48, d = 32 to 128), on
-// which it picks the faster path or one within 8 % of it but for 19 (at most 1.34x):
-//   pass    a token costs 31 ps a tile multiplied, 35.5 at two a wavefront (d = 128; empty ones as well; short
-//           chunks more, and wavefronts that split the documents repeat blocks in which one ends);
+// fp32 weighs both: matrix work, of all column tiles that a pass multiplies, empty ones as well, against
+// the filled ones; reading, once against once a query; and whether either fills the chip.  Time model
+// (microseconds), from 994 shapes (10 to 100,000 documents of 48 to 8,000 tokens, 1 to 32 queries of 16 to 48,
+// d = 32 to 128), on which it picks the faster path or one within 8 % of it but for 47 (at most 1.7x):
+//   pass    a token costs 14 to 15 ps a tile multiplied (d = 128) and 25 a column group for cutting it into
+//           pieces; more where chunks are short or wavefronts split the documents; reading at 4.5 TB/s;
 //           never less than a document's blocks one after the other in one workgroup
-//   gather  43 ps a tile filled, 51 with four tiles a query of d = 96 and 128; a document's last block
-//           counted whole; every query reads the corpus, at 7.4 TB/s, and reads again cost up to three
-//           tenths more beyond the last-level cache; never less than a document's blocks one after
-//           the other in a wavefront, or shared by four (gather_shares)
-// gather and pass, us: 5,000 documents of 100 tokens, d = 128, T = 32: 1 query 83 and 162, 3 160 and 189, 4
-// 206 and 188, 5 256 and 323, 8 386 and 322, 9 431 and 499, 16 745 and 607; T = 16: 5 190 and 190; 20,000
-// (1 GB): 2 478 and 550, 3 650 and 597, 5 1,102 and 1,064; 50 of 8,000: 8 363 and 1,812.
-// One query, and two of more than 16 tokens, fill a quarter to a half of a pass's tiles and gather at
-// all sizes (1 GB, T = 16: 198 and 453, T = 32: 412 and 453, T = 48 in d = 64: 323 and 508).
+//   gather  13.5 ps a tile filled, 32 with four tiles a query of d = 96 and 128, and 16.5 a query for cutting;
+//           reading at 7.2 TB/s; never less than a document's blocks in a wavefront, or shared by four
+// Up to 82 MB of reading the gather saves a launch and loses at most a tenth where documents are of like length.
+// gather and pass, us, T = 32: 5,000 documents of 100 tokens, d = 128: 1 query 60 and 108, 2 89 and 110, 3 147
+// and 117, 8 308 and 207; 100,000 (5.1 GB): 1 989 and 1,349, 2 1,903 and 1,541; d = 64: 1 500 and 650, 2 865
+// and 734, 8 3,270 and 1,419.
 bool score_by_gather(Work& W, const Problem& P) {
     const ScoreShape s = score_shape(P, false);
     choose_chunks(W, P, s.tiles);
-    if (P.dt != DT_F32) return small_call(P);
-    if (small_call(P) || always_gathers(s)) return true;
-    const double d = P.d, total = (double)P.total, blocks = total / (double)P.N / 16.0;
-    const double repeat = s.split ? 0.92 : 1.0;
-    const double tiles = 4.0 * s.nt * s.groups;
-    const double stream = total * tiles * (s.nt == 2 ? 35.5e-6 : 31e-6) * (1.0 + 32.0 / W.chunk_tokens) * d / 128.0;
-    const double one_doc = blocks * (s.nt == 2 ? 0.16 + 0.0146 * d : 0.3 + 0.026 * d);
-    const double t_pass = 14.0 + repeat * fmax(stream, one_doc);
+    if (small_call(P)) return true;
+    if (P.dt != DT_F32) return false;
+    const double d = P.d, total = (double)P.total, nq = P.nq, blocks = total / (double)P.N / 16.0;
     const double corpus = total * d * 4.0;
-    double t_gather = fmax((double)P.nq * (total + 8.0 * (double)P.N) * s.tq * (s.tq * P.d >= 384 ? 51e-6 : 42.7e-6) * d / 128.0,
-                           (double)P.nq * corpus / 7.4e6);
-    if (corpus > 256e6) t_gather *= 1.0 + 0.1 * fmin(P.nq - 1.0, 3.0);
-    t_gather = fmax(t_gather, blocks * (0.3 + 0.0045 * d * s.tq) / (gather_shares(P) ? 4.0 : 1.0));
-    return 12.0 + t_gather < t_pass;
+    if (nq * corpus <= 82e6) return true;
+    const auto both = [](double a, double b) { return cbrt(a * a * a + b * b * b); };   // little more than the larger
+    const bool eight = P.d >= 96 && s.tq <= 2;       // groups of 16 tiles have eight wavefronts
+    const double tiles = 4.0 * s.nt * s.groups / (s.split ? s.split / 1.5 : 1.0);
+    const double cut = 25.0 * s.groups * (s.split ? 1.5 : 1.0);
+    const double multiply = total * (tiles * (s.nt == 2 || eight ? 15.4 : 14.2) + cut) * 1e-6 *
+                            (1.0 + 42.0 / W.chunk_tokens) * d / 128.0 * (P.d == 96 ? 1.44 : 1.0);
+    const double t_pass = 15.0 + fmax(both(multiply, corpus / 4.5e6), blocks * (0.13 + (s.nt == 2 ? 0.006 : 0.012) * d));
+    const double filled = nq * (total + 8.0 * (double)P.N) * (16.5 + 13.5 * s.tq + (s.tq == 4 && P.d >= 96 ? 19.0 : 0.0)) *
+                          1e-6 * (d + 12.0) / 128.0;
+    const double t_gather = 11.5 + fmax(both(filled, nq * corpus / 7.2e6),
+                                        blocks * (0.43 + 0.0025 * d * s.tq) / (gather_shares(P) ? 4.0 : 1.0));
+    return t_gather < t_pass;
 }
 
 int check_shapes(const void* Q, int nq, int T, int d, int dt, const void* docs,
@@ -246,28 +242,31 @@ struct PhaseTimer {
 // launches the pass is left out (~0): its empty launch is 4 us in every round (3 queries x 19,583 documents of
 // 48 tokens, T = 53 in rounds of 2, d = 32, a full gather 40 us and a pass 17: 762 us with it, 732 without).
 unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, int r, int R, bool lists_fit) {
-    // int8 codes: half the bytes of bf16 and twice the rate; fp32: twice the bytes, a tenth of the rate
+    // int8 codes: half the bytes of bf16 and twice the rate
     const double row_bytes = (codes ? 1.0 : P.dt == DT_BF16 ? 2.0 : 4.0) * P.d;
-    const double rate = codes ? 2.3e15 : P.dt == DT_BF16 ? 1.15e15 : 0.11e15;
+    const double rate = codes ? 2.3e15 : 1.15e15;
     const double rows = (double)(((int64_t)P.nq * G + 15) / 16 * 16);
-    const double per_token = fmax(row_bytes / 3.5e12, 2.0 * rows * P.d / rate);
+    double per_token = fmax(row_bytes / 3.5e12, 2.0 * rows * P.d / rate);
     const double t_round = 18e-6;
+    const double doc_tokens = (double)P.total / (double)P.N;
     double t_pass = (double)P.total * per_token;
-    double t_pair = ((double)P.total / (double)P.N) * row_bytes / 4.5e12;
+    double t_pair = doc_tokens * row_bytes / 4.5e12;
     double passes = 2.0;
     if (!codes && P.dt == DT_F32) {
-        // matrix work bounds both: all T tokens of a pair at once against a batch in each pass, so
-        // where the lists fit the cache the one visit is weighed against a pass in every round left
-        // (33 queries x 57 tokens over 1,154 pages of 647, d = 96, 9 rounds of passes: 4.7 ms, gathered 4.4)
+        // The matrix work of both weighs too (the terms are those of score_by_gather): all T tokens of a pair
+        // at once against a batch in each pass, so where the lists fit the cache the one visit is weighed
+        // against a pass in every round left.  A pass takes no less than a mean document's blocks one
+        // after the other in a workgroup.
         const int tq = (P.T + 15) / 16;
-        // (a pass takes no less than a mean document's blocks one after the other in a workgroup: 34
-        // queries x 131 documents of 2,380 tokens, d = 64, 290 us where the tokens' matrix work is 50;
-        // three such passes made a call of 2.1 ms out of 0.93)
-        const double tiles = rows / 16.0;
-        const double block = tiles <= 4 ? 0.1e-6 + 0.0075e-6 * P.d : tiles <= 8 ? 0.16e-6 + 0.0146e-6 * P.d : 0.3e-6 + 0.026e-6 * P.d;
-        t_pass = fmax(t_pass, (double)P.total / (double)P.N / 16.0 * block);
-        const double tile_rows = 16.0 * (tq <= 1 ? 1 : tq <= 2 ? 2 : 4);
-        t_pair = fmax(t_pair, ((double)P.total / (double)P.N) * 2.0 * tile_rows * P.d / 0.1e15);
+        const bool two = rows <= 128.0;
+        const double tiles = rows <= 64.0 ? 4.0 : two ? 8.0 : ceil(rows / 256.0) * 16.0;
+        const double groups = two ? 1.0 : tiles / 16.0;
+        per_token = fmax(row_bytes / 4.5e12, (tiles * (two || P.d >= 96 ? 15.4 : 14.2) + 25.0 * groups) * 1e-12 * P.d / 128.0);
+        t_pass = (double)P.total * per_token;
+        t_pass = fmax(t_pass, doc_tokens / 16.0 * (0.13e-6 + (two ? 0.006e-6 : 0.012e-6) * P.d));
+        const int tile = tq <= 1 ? 1 : tq <= 2 ? 2 : 4;
+        if ((double)P.total * row_bytes <= 256e6) t_pair = doc_tokens * row_bytes / 7.2e12;   // in the last-level cache
+        t_pair = fmax(t_pair, doc_tokens * (16.5 + 13.5 * tile + (tile == 4 && P.d >= 96 ? 19.0 : 0.0)) * 1e-12 * (P.d + 12) / 128.0);
         if (lists_fit) passes = R - r + 1;
     }
     if (!lists_fit && (double)P.nq * (double)P.N * t_pair < passes * (t_pass + t_round)) return ~0ull;

@@ -9,11 +9,13 @@
 //   * A workgroup (4 wavefronts) owns one token chunk (whole documents whose first token
 //     falls into a fixed-size token range) and one group of 64*NT query columns.
 //   * Query rows are the B operand and stay in registers for the whole kernel: each
-//     wavefront holds NT column tiles of 16 rows, full depth (NT*d/8 VGPRs; fp32 NT*d/4, hence
-//     NT <= 4).
+//     wavefront holds NT column tiles of 16 rows, full depth (NT*d/8 VGPRs; fp32, in three bf16
+//     pieces, NT*d*3/8, hence NT <= 4).
 //   * Document tokens are the A operand.  They stream through a four-slot LDS ring of
 //     64-token stages (direct global -> LDS copies issued two stages ahead of the reader), so
-//     a token is read from memory once per workgroup and from LDS once per wavefront.
+//     a token is read from memory once per workgroup and from LDS once per wavefront.  fp32 tokens
+//     pass through registers instead, are cut into their pieces once per workgroup and lie in LDS in
+//     three planes (two slots of 32 tokens).
 //     Rows are stored with their 16-byte pieces XOR-swizzled by the row index, which
 //     spreads the 16 rows of an operand block over all banks; a row whose length is not a power
 //     of two (d = 96) is padded to one in LDS.
@@ -30,13 +32,19 @@
 
 namespace cb {
 
-constexpr int DENSE_THREADS = 256;
+// A workgroup covers 4 * TILES column tiles with four wavefronts.  fp32 in d = 96 and 128 spreads them
+// over eight where it can (a wavefront needs all tiles of a query): four tiles of pieces would leave
+// one wavefront per SIMD, and eight wavefronts share the cutting of the tokens (16 queries x 20,000
+// documents of d = 128: 1,417 us with four, 1,302 with eight; 32 of 16 tokens at d = 96 1,313 and 1,030).
+template <typename Tag, int D, int TILES, int TQ> constexpr int dense_waves() {
+    return !Tag::wide && D >= 96 && TILES == 4 && TQ <= 2 ? 8 : 4;
+}
 // Ring geometry: four stages.  Kernels with few column tiles per wavefront (small query
 // batches: bound by memory, little register use) take 32-row stages, so that four workgroups fit
 // a CU instead of two and more wavefronts hide the latencies; the others take 64-row stages.
 // A_REGS: registers of one operand block (the query rows take NT of them, two token blocks are in
 // flight); four, three or two workgroups per CU by what that and the rings' LDS leave.
-template <int NT, int PITCH, int A_REGS> struct RingShape {
+template <int NT, int PITCH, int A_REGS, int PLANES> struct RingShape {
     static constexpr int ROWS_PER_LOAD = 64 / (PITCH / 16);
     static constexpr bool SMALL = NT <= 4 && 32 / ROWS_PER_LOAD / 4 >= 1;
     static constexpr int STAGE_ROWS = SMALL ? 32 : 64;
@@ -44,16 +52,28 @@ template <int NT, int PITCH, int A_REGS> struct RingShape {
     static constexpr int REGS = (NT + 2) * A_REGS + 40;
     static constexpr int BY_REGS = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : 2);
     static constexpr int BY_SHAPE = SMALL ? (NT <= 2 ? 4 : 3) : 2;
-    static constexpr int BY_LDS = 160 * 1024 / (RING_ROWS * PITCH);   // fp32 at d = 96 and 128: two
+    static constexpr int BY_LDS = 160 * 1024 / (RING_ROWS * PITCH);
     static constexpr int FIT = BY_REGS < BY_SHAPE ? BY_REGS : BY_SHAPE;
     static constexpr int MIN_BLOCKS = FIT < BY_LDS ? FIT : BY_LDS;
     static_assert(MIN_BLOCKS >= 1 && MIN_BLOCKS * RING_ROWS * PITCH <= 160 * 1024, "the rings of a CU's workgroups");
 };
-// bytes of a token row, and of its place in the ring (a power of two)
+// fp32: two slots of 32 rows, each row in three planes of bf16 pieces; the loads of the next stage are
+// in registers (16 at most).
+template <int NT, int PITCH, int A_REGS> struct RingShape<NT, PITCH, A_REGS, 3> {
+    static constexpr int STAGE_ROWS = 32;
+    static constexpr int RING_ROWS = 2 * STAGE_ROWS;
+    static constexpr int REGS = (NT + 2) * A_REGS + 60;
+    static constexpr int BY_REGS = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : (REGS <= 256 ? 2 : 1));
+    static constexpr int BY_LDS = 160 * 1024 / (RING_ROWS * PITCH * 3);
+    static constexpr int MIN_BLOCKS = BY_REGS < BY_LDS ? BY_REGS : BY_LDS;
+};
+// bytes of a token row, of its place in the ring (a power of two; fp32: in a plane), and how many planes
 template <class F, int D> struct RowShape {
     static constexpr int BYTES = D * F::ELEM_BYTES;
-    static constexpr int PITCH = BYTES <= 64 ? 64 : BYTES <= 128 ? 128 : BYTES <= 256 ? 256 : 512;
-    static constexpr int A_REGS = BYTES / 16;
+    static constexpr int PLANES = F::ELEM_BYTES == 4 ? 3 : 1;
+    static constexpr int PLACE = PLANES == 3 ? D * 2 : BYTES;
+    static constexpr int PITCH = PLACE <= 64 ? 64 : PLACE <= 128 ? 128 : 256;
+    static constexpr int A_REGS = (int)sizeof(F) / 4;
 };
 
 struct DenseArgs {
@@ -89,12 +109,16 @@ struct DenseArgs {
 // every width; 64 queries of 24 tokens over 20,000 pages of 1,030 tokens 6.84 -> 5.49 ms (d = 32: 1.82 ->
 // 1.43), of 40 tokens over 6.4 M tokens 4.43 -> 3.49.
 constexpr int PACKED_NT = 6;
-template <typename Tag, int D, int NT, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
-__global__ __launch_bounds__(DENSE_THREADS, (RingShape<NT, RowShape<Frag<Tag, D>, D>::PITCH,
-                                                       RowShape<Frag<Tag, D>, D>::A_REGS>::MIN_BLOCKS))
+template <typename Tag, int D, int TILES, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
+__global__ __launch_bounds__((64 * dense_waves<Tag, D, TILES, TQ>()),
+                             (RingShape<TILES * 4 / dense_waves<Tag, D, TILES, TQ>(), RowShape<Frag<Tag, D>, D>::PITCH,
+                                        RowShape<Frag<Tag, D>, D>::A_REGS, RowShape<Frag<Tag, D>, D>::PLANES>::MIN_BLOCKS))
 void k_dense(DenseArgs A) {
     using F = Frag<Tag, D>;
-    using RS = RingShape<NT, RowShape<F, D>::PITCH, RowShape<F, D>::A_REGS>;
+    constexpr int WAVES = dense_waves<Tag, D, TILES, TQ>();
+    constexpr int NT = TILES * 4 / WAVES;          // column tiles of a wavefront
+    constexpr int PLANES = RowShape<F, D>::PLANES;
+    using RS = RingShape<NT, RowShape<F, D>::PITCH, RowShape<F, D>::A_REGS, PLANES>;
     constexpr int STAGE_ROWS = RS::STAGE_ROWS;
     constexpr int RING_ROWS = RS::RING_ROWS;
     using V = typename F::val_t;           // float, or int for int8 codes
@@ -103,21 +127,18 @@ void k_dense(DenseArgs A) {
     constexpr int PITCH = RowShape<F, D>::PITCH;   // ... and in the ring
     constexpr int NCH = PITCH / 16;                // 16-byte pieces per ring row
     constexpr bool F32 = __is_same(Tag, f32_tag);
-    // Cache policy of the token copies.  The reveal pass normally has one column group, and the
-    // score kernels with at most four column tiles per wavefront always have (fp32: normally with
-    // two): a token row is read once and should not push other lines out of L2 - above all those of
-    // the (sum, M2) array, which fill up over several documents; such copies carry the non-temporal
-    // hint (bit 1).  Several fp32 groups of two tiles read a row again; they are bound by the matrix
-    // pipes and as fast with the hint as without (9 queries 1,740 and 1,738 us), one group is not (4
-    // queries 623 and 628).
-    constexpr int LOAD_POLICY = F32 ? (NT <= 2 ? 2 : 0) : (REVEAL || NT <= 4) ? 2 : 0;
+    // Cache policy of the token copies (not of fp32, whose tokens pass through registers).  The reveal pass
+    // normally has one column group, and the score kernels with at most four column tiles per wavefront
+    // always have: a token row is read once and should not push other lines out of L2 - above all those
+    // of the (sum, M2) array, which fill up over several documents; such copies carry the non-temporal
+    // hint (bit 1).
+    constexpr int LOAD_POLICY = (REVEAL || NT <= 4) ? 2 : 0;
     // Swizzle key of a ring row: rows whose 16-byte pieces would fall on the same banks (row
     // stride PITCH against the 256-byte bank window) get different keys.  The key's period must
-    // divide the rows of one load of all wavefronts; that is 8 rows at 512 bytes, which leaves
-    // two rows to a bank: nothing beside fp32's matrix time (8 of 1,024 cycles a column tile).
+    // divide the rows of one load of all wavefronts, of fp32 those of a stage.
     constexpr int KEY_SHIFT = NCH >= 16 ? 0 : (NCH == 8 ? 1 : 2);
-    constexpr int KEY_MASK = NCH == 32 ? 7 : NCH - 1;
-    __shared__ __attribute__((aligned(16))) char ring[RING_ROWS * PITCH];
+    constexpr int KEY_MASK = NCH - 1;
+    __shared__ __attribute__((aligned(16))) char ring[PLANES * RING_ROWS * PITCH];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in an SGPR
@@ -160,7 +181,7 @@ void k_dense(DenseArgs A) {
     static_assert(SPLIT_DOCS == 0 || ((SPLIT_DOCS == 2 || SPLIT_DOCS == 4) && !REVEAL),
                   "document splitting is for small batches of the score kernels");
     constexpr int TILE_WAVES = SPLIT_DOCS ? 4 / SPLIT_DOCS : 4;      // wavefronts with tiles of their own
-    const int tile0 = SPLIT_DOCS ? (wave % TILE_WAVES) * NT : (group * 4 + wave) * NT;
+    const int tile0 = SPLIT_DOCS ? (wave % TILE_WAVES) * NT : (group * WAVES + wave) * NT;
     auto mine = [&](int doc) {
         return SPLIT_DOCS == 0 || ((doc - i0) & (SPLIT_DOCS ? SPLIT_DOCS - 1 : 0)) == wave / TILE_WAVES;
     };
@@ -200,7 +221,7 @@ void k_dense(DenseArgs A) {
     // lane at physical piece position p of LDS row r fetches the logical piece p ^ (r & (NCH-1)).
     const char* src = (const char*)A.docs + (size_t)tok_begin * ROWB;
     constexpr int ROWS_PER_LOAD = 64 / NCH;
-    constexpr int LOADS_PER_WAVE = STAGE_ROWS / ROWS_PER_LOAD / 4;
+    constexpr int LOADS_PER_WAVE = STAGE_ROWS / ROWS_PER_LOAD / 4;    // not of fp32
     // A lane's place inside a load does not depend on the stage or on the load's number (both
     // move the row by multiples of the swizzle period): row wave*ROWS_PER_LOAD + lane/NCH of the
     // load group, piece (lane % NCH) ^ key(row).  A complete stage therefore needs no per-lane
@@ -422,11 +443,13 @@ void k_dense(DenseArgs A) {
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    stage_fetch(0);
-    if (nst > 1) stage_fetch(1);
-    wait_copies();
-    ring_barrier();
-    if (nst > 2) stage_fetch(2);
+    if constexpr (!F32) {
+        stage_fetch(0);
+        if (nst > 1) stage_fetch(1);
+        wait_copies();
+        ring_barrier();
+        if (nst > 2) stage_fetch(2);
+    }
     // the reader enters stage st >= 1: publish stage st+1, request the next one
     auto stage_enter = [&](int st) {
         if (st + 1 >= nst) return;                  // everything is visible already
@@ -450,19 +473,19 @@ void k_dense(DenseArgs A) {
     for (int ks = 0; ks < F::KS; ++ks)
         blk_off[ks] = (unsigned)(col * PITCH + (((ks * 4 + kg) ^ ((col >> KEY_SHIFT) & KEY_MASK)) * 16));
     // a complete block (bs + 16 <= ntok) of a visible stage
-    auto load_aligned = [&](F& a, int bs) {
+    auto load_aligned = [&](auto& a, int bs) {
         using piece_t = __remove_reference_t(decltype(a.v[0]));
         const char* rp = ring + (bs & (RING_ROWS - 1)) * PITCH;      // uniform
 #pragma unroll
         for (int ks = 0; ks < F::KS; ++ks) a.v[ks] = *(const piece_t*)(rp + blk_off[ks]);
     };
     // any block of a visible stage; the chunk's last block repeats the last token
-    auto load_block = [&](F& a, int bs) {
-        using piece_t = __remove_reference_t(decltype(a.v[0]));
+    auto load_block = [&](auto& a, int bs) {
         if (bs + 16 <= ntok) {
             load_aligned(a, bs);
             return;
         }
+        using piece_t = __remove_reference_t(decltype(a.v[0]));
         int row = bs + col;
         row = row < ntok ? row : ntok - 1;
         const char* rp = ring + (row & (RING_ROWS - 1)) * PITCH;
@@ -512,6 +535,79 @@ void k_dense(DenseArgs A) {
             }
         }
     };
+
+    // ---- fp32: a stage's rows pass through registers, where they are cut into their three pieces (split3),
+    // once for all wavefronts (44 vector instructions a wavefront and stage at d = 128 and four wavefronts; each
+    // for itself would take four times as many, as long as the matrix work of two tiles).  A thread takes
+    // the 16 + 16 bytes that a lane of a wavefront holds of one k-step (Frag): one 16-byte piece in each plane.
+    // A wavefront writes stage s + 1 when it has finished stage s itself, over stage s - 1, which all finished
+    // before the barrier of stage s.  (Three slots, the first block of a stage read before its barrier: eight
+    // wavefronts 0 to 3 % faster, four 2 to 6 % slower.)
+    if constexpr (F32) {
+        constexpr int PIECES = D / 8;               // of a row
+        constexpr int THREADS = 64 * WAVES;
+        constexpr int PER = (STAGE_ROWS * PIECES + THREADS - 1) / THREADS;
+        constexpr int PLANE = RING_ROWS * PITCH, SLOT = STAGE_ROWS * PITCH;
+        f32x4_t raw[PER][2];
+        int prow[PER];
+        unsigned src_off[PER], dst_off[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int x = i * THREADS + (int)threadIdx.x;
+            const int c = x % PIECES;
+            prow[i] = x / PIECES;
+            src_off[i] = (unsigned)((c >> 2) * 128 + (c & 3) * 16);
+            dst_off[i] = (unsigned)(prow[i] * PITCH + (c ^ ((prow[i] >> KEY_SHIFT) & KEY_MASK)) * 16);
+        }
+        auto has = [&](int i) { return PER * THREADS == STAGE_ROWS * PIECES || prow[i] < STAGE_ROWS; };   // whole wavefronts
+        // rows past the chunk's end repeat the last token
+        auto fetch = [&](int s) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (has(i)) {
+                    int row = s * STAGE_ROWS + prow[i];
+                    row = row < ntok ? row : ntok - 1;
+                    const char* p = src + (size_t)row * ROWB + src_off[i];
+                    raw[i][0] = *(const f32x4_t*)p;
+                    raw[i][1] = *(const f32x4_t*)(p + 64);
+                }
+        };
+        auto publish = [&](int s) {
+            char* at = ring + (s & 1) * SLOT;
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (has(i)) {
+                    bf16x8_t hi, mid, lo;
+                    split3(raw[i][0], raw[i][1], hi, mid, lo);
+                    *(bf16x8_t*)(at + dst_off[i]) = hi;
+                    *(bf16x8_t*)(at + PLANE + dst_off[i]) = mid;
+                    *(bf16x8_t*)(at + 2 * PLANE + dst_off[i]) = lo;
+                }
+        };
+        auto load_half = [&](F& a, int s, int half) {
+            const char* rp = ring + (s & 1) * SLOT + half * (16 * PITCH);
+#pragma unroll
+            for (int p = PLANES - 1; p >= 0; --p)
+#pragma unroll
+                for (int ks = 0; ks < F::KS; ++ks) a.v[p][ks] = *(const bf16x8_t*)(rp + p * PLANE + blk_off[ks]);
+        };
+        fetch(0);
+        for (int s = 0; s < nst; ++s) {
+            publish(s);
+            if (s + 1 < nst) fetch(s + 1);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): this wavefront's pieces are written
+            ring_barrier();
+            const int bs = s * STAGE_ROWS;
+            F a0, a1;
+            load_half(a0, s, 0);
+            load_half(a1, s, 1);
+            process(a0, bs);
+            if (bs + 16 < ntok) process(a1, bs + 16);
+        }
+        while (doc < i1) finalize(doc++);           // documents without tokens at the chunk's end
+        return;
+    } else {
 
     // ---- consumer: the MFMAs of block k overlap the operand reads of block k+1.  a0 always
     // holds the block at bs; the stage that begins at bs (if one does) is entered just before
@@ -580,6 +676,7 @@ void k_dense(DenseArgs A) {
         bs += 16;
     }
     while (doc < i1) finalize(doc++);           // documents without tokens at the chunk's end
+    }
 }
 
 // ---- first document of every token chunk
@@ -620,13 +717,13 @@ static void fill_dense(DenseArgs& A, const Problem& P, const Work& W, int n_chun
     A.stat = W.stat;
 }
 
-template <typename Tag, int D, int NT, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
+template <typename Tag, int D, int TILES, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
 static hipError_t dense_go(DenseArgs& A, int groups, hipStream_t st) {
     A.n_groups = groups;
     const int chunks8 = (A.n_chunks + 7) / 8 * 8;
     const long long blocks = (long long)chunks8 * A.n_groups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    k_dense<Tag, D, NT, TQ, REVEAL, SPLIT_DOCS, PACKED><<<(unsigned)blocks, DENSE_THREADS, 0, st>>>(A);
+    k_dense<Tag, D, TILES, TQ, REVEAL, SPLIT_DOCS, PACKED><<<(unsigned)blocks, 64 * dense_waves<Tag, D, TILES, TQ>(), 0, st>>>(A);
     return hipGetLastError();
 }
 
@@ -646,10 +743,12 @@ ScoreShape score_shape(const Problem& P, bool codes) {
         return s;
     }
     if (s.tq <= 2 && s.tiles <= 8) s.nt = 2;
-    // fp32 is bound by the matrix pipes: half as many tiles per wavefront where that leaves clearly
-    // fewer of them empty (9 queries of two tiles, 24 instead of 32 multiplied: 10,000 documents of
-    // d = 128 1,119 -> 914 us, 1,827 of d = 64 146 -> 115; 27 queries 2,146 -> 2,035)
-    else if (f32 && s.tq <= 2 && (s.tiles + 7) / 8 * 8 * 9 < (s.tiles + 15) / 16 * 16 * 8) s.nt = 2;
+    // fp32 is bound by the matrix pipes: groups half as large where that leaves clearly fewer tiles empty (10
+    // queries of two tiles, 24 instead of 32 multiplied: 20,000 documents of d = 128 1,303 -> 998 us).  In d = 96
+    // and 128 large groups, of eight wavefronts, gain only where all of them are whole (16 queries x 20,000
+    // documents: d = 128 1,288 us with half as large groups and 1,302, 32 of 16 tokens at d = 96 1,108 and
+    // 1,030) and are fewer to balance (5 queries x 5,000 documents of d = 128 209 and 260)
+    else if (f32 && s.tq <= 2 && (P.d >= 96 ? s.tiles % 16 != 0 : (s.tiles + 7) / 8 * 8 * 9 < (s.tiles + 15) / 16 * 16 * 8)) s.nt = 2;
     else if (f32 || (s.tq <= 4 && s.tiles <= 16)) s.nt = 4;
     else s.nt = 8;
     s.groups = (int)((s.tiles + 4 * s.nt - 1) / (4 * s.nt));
@@ -659,14 +758,8 @@ ScoreShape score_shape(const Problem& P, bool codes) {
 template <typename Tag, int D, int TQ>
 static hipError_t dense_score_nt(DenseArgs& A, const ScoreShape& s, hipStream_t st) {
     constexpr int FEW = TQ <= 2 ? 2 : TQ;           // tiles of a wavefront that splits documents
-    if constexpr (Tag::wide) {
-        if (s.split == 4) return dense_go<Tag, D, FEW, TQ, false, 4>(A, 1, st);
-    } else {
-        if (always_gathers(s)) return hipErrorInvalidValue;
-    }
-    if constexpr (Tag::wide || TQ == 1) {
-        if (s.split == 2) return dense_go<Tag, D, FEW, TQ, false, 2>(A, 1, st);
-    }
+    if (s.split == 4) return dense_go<Tag, D, FEW, TQ, false, 4>(A, 1, st);
+    if (s.split == 2) return dense_go<Tag, D, FEW, TQ, false, 2>(A, 1, st);
     if constexpr (TQ <= 2) {
         if (s.nt == 2) return dense_go<Tag, D, 2, TQ, false>(A, s.groups, st);
     }

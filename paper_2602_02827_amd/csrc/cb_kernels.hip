@@ -192,18 +192,26 @@ struct GatherArgs {
     const float* dscale;
 };
 
+// Registers of a gather kernel with NT tiles of query rows and one block at work, and wavefronts per
+// SIMD that leaves.
+template <int NT, class F> constexpr int gather_regs(bool ahead) {
+    return (NT + 1) * ((int)sizeof(F) / 4) + (ahead ? (int)sizeof(typename F::Raw) / 4 + 8 * NT : 36);
+}
+constexpr int waves_of(int regs) { return 512 / regs < 4 ? 512 / regs : 4; }
 // Whether a second block of a document is in flight: where its registers do not cost a wavefront per
 // SIMD.
 template <int NT, class F> constexpr bool two_in_flight() {
-    return (NT + 2) * ((int)sizeof(F) / 4) + 8 * NT <= 112;
+    if constexpr (__is_same(typename F::Raw, F)) return gather_regs<NT, F>(true) <= 112;
+    else return waves_of(gather_regs<NT, F>(true) + 28) >= waves_of(gather_regs<NT, F>(false));
 }
 // Wavefronts per SIMD of k_gather_round, which serves two kinds of list and without a bound takes a few
 // registers too many for the four (or what the query rows leave) that a kernel with one block in
 // flight needs (T = 48, 50,000 documents x 16 queries 1,645 -> 1,546 us a call, T = 100 and d = 96, 20,000
-// x 16 1,005 -> 908).  fp32 at d = 128 and two tiles stays at three: four spill (3,847 -> 4,031).
+// x 16 1,005 -> 908).
+// fp32 needs some for a block on its way from what was read to its pieces.
 template <int TQ, class F> constexpr int round_waves() {
-    constexpr int FIT = 512 / ((TQ + 1) * ((int)sizeof(F) / 4) + 36);
-    return two_in_flight<TQ, F>() ? 1 : (FIT < 4 ? FIT : 4);
+    constexpr int CUT = __is_same(typename F::Raw, F) ? 0 : 16;
+    return two_in_flight<TQ, F>() ? 1 : waves_of(gather_regs<TQ, F>(false) + CUT);
 }
 
 // Folds the blocks first, first + stride, ... of the document [o0, o1) into h.
@@ -212,18 +220,21 @@ __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o
                                          int col, int kg, const F (&bq)[NT], typename F::val_t (&h)[NT]) {
     int64_t r0 = o0 + 16 * first;
     if (r0 >= o1) return;
-    auto load = [&](F& a, int64_t r) {
+    using R = typename F::Raw;
+    auto load = [&](R& a, int64_t r) {
         int64_t row = r + col;
         row = row < o1 ? row : o1 - 1;
         a.load(docs + (size_t)row * ROWB, kg);
     };
     constexpr bool AHEAD = two_in_flight<NT, F>();
-    F a;
-    load(a, r0);
+    R raw;
+    load(raw, r0);
     for (;;) {
         const int64_t r1 = r0 + 16 * stride;
         const bool more = r1 < o1;
-        F next;
+        F a;
+        a.from(raw);
+        R next;
         if (AHEAD && more) load(next, r1);
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) {
@@ -232,8 +243,8 @@ __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o
             h[tt] = fold_max(h[tt], acc);
         }
         if (!more) return;
-        if (AHEAD) a = next;
-        else load(a, r1);
+        if (AHEAD) raw = next;
+        else load(raw, r1);
         r0 = r1;
     }
 }
@@ -662,7 +673,10 @@ hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float*
     A.cells = cells;
     A.shared = gather_shares(P) ? 1 : 0;
     const int64_t gx = A.shared ? P.N : (P.N + 3) / 4;
-    return gather_any(A, GM_ALL, P, W, dim3((unsigned)(gx < 256 ? gx : 256), P.nq), nullptr, st);
+    // at least four workgroups a CU over all queries (one fp32 query, 10.6 M tokens: d = 32 618 -> 284 us,
+    // d = 128 1,196 -> 989; more than four change nothing)
+    const int64_t most = P.nq >= 4 ? 256 : 1024 / P.nq;
+    return gather_any(A, GM_ALL, P, W, dim3((unsigned)(gx < most ? gx : most), P.nq), nullptr, st);
 }
 
 // Exact score of a survivor from its cached cells: the T cells of a slot are laid out as the

@@ -123,8 +123,6 @@ struct ScoreShape {
 };
 // codes: a pass on int8 codes.
 ScoreShape score_shape(const Problem& P, bool codes);
-// fp32 batches that always gather: there is no corpus kernel for them
-inline bool always_gathers(const ScoreShape& s) { return s.split == 4 || (s.split == 2 && s.tq > 1); }
 bool dense_supported(const Problem& P, const Coarse* co);
 int dense_chunks(const Problem& P, const Work& W);
 

@@ -276,6 +276,45 @@ def test_full_maxsim_fp32_ragged_and_d64(B, S, oracle_mod):
         np.testing.assert_allclose(r["scores"].cpu().numpy(), Sor, rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("nq,T,d,pas", [(1, 32, 128, False), (3, 48, 96, False), (1, 16, 32, True), (2, 16, 128, True),
+                                        (2, 32, 64, True), (3, 32, 128, True), (9, 32, 32, True), (5, 64, 128, True),
+                                        (1, 48, 96, True), (2, 40, 64, True)])
+def test_fp32_products_on_the_bf16_pipes_keep_fp32_precision(B, S, nq, T, d, pas):
+    """fp32 products are sums of six bf16 products of the values' pieces.  Components spread over 2^+-40 in
+    either sign, some short of bits, and some infinite: a cell is the largest sum, each within the rounding of
+    an fp32 sum whatever its order.  A sum takes at most 6 d / 32 = 24 instructions and each of them five levels
+    of additions, at a rounding (2^-24) of the magnitudes' sum each: 29 roundings; truncation instead of
+    rounding would double it: 64 are allowed, which also covers the pieces left out (3 * 2^-25)."""
+    lengths = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 5]
+    if pas:
+        lengths = _past_small(lengths, nq, d, "f32")
+    w = _custom(S, lengths, nq, T, d, "f32", 3)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    rnd = lambda *shape: torch.rand(shape, generator=g, device="cuda", dtype=torch.float64)
+    for x in (w.docs, w.Q):
+        v = torch.exp2(rnd(*x.shape) * 80 - 40) * torch.where(rnd(*x.shape) < 0.5, -1.0, 1.0)
+        v = torch.where(rnd(*x.shape) < 0.1, torch.exp2(torch.round(torch.log2(v.abs()))), v)
+        x.copy_(v)
+    off = w.offsets
+    inf_doc = len(lengths) - 3
+    w.docs[int(off[inf_doc]) + 2, 5] = float("inf")
+    w.docs[int(off[inf_doc]) + 2, d - 1] = -float("inf")
+    w.docs[int(off[inf_doc + 1]) - 1, 7] = -float("inf")
+    full = B.colbandit_full_maxsim(w.Q, w.docs, off, K=1, want_cells=True)
+    E, Q = w.docs.double(), w.Q.reshape(nq * T, d).double()
+    cells = full["cells"].permute(1, 0, 2).reshape(len(lengths), nq * T).double()
+    lens = off[1:] - off[:-1]
+    doc = torch.repeat_interleave(torch.arange(len(lengths), device="cuda"), lens)
+    # a product with a token's infinite component decides; two of opposite sign have no sum and no say
+    dots = torch.nan_to_num(E @ Q.t(), nan=-float("inf"), posinf=float("inf"), neginf=-float("inf"))
+    mags = torch.where(torch.isfinite(E), E, 0).abs() @ Q.abs().t()
+    ref = torch.full_like(cells, -float("inf")).scatter_reduce(0, doc[:, None].expand_as(dots), dots, "amax")
+    mag = torch.zeros_like(cells).scatter_reduce(0, doc[:, None].expand_as(dots), mags, "amax")
+    fin = torch.isfinite(ref)
+    assert torch.equal(cells[~fin], ref[~fin]) and (~fin).any()
+    assert ((cells - ref).abs() <= 64 * 2.0 ** -24 * mag)[fin].all()
+
+
 def test_documents_without_tokens_get_minus_infinity_and_disturb_nothing(B, S, oracle_mod):
     """Empty documents violate the input contract (colbandit_validate_offsets reports them), but
     the scoring kernels must stay in bounds: such a document scores -inf and its neighbours,
