@@ -19,7 +19,8 @@
 // values fit the bins one by one, so that one pass at the speed of memory finds the clip.  A bound
 // that turns out too high or too low is noticed from the counts, and the two passes follow: such
 // inputs pay for the counting pass too (8,000,000 rows of 128: 1.07 ms with a bound that holds, 1.95 with
-// one that misses, 1.6 by the two passes alone).
+// one that misses, 1.6 by the two passes alone).  From 2^29 values on the clip is mostly guessed from a part
+// of them and confirmed by the coding pass, which reads the segment alone.
 #include "cb_launch.h"
 #include "cb_sample.h"
 
@@ -32,8 +33,10 @@ struct SelState {                 // per segment, in the workspace
     unsigned long long rank;      // remaining 1-based ascending rank inside the current prefix
     uint32_t prefix, mask;        // key bits fixed so far
     uint32_t bound;               // k_quant_tail: values below it are not counted
-    uint32_t done;                // the clip is known: the passes have nothing to do
+    uint32_t done;                // 1: the clip is known; 2: the codes are written as well; GUESSED: prefix is
+                                  // what a part of the segment says
 };
+constexpr uint32_t GUESSED = 4;
 
 template <bool BF16>
 __device__ __forceinline__ uint32_t abs_key(const void* x, int64_t i) {
@@ -171,6 +174,13 @@ constexpr int QT_BINS = 16384;                // their histogram: exponent and s
 constexpr int64_t QT_MIN_ELEMS = 1ll << 26;   // below, the sample and three launches (60 us) cost as much as
                                               // the atomics they save (1 us per million values)
 
+// From 2^29 values on a sixteenth of the segment is counted first.  bf16 values are so few that it names the clip
+// itself, but where the rank lies close to an edge of the values that round to it (at 6.8 G values of
+// unit vectors' components 0.6 % of the tail to either side, of 6 to 8).  Then one pass codes and counts, and
+// the count confirms the guess: 6.8 G values 6.58 -> 3.94 ms (20.4 GB; the pass 3.6 ms).  A guess that is wrong
+// after all costs a coding pass, none at all the sixteenth (0.17 ms).  (Below, the sixteenth's tail is too short to tell.)
+constexpr int64_t QT_GUESS_ELEMS = 1ll << 29;
+
 // Lower bound for k_quant_tail from pieces all over the segment (sample_piece): the largest histogram edge
 // with a sixth (and 40) more sampled values above it than the wanted rank calls for.
 // `above`: values of rank `rank` and higher.
@@ -219,58 +229,70 @@ __global__ __launch_bounds__(1024) void k_quant_sample(const void* x, int64_t se
     }
 }
 
-// Counts the values at or above the bound, bin = bf16 value relative to it (the last bin takes the
-// rest).  Bound by memory: 6.8 G values (13.6 GB) in 2.42 ms = 5.6 TB/s; the two histogram passes that
-// it replaces took 3.49 and 2.38 ms.
-__global__ __launch_bounds__(QH_THREADS) void k_quant_tail(const void* x, int64_t seg_elems,
-                                                           const SelState* st, unsigned long long* hist) {
-    __shared__ uint32_t lh[QH_BINS];
-    const int64_t seg = blockIdx.y;
-    const uint32_t lo = st[seg].bound >> 16;
-    for (int i = threadIdx.x; i < QH_BINS; i += QH_THREADS) lh[i] = 0;
-    __syncthreads();
-    const uint4* xv = (const uint4*)((const char*)x + seg * seg_elems * 2);
-    const int64_t nv = seg_elems / 8;
-    const int64_t stride = (int64_t)gridDim.x * QH_THREADS;
-    auto count = [&](const uint4& v) {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        unsigned hit = 0;
+// Counts those of 16 bytes' values that are at or above the bound in their bins: bf16 value relative to the
+// bound, the last bin takes the rest.  A few per mille of the values are.
+__device__ __forceinline__ void count_tail(const u32x4_t& w, uint32_t lo, uint32_t* lh) {
+    unsigned hit = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            hit |= (w[u] & 0x7fffu) >= lo ? 1u << (2 * u) : 0u;
-            hit |= ((w[u] >> 16) & 0x7fffu) >= lo ? 2u << (2 * u) : 0u;
-        }
-        while (hit) {                           // a few per mille of the values
-            const int b = __ffs((int)hit) - 1;
-            hit &= hit - 1;
-            const uint32_t p = b < 4 ? (b < 2 ? w[0] : w[1]) : (b < 6 ? w[2] : w[3]);
-            const uint32_t k = ((b & 1) ? p >> 16 : p) & 0x7fffu;
-            const uint32_t bin = k - lo < QH_BINS - 1 ? k - lo : QH_BINS - 1;
-            atomicAdd(&lh[bin], 1u);
-        }
-    };
-    int64_t i = (int64_t)blockIdx.x * QH_THREADS + threadIdx.x;
-    for (; i + 3 * stride < nv; i += 4 * stride) {
-        const uint4 a = xv[i], b = xv[i + stride], c = xv[i + 2 * stride], d = xv[i + 3 * stride];
-        count(a);
-        count(b);
-        count(c);
-        count(d);
+    for (int u = 0; u < 4; ++u) {
+        hit |= (w[u] & 0x7fffu) >= lo ? 1u << (2 * u) : 0u;
+        hit |= ((w[u] >> 16) & 0x7fffu) >= lo ? 2u << (2 * u) : 0u;
     }
-    for (; i < nv; i += stride) count(xv[i]);
+    while (hit) {
+        const int b = __ffs((int)hit) - 1;
+        hit &= hit - 1;
+        const uint32_t p = b < 4 ? (b < 2 ? w[0] : w[1]) : (b < 6 ? w[2] : w[3]);
+        const uint32_t k = ((b & 1) ? p >> 16 : p) & 0x7fffu;
+        const uint32_t bin = k - lo < QH_BINS - 1 ? k - lo : QH_BINS - 1;
+        atomicAdd(&lh[bin], 1u);
+    }
+}
+__device__ __forceinline__ void flush_tail(const uint32_t* lh, unsigned long long* gh) {
     __syncthreads();
-    unsigned long long* gh = hist + seg * QH_BINS;
     for (int j = threadIdx.x; j < QH_BINS; j += QH_THREADS)
         if (lh[j]) atomicAdd(&gh[j], (unsigned long long)lh[j]);
 }
 
-// one wavefront per segment: the value with `above` counted values at or above it, unless too few were
-// counted or it lies among the values that share the last bin; clears the bins
-__global__ __launch_bounds__(64) void k_quant_tail_pick(SelState* st, unsigned long long* hist,
-                                                        unsigned long long above) {
-    const int64_t seg = blockIdx.x;
-    unsigned long long* gh = hist + seg * QH_BINS;
-    const int lane = threadIdx.x;
+// Counts the values at or above the bound.  Bound by memory: 6.8 G values (13.6 GB) in 2.42 ms = 5.6 TB/s;
+// the two histogram passes that it replaces took 3.49 and 2.38 ms.  part: of every 16 runs of 4 KB only one, at
+// a mixed place (sample_piece).
+constexpr int QT_RUN = 256, QT_PART = 16;
+__global__ __launch_bounds__(QH_THREADS) void k_quant_tail(const void* x, int64_t seg_elems,
+                                                           const SelState* st, unsigned long long* hist, int part) {
+    __shared__ uint32_t lh[QH_BINS];
+    static_assert(QT_RUN == QH_THREADS, "a workgroup takes a run at a time");
+    const int64_t seg = blockIdx.y;
+    if (st[seg].done) return;
+    const uint32_t lo = st[seg].bound >> 16;
+    for (int i = threadIdx.x; i < QH_BINS; i += QH_THREADS) lh[i] = 0;
+    __syncthreads();
+    const u32x4_t* xv = (const u32x4_t*)((const char*)x + seg * seg_elems * 2);
+    const int64_t nv = seg_elems / 8;
+    if (part) {
+        const int64_t groups = nv / (QT_RUN * QT_PART);
+        for (int64_t g = blockIdx.x; g < groups; g += gridDim.x)
+            count_tail(xv[sample_piece((uint32_t)g, QT_PART) * QT_RUN + threadIdx.x], lo, lh);
+    } else {
+        const int64_t stride = (int64_t)gridDim.x * QH_THREADS;
+        int64_t i = (int64_t)blockIdx.x * QH_THREADS + threadIdx.x;
+        for (; i + 3 * stride < nv; i += 4 * stride) {
+            const u32x4_t a = xv[i], b = xv[i + stride], c = xv[i + 2 * stride], d = xv[i + 3 * stride];
+            count_tail(a, lo, lh);
+            count_tail(b, lo, lh);
+            count_tail(c, lo, lh);
+            count_tail(d, lo, lh);
+        }
+        for (; i < nv; i += stride) count_tail(xv[i], lo, lh);
+    }
+    flush_tail(lh, hist + seg * QH_BINS);
+}
+
+// What the counts of a wavefront's segment say of the value with `above` counted values at or above it: its
+// bin and the values counted above that bin and from it on.  False where too few were counted or it lies
+// among the values that share the last bin.
+__device__ __forceinline__ bool tail_bin(const unsigned long long* gh, unsigned long long above, int& bin,
+                                         unsigned long long& higher, unsigned long long& from) {
+    const int lane = threadIdx.x & 63;
     constexpr int PER = QH_BINS / 64;
     const int hi = QH_BINS - 1 - lane * PER;
     unsigned long long local = 0;
@@ -281,21 +303,60 @@ __global__ __launch_bounds__(64) void k_quant_tail_pick(SelState* st, unsigned l
         const unsigned long long t = __shfl_up(incl, o);
         if (lane >= o) incl += t;
     }
-    const unsigned long long excl = incl - local;
-    if (excl < above && above <= incl) {
-        unsigned long long run = excl;
-        int j = 0;
-        for (; j < PER - 1; ++j) {
-            run += gh[hi - j];
-            if (run >= above) break;
+    unsigned long long run = incl - local, next = run;
+    const bool mine = run < above && above <= incl;
+    int j = 0;
+    if (mine)
+        for (;; ++j) {
+            next = run + gh[hi - j];
+            if (next >= above || j == PER - 1) break;
+            run = next;
         }
-        if (hi - j < QH_BINS - 1) {
-            st[seg].prefix = ((st[seg].bound >> 16) + (uint32_t)(hi - j)) << 16;
-            st[seg].done = 1;
-        }
-    }
+    const unsigned long long m = __ballot(mine);
+    if (m == 0ull) return false;
+    const int src = __ffsll((long long)m) - 1;
+    bin = __shfl(hi - j, src);
+    higher = __shfl(run, src);
+    from = __shfl(next, src);
+    return bin < QH_BINS - 1;
+}
+__device__ __forceinline__ void clear_bins(unsigned long long* gh) {
     __syncthreads();
-    for (int i = lane; i < QH_BINS; i += 64) gh[i] = 0ull;
+    for (int i = threadIdx.x; i < QH_BINS; i += 64) gh[i] = 0ull;
+}
+
+// After the count of a part: its value of that rank, if the counts put the rank three deviations (of their
+// square root) or more inside the values that round to it.
+__global__ __launch_bounds__(64) void k_quant_guess(SelState* st, unsigned long long* hist, unsigned long long above) {
+    const int64_t seg = blockIdx.x;
+    unsigned long long* gh = hist + seg * QH_BINS;
+    int bin;
+    unsigned long long higher, from;
+    const bool found = tail_bin(gh, above, bin, higher, from);
+    const double margin = 3.0 * sqrt((double)above);
+    if (threadIdx.x == 0 && found && (double)(above - higher) >= margin && (double)(from - above) >= margin) {
+        st[seg].prefix = ((st[seg].bound >> 16) + (uint32_t)bin) << 16;
+        st[seg].done = GUESSED;
+    }
+    clear_bins(gh);
+}
+
+// After the count of the whole segment: its value of that rank.  A guess that it confirms has its codes.
+__global__ __launch_bounds__(64) void k_quant_tail_pick(SelState* st, unsigned long long* hist,
+                                                        unsigned long long above, uint32_t when) {
+    const int64_t seg = blockIdx.x;
+    unsigned long long* gh = hist + seg * QH_BINS;
+    const SelState s = st[seg];
+    if (s.done != when) return;
+    int bin;
+    unsigned long long higher, from;
+    const bool found = tail_bin(gh, above, bin, higher, from);
+    if (threadIdx.x == 0) {
+        const uint32_t clip = found ? ((s.bound >> 16) + (uint32_t)bin) << 16 : 0u;
+        st[seg].prefix = clip;
+        st[seg].done = !found ? 0u : s.done == GUESSED && clip == s.prefix ? 2u : 1u;
+    }
+    clear_bins(gh);
 }
 
 __device__ __forceinline__ int code_of(float v, float inv) {
@@ -308,13 +369,20 @@ __device__ __forceinline__ int code_of(float v, float inv) {
 // for itself: a launch less where the workgroups are few.
 // STREAM: a segment larger than the caches, whose values are not read again nor the codes by this
 // call: neither should stay in L2 (6.8 G values: 3.80 -> 3.60 ms).
-template <bool BF16, bool STREAM>
+// COUNT: with the guessed clip, and counts the tail on the way.
+template <bool BF16, bool STREAM, bool COUNT = false>
 __global__ __launch_bounds__(QH_THREADS) void k_quant_codes(const void* x, int64_t seg_elems,
-                                                            const SelState* st, const unsigned long long* hist,
+                                                            const SelState* st, unsigned long long* hist,
                                                             int nbins, int8_t* out, float* scales, int vec) {
     constexpr int VEC = QVec<BF16>::N;
     __shared__ uint32_t key;
+    __shared__ uint32_t lh[COUNT ? QH_BINS : 1];
     const int64_t seg = blockIdx.y;
+    const uint32_t done = st[seg].done;
+    if (COUNT ? done != GUESSED : done == 2u) return;
+    const uint32_t lo = COUNT ? st[seg].bound >> 16 : 0u;
+    if constexpr (COUNT)
+        for (int i = threadIdx.x; i < QH_BINS; i += QH_THREADS) lh[i] = 0;
     if (threadIdx.x < 64) {
         SelState s = st[seg];
         if (nbins > 0 && !s.done) s = pick_bin(s, hist + seg * QH_BINS, BF16 ? 10 : 0, nbins);
@@ -333,6 +401,7 @@ __global__ __launch_bounds__(QH_THREADS) void k_quant_codes(const void* x, int64
             u32x4_t w;
             if constexpr (STREAM) w = __builtin_nontemporal_load((const u32x4_t*)xv + i);
             else w = ((const u32x4_t*)xv)[i];
+            if constexpr (COUNT) count_tail(w, lo, lh);
             uint32_t packed[VEC / 4];
 #pragma unroll
             for (int j = 0; j < VEC / 4; ++j) packed[j] = 0;
@@ -352,6 +421,7 @@ __global__ __launch_bounds__(QH_THREADS) void k_quant_codes(const void* x, int64
                 else ((uint32_t*)(out + base))[i] = packed[0];
             }
         }
+        if constexpr (COUNT) flush_tail(lh, hist + seg * QH_BINS);
         return;
     }
     for (int64_t i = (int64_t)blockIdx.x * QH_THREADS + threadIdx.x; i < seg_elems;
@@ -472,10 +542,23 @@ hipError_t launch_quantize_i8(const void* x, int dt, int64_t n_segments, int64_t
     const int npass = bf ? 2 : 3;
     const unsigned long long above = (unsigned long long)seg_elems - (rank < 1 ? 1 : rank) + 1ull;
     if (bf && vec && seg_elems >= QT_MIN_ELEMS && above <= (unsigned long long)seg_elems / 64) {
-        k_quant_sample<<<(unsigned)n_segments, 1024, 0, st>>>(x, seg_elems, state, above);
-        const dim3 tail((unsigned)(bx < 2048 ? bx : 2048), (unsigned)n_segments);   // eight per CU
-        k_quant_tail<<<tail, QH_THREADS, 0, st>>>(x, seg_elems, state, hist);
-        k_quant_tail_pick<<<(unsigned)n_segments, 64, 0, st>>>(state, hist, above);
+        const unsigned nseg = (unsigned)n_segments;
+        k_quant_sample<<<nseg, 1024, 0, st>>>(x, seg_elems, state, above);
+        const dim3 tail((unsigned)(bx < 2048 ? bx : 2048), nseg);   // eight per CU
+        if (seg_elems >= QT_GUESS_ELEMS) {
+            const int64_t counted = seg_elems / 8 / (QT_RUN * QT_PART) * QT_RUN * 8;
+            const unsigned long long of_part = (unsigned long long)((double)above * ((double)counted / (double)seg_elems) + 0.5);
+            k_quant_tail<<<tail, QH_THREADS, 0, st>>>(x, seg_elems, state, hist, 1);
+            k_quant_guess<<<nseg, 64, 0, st>>>(state, hist, of_part < 1 ? 1 : of_part);
+            // 48 loads of 16 bytes a thread, or more for up to 32,768 workgroups (us: 6.8 G values 4,300 with 8,192,
+            // 4,040 with 16,384, 3,940 with 32,768, 4,005 with 65,536; 1.3 G 980, 920, 965, 1,590)
+            const int64_t blocks = seg_elems / (8 * QH_THREADS * 48);
+            const dim3 both((unsigned)(blocks < 32768 ? blocks : 32768), nseg);
+            k_quant_codes<true, true, true><<<both, QH_THREADS, 0, st>>>(x, seg_elems, state, hist, 0, codes, scales, vec);
+            k_quant_tail_pick<<<nseg, 64, 0, st>>>(state, hist, above, GUESSED);
+        }
+        k_quant_tail<<<tail, QH_THREADS, 0, st>>>(x, seg_elems, state, hist, 0);
+        k_quant_tail_pick<<<nseg, 64, 0, st>>>(state, hist, above, 0u);
     }
     // 16 KB of bins read by each workgroup of the coding pass against a launch: 4 M values 39.7 -> 38.3 us
     const bool pick_last = bx * n_segments <= 1024;

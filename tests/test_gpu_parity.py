@@ -1046,6 +1046,49 @@ def test_quantize_long_bf16_segment_by_its_tail(B, kind, permille):
         assert torch.equal(codes[lo:lo + (1 << 18)], want)
 
 
+@pytest.mark.parametrize("kind,done", [("normal", 2), ("edge", 1), ("biased", 1), ("constant", 2)])
+def test_quantize_guesses_the_clip_of_a_very_long_segment(B, kind, done):
+    """2^29 values and more: a sixteenth of the runs of 4 KB names the clip and one pass codes and counts.  The state
+    at the head of the workspace says whether that pass was enough (2) or the clip had to be found first (1): a
+    rank at the edge of equal values is not guessed, runs unlike the rest give a wrong guess.  Codes are those
+    of the exact clip either way."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    rows, d = (1 << 22) + 37, 128
+    # (times 0.86, and times 0.8 again, the clip lies well inside the values that round to it)
+    x = (torch.randn((rows, d), generator=g, device="cuda") * 0.86).to(torch.bfloat16)
+    n = x.numel()
+    drop = n - (n * 999 + 999) // 1000                  # values above the clip
+    flat = x.view(-1)
+    if kind == "constant":
+        x.fill_(-0.75)
+    elif kind == "edge":
+        x.clamp_(-1, 1)
+        at = torch.randint(0, n, (drop + 1 + n // 10000,), generator=g, device="cuda").unique()
+        flat[at[torch.randperm(at.numel(), generator=g, device="cuda")[:drop + 1]]] = 2.0
+    elif kind == "biased":
+        i = np.arange(n // 8 // (256 * 16), dtype=np.uint32)
+        h = i * np.uint32(0x9E3779B1)
+        h = (h ^ (h >> np.uint32(15))) * np.uint32(0x85EBCA77)
+        h ^= h >> np.uint32(13)
+        run = i.astype(np.int64) * 16 + ((h.astype(np.uint64) * np.uint64(16)) >> np.uint64(32)).astype(np.int64)
+        flat[:n // 2048 * 2048].view(-1, 2048)[torch.from_numpy(run).cuda()] *= 0.8
+    codes = torch.empty(x.shape, dtype=torch.int8, device="cuda")
+    scales = torch.empty(1, device="cuda")
+    ws = torch.zeros(B.lib().colbandit_quantize_workspace_bytes(1), dtype=torch.uint8, device="cuda")
+    rc = B.lib().colbandit_quantize_i8(x.data_ptr(), 1, 1, rows, d, 999, codes.data_ptr(), scales.data_ptr(),
+                                       ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and ws[:24].view(torch.int32)[5].item() == done
+    counts = sum(torch.bincount((p.view(torch.int16) & 0x7fff).to(torch.int32), minlength=32768) for p in flat.split(1 << 27))
+    key = int(torch.searchsorted(torch.cumsum(counts, 0), torch.tensor([n - drop], device="cuda"))[0])
+    clip = torch.tensor([key], dtype=torch.int16).view(torch.bfloat16).float().numpy()[0]
+    assert scales.cpu().numpy()[0] == clip / np.float32(127)
+    inv = float(np.float32(127) / clip)
+    for lo in range(0, rows, 1 << 19):
+        want = torch.clamp(torch.round(x[lo:lo + (1 << 19)].float() * inv), -127, 127).to(torch.int8)
+        assert torch.equal(codes[lo:lo + (1 << 19)], want)
+
+
 @pytest.mark.parametrize("nq,T,d", [(1, 32, 128), (5, 32, 128), (20, 24, 128), (3, 40, 128), (2, 100, 128),
                                     (4, 32, 64), (70, 16, 64)])
 def test_coarse_maxsim_cells_are_the_integer_maxima(B, S, oracle_mod, nq, T, d):
