@@ -270,7 +270,13 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
         if (lists_fit) passes = R - r + 1;
     }
     if (!lists_fit && (double)P.nq * (double)P.N * t_pair < passes * (t_pass + t_round)) return ~0ull;
-    const double thr = (passes * t_pass + (lists_fit ? (passes + R - r) * t_round : 0.0)) / t_pair;
+    const double worth = passes * t_pass + (lists_fit ? (passes + R - r) * t_round : 0.0);
+    // Queries that share a corpus of the last-level cache's size gather faster, and where lists fit and even full
+    // ones cost no more than what the gather saves, none of the later rounds is launched (7 queries x 6,007
+    // documents, d = 64, T = 21: 144 -> 109 us; 16 x 6,000 164 -> 107, with alpha 1.0, where they stay full, 339 -> 294).
+    if (lists_fit && (double)P.total * row_bytes <= 256e6 &&
+        (double)P.nq * (double)P.total * row_bytes / 7.5e12 <= worth) return ~0ull;
+    const double thr = worth / t_pair;
     return thr >= 1.8e19 ? ~0ull - 1 : (unsigned long long)thr;
 }
 
