@@ -524,7 +524,7 @@ int colbandit_doc_uniform(const void* Q, int n_queries, int T, int d, colbandit_
     }
     if (e == hipSuccess)
         e = launch_uniform_score(cells, n_queries, N, T, cells_per_doc, seed, out, masks, st);
-    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, false, out, K, topk_ids, topk_scores, st);
     return e == hipSuccess ? COLBANDIT_OK : COLBANDIT_ERR_HIP;
 }
 
@@ -609,7 +609,7 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
         e = hipMemcpyAsync(labels, lab, 4 * (size_t)n_queries * T, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess && centroids)
         e = hipMemcpyAsync(centroids, Cz, elem * (size_t)n_queries * T * d, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, false, out, K, topk_ids, topk_scores, st);
     return e == hipSuccess ? COLBANDIT_OK : COLBANDIT_ERR_HIP;
 }
 
@@ -654,7 +654,7 @@ int colbandit_full_maxsim(const void* Q, int n_queries, int T, int d, colbandit_
         if (e == hipSuccess) e = launch_dense_score(P, W, n_chunks, out, cells, nullptr, st);
     }
     mark();
-    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, out, K, topk_ids, topk_scores, st);
+    if (e == hipSuccess && K > 0) e = launch_topk(P, W, false, false, false, out, K, topk_ids, topk_scores, st);
     mark();
     if (phase_ms) {
         phase_ms[0] = phase_ms[1] = 0.f;
@@ -781,7 +781,8 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     // the smallest calls visit every document once: round 1 caches all cells of all documents
     const bool cache_all = loop && !dense && !force_gather && later_rounds == 0 && small_call(P) &&
                            N <= (int64_t)W.cache_cap;
-    if (e == hipSuccess) e = launch_init(P, W, kn, R, seed, user_pi, tr, n_chunks, st);
+    if (e == hipSuccess) e = cache_all ? launch_cache_all(P, W, kn, R, seed, user_pi, tr, co, st)
+                                       : launch_init(P, W, kn, R, seed, user_pi, tr, n_chunks, st);
     float kappa[COLBANDIT_MAX_ROUNDS + 1] = {};      // radius per unit sigma_hat of each round
     for (int r = 1; r <= R; ++r) {
         const double kap = colbandit_radius_prefactor(alpha_ef, delta, T, N, r * kn.B < T ? r * kn.B : T);
@@ -801,7 +802,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         rr.dense_thr = ~0ull;
         if (r == 1 && dense) {
             e = launch_dense_reveal(P, W, n_chunks, rr, G, co, st);
-        } else {
+        } else if (!cache_all) {
             if (r >= 2 && dense && later_rounds != 2) {
                 rr.dense_thr = later_rounds == 1 ? 0ull
                                                  : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap);
@@ -809,22 +810,23 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
             }
             round_thr[r] = rr.dense_thr;
             e = launch_dense_reveal_later(P, W, n_chunks, rr, G, co, st);
-            if (e == hipSuccess) e = launch_gather_round(P, W, rr, cache_all, co, st);
+            if (e == hipSuccess) e = launch_gather_round(P, W, rr, co, st);
         }
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
-        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, tr, st);
+        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, tr,
+                                                     cache_all && !co ? topk_ids : nullptr, topk_scores, st);
         pt.mark(PH_SELECT);
         // A gathered round in which every list fits the cell cache is the last one to launch:
         // k_select_prune runs all rounds of a cached query.
         if (cache_all || (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap)) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
-    // (after cache_all every query's survivors have them: no launch, 4 us of a call of 50).  Where no
+    // (after cache_all every query's survivors have them, and k_select_prune has gone on to the top-K).  Where no
     // round ran, all documents survive: shared by wavefronts only if they are few (296 documents of 18
     // tokens x 74 queries 86 -> 44 us a call)
     if (e == hipSuccess && !loop) e = launch_gather_all(P, W, W.rescored, nullptr, st);    // no round: all documents
-    else if (e == hipSuccess && !(cache_all && !co)) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, st);
-    if (e == hipSuccess) e = launch_topk(P, W, true, !co, W.rescored, K, topk_ids, topk_scores, st);
+    else if (e == hipSuccess && !(cache_all && !co)) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, cache_all, st);
+    if (e == hipSuccess && !(cache_all && !co)) e = launch_topk(P, W, true, !co, cache_all, W.rescored, K, topk_ids, topk_scores, st);
     pt.mark(PH_RESCORE);
     if (e != hipSuccess) {
         pt.destroy();

@@ -43,14 +43,9 @@ struct InitArgs {
 // only the exchanges run one after the other, between lanes' registers.  One thread per query drawing
 // them in turn took 14 us and the chunk table of the corpus pass 5 in a launch of its own, both together
 // take 7 here (T = 32).
-__global__ __launch_bounds__(256) void k_init(InitArgs A) {
-    if ((int)blockIdx.x >= A.init_blocks) {
-        chunk_docs((int64_t)((int)blockIdx.x - A.init_blocks) * 256 + threadIdx.x, A.off, A.N, A.chunk_tokens,
-                   A.n_chunks, A.chunk_doc);
-        return;
-    }
+__device__ __forceinline__ void init_queries(const InitArgs& A, int block) {
     const int lane = threadIdx.x & 63;
-    const int q = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int q = block * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (q == 0)                                     // pair counts, then their token counts
         for (int r = lane; r < 2 * (A.R + 2); r += 64) A.pairs[r] = 0ull;
     if (q >= A.nq) return;
@@ -101,6 +96,12 @@ __global__ __launch_bounds__(256) void k_init(InitArgs A) {
     if (lane < T) p[lane] = p0;
     if (lane + 64 < T) p[lane + 64] = p1;
 }
+__global__ __launch_bounds__(256) void k_init(InitArgs A) {
+    if ((int)blockIdx.x >= A.init_blocks)
+        chunk_docs((int64_t)((int)blockIdx.x - A.init_blocks) * 256 + threadIdx.x, A.off, A.N, A.chunk_tokens,
+                   A.n_chunks, A.chunk_doc);
+    else init_queries(A, (int)blockIdx.x);
+}
 
 __global__ void k_fill_f32(float* p, size_t n, float v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -113,8 +114,8 @@ __global__ void k_fill_u8(uint8_t* p, size_t n, uint8_t v) {
         p[i] = v;
 }
 
-hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
-                       const int32_t* user_pi, const Trace& tr, int n_chunks, hipStream_t st) {
+static InitArgs init_args(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
+                          const int32_t* user_pi, const Trace& tr, int n_chunks) {
     InitArgs A{};
     A.ctl = W.ctl;
     A.pi = W.pi;
@@ -135,15 +136,23 @@ hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, 
     A.chunk_tokens = W.chunk_tokens;
     A.n_chunks = n_chunks;
     A.chunk_doc = W.chunk_doc;
+    return A;
+}
+static void fill_trace(const Problem& P, int R, const Trace& tr, hipStream_t st) {
+    if (!tr.lcb) return;
+    const size_t n = (size_t)R * P.nq * P.N;
+    const int g = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
+    k_fill_f32<<<g, 256, 0, st>>>(tr.lcb, n, __builtin_nanf(""));
+    k_fill_f32<<<g, 256, 0, st>>>(tr.ucb, n, __builtin_nanf(""));
+    k_fill_u8<<<g, 256, 0, st>>>(tr.alive, n, 0);
+}
+
+hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
+                       const int32_t* user_pi, const Trace& tr, int n_chunks, hipStream_t st) {
+    const InitArgs A = init_args(P, W, kn, R, seed, user_pi, tr, n_chunks);
     const unsigned chunk_blocks = n_chunks > 0 ? (unsigned)((P.N + 1 + 255) / 256) : 0u;
     k_init<<<(unsigned)A.init_blocks + chunk_blocks, 256, 0, st>>>(A);
-    if (tr.lcb) {
-        const size_t n = (size_t)R * P.nq * P.N;
-        const int g = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-        k_fill_f32<<<g, 256, 0, st>>>(tr.lcb, n, __builtin_nanf(""));
-        k_fill_f32<<<g, 256, 0, st>>>(tr.ucb, n, __builtin_nanf(""));
-        k_fill_u8<<<g, 256, 0, st>>>(tr.alive, n, 0);
-    }
+    fill_trace(P, R, tr, st);
     return hipGetLastError();
 }
 
@@ -177,7 +186,8 @@ struct GatherArgs {
     const unsigned long long* work;      // its queries (work_item)
     unsigned long long dense_thr;        // ~0: this round cannot be a corpus pass
     // cell cache
-    int cache_all;            // round 1 caches the cells of all N documents (slot = document)
+    int cache_all;            // caches the cells of all N documents (slot = document); nothing else
+    int init_blocks;          // ... and the last workgroups of the launch set the queries up
     int cache_cap, TP;
     int32_t* cid;
     float2* cstat;
@@ -319,15 +329,21 @@ constexpr int64_t ALL_DOCS = 64;
 //                  list entry into a cache slot.  A gathered reveal is bound by the bytes of the
 //                  document, not by the cells computed from them, so a document is visited once
 //                  and the later rounds (and the rescore) read its cells back; the order in which
-//                  cells are REVEALED to the bounds is unchanged.  cache_all: so does round 1 of the
-//                  smallest calls, which then needs no second visit and no launch of a later round (1
-//                  query x 1,000 documents of 48 fp32 tokens: 63 -> 55 us a call).
+//                  cells are REVEALED to the bounds is unchanged.  cache_all: the smallest calls visit all
+//                  documents so before round 1, which takes its batch from the cells as well; the
+//                  launch also sets the queries up, which nothing in it needs, and two launches make
+//                  the call (1 query x 1,000 documents of 48 fp32 tokens: 45 -> 39 us).
 template <typename Tag, int D, int TQ>
-__global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gather_round(GatherArgs A) {
+__global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gather_round(GatherArgs A, InitArgs I) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
     __shared__ int ex[EX_FLOATS];
+    const int n_blocks = (int)gridDim.x - A.init_blocks;
+    if ((int)blockIdx.x >= n_blocks) {
+        init_queries(I, (int)blockIdx.x - n_blocks);
+        return;
+    }
     if (A.dense_thr != ~0ull && dense_round(A.pairs_r, A.dense_thr)) return;   // the corpus pass serves it
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -337,9 +353,9 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
     const unsigned long long head = A.pairs_r ? *A.pairs_r : (unsigned long long)A.nq * (unsigned long long)A.N;
     const long long total = (long long)(A.pairs_r ? pair_count(head) : head);
     const int n_work = A.pairs_r ? (int)work_count(head) : A.nq;
-    const bool coop = total <= (long long)gridDim.x;
+    const bool coop = total <= (long long)n_blocks;
     const int parts = coop ? 4 : 1;
-    const long long workers = coop ? gridDim.x : 4ll * gridDim.x;
+    const long long workers = coop ? n_blocks : 4ll * n_blocks;
     int me = coop ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
     if (me >= total) return;                        // in shared mode the same for the whole workgroup
     long long per = 1;
@@ -401,9 +417,13 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
             k_end = (int)(d0 + (x_end - first < block_docs ? x_end - first : block_docs));
         }
         x += k_end - k;
-        const QueryCtl c = A.ctl[q];
-        const int count = c.count;
-        int32_t* list = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+        int count = 0;
+        int32_t* list = nullptr;
+        if (!A.cache_all) {
+            const QueryCtl c = A.ctl[q];
+            count = c.count;
+            if (!c.implicit) list = (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+        }
         const float scale = A.qscale ? A.qscale[q] * A.dscale[0] : 1.f;
         if (!A.cache_all && (!list || count > A.cache_cap)) {
             F bq[1];
@@ -433,7 +453,7 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
             load_query<F, ROWB, TQ>(A, q, col, kg, bq);
             const int row = lane >> 4;
             // this round's batch: slot s (lane s of row 0) fetches cell pi[lo+s] from its owner
-            const int t = A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
+            const int t = A.cache_all ? 0 : A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
             const int tile = t >> 4;
             const int src = P::row_of_tile(tile) * 16 + (t & 15);
             for (; k < k_end; ++k) {
@@ -452,6 +472,7 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
 #pragma unroll
                 for (int j = 0; j < P::NW; ++j)
                     if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
+                if (A.cache_all) continue;
                 float v = __shfl(w[0], src);
                 if constexpr (P::NW > 1) {
                     const float v1 = __shfl(w[1], src);
@@ -486,7 +507,7 @@ __global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
     const QueryCtl c = A.ctl[q];
     if (c.mode != 0 && !A.score_slots) return;
     if ((int)blockIdx.x >= c.count) return;
-    const int32_t* slot_ids = c.mode != 0 ? A.cid + (size_t)q * A.cache_cap : nullptr;
+    const int32_t* slot_ids = c.mode != 0 && !A.cache_all ? A.cid + (size_t)q * A.cache_cap : nullptr;
     const int32_t* list = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -558,9 +579,9 @@ __global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
 enum { GM_ROUND = 0, GM_SURVIVORS = 1, GM_ALL = 2 };
 
 template <typename Tag, int D, int TQ>
-static hipError_t gather_mode(const GatherArgs& A, int mode, dim3 grid, hipStream_t st) {
+static hipError_t gather_mode(const GatherArgs& A, const InitArgs& I, int mode, dim3 grid, hipStream_t st) {
     const dim3 block(256);
-    if (mode == GM_ROUND) k_gather_round<Tag, D, TQ><<<grid, block, 0, st>>>(A);
+    if (mode == GM_ROUND) k_gather_round<Tag, D, TQ><<<grid, block, 0, st>>>(A, I);
     else if constexpr (!__is_same(Tag, i8_tag)) {   // scores come from the stored embeddings
         if (mode == GM_SURVIVORS) k_gather_survivors<Tag, D, TQ><<<grid, block, 0, st>>>(A);
         else k_gather_all<Tag, D, TQ><<<grid, block, 0, st>>>(A);
@@ -569,29 +590,29 @@ static hipError_t gather_mode(const GatherArgs& A, int mode, dim3 grid, hipStrea
 }
 
 template <typename Tag, int D>
-static hipError_t gather_tq(const GatherArgs& A, int mode, dim3 grid, hipStream_t st) {
+static hipError_t gather_tq(const GatherArgs& A, const InitArgs& I, int mode, dim3 grid, hipStream_t st) {
     const int tq = (A.T + 15) / 16;
-    if (tq <= 1) return gather_mode<Tag, D, 1>(A, mode, grid, st);
-    if (tq <= 2) return gather_mode<Tag, D, 2>(A, mode, grid, st);
-    if (tq <= 4) return gather_mode<Tag, D, 4>(A, mode, grid, st);
-    if constexpr (Tag::wide) return gather_mode<Tag, D, 8>(A, mode, grid, st);
+    if (tq <= 1) return gather_mode<Tag, D, 1>(A, I, mode, grid, st);
+    if (tq <= 2) return gather_mode<Tag, D, 2>(A, I, mode, grid, st);
+    if (tq <= 4) return gather_mode<Tag, D, 4>(A, I, mode, grid, st);
+    if constexpr (Tag::wide) return gather_mode<Tag, D, 8>(A, I, mode, grid, st);
     return hipErrorInvalidValue;
 }
 
 template <typename Tag>
-static hipError_t gather_by_d(const GatherArgs& A, int mode, int d, dim3 grid, hipStream_t st) {
-    if (d == 128) return gather_tq<Tag, 128>(A, mode, grid, st);
-    if (d == 64) return gather_tq<Tag, 64>(A, mode, grid, st);
+static hipError_t gather_by_d(const GatherArgs& A, const InitArgs& I, int mode, int d, dim3 grid, hipStream_t st) {
+    if (d == 128) return gather_tq<Tag, 128>(A, I, mode, grid, st);
+    if (d == 64) return gather_tq<Tag, 64>(A, I, mode, grid, st);
     // no codes in these widths: the int8 MFMA contracts 64 elements at a time
     if constexpr (!__is_same(Tag, i8_tag)) {
-        if (d == 96) return gather_tq<Tag, 96>(A, mode, grid, st);
-        if (d == 32) return gather_tq<Tag, 32>(A, mode, grid, st);
+        if (d == 96) return gather_tq<Tag, 96>(A, I, mode, grid, st);
+        if (d == 32) return gather_tq<Tag, 32>(A, I, mode, grid, st);
     }
     return hipErrorInvalidValue;
 }
 
 // co != nullptr: the reveal reads the int8 codes instead of the stored embeddings
-static hipError_t gather_any(GatherArgs& A, int mode, const Problem& P, const Work& W, dim3 grid,
+static hipError_t gather_any(GatherArgs& A, const InitArgs& I, int mode, const Problem& P, const Work& W, dim3 grid,
                              const Coarse* co, hipStream_t st) {
     A.Q = P.Q;
     A.docs = P.docs;
@@ -614,10 +635,10 @@ static hipError_t gather_any(GatherArgs& A, int mode, const Problem& P, const Wo
         A.docs = co->docs8;
         A.qscale = co->qscale;
         A.dscale = co->dscale;
-        return gather_by_d<i8_tag>(A, mode, P.d, grid, st);
+        return gather_by_d<i8_tag>(A, I, mode, P.d, grid, st);
     }
-    return P.dt == DT_BF16 ? gather_by_d<bf16_tag>(A, mode, P.d, grid, st)
-                           : gather_by_d<f32_tag>(A, mode, P.d, grid, st);
+    return P.dt == DT_BF16 ? gather_by_d<bf16_tag>(A, I, mode, P.d, grid, st)
+                           : gather_by_d<f32_tag>(A, I, mode, P.d, grid, st);
 }
 
 // Workgroups of a round's gather: enough that the hardware's dispatch evens out documents of
@@ -625,11 +646,9 @@ static hipError_t gather_any(GatherArgs& A, int mode, const Problem& P, const Wo
 // without pairs ends at once (8,192: 4.7 us; 256 per query at 128 queries: 9 us).
 constexpr long long GATHER_BLOCKS = 8192;
 
-hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, bool cache_all,
-                               const Coarse* co, hipStream_t st) {
+hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, const Coarse* co, hipStream_t st) {
     GatherArgs A{};
     A.ctl = W.ctl;
-    A.cache_all = cache_all ? 1 : 0;
     A.lo = rr.lo;
     A.nb = rr.nb;
     A.n_prev = rr.n_prev;
@@ -638,24 +657,37 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
     A.pairs_r = rr.r == 1 ? nullptr : W.pairs + rr.r;
     A.work = W.work;
     A.dense_thr = rr.dense_thr;
+    const long long blocks = (long long)P.nq * P.N;
+    return gather_any(A, InitArgs{}, GM_ROUND, P, W, dim3((unsigned)(blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS)), co, st);
+}
+
+hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
+                            const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st) {
+    GatherArgs A{};
+    A.cache_all = 1;
+    A.dense_thr = ~0ull;
+    const InitArgs I = init_args(P, W, kn, R, seed, user_pi, tr, 0);
+    A.init_blocks = I.init_blocks;
     long long blocks = (long long)P.nq * P.N;
-    // The smallest calls' whole matrix: a document shared by four wavefronts loads the query four times.
-    // From some three pairs a CU a wavefront per pair is faster (us a call: 1,000 pairs of 48 fp32
-    // tokens 112 -> 104, 2,000 of bf16 56 -> 50), below shared documents are (250 pairs 35 and 38, 250
-    // of 500 tokens 38 and 51).
-    if (cache_all && blocks >= 768) blocks = (blocks + 3) / 4;
-    return gather_any(A, GM_ROUND, P, W, dim3((unsigned)(blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS)), co, st);
+    // A document shared by four wavefronts loads the query four times.  From some three pairs a CU a
+    // wavefront per pair is faster (us a call: 1,000 pairs of 48 fp32 tokens 112 -> 104, 2,000 of bf16 56 -> 50),
+    // below shared documents are (250 pairs 35 and 38, 250 of 500 tokens 38 and 51).
+    if (blocks >= 768) blocks = (blocks + 3) / 4;
+    blocks = blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS;
+    fill_trace(P, R, tr, st);
+    return gather_any(A, I, GM_ROUND, P, W, dim3((unsigned)(blocks + I.init_blocks)), co, st);
 }
 
 hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,
-                                   bool score_slots, hipStream_t st) {
+                                   bool score_slots, bool cache_all, hipStream_t st) {
     GatherArgs A{};
     A.ctl = W.ctl;
     A.out = out;
     A.score_slots = score_slots ? 1 : 0;
+    A.cache_all = cache_all ? 1 : 0;
     // most queries end with at most K + M survivors
     const int64_t want = (int64_t)kn.K + kn.M < 256 ? (int64_t)kn.K + kn.M : 256;
-    return gather_any(A, GM_SURVIVORS, P, W, dim3((unsigned)(P.N < want ? P.N : want), P.nq), nullptr, st);
+    return gather_any(A, InitArgs{}, GM_SURVIVORS, P, W, dim3((unsigned)(P.N < want ? P.N : want), P.nq), nullptr, st);
 }
 
 // A workgroup per pair where wavefronts would be few, or where their last turn (1,024 SIMDs) would
@@ -676,7 +708,7 @@ hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float*
     // at least four workgroups a CU over all queries (one fp32 query, 10.6 M tokens: d = 32 618 -> 284 us,
     // d = 128 1,196 -> 989; more than four change nothing)
     const int64_t most = P.nq >= 4 ? 256 : 1024 / P.nq;
-    return gather_any(A, GM_ALL, P, W, dim3((unsigned)(gx < most ? gx : most), P.nq), nullptr, st);
+    return gather_any(A, InitArgs{}, GM_ALL, P, W, dim3((unsigned)(gx < most ? gx : most), P.nq), nullptr, st);
 }
 
 // Exact score of a survivor from its cached cells: the T cells of a slot are laid out as the
@@ -1097,7 +1129,12 @@ struct SelArgs {
     float* tr_ucb;
     uint8_t* tr_alive;
     int32_t* seg_cnt;                    // [nq][SEG_MAX]: candidates per segment (k_select_segments)
-    float kappa[COLBANDIT_MAX_ROUNDS + 1];   // radius per unit sigma_hat of each round
+    float kappa;                         // radius per unit sigma_hat of the round
+};
+// ... of every round.  A parameter of its own: indexed at run time, it would keep the whole of SelArgs, which
+// the compiler otherwise takes apart, in scratch memory.
+struct Kappas {
+    float of[COLBANDIT_MAX_ROUNDS + 1];
 };
 
 // Candidates that the segment workgroups left at the segment starts of `buf` -> one contiguous
@@ -1202,11 +1239,162 @@ __device__ __forceinline__ void note_pairs(const SelArgs& A, int count, unsigned
     if (threadIdx.x == 0) atomicAdd(A.pairs + 2, (unsigned long long)count);
 }
 
+// The remaining rounds of a cached list of at most WAVE_LIST entries, by one wavefront: entry u * 64 + lane.
+// A round of sixteen wavefronts takes 10 us however short its list (13 entries: 4.2 us for the batch's tokens
+// and then its cells, 4.4 for the selection and its three barriers); here the tokens are in registers, the
+// next round's cells are on their way during this one's selection, and nothing waits for another wavefront
+// (1 query x 1,000 documents, eight rounds of 13: 100 -> 45 us a call; 7 x 6,007, lists of 59: 110 -> 90).
+// Leaves the list in `out`, its length and the last round in sh.pick.
+constexpr int WAVE_E = 4;
+constexpr int WAVE_LIST = 64 * WAVE_E;
+__device__ __forceinline__ void prune_wave(const SelArgs& A, const Kappas& kappas, int q, const int32_t* in, int32_t* out,
+                                           const float2* stat, int ncand, int r, bool from_cells, SelShared& sh) {
+    constexpr int E = WAVE_E;
+    const int lane = threadIdx.x & 63;
+    const int T = A.T;
+    const int32_t* pi = A.pi + (size_t)q * T;
+    const int p0 = pi[lane < T ? lane : T - 1], p1 = pi[lane + 64 < T ? lane + 64 : T - 1];
+    auto token = [&](int p) { return p < 64 ? __builtin_amdgcn_readlane(p0, p) : __builtin_amdgcn_readlane(p1, p - 64); };
+    int parts = (ncand + 63) >> 6;                  // places of a lane in use
+    int e[E];
+    float2 st[E];
+    unsigned live = 0;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        const int i = u * 64 + lane;
+        live |= (i < ncand ? 1u : 0u) << u;
+        const int at = i < ncand ? i : ncand - 1;
+        e[u] = in ? in[at] : at;
+    }
+#pragma unroll
+    for (int u = 0; u < E; ++u) st[u] = stat[e[u]];     // (before round 1: not read)
+    const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
+    float cv[E][4];
+    auto fetch = [&](int round) {                   // a batch of at most four
+        const int lo = (round - 1) * A.B, nb = lo + A.B < T ? A.B : T - lo;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = token(lo + (i < nb ? i : 0));
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if (u < parts) cv[u][i] = rows[(unsigned)(e[u] * A.TP + t)];
+        }
+    };
+    if (A.B <= 4 && from_cells) fetch(r);
+    int count;
+    for (;; ++r, from_cells = true) {
+        const int lo = (r - 1) * A.B;
+        const int n = lo + A.B < T ? lo + A.B : T;
+        const int nb = n - lo;
+        if (from_cells) {
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if (u < parts) {
+                    float sb, m2b;
+                    if (A.B <= 4) {
+                        batch_stats_thread([&](int i) { return cv[u][i & 3]; }, nb, sb, m2b);
+                    } else {
+                        const float* crow = rows + (unsigned)(e[u] * A.TP);
+                        batch_stats_thread([&](int i) { return crow[token(lo + i)]; }, nb, sb, m2b);
+                    }
+                    merge_stats(st[u].x, st[u].y, lo, sb, m2b, nb);
+                }
+        }
+        if (A.B <= 4 && r < A.R) fetch(r + 1);
+        const float kappa = kappas.of[r];
+        uint32_t key[E];
+        float low[E], hi[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            key[u] = 0u;
+            low[u] = hi[u] = 0.f;
+            if (u < parts) {
+                interval(st[u].x, st[u].y, n, T, kappa, A.a, A.b, low[u], hi[u]);
+                if ((live >> u) & 1u) key[u] = float_key(low[u]);
+            }
+        }
+        uint32_t best = 0;                          // the K-th largest key, bit by bit
+        if (parts == 1) {
+            best = wave_kth_largest<32>(key[0], A.K);
+        } else {
+#pragma unroll 4
+            for (int bit = 31; bit >= 0; --bit) {
+                const uint32_t test = best | (1u << bit);
+                int reach = 0;
+#pragma unroll
+                for (int u = 0; u < E; ++u) reach += __popcll(__ballot(key[u] >= test));
+                if (reach >= A.K) best = test;
+            }
+        }
+        const float tau = key_float(best);
+        unsigned keep = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) keep |= (hi[u] >= tau ? 1u : 0u) << u;
+        keep &= live;
+        if (A.tr_lcb) {
+            const size_t tro = ((size_t)(r - 1) * A.nq + q) * A.N;
+            const int32_t* cid = A.cid + (size_t)q * A.cache_cap;
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if ((live >> u) & 1u) {
+                    const int id = A.cache_all ? e[u] : cid[e[u]];
+                    A.tr_lcb[tro + id] = low[u];
+                    A.tr_ucb[tro + id] = hi[u];
+                    A.tr_alive[tro + id] = (keep >> u) & 1u;
+                }
+        }
+        live = keep;
+        unsigned long long m[E];
+        count = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            m[u] = __ballot((live >> u) & 1u);
+            count += __popcll(m[u]);
+        }
+        if (lane == 0) note_round(sh, r, count, tau);
+        const bool more = count > A.KM && r < A.R;
+        if (more && r == 1 && A.note_pairs) note_pairs<E>(A, count, live, [&](int u) { return e[u]; });
+        if (more && (count + 63) >> 6 == parts) continue;
+        // the list's end, or fewer places are enough: entries move up, statistics through LDS
+        int base = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int at = base + __builtin_amdgcn_mbcnt_hi((unsigned)(m[u] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m[u], 0u));
+            if ((live >> u) & 1u) {
+                if (!more) out[at] = e[u];
+                sh.few[at] = (uint32_t)e[u];
+                sh.hist[2 * at] = __float_as_uint(st[u].x);
+                sh.hist[2 * at + 1] = __float_as_uint(st[u].y);
+            }
+            base += __popcll(m[u]);
+        }
+        if (!more) break;
+        __builtin_amdgcn_wave_barrier();            // a wavefront's LDS accesses are performed in order
+        asm volatile("" ::: "memory");
+        parts = (count + 63) >> 6;
+        live = 0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int i = u * 64 + lane;
+            live |= (i < count ? 1u : 0u) << u;
+            const int at = i < count ? i : count - 1;
+            e[u] = (int)sh.few[at];
+            st[u] = make_float2(__uint_as_float(sh.hist[2 * at]), __uint_as_float(sh.hist[2 * at + 1]));
+        }
+        asm volatile("" ::: "memory");
+        if (A.B <= 4) fetch(r + 1);
+    }
+    if (lane == 0) {
+        sh.pick[0] = count;
+        sh.pick[1] = r;
+    }
+}
+
 // The rounds of a query whose ncand <= SEL_REGS * SEL_THREADS candidates fit the registers, from
 // round r on.  Returns true when they are done; false when cached rounds remain and at most half of the
-// places that the list takes in each thread are still needed: then r is the next round, ncand the
+// places that the list takes in each thread are still needed, or a wavefront is enough (prune_wave): then r is the next round, ncand the
 // length of the list in `out`, and the statistics are stored.
-__device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, QueryCtl nc,
+__device__ __forceinline__ bool prune_regs(const SelArgs& A, const Kappas& kappas, int q, int count, QueryCtl nc,
                                            const int32_t* in, int32_t* out, float2* stat, const float2* bat,
                                            bool slots, bool fold_dense, bool segmented, int& ncand,
                                            int& r, bool from_cells, SelShared& sh, const int* seg_first,
@@ -1220,6 +1408,11 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
     const Spread sp(ncand);
     unsigned live = sp.mask<E>();
     auto used = [&](int u) { return u * 64 < sp.span; };   // uniform
+    // the reveal order, one token a lane: a round's tokens from memory would be waited for before its cells
+    const int32_t* pi = A.pi + (size_t)q * T;
+    const int lane = threadIdx.x & 63;
+    const int p0 = pi[lane < T ? lane : T - 1], p1 = pi[lane + 64 < T ? lane + 64 : T - 1];
+    auto token = [&](int p) { return p < 64 ? __builtin_amdgcn_readlane(p0, p) : __builtin_amdgcn_readlane(p1, p - 64); };
     int e[E];
     float2 st[E];
     if (segmented) {
@@ -1248,7 +1441,6 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
         const int n = lo + A.B < T ? lo + A.B : T;
         const int nb = n - lo;
         if (from_cells) {
-            const int32_t* pq = A.pi + (size_t)q * T + lo;
             const float* cells = A.ccell + (size_t)q * A.cache_cap * A.TP;
             if (nb <= 4) {                          // four entries' cells in flight
 #pragma unroll
@@ -1257,7 +1449,7 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
                         float cv[4][4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const int t = pq[i < nb ? i : 0];
+                            const int t = token(lo + (i < nb ? i : 0));
 #pragma unroll
                             for (int w = 0; w < 4; ++w) cv[w][i] = cells[(unsigned)(e[g + w] * A.TP + t)];
                         }
@@ -1275,12 +1467,12 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
                     if (used(u)) {
                         const float* crow = cells + (unsigned)(e[u] * A.TP);
                         float sb, m2b;
-                        batch_stats_thread([&](int i) { return crow[pq[i]]; }, nb, sb, m2b);
+                        batch_stats_thread([&](int i) { return crow[token(lo + i)]; }, nb, sb, m2b);
                         merge_stats(st[u].x, st[u].y, lo, sb, m2b, nb);
                     }
             }
         }
-        const float kappa = A.kappa[r];
+        const float kappa = kappas.of[r];
         uint32_t key[E];
         float hi[E];
 #pragma unroll
@@ -1304,7 +1496,7 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
 #pragma unroll
             for (int u = 0; u < E; ++u)
                 if ((live >> u) & 1u) {
-                    const int id = slots ? cid[e[u]] : e[u];
+                    const int id = slots && !A.cache_all ? cid[e[u]] : e[u];
                     float lcb, ucb;
                     interval(st[u].x, st[u].y, n, T, kappa, a, b, lcb, ucb);
                     A.tr_lcb[tro + id] = lcb;
@@ -1318,7 +1510,7 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
         if (threadIdx.x == 0) note_round(sh, r, nc.count, tau);
         const bool more = slots && nc.count > A.KM && r < A.R;
         if (more && r == 1 && A.note_pairs) note_pairs<E>(A, nc.count, live, [&](int u) { return e[u]; });
-        if (more && Spread(nc.count).span * 2 > sp.span) continue;
+        if (more && nc.count > WAVE_LIST && Spread(nc.count).span * 2 > sp.span) continue;
 #pragma unroll
         for (int u = 0; u < E; ++u)
             if ((live >> u) & 1u) {
@@ -1351,7 +1543,7 @@ __device__ __forceinline__ bool prune_regs(const SelArgs& A, int q, int count, Q
 // and upper bounds are held there, entries and statistics are read again.  Returns true when the
 // query's rounds are done; false when cached rounds remain: then r is the next round and ncand the
 // length of the list in `out`.
-__device__ __forceinline__ bool prune_tile(const SelArgs& A, int q, int count, QueryCtl nc,
+__device__ __forceinline__ bool prune_tile(const SelArgs& A, const Kappas& kappas, int q, int count, QueryCtl nc,
                                            const int32_t* in, int32_t* out, float2* stat, const float2* bat,
                                            bool slots, bool fold_dense, bool segmented, int& ncand,
                                            int& r, bool from_cells, SelShared& sh, const int* seg_first,
@@ -1362,7 +1554,7 @@ __device__ __forceinline__ bool prune_tile(const SelArgs& A, int q, int count, Q
     const int lo = (r - 1) * A.B;
     const int n = lo + A.B < T ? lo + A.B : T;
     const int nb = n - lo;
-    const float kappa = A.kappa[r];
+    const float kappa = kappas.of[r];
     const int32_t* pq = A.pi + (size_t)q * T + lo;
     const float* cells = A.ccell + (size_t)q * A.cache_cap * A.TP;
     const int len = seg_len(count);
@@ -1416,7 +1608,7 @@ __device__ __forceinline__ bool prune_tile(const SelArgs& A, int q, int count, Q
         for (int u = 0; u < E; ++u)
             if ((live >> u) & 1u) {
                 const int e = entry(u);
-                const int id = slots ? cid[e] : e;
+                const int id = slots && !A.cache_all ? cid[e] : e;
                 const float2 st = stat[e];          // stored above
                 float lcb, ucb;
                 interval(st.x, st.y, n, T, kappa, a, b, lcb, ucb);
@@ -1462,7 +1654,7 @@ __device__ __forceinline__ void prune_list(const SelArgs& A, int q, int count, Q
     const int lo = (r - 1) * A.B;
     const int n = lo + A.B < T ? lo + A.B : T;
     const int nb = n - lo;
-    const float kappa = A.kappa[r];
+    const float kappa = A.kappa;                    // (r is the launch's round)
     long long my_tokens = 0;
     merge_segments(out, A.seg_cnt + (size_t)q * SEG_MAX, count);
     if (fold_dense) {                        // the candidates' statistics take the round's batch
@@ -1634,14 +1826,212 @@ __device__ __forceinline__ void prune_list(const SelArgs& A, int q, int count, Q
     end_rounds(A, q, nc, r, false, my_tokens, sh, kept_tokens);
 }
 
+struct TopkArgs {
+    const QueryCtl* ctl;   // nullptr: all N documents, vals indexed by id
+    int32_t* list0;        // the list that is not the query's current one doubles as scratch
+    int32_t* list1;        // for candidate positions of long inputs
+    const int32_t* cid;
+    int cache_cap;
+    float* vals;           // [nq][N]; written here for survivors with exact cached cells
+    const float* ccell;    // nullptr: every value is there already
+    int T, TP;
+    int64_t N;
+    int K;
+    int64_t* out_ids;
+    float* out_scores;
+    int32_t* seg_cnt;      // [nq][SEG_MAX]
+};
+
+// The winners of at most E * SEL_THREADS candidates, held in registers: into cs / ci, in no order.
+template <int E>
+__device__ __forceinline__ void topk_regs(const float* vals, const int32_t* list, const int32_t* cid,
+                                          const int32_t* scratch, bool segmented, int count, int ncand, int Kq,
+                                          float* cs, int* ci, int* n_above, const int* seg_first, SelShared& sh) {
+    const Spread sp(ncand);
+    const unsigned on = sp.mask<E>();
+    int p[E];
+    float v[E];
+    uint32_t key[E];
+    if (segmented) {
+        const int len = seg_len(count);
+#pragma unroll
+        for (int u = 0; u < E; ++u) p[u] = scratch[segment_place(sp.at(u), len, seg_first)];
+    } else {
+#pragma unroll
+        for (int u = 0; u < E; ++u) p[u] = sp.at(u);
+    }
+#pragma unroll
+    for (int u = 0; u < E; ++u) v[u] = vals[p[u]];
+#pragma unroll
+    for (int u = 0; u < E; ++u) key[u] = float_key(v[u]);
+    const uint32_t tkey = kth_largest_regs<E>(key, on, Kq, sh);
+    // winners above the K-th value in any order (they are ranked below), those equal to
+    // it in index order as far as there is room
+    unsigned eq = 0;
+    auto put = [&](int slot, int u) {
+        const int e = list ? list[p[u]] : p[u];
+        cs[slot] = v[u];
+        ci[slot] = cid ? cid[e] : e;
+    };
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+        if ((on >> u) & 1u) {
+            if (key[u] > tkey) put(atomicAdd(n_above, 1), u);
+            else if (key[u] == tkey) eq |= 1u << u;
+        }
+    const Places<E> pl(eq, sh);         // its barrier completes n_above
+    const int n_gt = *n_above;
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+        if (((eq >> u) & 1u) && n_gt + pl.place(u) < Kq) put(n_gt + pl.place(u), u);
+}
+
+// Scores of a query's survivors from its cached cells, a wavefront each, by list position.
+__device__ __forceinline__ void score_cached(const TopkArgs& A, int q, int count, const int32_t* list) {
+    float* v = A.vals + (size_t)q * A.N;
+    const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
+    for (int k = my_wave(); k < count; k += SEL_WAVES) {
+        const float* crow = rows + (size_t)list[k] * A.TP;
+        const float x = A.TP == 16 ? cached_score<1>(crow, A.T)
+                      : A.TP == 32 ? cached_score<2>(crow, A.T)
+                      : A.TP == 64 ? cached_score<4>(crow, A.T) : cached_score<8>(crow, A.T);
+        if ((threadIdx.x & 63) == 0) v[k] = x;
+    }
+    __syncthreads();
+}
+
+// The top-K of a query: candidates 0..count-1 (list: the entries they stand for, cid: whose documents these
+// are; nullptr: themselves).  segmented: what k_topk_segments left of them in `scratch`.
+struct TopkShared {
+    float cs[1024];
+    int ci[1024];
+    int n_above;
+};
+__device__ __forceinline__ void topk_query(const TopkArgs& A, int q, int count, const int32_t* list, const int32_t* cid,
+                                           int32_t* scratch, bool segmented, SelShared& sh, int* seg_first, TopkShared& tk) {
+    float* cs = tk.cs;
+    int* ci = tk.ci;
+    const float* vals = A.vals + (size_t)q * A.N;
+    const int Kq = A.K < count ? A.K : count;
+    // few candidates, as after most elimination: one wavefront ranks them (k_topk 8 -> 5 us)
+    if (count <= 64 && !segmented) {
+        if (my_wave() == 0 && count > 0) {
+            const int lane = threadIdx.x & 63;
+            const int at = lane < count ? lane : count - 1;
+            const float v = vals[at];
+            int id = list ? list[at] : at;
+            if (cid) id = cid[id];
+            const uint32_t key = float_key(v);
+            int rank = 0;
+            for (int j = 0; j < count; ++j) {
+                const uint32_t other = __builtin_amdgcn_readlane(key, j);
+                rank += other > key || (other == key && __builtin_amdgcn_readlane(id, j) < id);
+            }
+            if (lane < count && rank < Kq) {
+                A.out_ids[(size_t)q * A.K + rank] = id;
+                A.out_scores[(size_t)q * A.K + rank] = v;
+            }
+        }
+    } else if (Kq > 0) {
+        if (threadIdx.x == 0) tk.n_above = 0;
+        clear_hist(sh);
+        // candidate positions: all of 0..count-1, or what the pre-filter left of a long input
+        // (survivors are few: a longer list of them is scanned whole)
+        int ncand = count;
+        if (segmented) ncand = segment_starts(A.seg_cnt + (size_t)q * SEG_MAX, count, seg_first);
+        if (ncand <= 4 * SEL_THREADS) {
+            topk_regs<4>(vals, list, cid, scratch, segmented, count, ncand, Kq, cs, ci, &tk.n_above, seg_first, sh);
+        } else if (ncand <= SEL_TILE) {
+            topk_regs<SEL_E>(vals, list, cid, scratch, segmented, count, ncand, Kq, cs, ci, &tk.n_above, seg_first, sh);
+        } else {
+            const int32_t* cand = nullptr;
+            if (segmented) {
+                ncand = merge_segments(scratch, A.seg_cnt + (size_t)q * SEG_MAX, count);
+                cand = scratch;
+            }
+            auto key_of = [&](int j) -> uint32_t { return float_key(vals[cand ? cand[j] : j]); };
+            const uint32_t tkey = kth_largest_list(ncand, Kq, key_of, sh);
+            // how many are strictly above the K-th value
+            int gt_local = 0;
+            for (int j = threadIdx.x; j < ncand; j += SEL_THREADS) gt_local += key_of(j) > tkey;
+            int n_gt;
+            block_excl_scan(gt_local, sh.wtot, n_gt);
+            const int need_eq = Kq - n_gt;
+            int base_gt = 0, base_eq = 0;
+            for (int start = 0; start < ncand; start += SEL_CHUNK) {
+                const int i0 = start + threadIdx.x * SEL_ITEMS;
+                float v[SEL_ITEMS];
+                int p[SEL_ITEMS];
+                unsigned gt = 0, eq = 0;
+#pragma unroll
+                for (int u = 0; u < SEL_ITEMS; ++u) {
+                    p[u] = (i0 + u < ncand) ? (cand ? cand[i0 + u] : i0 + u) : 0;
+                    v[u] = (i0 + u < ncand) ? vals[p[u]] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < SEL_ITEMS; ++u) {
+                    if (i0 + u < ncand) {
+                        const uint32_t key = float_key(v[u]);
+                        gt |= (key > tkey ? 1u : 0u) << u;
+                        eq |= (key == tkey ? 1u : 0u) << u;
+                    }
+                }
+                if (__syncthreads_or((gt | eq) != 0)) {      // most chunks hold no winner
+                    int tot;
+                    const int pos = block_excl_scan(__popc(gt) | (__popc(eq) << 16), sh.wtot, tot);
+                    int pg = base_gt + (pos & 0xffff), pe = base_eq + (pos >> 16);
+#pragma unroll
+                    for (int u = 0; u < SEL_ITEMS; ++u) {
+                        int slot = -1;
+                        if (gt & (1u << u)) slot = pg++;
+                        else if (eq & (1u << u)) {
+                            if (pe < need_eq) slot = n_gt + pe;
+                            ++pe;
+                        }
+                        if (slot >= 0) {
+                            const int e = list ? list[p[u]] : p[u];
+                            cs[slot] = v[u];
+                            ci[slot] = cid ? cid[e] : e;
+                        }
+                    }
+                    base_gt += tot & 0xffff;
+                    base_eq += tot >> 16;
+                }
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < Kq) {
+            const float v = cs[threadIdx.x];
+            const int id = ci[threadIdx.x];
+            int rank = 0;
+            for (int j = 0; j < Kq; ++j) {
+                const float u = cs[j];
+                rank += (u > v) || (u == v && ci[j] < id);
+            }
+            A.out_ids[(size_t)q * A.K + rank] = id;
+            A.out_scores[(size_t)q * A.K + rank] = v;
+        }
+    }
+    for (int k = Kq + threadIdx.x; k < A.K; k += SEL_THREADS) {
+        A.out_ids[(size_t)q * A.K + k] = -1;
+        A.out_scores[(size_t)q * A.K + k] = -__builtin_inff();
+    }
+}
+
 // Bound by latency and instructions, not by bytes: a list that fits the registers is read once, and
 // selection, prune and count of all its rounds run there.
-__global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
+// TOPK (cache_all): every query ends in this launch, which goes on to its top-K; a launch for that cost
+// 6 us of a call of 50.
+template <bool TOPK>
+__global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas kappas, TopkArgs P) {
     __shared__ SelShared sh;
     __shared__ int seg_first[SEG_MAX + 1];
     __shared__ unsigned long long kept_tokens;
     const int q = blockIdx.x;
-    const QueryCtl c = A.ctl[q];
+    QueryCtl c{};
+    c.count = (int)A.N;
+    c.implicit = c.active = 1;
+    if constexpr (!TOPK) c = A.ctl[q];              // (cache_all: round 1, all documents)
     if (!c.active) return;
     const int count = c.count;
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
@@ -1667,18 +2057,35 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A) {
     nc.mode = slots ? 1 : 0;
     nc.bound = nc.pad1 = nc.pad2 = 0;
     int r = A.r;
-    bool from_cells = false;                        // the round's batch still has to be folded in
+    bool from_cells = A.cache_all != 0;             // the round's batch still has to be folded in
     bool seg = segmented, fold = fold_dense;
     if (ncand > SEL_TILE) {
         prune_list(A, q, count, nc, out, stat, bat, fold, ncand, r, sh, &kept_tokens);
         return;
     }
     for (;;) {
-        const bool done =
+        bool done = true;
+        if (slots && ncand <= WAVE_LIST) {
+            if (my_wave() == 0) prune_wave(A, kappas, q, in, out, stat, ncand, r, from_cells, sh);
+            __syncthreads();
+            nc.count = sh.pick[0];
+            r = sh.pick[1];
+            nc.active = 0;
+            end_rounds(A, q, nc, r, true, 0, sh, &kept_tokens);
+        } else done =
             ncand <= SEL_REGS * SEL_THREADS
-                ? prune_regs(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens)
-                : prune_tile(A, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens);
-        if (done) return;
+                ? prune_regs(A, kappas, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens)
+                : prune_tile(A, kappas, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens);
+        if (done) {
+            if constexpr (TOPK) {
+                __shared__ TopkShared tk;
+                __syncthreads();                    // the list is read by other threads next
+                const int left = sh.round_count[r - 1];
+                score_cached(P, q, left, out);
+                topk_query(P, q, left, out, nullptr, nullptr, false, sh, seg_first, tk);
+            }
+            return;
+        }
         // cached rounds remain: on from the shorter list, into the other buffer
         from_cells = true;
         seg = fold = false;
@@ -1736,7 +2143,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
     const QueryCtl c = A.ctl[q];
     if (!c.active || !c.implicit || c.count <= SEL_TILE) return;
     const float2* stat = A.stat + (size_t)q * A.N;
-    const FastBounds fb = fast_bounds_consts(A.n, A.T, A.kappa[A.r], A.a, A.b);
+    const FastBounds fb = fast_bounds_consts(A.n, A.T, A.kappa, A.a, A.b);
     clear_hist(sh);
     const int run_stride = c.count / (SEL_TILE / SEL_RUN);
     float2 st[SEL_E];
@@ -1780,7 +2187,7 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     const float2* bat = A.stat2 + (size_t)q * A.N;
     const bool fold = dense && in != nullptr;
     const int n = A.n, T = A.T;
-    const float kappa = A.kappa[A.r], a = A.a, b = A.b;
+    const float kappa = A.kappa, a = A.a, b = A.b;
     const FastBounds fb = fast_bounds_consts(n, T, kappa, a, b);
     const size_t tro = ((size_t)(A.r - 1) * A.nq + q) * A.N;
     clear_hist(sh);
@@ -1864,12 +2271,34 @@ static unsigned segments_of(int64_t N) {
     return (unsigned)(tiles < SEG_MAX ? tiles : SEG_MAX);
 }
 
+static TopkArgs topk_args(const Problem& P, const Work& W, bool use_ctl, bool cached, float* vals, int K,
+                          int64_t* out_ids, float* out_scores) {
+    TopkArgs A{};
+    A.ctl = use_ctl ? W.ctl : nullptr;
+    A.list0 = W.list[0];
+    A.list1 = W.list[1];
+    A.cid = W.cid;
+    A.cache_cap = W.cache_cap;
+    A.vals = vals;
+    A.ccell = cached ? W.ccell : nullptr;
+    A.T = P.T;
+    A.TP = W.TP;
+    A.N = P.N;
+    A.K = K;
+    A.out_ids = out_ids;
+    A.out_scores = out_scores;
+    A.seg_cnt = W.seg_cnt;
+    return A;
+}
+
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, const Trace& tr, hipStream_t st) {
+                               bool note_pairs, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st) {
     SelArgs A{};
     A.cache_all = cache_all ? 1 : 0;
     A.note_pairs = cache_all && note_pairs ? 1 : 0;
+    TopkArgs top{};
+    if (topk_ids) top = topk_args(P, W, false, true, W.rescored, kn.K, topk_ids, topk_scores);
     A.ctl = W.ctl;
     A.list0 = W.list[0];
     A.list1 = W.list[1];
@@ -1906,7 +2335,9 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.tr_ucb = tr.ucb;
     A.tr_alive = tr.alive;
     A.seg_cnt = W.seg_cnt;
-    for (int r = 0; r <= R; ++r) A.kappa[r] = kappa[r];
+    A.kappa = kappa[rr.r];
+    Kappas kappas{};
+    for (int r = 0; r <= R; ++r) kappas.of[r] = kappa[r];
     // lists that do not fit one workgroup's registers are first cut down, one workgroup per tile
     if (P.N > SEL_TILE) {
         unsigned gx = segments_of(P.N);
@@ -1919,7 +2350,8 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
         }
         k_select_segments<<<dim3(gx, P.nq), SEL_THREADS, 0, st>>>(A);
     }
-    k_select_prune<<<P.nq, SEL_THREADS, 0, st>>>(A);
+    if (topk_ids) k_select_prune<true><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
+    else k_select_prune<false><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
     return hipGetLastError();
 }
 
@@ -1928,22 +2360,6 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
 // (Eq. (3); final step of Algorithm 1).  Candidates arrive in ascending id order, so
 // ties at the K-th value are resolved towards the lower index by taking them in order.
 // =====================================================================================
-struct TopkArgs {
-    const QueryCtl* ctl;   // nullptr: all N documents, vals indexed by id
-    int32_t* list0;        // the list that is not the query's current one doubles as scratch
-    int32_t* list1;        // for candidate positions of long inputs
-    const int32_t* cid;
-    int cache_cap;
-    float* vals;           // [nq][N]; written here for survivors with exact cached cells
-    const float* ccell;    // nullptr: every value is there already
-    int T, TP;
-    int64_t N;
-    int K;
-    int64_t* out_ids;
-    float* out_scores;
-    int32_t* seg_cnt;      // [nq][SEG_MAX]
-};
-
 // The pre-filter of k_topk for long all-documents inputs, a workgroup per segment: each tile is
 // read once, and the positions whose value reaches a lower bound of the tile's own K-th
 // largest (lower_bound_key) go, in order, to the segment's start of the scratch list.
@@ -1986,56 +2402,10 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_topk_segments(TopkArgs A) {
     if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
 }
 
-// The winners of at most E * SEL_THREADS candidates, held in registers: into cs / ci, in no order.
-template <int E>
-__device__ __forceinline__ void topk_regs(const float* vals, const int32_t* list, const int32_t* cid,
-                                          const int32_t* scratch, bool segmented, int count, int ncand, int Kq,
-                                          float* cs, int* ci, int* n_above, const int* seg_first, SelShared& sh) {
-    const Spread sp(ncand);
-    const unsigned on = sp.mask<E>();
-    int p[E];
-    float v[E];
-    uint32_t key[E];
-    if (segmented) {
-        const int len = seg_len(count);
-#pragma unroll
-        for (int u = 0; u < E; ++u) p[u] = scratch[segment_place(sp.at(u), len, seg_first)];
-    } else {
-#pragma unroll
-        for (int u = 0; u < E; ++u) p[u] = sp.at(u);
-    }
-#pragma unroll
-    for (int u = 0; u < E; ++u) v[u] = vals[p[u]];
-#pragma unroll
-    for (int u = 0; u < E; ++u) key[u] = float_key(v[u]);
-    const uint32_t tkey = kth_largest_regs<E>(key, on, Kq, sh);
-    // winners above the K-th value in any order (they are ranked below), those equal to
-    // it in index order as far as there is room
-    unsigned eq = 0;
-    auto put = [&](int slot, int u) {
-        const int e = list ? list[p[u]] : p[u];
-        cs[slot] = v[u];
-        ci[slot] = cid ? cid[e] : e;
-    };
-#pragma unroll
-    for (int u = 0; u < E; ++u)
-        if ((on >> u) & 1u) {
-            if (key[u] > tkey) put(atomicAdd(n_above, 1), u);
-            else if (key[u] == tkey) eq |= 1u << u;
-        }
-    const Places<E> pl(eq, sh);         // its barrier completes n_above
-    const int n_gt = *n_above;
-#pragma unroll
-    for (int u = 0; u < E; ++u)
-        if (((eq >> u) & 1u) && n_gt + pl.place(u) < Kq) put(n_gt + pl.place(u), u);
-}
-
 __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
     __shared__ SelShared sh;
     __shared__ int seg_first[SEG_MAX + 1];
-    __shared__ float cs[1024];
-    __shared__ int ci[1024];
-    __shared__ int n_above;
+    __shared__ TopkShared tk;
     const int q = blockIdx.x;
     int count = (int)A.N;
     const int32_t* list = nullptr;
@@ -2048,126 +2418,16 @@ __global__ __launch_bounds__(SEL_THREADS) void k_topk(TopkArgs A) {
             list = (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
             scratch = (c.cur ? A.list0 : A.list1) + (size_t)q * A.N;
         }
-        if (c.mode == 1) cid = A.cid + (size_t)q * A.cache_cap;
-        if (c.mode == 1 && A.ccell) {               // a wavefront per survivor
-            float* v = A.vals + (size_t)q * A.N;
-            const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
-            for (int k = my_wave(); k < count; k += SEL_WAVES) {
-                const float* crow = rows + (size_t)list[k] * A.TP;
-                const float x = A.TP == 16 ? cached_score<1>(crow, A.T)
-                              : A.TP == 32 ? cached_score<2>(crow, A.T)
-                              : A.TP == 64 ? cached_score<4>(crow, A.T) : cached_score<8>(crow, A.T);
-                if ((threadIdx.x & 63) == 0) v[k] = x;
-            }
-            __syncthreads();
-        }
+        if (c.mode == 1 && A.cid) cid = A.cid + (size_t)q * A.cache_cap;
+        if (c.mode == 1 && A.ccell) score_cached(A, q, count, list);
     }
-    const float* vals = A.vals + (size_t)q * A.N;
-    const int Kq = A.K < count ? A.K : count;
-    if (Kq > 0) {
-        if (threadIdx.x == 0) n_above = 0;
-        clear_hist(sh);
-        // candidate positions: all of 0..count-1, or what the pre-filter left of a long input
-        // (survivors are few: a longer list of them is scanned whole)
-        const bool segmented = !A.ctl && count > SEL_TILE;
-        int ncand = count;
-        if (segmented) ncand = segment_starts(A.seg_cnt + (size_t)q * SEG_MAX, count, seg_first);
-        if (ncand <= 4 * SEL_THREADS) {
-            topk_regs<4>(vals, list, cid, scratch, segmented, count, ncand, Kq, cs, ci, &n_above, seg_first, sh);
-        } else if (ncand <= SEL_TILE) {
-            topk_regs<SEL_E>(vals, list, cid, scratch, segmented, count, ncand, Kq, cs, ci, &n_above, seg_first, sh);
-        } else {
-            const int32_t* cand = nullptr;
-            if (segmented) {
-                ncand = merge_segments(scratch, A.seg_cnt + (size_t)q * SEG_MAX, count);
-                cand = scratch;
-            }
-            auto key_of = [&](int j) -> uint32_t { return float_key(vals[cand ? cand[j] : j]); };
-            const uint32_t tkey = kth_largest_list(ncand, Kq, key_of, sh);
-            // how many are strictly above the K-th value
-            int gt_local = 0;
-            for (int j = threadIdx.x; j < ncand; j += SEL_THREADS) gt_local += key_of(j) > tkey;
-            int n_gt;
-            block_excl_scan(gt_local, sh.wtot, n_gt);
-            const int need_eq = Kq - n_gt;
-            int base_gt = 0, base_eq = 0;
-            for (int start = 0; start < ncand; start += SEL_CHUNK) {
-                const int i0 = start + threadIdx.x * SEL_ITEMS;
-                float v[SEL_ITEMS];
-                int p[SEL_ITEMS];
-                unsigned gt = 0, eq = 0;
-#pragma unroll
-                for (int u = 0; u < SEL_ITEMS; ++u) {
-                    p[u] = (i0 + u < ncand) ? (cand ? cand[i0 + u] : i0 + u) : 0;
-                    v[u] = (i0 + u < ncand) ? vals[p[u]] : 0.f;
-                }
-#pragma unroll
-                for (int u = 0; u < SEL_ITEMS; ++u) {
-                    if (i0 + u < ncand) {
-                        const uint32_t key = float_key(v[u]);
-                        gt |= (key > tkey ? 1u : 0u) << u;
-                        eq |= (key == tkey ? 1u : 0u) << u;
-                    }
-                }
-                if (__syncthreads_or((gt | eq) != 0)) {      // most chunks hold no winner
-                    int tot;
-                    const int pos = block_excl_scan(__popc(gt) | (__popc(eq) << 16), sh.wtot, tot);
-                    int pg = base_gt + (pos & 0xffff), pe = base_eq + (pos >> 16);
-#pragma unroll
-                    for (int u = 0; u < SEL_ITEMS; ++u) {
-                        int slot = -1;
-                        if (gt & (1u << u)) slot = pg++;
-                        else if (eq & (1u << u)) {
-                            if (pe < need_eq) slot = n_gt + pe;
-                            ++pe;
-                        }
-                        if (slot >= 0) {
-                            const int e = list ? list[p[u]] : p[u];
-                            cs[slot] = v[u];
-                            ci[slot] = cid ? cid[e] : e;
-                        }
-                    }
-                    base_gt += tot & 0xffff;
-                    base_eq += tot >> 16;
-                }
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < Kq) {
-            const float v = cs[threadIdx.x];
-            const int id = ci[threadIdx.x];
-            int rank = 0;
-            for (int j = 0; j < Kq; ++j) {
-                const float u = cs[j];
-                rank += (u > v) || (u == v && ci[j] < id);
-            }
-            A.out_ids[(size_t)q * A.K + rank] = id;
-            A.out_scores[(size_t)q * A.K + rank] = v;
-        }
-    }
-    for (int k = Kq + threadIdx.x; k < A.K; k += SEL_THREADS) {
-        A.out_ids[(size_t)q * A.K + k] = -1;
-        A.out_scores[(size_t)q * A.K + k] = -__builtin_inff();
-    }
+    topk_query(A, q, count, list, cid, scratch, !A.ctl && count > SEL_TILE, sh, seg_first, tk);
 }
 
-hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, bool cached, float* vals, int K,
+hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, bool cached, bool cache_all, float* vals, int K,
                        int64_t* out_ids, float* out_scores, hipStream_t st) {
-    TopkArgs A{};
-    A.ctl = use_ctl ? W.ctl : nullptr;
-    A.list0 = W.list[0];
-    A.list1 = W.list[1];
-    A.cid = W.cid;
-    A.cache_cap = W.cache_cap;
-    A.vals = vals;
-    A.ccell = cached ? W.ccell : nullptr;
-    A.T = P.T;
-    A.TP = W.TP;
-    A.N = P.N;
-    A.K = K;
-    A.out_ids = out_ids;
-    A.out_scores = out_scores;
-    A.seg_cnt = W.seg_cnt;
+    TopkArgs A = topk_args(P, W, use_ctl, cached, vals, K, out_ids, out_scores);
+    if (cache_all) A.cid = nullptr;                 // slots are documents
     if (!use_ctl && P.N > SEL_TILE)
         k_topk_segments<<<dim3(segments_of(P.N), P.nq), SEL_THREADS, 0, st>>>(A);
     k_topk<<<P.nq, SEL_THREADS, 0, st>>>(A);

@@ -86,16 +86,19 @@ hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, 
 
 // Reveal round rr by gathering the documents of every active (query, document) pair.  Queries whose
 // list fits the cell cache get all T cells of their documents computed once and cached;
-// k_select_prune and the rescore read them back.  cache_all (round 1): so do all queries at once.
-hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, bool cache_all,
-                               const Coarse* co, hipStream_t st);
+// k_select_prune and the rescore read them back.
+hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, const Coarse* co, hipStream_t st);
+// The smallest calls, in the place of launch_init: all cells of all documents go to the cell cache (slot =
+// document), and the queries are set up in the same launch.
+hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
+                            const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st);
 
 // Exact scores from the stored embeddings.  Survivors: of the current active sets, written by
 // list position (score_slots: including the queries whose list holds cache slots, whose cached
 // cells are coarse and cannot give the exact score).  All: every document of every query, written
 // by doc id into `out` ([nq][N]).
 hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,
-                                   bool score_slots, hipStream_t st);
+                                   bool score_slots, bool cache_all, hipStream_t st);
 hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float* cells, hipStream_t st);
 bool gather_shares(const Problem& P);   // launch_gather_all gives a pair a workgroup
 
@@ -128,15 +131,16 @@ int dense_chunks(const Problem& P, const Work& W);
 
 // Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
 // this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
-// per unit sigma_hat of round r.
+// per unit sigma_hat of round r.  topk_ids (after launch_cache_all, exact cells): the launch ends with the top-K.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, const Trace& tr, hipStream_t st);
+                               bool note_pairs, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
 // list position); else all N documents (vals indexed by id).  cached: the queries whose list holds
-// cache slots take their survivors' scores from the cached cells (and store them in vals).
-hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, bool cached, float* vals, int K,
+// cache slots take their survivors' scores from the cached cells (and store them in vals).  cache_all: slots
+// are documents.
+hipError_t launch_topk(const Problem& P, const Work& W, bool use_ctl, bool cached, bool cache_all, float* vals, int K,
                        int64_t* out_ids, float* out_scores, hipStream_t st);
 
 // int8 codes of x ([n_segments][seg_elems] values of dtype dt): per segment, clip = the
