@@ -615,11 +615,11 @@ void k_dense(DenseArgs A) {
     // that holds nothing but the operand reads and the MFMAs of two blocks (and, every fourth
     // block, the stage entry); it covers the rows below tight_end, where every block has a
     // complete successor and every stage entered requests a complete stage.  A block in which a
-    // document ends, and the chunk's last stages, take the general path.  Kernels with at most
-    // four column tiles per wavefront are bound by memory more than by the matrix pipes, and run
-    // at a higher occupancy with fewer registers: they keep to the general path.
-    constexpr bool TIGHT_RUNS = NT >= PACKED_NT && SPLIT_DOCS == 0;
-    const int tight_end = TIGHT_RUNS ? (nfull - 2) * STAGE_ROWS : 0;
+    // document ends, and the chunk's last stages, take the general path.  (The loop without it for up to
+    // four tiles a wavefront, us: 64 queries x 20,000 pages, Col-Bandit, 3,015 with the general path and 2,805,
+    // 64 x 50,000 495 and 482, 8 x 200,000 exhaustive 1,380 and 1,285, 3 x 200,000 in d = 32 408 and 304; where
+    // wavefronts split the documents 1 x 500,000 1,993 and 1,926, 1 x 200,000 of 100 tokens 1,692 and 1,412.)
+    const int tight_end = (nfull - 2) * STAGE_ROWS;
     auto stage_enter_full = [&](int bs) {        // bs < tight_end is a stage boundary
         wait_copies();
         ring_barrier();
@@ -637,11 +637,18 @@ void k_dense(DenseArgs A) {
     int bs = 0;
     load_block(a0, 0);
     while (bs < ntok) {
-        if (TIGHT_RUNS && bs < tight_end) {
+        if (bs < tight_end) {
             // blocks from bs on that end before the current document does
             int run = doc < i1 ? (dend - bs - 1) >> 4 : RING_ROWS;
             const int left = (tight_end - bs) >> 4;
             run = run < 0 ? 0 : (run > left ? left : run);
+            if (SPLIT_DOCS != 0 && run >= 1 && !mine(doc)) {    // another wavefront's: on to the run's end
+                for (; run >= 1; --run) {
+                    if (at_boundary(bs)) stage_enter_full(bs);
+                    bs += 16;
+                }
+                load_aligned(a0, bs);
+            }
             if (run >= 1 && (bs & 16)) {        // to an even block: pairs never straddle a stage
                 load_aligned(a1, bs + 16);
                 __builtin_amdgcn_sched_barrier(0);
