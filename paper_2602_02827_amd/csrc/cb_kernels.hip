@@ -186,8 +186,7 @@ struct GatherArgs {
     const unsigned long long* work;      // its queries (work_item)
     unsigned long long dense_thr;        // ~0: this round cannot be a corpus pass
     // cell cache
-    int cache_all;            // caches the cells of all N documents (slot = document); nothing else
-    int init_blocks;          // ... and the last workgroups of the launch set the queries up
+    int cache_all;            // slots are documents (k_cache_all)
     int cache_cap, TP;
     int32_t* cid;
     float2* cstat;
@@ -333,17 +332,12 @@ constexpr int64_t ALL_DOCS = 64;
 //                  documents so before round 1, which takes its batch from the cells as well; the
 //                  launch also sets the queries up, which nothing in it needs, and two launches make
 //                  the call (1 query x 1,000 documents of 48 fp32 tokens: 45 -> 39 us).
-template <typename Tag, int D, int TQ>
-__global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gather_round(GatherArgs A, InitArgs I) {
+template <typename Tag, int D, int TQ, bool CACHE_ALL>
+__device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
     __shared__ int ex[EX_FLOATS];
-    const int n_blocks = (int)gridDim.x - A.init_blocks;
-    if ((int)blockIdx.x >= n_blocks) {
-        init_queries(I, (int)blockIdx.x - n_blocks);
-        return;
-    }
     if (A.dense_thr != ~0ull && dense_round(A.pairs_r, A.dense_thr)) return;   // the corpus pass serves it
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -419,13 +413,13 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
         x += k_end - k;
         int count = 0;
         int32_t* list = nullptr;
-        if (!A.cache_all) {
+        if (!CACHE_ALL) {
             const QueryCtl c = A.ctl[q];
             count = c.count;
             if (!c.implicit) list = (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
         }
         const float scale = A.qscale ? A.qscale[q] * A.dscale[0] : 1.f;
-        if (!A.cache_all && (!list || count > A.cache_cap)) {
+        if (!CACHE_ALL && (!list || count > A.cache_cap)) {
             F bq[1];
             const int trow = A.pi[(size_t)q * A.T + A.lo + (col < A.nb ? col : 0)];
             bq[0].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg);
@@ -453,7 +447,7 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
             load_query<F, ROWB, TQ>(A, q, col, kg, bq);
             const int row = lane >> 4;
             // this round's batch: slot s (lane s of row 0) fetches cell pi[lo+s] from its owner
-            const int t = A.cache_all ? 0 : A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
+            const int t = CACHE_ALL ? 0 : A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
             const int tile = t >> 4;
             const int src = P::row_of_tile(tile) * 16 + (t & 15);
             for (; k < k_end; ++k) {
@@ -472,7 +466,7 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
 #pragma unroll
                 for (int j = 0; j < P::NW; ++j)
                     if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
-                if (A.cache_all) continue;
+                if (CACHE_ALL) continue;
                 float v = __shfl(w[0], src);
                 if constexpr (P::NW > 1) {
                     const float v1 = __shfl(w[1], src);
@@ -491,6 +485,18 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gath
             }
         }
     }
+}
+
+template <typename Tag, int D, int TQ>
+__global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gather_round(GatherArgs A) {
+    gather_round<Tag, D, TQ, false>(A, (int)gridDim.x);
+}
+// (a kernel of its own: the longer argument list cost every launch of a round 1 us)
+template <typename Tag, int D, int TQ>
+__global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_cache_all(GatherArgs A, InitArgs I) {
+    const int n_blocks = (int)gridDim.x - I.init_blocks;
+    if ((int)blockIdx.x < n_blocks) gather_round<Tag, D, TQ, true>(A, n_blocks);
+    else init_queries(I, (int)blockIdx.x - n_blocks);
 }
 
 // Exact scores of the survivors of the queries whose list holds ids (score_slots: of all), by
@@ -576,12 +582,13 @@ __global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
     }
 }
 
-enum { GM_ROUND = 0, GM_SURVIVORS = 1, GM_ALL = 2 };
+enum { GM_ROUND = 0, GM_SURVIVORS = 1, GM_ALL = 2, GM_CACHE_ALL = 3 };
 
 template <typename Tag, int D, int TQ>
 static hipError_t gather_mode(const GatherArgs& A, const InitArgs& I, int mode, dim3 grid, hipStream_t st) {
     const dim3 block(256);
-    if (mode == GM_ROUND) k_gather_round<Tag, D, TQ><<<grid, block, 0, st>>>(A, I);
+    if (mode == GM_ROUND) k_gather_round<Tag, D, TQ><<<grid, block, 0, st>>>(A);
+    else if (mode == GM_CACHE_ALL) k_cache_all<Tag, D, TQ><<<grid, block, 0, st>>>(A, I);
     else if constexpr (!__is_same(Tag, i8_tag)) {   // scores come from the stored embeddings
         if (mode == GM_SURVIVORS) k_gather_survivors<Tag, D, TQ><<<grid, block, 0, st>>>(A);
         else k_gather_all<Tag, D, TQ><<<grid, block, 0, st>>>(A);
@@ -664,10 +671,8 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
 hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
                             const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st) {
     GatherArgs A{};
-    A.cache_all = 1;
     A.dense_thr = ~0ull;
     const InitArgs I = init_args(P, W, kn, R, seed, user_pi, tr, 0);
-    A.init_blocks = I.init_blocks;
     long long blocks = (long long)P.nq * P.N;
     // A document shared by four wavefronts loads the query four times.  From some three pairs a CU a
     // wavefront per pair is faster (us a call: 1,000 pairs of 48 fp32 tokens 112 -> 104, 2,000 of bf16 56 -> 50),
@@ -675,7 +680,7 @@ hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, in
     if (blocks >= 768) blocks = (blocks + 3) / 4;
     blocks = blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS;
     fill_trace(P, R, tr, st);
-    return gather_any(A, I, GM_ROUND, P, W, dim3((unsigned)(blocks + I.init_blocks)), co, st);
+    return gather_any(A, I, GM_CACHE_ALL, P, W, dim3((unsigned)(blocks + I.init_blocks)), co, st);
 }
 
 hipError_t launch_gather_survivors(const Problem& P, const Work& W, const Knobs& kn, float* out,

@@ -678,6 +678,29 @@ def test_smallest_calls_that_visit_every_document_once(B, S, oracle_mod, dtype, 
         _run_colbandit_case(B, oracle_mod, w, 5, 5, Bsz, alpha, seed=3)
 
 
+@pytest.mark.parametrize("N,T,Bsz,K,M,coarse", [(64, 32, 4, 5, 0, False), (65, 32, 4, 5, 5, False), (128, 21, 4, 1, 0, False),
+                                              (129, 100, 3, 7, 0, False), (192, 70, 16, 30, 3, False), (255, 32, 5, 60, 4, False),
+                                              (256, 32, 4, 250, 0, False), (257, 24, 2, 5, 0, False), (300, 32, 4, 64, 0, True),
+                                              (1000, 128, 7, 65, 1, False), (1030, 32, 1, 3, 2, True)])
+def test_short_cached_lists_by_one_wavefront(B, S, N, T, Bsz, K, M, coarse):
+    """Lists around 64, 128, 192 and 256 entries, which one wavefront takes from some round on (batches of up to
+    four and of more, reveal orders beyond 64 tokens, lists that shrink by a place or not), and final lists
+    around 64: every round's survivors, bounds and threshold, and the top-K, are those of rounds that read
+    nothing from a cache."""
+    rng = np.random.default_rng(N + T)
+    w = _custom(S, rng.integers(1, 40, N).tolist(), 3, T, 64, "bf16", N)
+    more = {}
+    if coarse:
+        more["docs_i8"], more["docs_scale"] = B.colbandit_quantize_i8(w.docs)
+    for alpha in (0.1, 0.3, 1.0):
+        r = [B.colbandit_topk(w.Q, w.docs, w.offsets, K, alpha, 0.01, M, 3, B=Bsz, trace=True, no_cell_cache=c, **more)
+             for c in (False, True)]
+        torch.cuda.synchronize()
+        _same_run(*r)
+        plain = B.colbandit_topk(w.Q, w.docs, w.offsets, K, alpha, 0.01, M, 3, B=Bsz, want_stats=False, **more)
+        assert torch.equal(plain["topk_ids"], r[0]["topk_ids"]) and torch.equal(plain["topk_scores"], r[0]["topk_scores"])
+
+
 @pytest.mark.parametrize("alpha,Bsz,T,nq", [(1.0, 4, 32, 4), (0.5, 3, 24, 9), (1.0, 16, 100, 2), (0.2, 4, 32, 40)])
 def test_later_rounds_by_corpus_pass_or_by_gather_are_identical(B, S, oracle_mod, alpha, Bsz, T, nq):
     """Rounds >= 2 revealed by the corpus-streaming pass (merged into the running statistics by
