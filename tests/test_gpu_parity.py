@@ -636,6 +636,22 @@ def test_rounds_that_a_pass_could_not_shorten_launch_none(B, S):
     _same_run(call(trace=True), call(trace=True, later_rounds=1))
 
 
+@pytest.mark.parametrize("nq,T,d,coarse", [(7, 21, 64, False), (12, 32, 64, False), (7, 24, 128, True)])
+def test_full_lists_of_a_corpus_in_the_last_level_cache_launch_no_later_round(B, S, nq, T, d, coarse):
+    """Lists that fit the cell cache, over documents few enough to gather whole: one gathered round, and the same run
+    as with a corpus pass in every round."""
+    w = _custom(S, np.random.default_rng(nq).integers(1, 260, 5000).tolist(), nq, T, d, "bf16", 9)
+    more = {}
+    if coarse:
+        more["docs_i8"], more["docs_scale"] = B.colbandit_quantize_i8(w.docs)
+    for alpha in (0.2, 1.0):
+        names = _kernels(lambda: B.colbandit_topk(w.Q, w.docs, w.offsets, 10, alpha, 0.01, 5, 3, want_stats=False, **more))
+        assert names.count("k_gather_round<") == 1 and names.count("k_dense<") == 1
+        r = [B.colbandit_topk(w.Q, w.docs, w.offsets, 10, alpha, 0.01, 5, 3, trace=True, later_rounds=m, **more) for m in (0, 1)]
+        torch.cuda.synchronize()
+        _same_run(*r)
+
+
 @pytest.mark.parametrize("N,nq,T,longest", [(20000, 5, 32, 3), (40000, 3, 48, 2), (9000, 9, 24, 5), (30000, 2, 100, 2)])
 def test_gathered_rounds_of_more_pairs_than_workers(B, S, N, nq, T, longest):
     """Lists of unequal length whose pairs (beyond 32,768) are dealt out in streams, held as ids and in
