@@ -227,8 +227,10 @@ int colbandit_coarse_maxsim(const void *Q, int n_queries, int T, int d, colbandi
  *                                on `stream`
  *   workspace                    DEVICE, 256-byte aligned, >= colbandit_workspace_bytes
  * bf16 inputs are multiplied on the matrix cores with fp32 accumulation; fp32 inputs
- * are cut into three bf16 pieces each, exactly, whose products are summed in fp32 (the precision of
- * an fp32 sum).  Fully asynchronous unless phase_ms is given.
+ * are cut into three bf16 pieces each and the six larger products of pieces summed in fp32: the precision
+ * of an fp32 sum (what is left out is 2^-24 of a product at most) for all finite components of magnitude
+ * 2^-110 or more; of smaller ones what lies below 2^-133 is lost.  Infinite components and products that
+ * overflow give what fp32 products give.  Fully asynchronous unless phase_ms is given.
  */
 int colbandit_full_maxsim(const void *Q, int n_queries, int T, int d, colbandit_dtype dt,
                           const void *doc_tokens, const int64_t *doc_offsets, int64_t N,

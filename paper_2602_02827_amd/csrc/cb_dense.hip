@@ -189,6 +189,7 @@ void k_dense(DenseArgs A) {
     constexpr int QPW = 8 / TQ;                     // PACKED: queries of a wavefront
     const int pq0 = (group * 4 + wave) * QPW;
     F bq[NT];
+    bool query_wild = false;
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
         const int g = tile0 + tt;
@@ -212,8 +213,9 @@ void k_dense(DenseArgs A) {
             q = q < A.nq ? q : 0;
             trow = t < A.T ? t : 0;
         }
-        bq[tt].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg);
+        query_wild |= bq[tt].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg);
     }
+    query_wild = __ballot(query_wild) != 0ull;
 
     // ---- stage loader: 64 rows x ROWB bytes, copied global -> LDS without passing through
     // registers (global_load_lds_dwordx4: every lane names its 16 global bytes, the wavefront's
@@ -496,15 +498,15 @@ void k_dense(DenseArgs A) {
     int doc = i0;                   // document whose maxima are being accumulated
     int dend = rel_off(i0 + 1);     // its end, relative to the chunk
     const int rowbase = 4 * kg;
-    auto process = [&](const F& a, int bs) {
+    auto process = [&](const F& a, int bs, bool wild = false) {
         int b = dend - bs;
         if (b > 16 || doc >= i1) {              // the block lies inside the current document
-            if (mine(doc)) block_mma<NT>(a, bq, h);
+            if (mine(doc)) block_mma<NT>(a, bq, h, wild);
             return;
         }
         int lo = 0;
         if (b == 16) {                          // it ends exactly with the block: no split needed
-            block_mma<NT>(a, bq, h);
+            block_mma<NT>(a, bq, h, wild);
             finalize(doc);
             ++doc;
             if (doc >= i1) return;
@@ -521,7 +523,7 @@ void k_dense(DenseArgs A) {
             // the usual case - one document end in the block - takes the fold specialised by the
             // row of the end (six and eight tiles only: it is 15 copies of the block's code)
             if (NT >= PACKED_NT && lo == 0 && bb >= 1 && bb <= 15) block_mma_split_rows<NT>(a, bq, h, hB, bb);
-            else block_mma_split<NT>(a, bq, h, hB, lo, bb, rowbase);
+            else block_mma_split<NT>(a, bq, h, hB, lo, bb, rowbase, wild);
             finalize(doc);
             ++doc;
             if (doc >= i1) return;
@@ -536,7 +538,7 @@ void k_dense(DenseArgs A) {
         }
     };
 
-    // ---- fp32: a stage's rows pass through registers, where they are cut into their three pieces (split3),
+    // ---- fp32: a stage's rows pass through registers, where they are cut into their three pieces (split_first),
     // once for all wavefronts (44 vector instructions a wavefront and stage at d = 128 and four wavefronts; each
     // for itself would take four times as many, as long as the matrix work of two tiles).  A thread takes
     // the 16 + 16 bytes that a lane of a wavefront holds of one k-step (Frag): one 16-byte piece in each plane.
@@ -548,7 +550,10 @@ void k_dense(DenseArgs A) {
         constexpr int THREADS = 64 * WAVES;
         constexpr int PER = (STAGE_ROWS * PIECES + THREADS - 1) / THREADS;
         constexpr int PLANE = RING_ROWS * PITCH, SLOT = STAGE_ROWS * PITCH;
-        f32x4_t raw[PER][2];
+        __shared__ int wild_stage[2];               // by slot: the stage (and one) if it holds a wild value (Frag)
+        if (threadIdx.x < 2) wild_stage[threadIdx.x] = 0;
+        __syncthreads();
+        f32x4_t raw[PER][2] = {};
         int prow[PER];
         unsigned src_off[PER], dst_off[PER];
 #pragma unroll
@@ -574,15 +579,17 @@ void k_dense(DenseArgs A) {
         };
         auto publish = [&](int s) {
             char* at = ring + (s & 1) * SLOT;
+            bf16x8_t hi[PER], mid, lo;
+            const bool wild = split_first<PER>(raw, hi);
 #pragma unroll
             for (int i = 0; i < PER; ++i)
                 if (has(i)) {
-                    bf16x8_t hi, mid, lo;
-                    split3(raw[i][0], raw[i][1], hi, mid, lo);
-                    *(bf16x8_t*)(at + dst_off[i]) = hi;
+                    split_rest(raw[i], hi[i], mid, lo);
+                    *(bf16x8_t*)(at + dst_off[i]) = hi[i];
                     *(bf16x8_t*)(at + PLANE + dst_off[i]) = mid;
                     *(bf16x8_t*)(at + 2 * PLANE + dst_off[i]) = lo;
                 }
+            if (wild) wild_stage[s & 1] = s + 1;
         };
         auto load_half = [&](F& a, int s, int half) {
             const char* rp = ring + (s & 1) * SLOT + half * (16 * PITCH);
@@ -602,8 +609,9 @@ void k_dense(DenseArgs A) {
             F a0, a1;
             load_half(a0, s, 0);
             load_half(a1, s, 1);
-            process(a0, bs);
-            if (bs + 16 < ntok) process(a1, bs + 16);
+            const bool wild = query_wild || __builtin_amdgcn_readfirstlane(wild_stage[s & 1]) == s + 1;
+            process(a0, bs, wild);
+            if (bs + 16 < ntok) process(a1, bs + 16, wild);
         }
         while (doc < i1) finalize(doc++);           // documents without tokens at the chunk's end
         return;
@@ -652,7 +660,7 @@ void k_dense(DenseArgs A) {
             if (run >= 1 && (bs & 16)) {        // to an even block: pairs never straddle a stage
                 load_aligned(a1, bs + 16);
                 __builtin_amdgcn_sched_barrier(0);
-                block_mma<NT>(a0, bq, h);
+                block_mma<NT>(a0, bq, h, false);
                 a0 = a1;
                 bs += 16;
                 --run;
@@ -661,16 +669,16 @@ void k_dense(DenseArgs A) {
             for (; run >= 2; run -= 2) {
                 if (at_boundary(bs)) stage_enter_full(bs);
                 load_aligned(a1, bs + 16);
-                block_mma<NT>(a0, bq, h);
+                block_mma<NT>(a0, bq, h, false);
                 load_aligned(a0, bs + 32);
-                block_mma<NT>(a1, bq, h);
+                block_mma<NT>(a1, bq, h, false);
                 bs += 32;
             }
             if (run == 1) {
                 if (at_boundary(bs)) stage_enter_full(bs);
                 load_aligned(a1, bs + 16);
                 __builtin_amdgcn_sched_barrier(0);
-                block_mma<NT>(a0, bq, h);
+                block_mma<NT>(a0, bq, h, false);
                 a0 = a1;
                 bs += 16;
             }

@@ -81,10 +81,10 @@ __device__ __forceinline__ bool dense_round(const unsigned long long* pairs_r,
 // Operand fragments for the 16x16 MFMA family.  One fragment holds, for the lane's row
 // (lane & 15) of a 16-row operand block, the d/4 elements that the lane's k-group
 // (lane >> 4) contributes.  A (document tokens) and B (query rows) use the same
-// k mapping, so every product q[k]*e[k] is formed exactly once.
+// k mapping, so every q[k] meets its e[k] once.
 //   bf16: v_mfma_f32_16x16x32_bf16, k-step s covers k in [32s, 32s+32); the lane
 //         holds k = 32s + 8*(lane>>4) .. +7 (one 16-byte load).
-//   fp32: the bf16 instruction on three bf16 pieces of each value (split3); k-step s covers
+//   fp32: the bf16 instruction on three bf16 pieces of each value (split_first); k-step s covers
 //         [32s, 32s+32), of which the lane holds 32s + 4*(lane>>4) .. +3 and the same 16 further
 //         on (two 16-byte loads, each 64 bytes of a row over the lanes).
 //   int8: v_mfma_i32_16x16x64_i8, k-step s covers k in [64s, 64s+64); the lane holds
@@ -100,20 +100,21 @@ template <int D> struct Frag<bf16_tag, D> {
     using val_t = float;
     bf16x8_t v[KS];
     using Raw = Frag;                               // as it comes from memory
-    __device__ __forceinline__ void from(const Raw& r) { *this = r; }
-    __device__ __forceinline__ void load(const void* row, int kgroup) {
+    __device__ __forceinline__ bool from(const Raw& r) { *this = r; return false; }
+    __device__ __forceinline__ bool load(const void* row, int kgroup) {
         const char* p = (const char*)row + kgroup * 16;
 #pragma unroll
         for (int s = 0; s < KS; ++s) v[s] = *(const bf16x8_t*)(p + s * 64);
+        return false;
     }
-    __device__ __forceinline__ static void mma(f32x4_t& acc, const Frag& a, const Frag& b) {
+    __device__ __forceinline__ static void mma(f32x4_t& acc, const Frag& a, const Frag& b, bool) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[s], b.v[s], acc, 0, 0, 0);
     }
     // two independent accumulation chains, interleaved step by step
     __device__ __forceinline__ static void mma2(f32x4_t& c0, f32x4_t& c1, const Frag& a,
-                                                const Frag& b0, const Frag& b1) {
+                                                const Frag& b0, const Frag& b1, bool) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[s], b0.v[s], c0, 0, 0, 0);
@@ -123,23 +124,51 @@ template <int D> struct Frag<bf16_tag, D> {
 };
 
 // Three bf16 values whose sum is x: each takes the leading 8 bits of what the ones before it left
-// (rounded to nearest, so the remainders carry signs of their own), 24 bits in all.  Exact for every
-// x up to 3.38e38 whose last piece is not below bf16's smallest number.
-__device__ __forceinline__ void split3(const f32x4_t& a, const f32x4_t& b, bf16x8_t& hi, bf16x8_t& mid, bf16x8_t& lo) {
-    const f32x8_t x = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-    hi = __builtin_convertvector(x, bf16x8_t);
-    const f32x8_t r = x - __builtin_convertvector(hi, f32x8_t);
+// (rounded to nearest, so the remainders carry signs of their own), 24 bits in all.  Exact for every finite x
+// of 2^-110 or more; of smaller ones what lies below bf16's smallest number, 2^-133, is lost.
+// split_first: the first pieces of P times eight values, and whether any of these is infinite, NaN or
+// of 2^40 or more (Frag::mma).  A large x whose rounding would be infinite is rounded towards zero instead (the
+// remainder's 16 bits fit the other two).  Both are looked for only where some value is 2 or more.
+template <int P>
+__device__ __forceinline__ bool split_first(const f32x4_t (&x)[P][2], bf16x8_t (&hi)[P]) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        hi[p] = __builtin_convertvector(__builtin_shufflevector(x[p][0], x[p][1], 0, 1, 2, 3, 4, 5, 6, 7), bf16x8_t);
+        const u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
+        any |= w[0] | w[1] | w[2] | w[3];
+    }
+    bool wild = false;
+    if ((any & 0x40004000u) != 0u) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t mag = __float_as_uint(x[p][i >> 2][i & 3]) & 0x7fffffffu;
+                wild |= mag >= 0x53800000u;
+                if (mag - 0x7f7f8000u < 0x8000u) w[i >> 1] -= i & 1 ? 0x10000u : 1u;
+            }
+            hi[p] = __builtin_bit_cast(bf16x8_t, w);
+        }
+    }
+    return wild;
+}
+__device__ __forceinline__ void split_rest(const f32x4_t (&x)[2], const bf16x8_t& hi, bf16x8_t& mid, bf16x8_t& lo) {
+    const f32x8_t r = __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7) - __builtin_convertvector(hi, f32x8_t);
     mid = __builtin_convertvector(r, bf16x8_t);
     lo = __builtin_convertvector(r - __builtin_convertvector(mid, f32x8_t), bf16x8_t);
 }
 
 // The fp32 pipes take a sixteenth of the bf16 pipes' rate, so a product of fp32 values is made of six
 // bf16 products of their pieces, smallest first: lo*hi + hi*lo + mid*mid + mid*hi + hi*mid, then hi*hi.
-// The three left out (mid*lo, lo*mid, lo*lo) are 2^-25 of a product at most and of
+// The three left out (mid*lo, lo*mid, lo*lo) are 2^-24 of a product at most, together, and of
 // either sign; what is left is the rounding of the fp32 sums.  16 queries x 20,000 documents: 2,148 ->
 // 1,290 us, error against 64 bits 5.2e-8 -> 4.3e-8.
-// An infinity's pieces are inf, NaN, NaN: hi*hi is what the product of the values would be, and the sum of
-// the others is kept finite before it (med3 of a NaN is the least of the other two; 2 %, d = 32 6 %).
+// wild: some value is infinite, NaN or large (split_first).  The smaller products of an infinity are NaN or of
+// either sign, and those of two large values may overflow where hi*hi says by itself what their
+// product would be: their sum is made finite before hi*hi is added, by integer instructions (this
+// code is compiled without regard to NaN).
 template <int D> struct Frag<f32_tag, D> {
     static constexpr int KS = D / 32;
     static constexpr int ELEM_BYTES = 4;
@@ -147,42 +176,46 @@ template <int D> struct Frag<f32_tag, D> {
     using val_t = float;
     bf16x8_t v[3][KS];                              // hi, mid, lo
     struct Raw {
-        f32x4_t x[2 * KS];
+        f32x4_t x[KS][2];
         __device__ __forceinline__ void load(const void* row, int kgroup) {
             const char* p = (const char*)row + kgroup * 16;
 #pragma unroll
-            for (int j = 0; j < 2 * KS; ++j) x[j] = *(const f32x4_t*)(p + j * 64);
+            for (int j = 0; j < 2 * KS; ++j) x[j >> 1][j & 1] = *(const f32x4_t*)(p + j * 64);
         }
     };
-    __device__ __forceinline__ void from(const Raw& r) {
+    __device__ __forceinline__ bool from(const Raw& r) {
+        const bool wild = split_first<KS>(r.x, v[0]);
 #pragma unroll
-        for (int s = 0; s < KS; ++s) split3(r.x[2 * s], r.x[2 * s + 1], v[0][s], v[1][s], v[2][s]);
+        for (int s = 0; s < KS; ++s) split_rest(r.x[s], v[0][s], v[1][s], v[2][s]);
+        return wild;
     }
-    __device__ __forceinline__ void load(const void* row, int kgroup) {
+    __device__ __forceinline__ bool load(const void* row, int kgroup) {
         Raw r;
         r.load(row, kgroup);
-        from(r);
+        return from(r);
     }
     static constexpr int PIECE[5][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}};
-    __device__ __forceinline__ static f32x4_t finite(const f32x4_t& x) {
-        f32x4_t y;
+    __device__ __forceinline__ static void make_finite(f32x4_t& x) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[i] = __builtin_amdgcn_fmed3f(x[i], -3e38f, 3e38f);
-        return y;
+        for (int i = 0; i < 4; ++i) {               // to +-3e38: positive bits order as integers, negative as unsigned ones
+            const int p = (int)__float_as_uint(x[i]);
+            const uint32_t n = (uint32_t)(p < 0x7f61b1e6 ? p : 0x7f61b1e6);
+            x[i] = __uint_as_float(n < 0xff61b1e6u ? n : 0xff61b1e6u);
+        }
     }
     // (acc: zero on entry)
-    __device__ __forceinline__ static void mma(f32x4_t& acc, const Frag& a, const Frag& b) {
+    __device__ __forceinline__ static void mma(f32x4_t& acc, const Frag& a, const Frag& b, bool wild) {
 #pragma unroll
         for (int p = 0; p < 5; ++p)
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[PIECE[p][0]][s], b.v[PIECE[p][1]][s], acc, 0, 0, 0);
-        acc = finite(acc);
+        if (wild) make_finite(acc);
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[0][s], b.v[0][s], acc, 0, 0, 0);
     }
     __device__ __forceinline__ static void mma2(f32x4_t& c0, f32x4_t& c1, const Frag& a,
-                                                const Frag& b0, const Frag& b1) {
+                                                const Frag& b0, const Frag& b1, bool wild) {
 #pragma unroll
         for (int p = 0; p < 5; ++p)
 #pragma unroll
@@ -190,8 +223,10 @@ template <int D> struct Frag<f32_tag, D> {
                 c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[PIECE[p][0]][s], b0.v[PIECE[p][1]][s], c0, 0, 0, 0);
                 c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[PIECE[p][0]][s], b1.v[PIECE[p][1]][s], c1, 0, 0, 0);
             }
-        c0 = finite(c0);
-        c1 = finite(c1);
+        if (wild) {
+            make_finite(c0);
+            make_finite(c1);
+        }
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[0][s], b0.v[0][s], c0, 0, 0, 0);
@@ -207,19 +242,20 @@ template <int D> struct Frag<i8_tag, D> {
     using val_t = int;
     i32x4_t v[KS];
     using Raw = Frag;
-    __device__ __forceinline__ void from(const Raw& r) { *this = r; }
-    __device__ __forceinline__ void load(const void* row, int kgroup) {
+    __device__ __forceinline__ bool from(const Raw& r) { *this = r; return false; }
+    __device__ __forceinline__ bool load(const void* row, int kgroup) {
         const char* p = (const char*)row + kgroup * 16;
 #pragma unroll
         for (int s = 0; s < KS; ++s) v[s] = *(const i32x4_t*)(p + s * 64);
+        return false;
     }
-    __device__ __forceinline__ static void mma(i32x4_t& acc, const Frag& a, const Frag& b) {
+    __device__ __forceinline__ static void mma(i32x4_t& acc, const Frag& a, const Frag& b, bool) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
             acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.v[s], b.v[s], acc, 0, 0, 0);
     }
     __device__ __forceinline__ static void mma2(i32x4_t& c0, i32x4_t& c1, const Frag& a,
-                                                const Frag& b0, const Frag& b1) {
+                                                const Frag& b0, const Frag& b1, bool) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             c0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.v[s], b0.v[s], c0, 0, 0, 0);
@@ -255,21 +291,21 @@ __device__ __forceinline__ int fold_max(int h, const i32x4_t& c) {
 // One block of 16 document tokens against NT column tiles, folded into the running
 // maxima h.  Tiles go in pairs: the two accumulation chains of a pair are interleaved
 // (no back-to-back dependent MFMAs) and a pair's maxima are taken while the next pair's
-// MFMAs run.
+// MFMAs run.  wild (uniform; fp32 only): see Frag<f32_tag>.
 template <int NT, class F>
 __device__ __forceinline__ void block_mma(const F& a, const F (&bq)[NT],
-                                          typename F::val_t (&h)[NT]) {
+                                          typename F::val_t (&h)[NT], bool wild) {
     using acc_t = typename F::acc_t;
     if constexpr (NT == 1) {
         acc_t acc = {0, 0, 0, 0};
-        F::mma(acc, a, bq[0]);
+        F::mma(acc, a, bq[0], wild);
         h[0] = fold_max(h[0], acc);
     } else {
         acc_t p0 = {0, 0, 0, 0}, p1 = p0;
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) {
             acc_t c0 = {0, 0, 0, 0}, c1 = c0;
-            F::mma2(c0, c1, a, bq[2 * p], bq[2 * p + 1]);
+            F::mma2(c0, c1, a, bq[2 * p], bq[2 * p + 1], wild);
             if (p > 0) {
                 h[2 * p - 2] = fold_max(h[2 * p - 2], p0);
                 h[2 * p - 1] = fold_max(h[2 * p - 1], p1);
@@ -304,7 +340,7 @@ template <int NT, class F>
 __device__ __forceinline__ void block_mma_split(const F& a, const F (&bq)[NT],
                                                 typename F::val_t (&hA)[NT],
                                                 typename F::val_t (&hB)[NT], int lo, int b,
-                                                int rowbase) {
+                                                int rowbase, bool wild) {
     using acc_t = typename F::acc_t;
     bool inA[4], inB[4];
 #pragma unroll
@@ -315,13 +351,13 @@ __device__ __forceinline__ void block_mma_split(const F& a, const F (&bq)[NT],
     }
     if constexpr (NT == 1) {
         acc_t acc = {0, 0, 0, 0};
-        F::mma(acc, a, bq[0]);
+        F::mma(acc, a, bq[0], wild);
         fold_split(hA[0], hB[0], acc, inA, inB);
     } else {
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) {
             acc_t c0 = {0, 0, 0, 0}, c1 = c0;
-            F::mma2(c0, c1, a, bq[2 * p], bq[2 * p + 1]);
+            F::mma2(c0, c1, a, bq[2 * p], bq[2 * p + 1], wild);
             fold_split(hA[2 * p], hB[2 * p], c0, inA, inB);
             fold_split(hA[2 * p + 1], hB[2 * p + 1], c1, inA, inB);
         }
@@ -418,13 +454,13 @@ __device__ __forceinline__ void block_mma_split_at(const F& a, const F (&bq)[NT]
     using acc_t = typename F::acc_t;
     if constexpr (NT == 1) {
         acc_t acc = {0, 0, 0, 0};
-        F::mma(acc, a, bq[0]);
+        F::mma(acc, a, bq[0], false);
         fold_split_at<KB, KR>(hA[0], hB[0], acc);
     } else {
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) {
             acc_t c0 = {0, 0, 0, 0}, c1 = c0;
-            F::mma2(c0, c1, a, bq[2 * p], bq[2 * p + 1]);
+            F::mma2(c0, c1, a, bq[2 * p], bq[2 * p + 1], false);
             fold_split_at<KB, KR>(hA[2 * p], hB[2 * p], c0);
             fold_split_at<KB, KR>(hA[2 * p + 1], hB[2 * p + 1], c1);
         }

@@ -226,7 +226,8 @@ template <int TQ, class F> constexpr int round_waves() {
 // Folds the blocks first, first + stride, ... of the document [o0, o1) into h.
 template <int ROWB, int NT, class F>
 __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o1, int first, int stride,
-                                         int col, int kg, const F (&bq)[NT], typename F::val_t (&h)[NT]) {
+                                         int col, int kg, const F (&bq)[NT], bool query_wild,
+                                         typename F::val_t (&h)[NT]) {
     int64_t r0 = o0 + 16 * first;
     if (r0 >= o1) return;
     using R = typename F::Raw;
@@ -242,13 +243,13 @@ __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o
         const int64_t r1 = r0 + 16 * stride;
         const bool more = r1 < o1;
         F a;
-        a.from(raw);
+        const bool wild = __ballot(a.from(raw)) != 0ull || query_wild;
         R next;
         if (AHEAD && more) load(next, r1);
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) {
             typename F::acc_t acc = {0, 0, 0, 0};
-            F::mma(acc, a, bq[tt]);
+            F::mma(acc, a, bq[tt], wild);
             h[tt] = fold_max(h[tt], acc);
         }
         if (!more) return;
@@ -298,15 +299,17 @@ __device__ __forceinline__ void doc_range(const GatherArgs& A, int id, int64_t& 
     o1 = o1 < o0 ? o0 : (o1 > A.total ? A.total : o1);
 }
 
-// the T rows of a query as the B operands of TQ column tiles
+// the T rows of a query as the B operands of TQ column tiles; whether any of their values is wild (Frag)
 template <class F, int ROWB, int TQ>
-__device__ __forceinline__ void load_query(const GatherArgs& A, int q, int col, int kg, F (&bq)[TQ]) {
+__device__ __forceinline__ bool load_query(const GatherArgs& A, int q, int col, int kg, F (&bq)[TQ]) {
     const char* Qq = (const char*)A.Q + (size_t)q * A.T * ROWB;
+    bool wild = false;
 #pragma unroll
     for (int tt = 0; tt < TQ; ++tt) {
         const int t = tt * 16 + col;
-        bq[tt].load(Qq + (size_t)(t < A.T ? t : 0) * ROWB, kg);
+        wild |= bq[tt].load(Qq + (size_t)(t < A.T ? t : 0) * ROWB, kg);
     }
+    return __ballot(wild) != 0ull;
 }
 
 constexpr int64_t ALL_DOCS = 64;
@@ -422,13 +425,13 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
         if (!CACHE_ALL && (!list || count > A.cache_cap)) {
             F bq[1];
             const int trow = A.pi[(size_t)q * A.T + A.lo + (col < A.nb ? col : 0)];
-            bq[0].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg);
+            const bool query_wild = __ballot(bq[0].load((const char*)A.Q + ((size_t)q * A.T + trow) * ROWB, kg)) != 0ull;
             for (; k < k_end; ++k) {
                 const int id = list ? list[k] : k;
                 int64_t o0, o1;
                 doc_range(A, id, o0, o1);
                 V h[1] = {lowest_val<V>()};
-                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, h);
+                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
                 float w[1];
                 doc_cells(h, parts, scale, ex, w);
                 float sb, m2b;
@@ -444,7 +447,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
         } else {
             using P = Pack<TQ>;
             F bq[TQ];
-            load_query<F, ROWB, TQ>(A, q, col, kg, bq);
+            const bool query_wild = load_query<F, ROWB, TQ>(A, q, col, kg, bq);
             const int row = lane >> 4;
             // this round's batch: slot s (lane s of row 0) fetches cell pi[lo+s] from its owner
             const int t = CACHE_ALL ? 0 : A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
@@ -457,7 +460,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
                 V h[TQ];
 #pragma unroll
                 for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, h);
+                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
                 float w[P::NW];
                 doc_cells(h, parts, scale, ex, w);
                 if (coop && wave > 0) continue;
@@ -520,7 +523,7 @@ __global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
     const int col = lane & 15;
     const int kg = lane >> 4;
     F bq[TQ];
-    load_query<F, ROWB, TQ>(A, q, col, kg, bq);
+    const bool query_wild = load_query<F, ROWB, TQ>(A, q, col, kg, bq);
     for (int k = blockIdx.x; k < c.count; k += gridDim.x) {
         int id = list ? list[k] : k;
         if (slot_ids) id = slot_ids[id];
@@ -529,7 +532,7 @@ __global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
         V h[TQ];
 #pragma unroll
         for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-        fold_doc<ROWB>((const char*)A.docs, o0, o1, wave, 4, col, kg, bq, h);
+        fold_doc<ROWB>((const char*)A.docs, o0, o1, wave, 4, col, kg, bq, query_wild, h);
         float w[Pack<TQ>::NW];
         doc_cells(h, 4, 1.f, ex, w);
         using SC = Score<TQ, TQ>;
@@ -556,14 +559,14 @@ __global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
     const int first = A.shared ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
     if (first >= (int)A.N) return;                  // shared: the same for the whole workgroup
     F bq[TQ];
-    load_query<F, ROWB, TQ>(A, q, col, kg, bq);
+    const bool query_wild = load_query<F, ROWB, TQ>(A, q, col, kg, bq);
     for (int id = first; id < (int)A.N; id += (int)gridDim.x * (4 / parts)) {
         int64_t o0, o1;
         doc_range(A, id, o0, o1);
         V h[TQ];
 #pragma unroll
         for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-        fold_doc<ROWB>((const char*)A.docs, o0, o1, A.shared ? wave : 0, parts, col, kg, bq, h);
+        fold_doc<ROWB>((const char*)A.docs, o0, o1, A.shared ? wave : 0, parts, col, kg, bq, query_wild, h);
         float w[Pack<TQ>::NW];
         doc_cells(h, parts, 1.f, ex, w);
         if (A.shared && wave > 0) continue;

@@ -284,7 +284,7 @@ def test_fp32_products_on_the_bf16_pipes_keep_fp32_precision(B, S, nq, T, d, pas
     either sign, some short of bits, and some infinite: a cell is the largest sum, each within the rounding of
     an fp32 sum whatever its order.  A sum takes at most 6 d / 32 = 24 instructions and each of them five levels
     of additions, at a rounding (2^-24) of the magnitudes' sum each: 29 roundings; truncation instead of
-    rounding would double it: 64 are allowed, which also covers the pieces left out (3 * 2^-25)."""
+    rounding would double it: 64 are allowed, which also covers the pieces left out (2^-24)."""
     lengths = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 5]
     if pas:
         lengths = _past_small(lengths, nq, d, "f32")
@@ -312,6 +312,48 @@ def test_fp32_products_on_the_bf16_pipes_keep_fp32_precision(B, S, nq, T, d, pas
     mag = torch.zeros_like(cells).scatter_reduce(0, doc[:, None].expand_as(dots), mags, "amax")
     fin = torch.isfinite(ref)
     assert torch.equal(cells[~fin], ref[~fin]) and (~fin).any()
+    assert ((cells - ref).abs() <= 64 * 2.0 ** -24 * mag)[fin].all()
+
+
+@pytest.mark.parametrize("nq,T,d,N,kernel", [(1, 32, 128, 300, "k_gather_all"), (2, 50, 96, 300, "k_gather_all"),
+                                             (1, 16, 32, 300, "k_gather_all"), (32, 32, 128, 1000, "k_dense"),
+                                             (40, 32, 32, 1000, "k_dense"), (32, 32, 64, 1000, "k_dense")])
+def test_fp32_components_as_large_as_they_get(B, nq, T, d, N, kernel):
+    """Components between bf16's largest number and fp32's, which a rounding to bf16 would make infinite, and around
+    the limits from which the pieces are looked at (2, 2^40), keep the precision of fp32; products that
+    overflow are infinite, and so are those of an infinity.  Bound: as for ordinary components, 64 roundings
+    of the magnitudes' sum."""
+    g = torch.Generator(device="cuda").manual_seed(nq + d)
+    lengths = torch.randint(1, 95, (N,), generator=g, device="cuda")
+    off = torch.zeros(N + 1, dtype=torch.int64, device="cuda")
+    off[1:] = torch.cumsum(lengths, 0)
+    n = int(off[-1])
+    docs = torch.randn((n, d), generator=g, device="cuda")
+    Q = torch.randn((nq, T, d), generator=g, device="cuda") * 2.0 ** -30
+    top = torch.tensor([0x7f7fffff, 0x7f7f8000, 0x7f7f7fff, 0x7f7f0001, 0x7e123457, 0x537fffff, 0x53800001, 0x40000000, 0x3fffffff],
+                       dtype=torch.int32, device="cuda").view(torch.float32)
+    at = torch.randperm(n, generator=g, device="cuda")
+    for i in range(6 * top.numel()):                    # one large component in a token
+        docs[at[i], (7 * i) % d] = top[i % top.numel()] * (1 if i % 4 < 2 else -1)
+    a, b = at[100], at[101]
+    docs[a, 5], docs[b, d - 1] = 1.2345678 * 2.0 ** 100, float("inf")
+    q = nq - 1
+    Q[q, 0, 5], Q[q, 1, 5] = 1.3456789 * 2.0 ** 60, -1.3456789 * 2.0 ** 60     # both signs: one overflows to +inf
+    Q[q, 2, 9] = float("inf")
+    res = []
+    names = _kernels(lambda: B.colbandit_full_maxsim(Q, docs, off, K=1, want_cells=True), res)
+    assert kernel + "<cb::f32_tag" in names
+    cells = res[0]["cells"].permute(1, 0, 2).reshape(N, nq * T).double()
+    E, R = docs.double(), Q.reshape(nq * T, d).double()
+    doc = torch.repeat_interleave(torch.arange(N, device="cuda"), lengths)
+    dots = E @ R.t()
+    dots = torch.nan_to_num(dots, nan=-float("inf"), posinf=float("inf"), neginf=-float("inf"))
+    dots[dots > 3.5e38], dots[dots < -3.5e38] = float("inf"), -float("inf")
+    mags = torch.where(torch.isfinite(E), E, 0).abs() @ torch.where(torch.isfinite(R), R, 0).abs().t()
+    ref = torch.full_like(cells, -float("inf")).scatter_reduce(0, doc[:, None].expand_as(dots), dots, "amax")
+    mag = torch.zeros_like(cells).scatter_reduce(0, doc[:, None].expand_as(dots), mags, "amax")
+    fin = torch.isfinite(ref)
+    assert (ref == float("inf")).any() and torch.equal(cells[~fin], ref[~fin])
     assert ((cells - ref).abs() <= 64 * 2.0 ** -24 * mag)[fin].all()
 
 
