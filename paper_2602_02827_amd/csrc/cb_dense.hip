@@ -580,7 +580,7 @@ void k_dense(DenseArgs A) {
         auto publish = [&](int s) {
             char* at = ring + (s & 1) * SLOT;
             bf16x8_t hi[PER], mid, lo;
-            const bool wild = split_first<PER>(raw, hi);
+            split_first<PER>(raw, hi, [&]() { wild_stage[s & 1] = s + 1; });
 #pragma unroll
             for (int i = 0; i < PER; ++i)
                 if (has(i)) {
@@ -589,7 +589,6 @@ void k_dense(DenseArgs A) {
                     *(bf16x8_t*)(at + PLANE + dst_off[i]) = mid;
                     *(bf16x8_t*)(at + 2 * PLANE + dst_off[i]) = lo;
                 }
-            if (wild) wild_stage[s & 1] = s + 1;
         };
         auto load_half = [&](F& a, int s, int half) {
             const char* rp = ring + (s & 1) * SLOT + half * (16 * PITCH);
@@ -606,10 +605,11 @@ void k_dense(DenseArgs A) {
             __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): this wavefront's pieces are written
             ring_barrier();
             const int bs = s * STAGE_ROWS;
+            const int flag = wild_stage[s & 1];     // (read first: its wait is not one for the operands)
             F a0, a1;
             load_half(a0, s, 0);
             load_half(a1, s, 1);
-            const bool wild = query_wild || __builtin_amdgcn_readfirstlane(wild_stage[s & 1]) == s + 1;
+            const bool wild = query_wild | (__builtin_amdgcn_readfirstlane(flag) == s + 1);
             process(a0, bs, wild);
             if (bs + 16 < ntok) process(a1, bs + 16, wild);
         }

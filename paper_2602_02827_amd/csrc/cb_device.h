@@ -126,11 +126,11 @@ template <int D> struct Frag<bf16_tag, D> {
 // Three bf16 values whose sum is x: each takes the leading 8 bits of what the ones before it left
 // (rounded to nearest, so the remainders carry signs of their own), 24 bits in all.  Exact for every finite x
 // of 2^-110 or more; of smaller ones what lies below bf16's smallest number, 2^-133, is lost.
-// split_first: the first pieces of P times eight values, and whether any of these is infinite, NaN or
+// split_first: the first pieces of P times eight values; calls on_wild where one of these is infinite, NaN or
 // of 2^40 or more (Frag::mma).  A large x whose rounding would be infinite is rounded towards zero instead (the
 // remainder's 16 bits fit the other two).  Both are looked for only where some value is 2 or more.
-template <int P>
-__device__ __forceinline__ bool split_first(const f32x4_t (&x)[P][2], bf16x8_t (&hi)[P]) {
+template <int P, class W>
+__device__ __forceinline__ void split_first(const f32x4_t (&x)[P][2], bf16x8_t (&hi)[P], W&& on_wild) {
     uint32_t any = 0;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -138,8 +138,8 @@ __device__ __forceinline__ bool split_first(const f32x4_t (&x)[P][2], bf16x8_t (
         const u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
         any |= w[0] | w[1] | w[2] | w[3];
     }
-    bool wild = false;
-    if ((any & 0x40004000u) != 0u) {
+    if (__ballot((any & 0x40004000u) != 0u) != 0ull) {
+        bool wild = false;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
@@ -151,8 +151,8 @@ __device__ __forceinline__ bool split_first(const f32x4_t (&x)[P][2], bf16x8_t (
             }
             hi[p] = __builtin_bit_cast(bf16x8_t, w);
         }
+        if (wild) on_wild();
     }
-    return wild;
 }
 __device__ __forceinline__ void split_rest(const f32x4_t (&x)[2], const bf16x8_t& hi, bf16x8_t& mid, bf16x8_t& lo) {
     const f32x8_t r = __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7) - __builtin_convertvector(hi, f32x8_t);
@@ -184,7 +184,8 @@ template <int D> struct Frag<f32_tag, D> {
         }
     };
     __device__ __forceinline__ bool from(const Raw& r) {
-        const bool wild = split_first<KS>(r.x, v[0]);
+        bool wild = false;
+        split_first<KS>(r.x, v[0], [&]() { wild = true; });
 #pragma unroll
         for (int s = 0; s < KS; ++s) split_rest(r.x[s], v[0][s], v[1][s], v[2][s]);
         return wild;
