@@ -207,24 +207,28 @@ template <int NT, class F> constexpr int gather_regs(bool ahead) {
     return (NT + 1) * ((int)sizeof(F) / 4) + (ahead ? (int)sizeof(typename F::Raw) / 4 + 8 * NT : 36);
 }
 constexpr int waves_of(int regs) { return 512 / regs < 4 ? 512 / regs : 4; }
-// Whether a second block of a document is in flight: where its registers do not cost a wavefront per
-// SIMD.
-template <int NT, class F> constexpr bool two_in_flight() {
-    if constexpr (__is_same(typename F::Raw, F)) return gather_regs<NT, F>(true) <= 112;
-    else return waves_of(gather_regs<NT, F>(true) + 28) >= waves_of(gather_regs<NT, F>(false));
-}
+// fp32: a block is cut into its pieces after it was read
+template <class F> constexpr bool cuts() { return !__is_same(typename F::Raw, F); }
+// Whether a second block of a document is in flight.  bf16 and codes: where its registers do not cost a wavefront
+// per SIMD.
+// fp32 always in the kernels that only score, held to the wavefronts that its registers leave (one query x
+// 200 documents of 1,030 tokens in d = 96, T = 32: 28.5 -> 24.0 us, T = 48 35.3 -> 30.0; d = 64 23.9 -> 19.2), and
+// never in those of a round, which have no registers for it: d = 128 and T <= 16 took 197, two wavefronts
+// (20,000 documents x 4 queries, Col-Bandit, 267 -> 257 us), and held to three they spill.
+template <int NT, class F> constexpr bool score_ahead() { return cuts<F>() || gather_regs<NT, F>(true) <= 112; }
+template <int NT, class F> constexpr bool round_ahead() { return !cuts<F>() && gather_regs<NT, F>(true) <= 112; }
+template <int TQ, class F> constexpr int score_waves() { return cuts<F>() ? waves_of(gather_regs<TQ, F>(true)) : 1; }
 // Wavefronts per SIMD of k_gather_round, which serves two kinds of list and without a bound takes a few
 // registers too many for the four (or what the query rows leave) that a kernel with one block in
 // flight needs (T = 48, 50,000 documents x 16 queries 1,645 -> 1,546 us a call, T = 100 and d = 96, 20,000
 // x 16 1,005 -> 908).
 // fp32 needs some for a block on its way from what was read to its pieces.
 template <int TQ, class F> constexpr int round_waves() {
-    constexpr int CUT = __is_same(typename F::Raw, F) ? 0 : 16;
-    return two_in_flight<TQ, F>() ? 1 : waves_of(gather_regs<TQ, F>(false) + CUT);
+    return round_ahead<TQ, F>() ? 1 : waves_of(gather_regs<TQ, F>(false) + (cuts<F>() ? 16 : 0));
 }
 
 // Folds the blocks first, first + stride, ... of the document [o0, o1) into h.
-template <int ROWB, int NT, class F>
+template <int ROWB, bool AHEAD, int NT, class F>
 __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o1, int first, int stride,
                                          int col, int kg, const F (&bq)[NT], bool query_wild,
                                          typename F::val_t (&h)[NT]) {
@@ -236,7 +240,6 @@ __device__ __forceinline__ void fold_doc(const char* docs, int64_t o0, int64_t o
         row = row < o1 ? row : o1 - 1;
         a.load(docs + (size_t)row * ROWB, kg);
     };
-    constexpr bool AHEAD = two_in_flight<NT, F>();
     R raw;
     load(raw, r0);
     for (;;) {
@@ -431,7 +434,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
                 int64_t o0, o1;
                 doc_range(A, id, o0, o1);
                 V h[1] = {lowest_val<V>()};
-                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
+                fold_doc<ROWB, round_ahead<1, F>()>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
                 float w[1];
                 doc_cells(h, parts, scale, ex, w);
                 float sb, m2b;
@@ -460,7 +463,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
                 V h[TQ];
 #pragma unroll
                 for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-                fold_doc<ROWB>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
+                fold_doc<ROWB, round_ahead<TQ, F>()>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
                 float w[P::NW];
                 doc_cells(h, parts, scale, ex, w);
                 if (coop && wave > 0) continue;
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_cach
 // few: latency).  128 queries x 10 pairs of 106 tokens that no cache holds: 87 us with a
 // wavefront per pair and one block in flight, 12 us so; 64 queries x 10 pages of 1,030 tokens 81 -> 18.
 template <typename Tag, int D, int TQ>
-__global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
+__global__ __launch_bounds__(256, (score_waves<TQ, Frag<Tag, D>>())) void k_gather_survivors(GatherArgs A) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
@@ -532,7 +535,7 @@ __global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
         V h[TQ];
 #pragma unroll
         for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-        fold_doc<ROWB>((const char*)A.docs, o0, o1, wave, 4, col, kg, bq, query_wild, h);
+        fold_doc<ROWB, score_ahead<TQ, F>()>((const char*)A.docs, o0, o1, wave, 4, col, kg, bq, query_wild, h);
         float w[Pack<TQ>::NW];
         doc_cells(h, 4, 1.f, ex, w);
         using SC = Score<TQ, TQ>;
@@ -545,7 +548,7 @@ __global__ __launch_bounds__(256) void k_gather_survivors(GatherArgs A) {
 // All documents of all queries, a wavefront per pair, or (shared) a workgroup, whose wavefronts share
 // the document's blocks.
 template <typename Tag, int D, int TQ>
-__global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
+__global__ __launch_bounds__(256, (score_waves<TQ, Frag<Tag, D>>())) void k_gather_all(GatherArgs A) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(256) void k_gather_all(GatherArgs A) {
         V h[TQ];
 #pragma unroll
         for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
-        fold_doc<ROWB>((const char*)A.docs, o0, o1, A.shared ? wave : 0, parts, col, kg, bq, query_wild, h);
+        fold_doc<ROWB, score_ahead<TQ, F>()>((const char*)A.docs, o0, o1, A.shared ? wave : 0, parts, col, kg, bq, query_wild, h);
         float w[Pack<TQ>::NW];
         doc_cells(h, parts, 1.f, ex, w);
         if (A.shared && wave > 0) continue;
