@@ -34,9 +34,9 @@ struct SelState {                 // per segment, in the workspace
     uint32_t prefix, mask;        // key bits fixed so far
     uint32_t bound;               // k_quant_tail: values below it are not counted
     uint32_t done;                // 1: the clip is known; 2: the codes are written as well; GUESSED: prefix is
-                                  // what a part of the segment says
+                                  // what a part of the segment says; NO_TAIL: the bound is of no use
 };
-constexpr uint32_t GUESSED = 4;
+constexpr uint32_t FOUND = 3, GUESSED = 4, NO_TAIL = 8;
 
 template <bool BF16>
 __device__ __forceinline__ uint32_t abs_key(const void* x, int64_t i) {
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(QH_THREADS) void k_quant_hist(const void* x, int64_
     for (int i = threadIdx.x; i < QH_BINS; i += QH_THREADS) lh[i] = 0;
     __syncthreads();
     const SelState s = st[seg];
-    if (s.done) return;
+    if (s.done & FOUND) return;
     const uint32_t prefix = s.prefix, mask = s.mask;
     const int64_t base = seg * seg_elems;
     // a block's share stays below 2^32 elements (the launch gives every block <= 2^32)
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(64) void k_quant_pick(SelState* st, unsigned long l
     const int64_t seg = blockIdx.x;
     unsigned long long* gh = hist + seg * QH_BINS;
     const SelState s = st[seg];
-    if (s.done) return;
+    if (s.done & FOUND) return;
     const SelState next = pick_bin(s, gh, shift, nbins);
     if (threadIdx.x == 0) st[seg] = next;
     __syncthreads();
@@ -341,7 +341,8 @@ __global__ __launch_bounds__(64) void k_quant_guess(SelState* st, unsigned long 
     clear_bins(gh);
 }
 
-// After the count of the whole segment: its value of that rank.  A guess that it confirms has its codes.
+// After the count of the whole segment: its value of that rank.  A guess that it confirms has its codes; where
+// the count finds none (too few values from the bound on), another would not either.
 __global__ __launch_bounds__(64) void k_quant_tail_pick(SelState* st, unsigned long long* hist,
                                                         unsigned long long above, uint32_t when) {
     const int64_t seg = blockIdx.x;
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(64) void k_quant_tail_pick(SelState* st, unsigned l
     if (threadIdx.x == 0) {
         const uint32_t clip = found ? ((s.bound >> 16) + (uint32_t)bin) << 16 : 0u;
         st[seg].prefix = clip;
-        st[seg].done = !found ? 0u : s.done == GUESSED && clip == s.prefix ? 2u : 1u;
+        st[seg].done = !found ? NO_TAIL : s.done == GUESSED && clip == s.prefix ? 2u : 1u;
     }
     clear_bins(gh);
 }
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(QH_THREADS) void k_quant_codes(const void* x, int64
         for (int i = threadIdx.x; i < QH_BINS; i += QH_THREADS) lh[i] = 0;
     if (threadIdx.x < 64) {
         SelState s = st[seg];
-        if (nbins > 0 && !s.done) s = pick_bin(s, hist + seg * QH_BINS, BF16 ? 10 : 0, nbins);
+        if (nbins > 0 && !(s.done & FOUND)) s = pick_bin(s, hist + seg * QH_BINS, BF16 ? 10 : 0, nbins);
         if (threadIdx.x == 0) key = s.prefix;
     }
     __syncthreads();

@@ -1170,6 +1170,60 @@ def test_quantize_guesses_the_clip_of_a_very_long_segment(B, kind, done):
         assert torch.equal(codes[lo:lo + (1 << 19)], want)
 
 
+def _sampled(n, step):
+    """The places of n samples, one of each run of `step` (the library's sample_piece)."""
+    i = np.arange(n, dtype=np.uint32)
+    h = i * np.uint32(0x9E3779B1)
+    h = (h ^ (h >> np.uint32(15))) * np.uint32(0x85EBCA77)
+    h ^= h >> np.uint32(13)
+    at = i.astype(np.int64) * step + ((h.astype(np.uint64) * np.uint64(step)) >> np.uint64(32)).astype(np.int64)
+    return torch.from_numpy(at).cuda()
+
+
+@pytest.mark.parametrize("kind,permille,work", [
+    ("alike", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [0, 0], "k_quant_codes<true, true, false>": [0]}),
+    ("high", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [1, 1], "k_quant_codes<true, true, false>": [1]})])
+def test_passes_that_code_a_very_long_segment(B, kind, permille, work):
+    """Which passes read the segment (more than 60 us: a pass over 1.07 GB takes 150 at least, one that returns at
+    once 10 at most).  high: the sampled pieces
+    and the runs of the sixteenth are twice as large as the rest, the bound is too high for the whole segment, and
+    no second count is made with it."""
+    from torch.profiler import ProfilerActivity, profile
+    g = torch.Generator(device="cuda").manual_seed(13)
+    rows, d = 1 << 22, 128
+    n = rows * d
+    # (times 0.8594 the clip lies in the middle of the values that round to it, 3 % of the tail from either edge)
+    x = torch.randn((rows, d), generator=g, device="cuda") * 0.8594
+    x = x.to(torch.bfloat16)
+    runs = x.view(-1, 2048)
+    if kind == "high":
+        runs[_sampled(n // 8 // 4096, 16)] *= 2
+        pieces = _sampled(16384, n // 8 // 16384)
+        pieces = pieces[~torch.isin(pieces // 256, _sampled(n // 8 // 4096, 16))]
+        x.view(-1, 8)[pieces] *= 2
+    B.colbandit_quantize_i8(x[:1024])
+    for _ in range(5):
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            codes, scales = B.colbandit_quantize_i8(x, permille=permille)
+            torch.cuda.synchronize()
+        ran = sorted((e.time_range.start, e.key, e.time_range.elapsed_us()) for e in p.events() if "k_quant" in e.key)
+        if ran:
+            break
+    got = {k: [int(us > 60) for _, name, us in ran if k in name] for k in work}
+    got["k_quant_tail"] = [int(us > 60) for _, name, us in ran if "k_quant_tail(" in name][len(work["k_quant_codes<true, true, true>"]):]
+    assert got == work, [(name, us) for _, name, us in ran]
+    counts = sum(torch.bincount((p.view(torch.int16) & 0x7fff).to(torch.int32), minlength=32768) for p in x.view(-1).split(1 << 27))
+    rank = (n * permille + 999) // 1000
+    key = int(torch.searchsorted(torch.cumsum(counts, 0), torch.tensor([rank], device="cuda"))[0])
+    clip = torch.tensor([key], dtype=torch.int16).view(torch.bfloat16).float().numpy()[0]
+    assert scales.cpu().numpy()[0] == clip / np.float32(127)
+    inv = float(np.float32(127) / clip)
+    for lo in range(0, rows, 1 << 19):
+        want = torch.clamp(torch.round(x[lo:lo + (1 << 19)].float() * inv), -127, 127).to(torch.int8)
+        assert torch.equal(codes[lo:lo + (1 << 19)], want)
+
+
 @pytest.mark.parametrize("nq,T,d", [(1, 32, 128), (5, 32, 128), (20, 24, 128), (3, 40, 128), (2, 100, 128),
                                     (4, 32, 64), (70, 16, 64)])
 def test_coarse_maxsim_cells_are_the_integer_maxima(B, S, oracle_mod, nq, T, d):
