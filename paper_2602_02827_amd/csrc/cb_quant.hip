@@ -175,10 +175,11 @@ constexpr int64_t QT_MIN_ELEMS = 1ll << 26;   // below, the sample and three lau
                                               // the atomics they save (1 us per million values)
 
 // From 2^29 values on a sixteenth of the segment is counted first.  bf16 values are so few that it names the clip
-// itself, but where the rank lies close to an edge of the values that round to it (at 6.8 G values of
-// unit vectors' components 0.6 % of the tail to either side, of 6 to 8).  Then one pass codes and counts, and
-// the count confirms the guess: 6.8 G values 6.58 -> 3.94 ms (20.4 GB; the pass 3.6 ms).  A guess that is wrong
-// after all costs a coding pass, none at all the sixteenth (0.17 ms).  (Below, the sixteenth's tail is too short to tell.)
+// itself, but where the rank lies close to an edge of the values that round to it (at 6.8 G independent
+// values 0.46 % of the tail to either side, of 6 to 8; k_quant_guess).  Then one pass codes and counts, and
+// the count confirms the guess: 6.8 G values 6.55 -> 3.95 ms (20.4 GB; the pass 3.6 ms).  No guess costs the
+// sixteenth (6.75 ms), one that is wrong after all a coding pass (8.09), and one made where the bound was
+// wrong too 13.9 ms in the place of 12.5.  (Below, the sixteenth's tail is too short to tell.)
 constexpr int64_t QT_GUESS_ELEMS = 1ll << 29;
 
 // Lower bound for k_quant_tail from pieces all over the segment (sample_piece): the largest histogram edge
@@ -230,7 +231,8 @@ __global__ __launch_bounds__(1024) void k_quant_sample(const void* x, int64_t se
 }
 
 // Counts those of 16 bytes' values that are at or above the bound in their bins: bf16 value relative to the
-// bound, the last bin takes the rest.  A few per mille of the values are.
+// bound, bin LAST takes the rest.  A few per mille of the values are.
+template <int LAST>
 __device__ __forceinline__ void count_tail(const u32x4_t& w, uint32_t lo, uint32_t* lh) {
     unsigned hit = 0;
 #pragma unroll
@@ -243,7 +245,7 @@ __device__ __forceinline__ void count_tail(const u32x4_t& w, uint32_t lo, uint32
         hit &= hit - 1;
         const uint32_t p = b < 4 ? (b < 2 ? w[0] : w[1]) : (b < 6 ? w[2] : w[3]);
         const uint32_t k = ((b & 1) ? p >> 16 : p) & 0x7fffu;
-        const uint32_t bin = k - lo < QH_BINS - 1 ? k - lo : QH_BINS - 1;
+        const uint32_t bin = k - lo < LAST ? k - lo : LAST;
         atomicAdd(&lh[bin], 1u);
     }
 }
@@ -254,37 +256,50 @@ __device__ __forceinline__ void flush_tail(const uint32_t* lh, unsigned long lon
 }
 
 // Counts the values at or above the bound.  Bound by memory: 6.8 G values (13.6 GB) in 2.42 ms = 5.6 TB/s;
-// the two histogram passes that it replaces took 3.49 and 2.38 ms.  part: of every 16 runs of 4 KB only one, at
-// a mixed place (sample_piece).
+// the two histogram passes that it replaces took 3.49 and 2.38 ms.  groups > 0: of every 16 runs of 4 KB only
+// one, at a mixed place (sample_piece), `groups` of them, as many in each workgroup; the two bins behind
+// PART_LAST take the sum of the workgroups' counts and of their squares.
 constexpr int QT_RUN = 256, QT_PART = 16;
+constexpr int PART_LAST = QH_BINS - 3;
 __global__ __launch_bounds__(QH_THREADS) void k_quant_tail(const void* x, int64_t seg_elems,
-                                                           const SelState* st, unsigned long long* hist, int part) {
+                                                           const SelState* st, unsigned long long* hist, int64_t groups) {
     __shared__ uint32_t lh[QH_BINS];
+    __shared__ uint32_t counted;
     static_assert(QT_RUN == QH_THREADS, "a workgroup takes a run at a time");
     const int64_t seg = blockIdx.y;
     if (st[seg].done) return;
     const uint32_t lo = st[seg].bound >> 16;
     for (int i = threadIdx.x; i < QH_BINS; i += QH_THREADS) lh[i] = 0;
+    if (threadIdx.x == 0) counted = 0;
     __syncthreads();
     const u32x4_t* xv = (const u32x4_t*)((const char*)x + seg * seg_elems * 2);
     const int64_t nv = seg_elems / 8;
-    if (part) {
-        const int64_t groups = nv / (QT_RUN * QT_PART);
+    unsigned long long* gh = hist + seg * QH_BINS;
+    if (groups > 0) {
         for (int64_t g = blockIdx.x; g < groups; g += gridDim.x)
-            count_tail(xv[sample_piece((uint32_t)g, QT_PART) * QT_RUN + threadIdx.x], lo, lh);
+            count_tail<PART_LAST>(xv[sample_piece((uint32_t)g, QT_PART) * QT_RUN + threadIdx.x], lo, lh);
+        __syncthreads();
+        uint32_t mine = 0;
+        for (int j = threadIdx.x; j < QH_BINS; j += QH_THREADS) mine += lh[j];
+        if (mine) atomicAdd(&counted, mine);
+        __syncthreads();
+        if (threadIdx.x == 0 && counted) {
+            atomicAdd(&gh[PART_LAST + 1], (unsigned long long)counted);
+            atomicAdd(&gh[PART_LAST + 2], (unsigned long long)counted * counted);
+        }
     } else {
         const int64_t stride = (int64_t)gridDim.x * QH_THREADS;
         int64_t i = (int64_t)blockIdx.x * QH_THREADS + threadIdx.x;
         for (; i + 3 * stride < nv; i += 4 * stride) {
             const u32x4_t a = xv[i], b = xv[i + stride], c = xv[i + 2 * stride], d = xv[i + 3 * stride];
-            count_tail(a, lo, lh);
-            count_tail(b, lo, lh);
-            count_tail(c, lo, lh);
-            count_tail(d, lo, lh);
+            count_tail<QH_BINS - 1>(a, lo, lh);
+            count_tail<QH_BINS - 1>(b, lo, lh);
+            count_tail<QH_BINS - 1>(c, lo, lh);
+            count_tail<QH_BINS - 1>(d, lo, lh);
         }
-        for (; i < nv; i += stride) count_tail(xv[i], lo, lh);
+        for (; i < nv; i += stride) count_tail<QH_BINS - 1>(xv[i], lo, lh);
     }
-    flush_tail(lh, hist + seg * QH_BINS);
+    flush_tail(lh, gh);
 }
 
 // What the counts of a wavefront's segment say of the value with `above` counted values at or above it: its
@@ -325,15 +340,24 @@ __device__ __forceinline__ void clear_bins(unsigned long long* gh) {
     for (int i = threadIdx.x; i < QH_BINS; i += 64) gh[i] = 0ull;
 }
 
-// After the count of a part: its value of that rank, if the counts put the rank three deviations (of their
-// square root) or more inside the values that round to it.
-__global__ __launch_bounds__(64) void k_quant_guess(SelState* st, unsigned long long* hist, unsigned long long above) {
+// After the count of a part: its value of that rank, if the counts put the rank three deviations or more of independent
+// values (the square root of the count) inside the values that round to it, and two of these.  These: how much
+// more the workgroups' counts vary.  Neighbouring rows of a corpus are alike; tokens of documents with a
+// topic vary 1.8 times as much in d = 128, 3 times in d = 64.  (A guess that is right 39 times of 40 saves 2.8 ms of 6.7
+// and costs 4.1 when it is wrong.)
+__global__ __launch_bounds__(64) void k_quant_guess(SelState* st, unsigned long long* hist, unsigned long long above,
+                                                    int workgroups) {
     const int64_t seg = blockIdx.x;
     unsigned long long* gh = hist + seg * QH_BINS;
+    const double sum = (double)gh[PART_LAST + 1], squares = (double)gh[PART_LAST + 2];
+    __syncthreads();
+    if (threadIdx.x < 2) gh[PART_LAST + 1 + threadIdx.x] = 0ull;
+    __syncthreads();
     int bin;
     unsigned long long higher, from;
-    const bool found = tail_bin(gh, above, bin, higher, from);
-    const double margin = 3.0 * sqrt((double)above);
+    const bool found = tail_bin(gh, above, bin, higher, from) && bin < PART_LAST;
+    const double mean = sum / workgroups, variance = (squares - sum * mean) / (workgroups - 1);
+    const double margin = fmax(3.0 * sqrt((double)above), 2.0 * sqrt((double)above * variance / fmax(mean, 1.0)));
     if (threadIdx.x == 0 && found && (double)(above - higher) >= margin && (double)(from - above) >= margin) {
         st[seg].prefix = ((st[seg].bound >> 16) + (uint32_t)bin) << 16;
         st[seg].done = GUESSED;
@@ -402,7 +426,7 @@ __global__ __launch_bounds__(QH_THREADS) void k_quant_codes(const void* x, int64
             u32x4_t w;
             if constexpr (STREAM) w = __builtin_nontemporal_load((const u32x4_t*)xv + i);
             else w = ((const u32x4_t*)xv)[i];
-            if constexpr (COUNT) count_tail(w, lo, lh);
+            if constexpr (COUNT) count_tail<QH_BINS - 1>(w, lo, lh);
             uint32_t packed[VEC / 4];
 #pragma unroll
             for (int j = 0; j < VEC / 4; ++j) packed[j] = 0;
@@ -547,10 +571,11 @@ hipError_t launch_quantize_i8(const void* x, int dt, int64_t n_segments, int64_t
         k_quant_sample<<<nseg, 1024, 0, st>>>(x, seg_elems, state, above);
         const dim3 tail((unsigned)(bx < 2048 ? bx : 2048), nseg);   // eight per CU
         if (seg_elems >= QT_GUESS_ELEMS) {
-            const int64_t counted = seg_elems / 8 / (QT_RUN * QT_PART) * QT_RUN * 8;
+            const int64_t groups = seg_elems / 8 / (QT_RUN * QT_PART) / tail.x * tail.x;
+            const int64_t counted = groups * QT_RUN * 8;
             const unsigned long long of_part = (unsigned long long)((double)above * ((double)counted / (double)seg_elems) + 0.5);
-            k_quant_tail<<<tail, QH_THREADS, 0, st>>>(x, seg_elems, state, hist, 1);
-            k_quant_guess<<<nseg, 64, 0, st>>>(state, hist, of_part < 1 ? 1 : of_part);
+            k_quant_tail<<<tail, QH_THREADS, 0, st>>>(x, seg_elems, state, hist, groups);
+            k_quant_guess<<<nseg, 64, 0, st>>>(state, hist, of_part < 1 ? 1 : of_part, (int)tail.x);
             // 48 loads of 16 bytes a thread, or more for up to 32,768 workgroups (us: 6.8 G values 4,300 with 8,192,
             // 4,040 with 16,384, 3,940 with 32,768, 4,005 with 65,536; 1.3 G 980, 920, 965, 1,590)
             const int64_t blocks = seg_elems / (8 * QH_THREADS * 48);

@@ -1182,10 +1182,13 @@ def _sampled(n, step):
 
 @pytest.mark.parametrize("kind,permille,work", [
     ("alike", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [0, 0], "k_quant_codes<true, true, false>": [0]}),
+    ("clusters", 999, {"k_quant_codes<true, true, true>": [0], "k_quant_tail": [1], "k_quant_hist": [0, 0], "k_quant_codes<true, true, false>": [1]}),
     ("high", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [1, 1], "k_quant_codes<true, true, false>": [1]})])
 def test_passes_that_code_a_very_long_segment(B, kind, permille, work):
     """Which passes read the segment (more than 60 us: a pass over 1.07 GB takes 150 at least, one that returns at
-    once 10 at most).  high: the sampled pieces
+    once 10 at most).  clusters: the values of the tail lie in an eighth of the runs of 4 KB, so that a sixteenth says
+    less of them than of independent ones (one deviation is 2.1 % of the tail, not 0.55; the values that round to the
+    clip are 6 %), and no guess is made where one from independent values would be.  high: the sampled pieces
     and the runs of the sixteenth are twice as large as the rest, the bound is too high for the whole segment, and
     no second count is made with it."""
     from torch.profiler import ProfilerActivity, profile
@@ -1194,6 +1197,9 @@ def test_passes_that_code_a_very_long_segment(B, kind, permille, work):
     n = rows * d
     # (times 0.8594 the clip lies in the middle of the values that round to it, 3 % of the tail from either edge)
     x = torch.randn((rows, d), generator=g, device="cuda") * 0.8594
+    if kind == "clusters":                              # (the clip of the whole stays in the middle of its values)
+        hot = torch.rand(n // 2048, generator=g, device="cuda") < 0.125
+        x.view(-1, 2048).mul_(torch.where(hot, 0.38876 / 0.8594, 0.1)[:, None])
     x = x.to(torch.bfloat16)
     runs = x.view(-1, 2048)
     if kind == "high":
