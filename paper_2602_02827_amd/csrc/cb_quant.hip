@@ -570,12 +570,13 @@ hipError_t launch_quantize_i8(const void* x, int dt, int64_t n_segments, int64_t
         const unsigned nseg = (unsigned)n_segments;
         k_quant_sample<<<nseg, 1024, 0, st>>>(x, seg_elems, state, above);
         const dim3 tail((unsigned)(bx < 2048 ? bx : 2048), nseg);   // eight per CU
-        if (seg_elems >= QT_GUESS_ELEMS) {
-            const int64_t groups = seg_elems / 8 / (QT_RUN * QT_PART) / tail.x * tail.x;
-            const int64_t counted = groups * QT_RUN * 8;
-            const unsigned long long of_part = (unsigned long long)((double)above * ((double)counted / (double)seg_elems) + 0.5);
+        const int64_t groups = seg_elems / 8 / (QT_RUN * QT_PART) / tail.x * tail.x;
+        const int64_t counted = groups * QT_RUN * 8;
+        const unsigned long long of_part = (unsigned long long)((double)above * ((double)counted / (double)seg_elems) + 0.5);
+        // (fewer than nine: k_quant_guess's margin is more than there are)
+        if (seg_elems >= QT_GUESS_ELEMS && of_part >= 9) {
             k_quant_tail<<<tail, QH_THREADS, 0, st>>>(x, seg_elems, state, hist, groups);
-            k_quant_guess<<<nseg, 64, 0, st>>>(state, hist, of_part < 1 ? 1 : of_part, (int)tail.x);
+            k_quant_guess<<<nseg, 64, 0, st>>>(state, hist, of_part, (int)tail.x);
             // 48 loads of 16 bytes a thread, or more for up to 32,768 workgroups (us: 6.8 G values 4,300 with 8,192,
             // 4,040 with 16,384, 3,940 with 32,768, 4,005 with 65,536; 1.3 G 980, 920, 965, 1,590)
             const int64_t blocks = seg_elems / (8 * QH_THREADS * 48);

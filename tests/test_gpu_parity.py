@@ -1183,14 +1183,15 @@ def _sampled(n, step):
 @pytest.mark.parametrize("kind,permille,work", [
     ("alike", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [0, 0], "k_quant_codes<true, true, false>": [0]}),
     ("clusters", 999, {"k_quant_codes<true, true, true>": [0], "k_quant_tail": [1], "k_quant_hist": [0, 0], "k_quant_codes<true, true, false>": [1]}),
-    ("high", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [1, 1], "k_quant_codes<true, true, false>": [1]})])
+    ("high", 999, {"k_quant_codes<true, true, true>": [1], "k_quant_tail": [0], "k_quant_hist": [1, 1], "k_quant_codes<true, true, false>": [1]}),
+    ("alike", 1000, {"k_quant_codes<true, true, true>": [], "k_quant_tail": [1], "k_quant_hist": [0, 0], "k_quant_codes<true, true, false>": [1]})])
 def test_passes_that_code_a_very_long_segment(B, kind, permille, work):
     """Which passes read the segment (more than 60 us: a pass over 1.07 GB takes 150 at least, one that returns at
     once 10 at most).  clusters: the values of the tail lie in an eighth of the runs of 4 KB, so that a sixteenth says
     less of them than of independent ones (one deviation is 2.1 % of the tail, not 0.55; the values that round to the
     clip are 6 %), and no guess is made where one from independent values would be.  high: the sampled pieces
     and the runs of the sixteenth are twice as large as the rest, the bound is too high for the whole segment, and
-    no second count is made with it."""
+    no second count is made with it.  permille 1000: one value decides, which no sixteenth can name."""
     from torch.profiler import ProfilerActivity, profile
     g = torch.Generator(device="cuda").manual_seed(13)
     rows, d = 1 << 22, 128
