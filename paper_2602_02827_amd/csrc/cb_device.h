@@ -138,7 +138,7 @@ __device__ __forceinline__ void split_first(const f32x4_t (&x)[P][2], bf16x8_t (
         const u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
         any |= w[0] | w[1] | w[2] | w[3];
     }
-    if (__ballot((any & 0x40004000u) != 0u) != 0ull) {
+    if (__builtin_expect(__ballot((any & 0x40004000u) != 0u) != 0ull, 0)) {
         bool wild = false;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
@@ -211,7 +211,7 @@ template <int D> struct Frag<f32_tag, D> {
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[PIECE[p][0]][s], b.v[PIECE[p][1]][s], acc, 0, 0, 0);
-        if (wild) make_finite(acc);
+        if (__builtin_expect(wild, 0)) make_finite(acc);
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[0][s], b.v[0][s], acc, 0, 0, 0);
     }
@@ -224,7 +224,7 @@ template <int D> struct Frag<f32_tag, D> {
                 c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[PIECE[p][0]][s], b0.v[PIECE[p][1]][s], c0, 0, 0, 0);
                 c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[PIECE[p][0]][s], b1.v[PIECE[p][1]][s], c1, 0, 0, 0);
             }
-        if (wild) {
+        if (__builtin_expect(wild, 0)) {
             make_finite(c0);
             make_finite(c1);
         }
