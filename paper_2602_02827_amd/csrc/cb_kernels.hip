@@ -211,12 +211,16 @@ constexpr int waves_of(int regs) { return 512 / regs < 4 ? 512 / regs : 4; }
 template <class F> constexpr bool cuts() { return !__is_same(typename F::Raw, F); }
 // Whether a second block of a document is in flight.  bf16 and codes: where its registers do not cost a wavefront
 // per SIMD.
-// fp32 always in the kernels that only score, held to the wavefronts that its registers leave (one query x
-// 200 documents of 1,030 tokens in d = 96, T = 32: 28.5 -> 24.0 us, T = 48 35.3 -> 30.0; d = 64 23.9 -> 19.2), and
-// never in those of a round, which have no registers for it: d = 128 and T <= 16 took 197, two wavefronts
-// (20,000 documents x 4 queries, Col-Bandit, 267 -> 257 us), and held to three they spill.
+// fp32: in the kernels that only score, always, held to the wavefronts that its registers leave (one query x
+// 200 documents of 1,030 tokens in d = 96, T = 32: 28.5 -> 24.0 us, T = 48 35.3 -> 30.0; d = 64 23.9 -> 19.2); in those of
+// a round, which need 48 more, where that costs no wavefront: d = 128 and T <= 16 took 197, two
+// wavefronts (20,000 documents x 4 queries, Col-Bandit, 267 -> 257 us; held to three they spill), while one block in flight
+// cost 5,000 documents x 60 queries of 32 tokens 491 us in the place of 488, of 64 tokens 515 and 512.
 template <int NT, class F> constexpr bool score_ahead() { return cuts<F>() || gather_regs<NT, F>(true) <= 112; }
-template <int NT, class F> constexpr bool round_ahead() { return !cuts<F>() && gather_regs<NT, F>(true) <= 112; }
+template <int NT, class F> constexpr bool round_ahead() {
+    return cuts<F>() ? waves_of(gather_regs<NT, F>(true) + 48) >= waves_of(gather_regs<NT, F>(false) + 16)
+                     : gather_regs<NT, F>(true) <= 112;
+}
 template <int TQ, class F> constexpr int score_waves() { return cuts<F>() ? waves_of(gather_regs<TQ, F>(true)) : 1; }
 // Wavefronts per SIMD of k_gather_round, which serves two kinds of list and without a bound takes a few
 // registers too many for the four (or what the query rows leave) that a kernel with one block in
