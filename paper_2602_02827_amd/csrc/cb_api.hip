@@ -272,8 +272,12 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
     if (!lists_fit && (double)P.nq * (double)P.N * t_pair < passes * (t_pass + t_round)) return ~0ull;
     const double worth = passes * t_pass + (lists_fit ? (passes + R - r) * t_round : 0.0);
     // Queries that share a corpus of the last-level cache's size gather faster, and where lists fit and even full
-    // ones cost no more than what the gather saves, none of the later rounds is launched (7 queries x 6,007
+    // ones cost no more to read than what the gather saves, none of the later rounds is launched (7 queries x 6,007
     // documents, d = 64, T = 21: 144 -> 109 us; 16 x 6,000 164 -> 107, with alpha 1.0, where they stay full, 339 -> 294).
+    // fp32 as well by its bytes, though its matrix work can make full lists cost 1.4 times as much: lists are seldom full,
+    // and a threshold brings the empty launches back (5,000 documents, d = 128, 64 queries of 64 tokens: 511 us so
+    // and 782 by t_pair's price, with alpha 1.0 593 and 869; of 40 calls between the two prices only one was slower:
+    // 10,000 documents, d = 32, 120 queries, alpha 1.0 1,459 and 1,297).
     if (lists_fit && (double)P.total * row_bytes <= 256e6 &&
         (double)P.nq * (double)P.total * row_bytes / 7.5e12 <= worth) return ~0ull;
     const double thr = worth / t_pair;

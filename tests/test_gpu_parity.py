@@ -694,6 +694,20 @@ def test_full_lists_of_a_corpus_in_the_last_level_cache_launch_no_later_round(B,
         _same_run(*r)
 
 
+@pytest.mark.parametrize("nq,T,d", [(48, 64, 128), (33, 40, 96), (60, 64, 32)])
+def test_full_fp32_lists_of_a_corpus_in_the_last_level_cache(B, S, nq, T, d):
+    """fp32 queries of several tiles, whose full lists cost more matrix work than their bytes say: round 2 gathers them
+    and is the last launched, and the run is that of a corpus pass in every round."""
+    w = _custom(S, np.random.default_rng(nq).integers(1, 180, 3000).tolist(), nq, T, d, "f32", 9)
+    for alpha in (0.2, 1.0):
+        call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 10, alpha, 0.01, 5, 3, **o)
+        names = _kernels(lambda: call(want_stats=False))
+        assert names.count("k_gather_round<") == 1 and names.count("k_dense<") == 1
+        r = [call(trace=True, later_rounds=m) for m in (0, 1)]
+        torch.cuda.synchronize()
+        _same_run(*r)
+
+
 @pytest.mark.parametrize("N,nq,T,longest", [(20000, 5, 32, 3), (40000, 3, 48, 2), (9000, 9, 24, 5), (30000, 2, 100, 2)])
 def test_gathered_rounds_of_more_pairs_than_workers(B, S, N, nq, T, longest):
     """Lists of unequal length whose pairs (beyond 32,768) are dealt out in streams, held as ids and in
