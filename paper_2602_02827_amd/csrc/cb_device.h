@@ -128,7 +128,8 @@ template <int D> struct Frag<bf16_tag, D> {
 // of 2^-110 or more; of smaller ones what lies below bf16's smallest number, 2^-133, is lost.
 // split_first: the first pieces of P times eight values; calls on_wild where one of these is infinite, NaN or
 // of 2^40 or more (Frag::mma).  A large x whose rounding would be infinite is rounded towards zero instead (the
-// remainder's 16 bits fit the other two).  Both are looked for only where some value is 2 or more.
+// remainder's 16 bits fit the other two).  Two bits of each pair of pieces tell whether any is 2 or more, which
+// components of unit vectors never are (16 instructions a block of d = 128); only then the largest is looked for.
 template <int P, class W>
 __device__ __forceinline__ void split_first(const f32x4_t (&x)[P][2], bf16x8_t (&hi)[P], W&& on_wild) {
     uint32_t any = 0;
@@ -138,21 +139,26 @@ __device__ __forceinline__ void split_first(const f32x4_t (&x)[P][2], bf16x8_t (
         const u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
         any |= w[0] | w[1] | w[2] | w[3];
     }
-    if (__builtin_expect(__ballot((any & 0x40004000u) != 0u) != 0ull, 0)) {
-        bool wild = false;
+    if (__builtin_expect(__ballot((any & 0x40004000u) != 0u) == 0ull, 1)) return;
+    float most = 0.f;
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
+    for (int p = 0; p < P; ++p)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t mag = __float_as_uint(x[p][i >> 2][i & 3]) & 0x7fffffffu;
-                wild |= mag >= 0x53800000u;
-                if (mag - 0x7f7f8000u < 0x8000u) w[i >> 1] -= i & 1 ? 0x10000u : 1u;
-            }
-            hi[p] = __builtin_bit_cast(bf16x8_t, w);
+        for (int i = 0; i < 8; ++i) most = fmaxf(most, fabsf(x[p][i >> 2][i & 3]));
+    if (__builtin_expect(__ballot(!(most < 0x1p40f)) == 0ull, 1)) return;
+    bool wild = false;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        u32x4_t w = __builtin_bit_cast(u32x4_t, hi[p]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t mag = __float_as_uint(x[p][i >> 2][i & 3]) & 0x7fffffffu;
+            wild |= mag >= 0x53800000u;
+            if (mag - 0x7f7f8000u < 0x8000u) w[i >> 1] -= i & 1 ? 0x10000u : 1u;
         }
-        if (wild) on_wild();
+        hi[p] = __builtin_bit_cast(bf16x8_t, w);
     }
+    if (wild) on_wild();
 }
 __device__ __forceinline__ void split_rest(const f32x4_t (&x)[2], const bf16x8_t& hi, bf16x8_t& mid, bf16x8_t& lo) {
     const f32x8_t r = __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7) - __builtin_convertvector(hi, f32x8_t);
