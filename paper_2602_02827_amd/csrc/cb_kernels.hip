@@ -720,9 +720,12 @@ hipError_t launch_gather_all(const Problem& P, const Work& W, float* out, float*
     A.cells = cells;
     A.shared = gather_shares(P) ? 1 : 0;
     const int64_t gx = A.shared ? P.N : (P.N + 3) / 4;
-    // at least four workgroups a CU over all queries (one fp32 query, 10.6 M tokens: d = 32 618 -> 284 us,
-    // d = 128 1,196 -> 989; more than four change nothing)
-    const int64_t most = P.nq >= 4 ? 256 : 1024 / P.nq;
+    int64_t most = P.nq >= 4 ? 256 : 1024 / P.nq;   // four workgroups a CU over all queries
+    // fp32 with a wavefront per document: as many as the registers hold and no more, or fewer.  (us, two queries x
+    // 20,000 documents of 100 tokens: d = 128, T = 16 with 512 workgroups 285, 768 304, 1,024 372; d = 96, T = 32 237, 240, 278;
+    // d = 64, T = 48 223, 209, 232; d = 32, T = 16 89, 75, 74; 16 x 5,000 of d = 32, T = 32, 1,024 132, 4,096 156.)
+    if (P.dt == DT_F32 && !A.shared) most = (P.d >= 96 ? 512 : P.d == 64 ? 768 : 1024) / P.nq;
+    if (most < 1) most = 1;
     return gather_any(A, InitArgs{}, GM_ALL, P, W, dim3((unsigned)(gx < most ? gx : most), P.nq), nullptr, st);
 }
 
