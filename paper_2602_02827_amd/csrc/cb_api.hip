@@ -135,17 +135,19 @@ bool small_call(const Problem& P) {
 // Scores of all pairs: by gathering, or by a corpus pass, for which the chunks are set.  bf16: small_call.
 // fp32 weighs both: matrix work, of all column tiles that a pass multiplies, empty ones as well, against
 // the filled ones; reading, once against once a query; and whether either fills the chip.  Time model
-// (microseconds), from 994 shapes (10 to 100,000 documents of 48 to 8,000 tokens, 1 to 32 queries of 16 to 48,
-// d = 32 to 128), on which it picks the faster path or one within 8 % of it but for 47 (at most 1.7x):
-//   pass    a token costs 14 to 15 ps a tile multiplied (d = 128) and 25 a column group for cutting it into
-//           pieces; more where chunks are short or wavefronts split the documents; reading at 4.5 TB/s;
-//           never less than a document's blocks one after the other in one workgroup
-//   gather  13.5 ps a tile filled, 32 with four tiles a query of d = 96 and 128, and 16.5 a query for cutting;
-//           reading at 7.2 TB/s; never less than a document's blocks in a wavefront, or shared by four
+// (microseconds), from 1,171 shapes (10 to 100,000 documents of 48 to 8,000 tokens, 1 to 32 queries of 16 to 48,
+// d = 32 to 128), on which it picks the faster path or one within 8 % of it but for 32 (1.3x: 8 queries of 32 tokens
+// x 200 documents of 1,030 in d = 96, a pass of 122 us for a gather of 94; the others 1.2x at most):
+//   pass    a token costs 13 to 13.6 ps a tile multiplied (d = 128), 1.3 times that with four tiles a query of d = 96
+//           and 128, and 33 a column group for cutting it into pieces; more where chunks are short or wavefronts split
+//           the documents; reading at 5.8 TB/s; never less than a document's blocks one after the other in one workgroup
+//   gather  14.4 ps a tile filled, 17.6 with four tiles a query of d = 96 and 128, and 7 a query for cutting;
+//           reading at 9.7 TB/s (partly from the last-level cache), by several queries of a larger corpus 8.3;
+//           never less than a document's blocks in a wavefront, or shared by four
 // Up to 82 MB of reading the gather saves a launch and loses at most a tenth where documents are of like length.
-// gather and pass, us, T = 32: 5,000 documents of 100 tokens, d = 128: 1 query 60 and 108, 2 89 and 110, 3 147
-// and 117, 8 308 and 207; 100,000 (5.1 GB): 1 989 and 1,349, 2 1,903 and 1,541; d = 64: 1 500 and 650, 2 865
-// and 734, 8 3,270 and 1,419.
+// gather and pass, us, T = 32: 5,000 documents of 100 tokens, d = 128: 1 query 53 and 114, 2 83 and 117, 3 124
+// and 122, 8 264 and 269; 100,000 (5.1 GB): 1 914 and 1,294, 2 1,706 and 1,510; d = 64: 1 450 and 636, 2 784
+// and 728, 8 2,683 and 1,451.
 bool score_by_gather(Work& W, const Problem& P) {
     const ScoreShape s = score_shape(P, false);
     choose_chunks(W, P, s.tiles);
@@ -153,18 +155,20 @@ bool score_by_gather(Work& W, const Problem& P) {
     if (P.dt != DT_F32) return false;
     const double d = P.d, total = (double)P.total, nq = P.nq, blocks = total / (double)P.N / 16.0;
     const double corpus = total * d * 4.0;
-    if (nq * corpus <= 82e6) return true;
-    const auto both = [](double a, double b) { return cbrt(a * a * a + b * b * b); };   // little more than the larger
+    if (always_gathers(s, P.d) || nq * corpus <= 82e6) return true;
+    // a little more than the larger (n: how little)
+    const auto both = [](double a, double b, double n) { return pow(pow(a, n) + pow(b, n), 1.0 / n); };
     const bool eight = P.d >= 96 && s.tq <= 2;       // groups of 16 tiles have eight wavefronts
-    const double tiles = 4.0 * s.nt * s.groups / (s.split ? s.split / 1.5 : 1.0);
-    const double cut = 25.0 * s.groups * (s.split ? 1.5 : 1.0);
-    const double multiply = total * (tiles * (s.nt == 2 || eight ? 15.4 : 14.2) + cut) * 1e-6 *
-                            (1.0 + 42.0 / W.chunk_tokens) * d / 128.0 * (P.d == 96 ? 1.44 : 1.0);
-    const double t_pass = 15.0 + fmax(both(multiply, corpus / 4.5e6), blocks * (0.13 + (s.nt == 2 ? 0.006 : 0.012) * d));
-    const double filled = nq * (total + 8.0 * (double)P.N) * (16.5 + 13.5 * s.tq + (s.tq == 4 && P.d >= 96 ? 19.0 : 0.0)) *
-                          1e-6 * (d + 12.0) / 128.0;
-    const double t_gather = 11.5 + fmax(both(filled, nq * corpus / 7.2e6),
-                                        blocks * (0.43 + 0.0025 * d * s.tq) / (gather_shares(P) ? 4.0 : 1.0));
+    const bool four = P.d >= 96 && s.tq == 4;        // one or two wavefronts per SIMD
+    const double tiles = 4.0 * s.nt * s.groups / (s.split ? s.split / 1.3 : 1.0);
+    const double cut = 33.0 * s.groups * (s.split ? 1.7 : 1.0);
+    const double multiply = total * (tiles * (s.nt == 2 || eight ? 13.0 : 13.6) * (four ? 1.3 : 1.0) + cut) * 1e-6 *
+                            (1.0 + 58.0 / W.chunk_tokens) * d / 128.0 * (P.d == 96 ? 1.2 : 1.0);
+    const double t_pass = 13.0 + fmax(both(multiply, corpus / 5.8e6, 3.0), blocks * (0.19 + (s.nt == 2 ? 0.0058 : 0.0085) * d));
+    const double filled = nq * (total + 8.0 * (double)P.N) * (7.0 + 14.4 * s.tq + (four ? 13.0 : 0.0)) * 1e-6 * (d + 3.8) / 128.0;
+    const double read = nq * corpus / (corpus > 256e6 && P.nq > 1 ? 8.3e6 : 9.7e6);
+    const double t_gather = 14.0 + fmax(both(filled, read, 2.3),
+                                        blocks * (0.12 + 0.00082 * d * (s.tq + 5)) / (gather_shares(P) ? 4.0 : 1.0));
     return t_gather < t_pass;
 }
 
@@ -253,7 +257,7 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
     double t_pair = doc_tokens * row_bytes / 4.5e12;
     double passes = 2.0;
     if (!codes && P.dt == DT_F32) {
-        // The matrix work of both weighs too (the terms are those of score_by_gather): all T tokens of a pair
+        // The matrix work of both weighs too (terms as in score_by_gather; a round's kernels are a little slower): all T tokens of a pair
         // at once against a batch in each pass, so where the lists fit the cache the one visit is weighed
         // against a pass in every round left.  A pass takes no less than a mean document's blocks one
         // after the other in a workgroup.

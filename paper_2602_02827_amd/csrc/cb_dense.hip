@@ -773,8 +773,15 @@ ScoreShape score_shape(const Problem& P, bool codes) {
 template <typename Tag, int D, int TQ>
 static hipError_t dense_score_nt(DenseArgs& A, const ScoreShape& s, hipStream_t st) {
     constexpr int FEW = TQ <= 2 ? 2 : TQ;           // tiles of a wavefront that splits documents
-    if (s.split == 4) return dense_go<Tag, D, FEW, TQ, false, 4>(A, 1, st);
-    if (s.split == 2) return dense_go<Tag, D, FEW, TQ, false, 2>(A, 1, st);
+    if constexpr (!Tag::wide) {
+        if (always_gathers(s, D)) return hipErrorInvalidValue;
+    }
+    if constexpr (Tag::wide || TQ == 1) {
+        if (s.split == 4) return dense_go<Tag, D, FEW, TQ, false, 4>(A, 1, st);
+    }
+    if constexpr (Tag::wide || TQ == 1 || (TQ == 2 && D != 96)) {
+        if (s.split == 2) return dense_go<Tag, D, FEW, TQ, false, 2>(A, 1, st);
+    }
     if constexpr (TQ <= 2) {
         if (s.nt == 2) return dense_go<Tag, D, 2, TQ, false>(A, s.groups, st);
     }

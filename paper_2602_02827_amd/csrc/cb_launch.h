@@ -126,6 +126,12 @@ struct ScoreShape {
 };
 // codes: a pass on int8 codes.
 ScoreShape score_shape(const Problem& P, bool codes);
+// fp32 batches that always gather, whatever the corpus (us, 100,000 documents of 100 tokens or 4,000 of 1,030: one query of
+// 32 tokens 367 and 487 by a pass, of 48 in d = 64 222 and 391, two of 48 in d = 128 2,467 and 3,410, in d = 32 579 and
+// 581, two of 32 in d = 96 within 6 %): there is no corpus kernel for them.
+inline bool always_gathers(const ScoreShape& s, int d) {
+    return s.split != 0 && (s.tq == 4 || (s.tq == 2 && (s.split == 4 || d == 96)));
+}
 bool dense_supported(const Problem& P, const Coarse* co);
 int dense_chunks(const Problem& P, const Work& W);
 

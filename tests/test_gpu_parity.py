@@ -276,33 +276,50 @@ def test_full_maxsim_fp32_ragged_and_d64(B, S, oracle_mod):
         np.testing.assert_allclose(r["scores"].cpu().numpy(), Sor, rtol=1e-5, atol=1e-6)
 
 
-@pytest.mark.parametrize("nq,T,d,pas", [(1, 32, 128, False), (3, 48, 96, False), (1, 16, 32, True), (2, 16, 128, True),
-                                        (2, 32, 64, True), (3, 32, 128, True), (9, 32, 32, True), (5, 64, 128, True),
-                                        (1, 48, 96, True), (2, 40, 64, True)])
-def test_fp32_products_on_the_bf16_pipes_keep_fp32_precision(B, S, nq, T, d, pas):
+GATHER = "k_gather_all<cb::f32_tag"
+
+
+@pytest.mark.parametrize("nq,T,d,times,kernel", [
+    (1, 32, 128, 1, GATHER), (3, 48, 96, 1, GATHER), (1, 48, 96, 250, GATHER), (2, 40, 64, 2000, GATHER), (1, 32, 64, 9000, GATHER),
+    # two and one of four wavefronts take the tiles of the batch and split the documents
+    (2, 16, 32, 5300, "32, 2, 1, false, 4"), (1, 9, 64, 1, GATHER), (2, 16, 64, 2800, "64, 2, 1, false, 4"),
+    (2, 16, 96, 11000, "96, 2, 1, false, 4"), (2, 13, 128, 1400, "128, 2, 1, false, 4"),
+    (3, 14, 32, 1400, "32, 2, 1, false, 2"), (4, 16, 64, 240, "64, 2, 1, false, 2"), (3, 14, 96, 1900, "96, 2, 1, false, 2"),
+    (4, 16, 128, 150, "128, 2, 1, false, 2"), (2, 32, 32, 6000, "32, 2, 2, false, 2"), (2, 32, 64, 6000, "64, 2, 2, false, 2"),
+    (2, 20, 128, 11500, "128, 2, 2, false, 2"),
+    # every wavefront its own tiles; eight wavefronts with 16 tiles in d = 96 and 128
+    (3, 32, 128, 1400, "128, 2, 2, false, 0"), (9, 32, 32, 250, "32, 2, 2, false, 0"), (16, 32, 128, 150, "128, 4, 2, false, 0"),
+    (16, 32, 96, 150, "96, 4, 2, false, 0"), (8, 64, 128, 1500, "128, 4, 4, false, 0")])
+def test_fp32_products_on_the_bf16_pipes_keep_fp32_precision(B, S, nq, T, d, times, kernel):
     """fp32 products are sums of six bf16 products of the values' pieces.  Components spread over 2^+-40 in
     either sign, some short of bits, and some infinite: a cell is the largest sum, each within the rounding of
     an fp32 sum whatever its order.  A sum takes at most 6 d / 32 = 24 instructions and each of them five levels
     of additions, at a rounding (2^-24) of the magnitudes' sum each: 29 roundings; truncation instead of
-    rounding would double it: 64 are allowed, which also covers the pieces left out (2^-24)."""
-    lengths = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 5]
-    if pas:
-        lengths = _past_small(lengths, nq, d, "f32")
-    w = _custom(S, lengths, nq, T, d, "f32", 3)
+    rounding would double it: 64 are allowed, which also covers the pieces left out (2^-24).  kernel: what serves the call,
+    the gather or a corpus kernel of those compiled for fp32; documents end in the middle of blocks, at their
+    ends and several in one."""
+    lengths = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 5] * times
+    off = torch.zeros(len(lengths) + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(torch.tensor(lengths), 0)
+    docs, Q = torch.empty((int(off[-1]), d), device="cuda"), torch.empty((nq, T, d), device="cuda")
+    w = S.Workload("wide-f32", "f32", Q, docs, off.cuda(), seed=3)
     g = torch.Generator(device="cuda").manual_seed(4)
     rnd = lambda *shape: torch.rand(shape, generator=g, device="cuda", dtype=torch.float64)
     for x in (w.docs, w.Q):
         v = torch.exp2(rnd(*x.shape) * 80 - 40) * torch.where(rnd(*x.shape) < 0.5, -1.0, 1.0)
         v = torch.where(rnd(*x.shape) < 0.1, torch.exp2(torch.round(torch.log2(v.abs()))), v)
         x.copy_(v)
+        del v
     off = w.offsets
     inf_doc = len(lengths) - 3
     w.docs[int(off[inf_doc]) + 2, 5] = float("inf")
     w.docs[int(off[inf_doc]) + 2, d - 1] = -float("inf")
     w.docs[int(off[inf_doc + 1]) - 1, 7] = -float("inf")
-    full = B.colbandit_full_maxsim(w.Q, w.docs, off, K=1, want_cells=True)
+    res = []
+    names = _kernels(lambda: B.colbandit_full_maxsim(w.Q, w.docs, off, K=1, want_cells=True), res)
+    assert (kernel if kernel is GATHER else f"k_dense<cb::f32_tag, {kernel}") in names
     E, Q = w.docs.double(), w.Q.reshape(nq * T, d).double()
-    cells = full["cells"].permute(1, 0, 2).reshape(len(lengths), nq * T).double()
+    cells = res[0]["cells"].permute(1, 0, 2).reshape(len(lengths), nq * T).double()
     lens = off[1:] - off[:-1]
     doc = torch.repeat_interleave(torch.arange(len(lengths), device="cuda"), lens)
     # a product with a token's infinite component decides; two of opposite sign have no sum and no say
