@@ -121,7 +121,9 @@ typedef struct {
                                                          (all queries of the batch)    */
     float ms_first_reveal;                            /* of which: reveal of round 1   */
     float ms_later_reveals;                           /* reveals of rounds >= 2        */
-    float ms_select_prune;                            /* thresholds and pruning        */
+    float ms_select_prune;                            /* thresholds and pruning (of the smallest
+                                                         calls, whose last launch goes on to it,
+                                                         also the final top-K)               */
     float ms_rescore_topk;                            /* rescore and final top-K
                                                          (cf. the paper's stage split in
                                                          its overhead-breakdown table)  */
