@@ -539,8 +539,8 @@ void k_dense(DenseArgs A) {
     };
 
     // ---- fp32: a stage's rows pass through registers, where they are cut into their three pieces (split_first),
-    // once for all wavefronts (44 vector instructions a wavefront and stage at d = 128 and four wavefronts; each
-    // for itself would take four times as many, as long as the matrix work of two tiles).  A thread takes
+    // once for all wavefronts (50 vector instructions a wavefront and stage at d = 128 with eight wavefronts, twice as many
+    // with four; each for itself would take 400, as long as the matrix work of two tiles).  A thread takes
     // the 16 + 16 bytes that a lane of a wavefront holds of one k-step (Frag): one 16-byte piece in each plane.
     // A wavefront writes stage s + 1 when it has finished stage s itself, over stage s - 1, which all finished
     // before the barrier of stage s.  (Three slots, the first block of a stage read before its barrier: eight
