@@ -245,7 +245,7 @@ struct PhaseTimer {
 // either way, and where even full ones are gathered for no more than twice a pass and a round's
 // launches the pass is left out (~0): its empty launch is 4 us in every round (3 queries x 19,583 documents of
 // 48 tokens, T = 53 in rounds of 2, d = 32, a full gather 40 us and a pass 17: 762 us with it, 732 without).
-unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, int r, int R, bool lists_fit) {
+unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, int r, int R, bool lists_fit, double* t_gather) {
     // int8 codes: half the bytes of bf16 and twice the rate
     const double row_bytes = (codes ? 1.0 : P.dt == DT_BF16 ? 2.0 : 4.0) * P.d;
     const double rate = codes ? 2.3e15 : 1.15e15;
@@ -285,6 +285,7 @@ unsigned long long dense_pairs_threshold(const Problem& P, int G, bool codes, in
     if (lists_fit && (double)P.total * row_bytes <= 256e6 &&
         (double)P.nq * (double)P.total * row_bytes / 7.5e12 <= worth) return ~0ull;
     const double thr = worth / t_pair;
+    *t_gather = t_pair;
     return thr >= 1.8e19 ? ~0ull - 1 : (unsigned long long)thr;
 }
 
@@ -601,7 +602,7 @@ int colbandit_ball_carving(const void* Q, int n_queries, int T, int d, colbandit
             rr.lo = 0;
             rr.nb = 4;
             rr.n = 4;
-            rr.dense_thr = ~0ull;
+            rr.dense = kNeverDense;
             e = launch_dense_reveal(P2, W2, n_chunks, rr, 4, nullptr, st);
         }
         if (e == hipSuccess) e = launch_ball_reduce((const float*)part, 2, goff, n_queries, N, out, st);
@@ -790,14 +791,15 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     const bool cache_all = loop && !dense && !force_gather && later_rounds == 0 && small_call(P) &&
                            N <= (int64_t)W.cache_cap;
     if (e == hipSuccess) e = cache_all ? launch_cache_all(P, W, kn, R, seed, user_pi, tr, co, st)
-                                       : launch_init(P, W, kn, R, seed, user_pi, tr, n_chunks, st);
+                                       : launch_init(P, W, kn, R, seed, user_pi, tr, co, n_chunks, st);
     float kappa[COLBANDIT_MAX_ROUNDS + 1] = {};      // radius per unit sigma_hat of each round
     for (int r = 1; r <= R; ++r) {
         const double kap = colbandit_radius_prefactor(alpha_ef, delta, T, N, r * kn.B < T ? r * kn.B : T);
         kappa[r] = isinf(kap) ? 0.f : (float)kap;    // unused by the kernels when n <= 1
     }
-    unsigned long long round_thr[COLBANDIT_MAX_ROUNDS + 2];
-    for (int r = 0; r <= R + 1; ++r) round_thr[r] = ~0ull;
+    DenseRule round_rule[COLBANDIT_MAX_ROUNDS + 2];
+    for (int r = 0; r <= R + 1; ++r) round_rule[r] = kNeverDense;
+    const bool share = loop && !cache_all && shares_documents(P, W, co);
     for (int r = 1; e == hipSuccess && loop && r <= R; ++r) {
         RevealRound rr{};
         rr.r = r;
@@ -807,26 +809,40 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         rr.n = rr.lo + rr.nb;
         int G = 1;
         while (G < rr.nb) G <<= 1;
-        rr.dense_thr = ~0ull;
+        rr.dense = kNeverDense;
         if (r == 1 && dense) {
             e = launch_dense_reveal(P, W, n_chunks, rr, G, co, st);
         } else if (!cache_all) {
             if (r >= 2 && dense && later_rounds != 2) {
-                rr.dense_thr = later_rounds == 1 ? 0ull
-                                                 : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap);
-                if (rr.dense_thr >= (unsigned long long)n_queries * (unsigned long long)N) rr.dense_thr = ~0ull;
+                double t_pair = 0.0;
+                const unsigned long long thr = later_rounds == 1 ? 0ull
+                    : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap, &t_pair);
+                if (thr < (unsigned long long)n_queries * (unsigned long long)N) rr.dense.thr = thr;
+                // by document: the corpus at 5.5 TB/s, and the documents again, from the last-level cache, for every
+                // group of queries
+                if (t_pair > 0.0) rr.dense.base = (uint32_t)fmin((double)P.total * P.d * (co ? 1.0 : 2.0) / 5.5e12 / t_pair, 4e9);
+                rr.dense.lg_per = (uint16_t)(1 + share_group_lg(T));
+                // Lists that fit the cache, and cost no more even if they are full (and those that are not entered by document
+                // hold N pairs): round 2 is the last to launch.
+                if (share && later_rounds != 1 && N <= (int64_t)W.cache_cap &&
+                    rr.dense.base + (((unsigned long long)N * (unsigned)n_queries) >> rr.dense.lg_per) + (unsigned long long)N <= rr.dense.thr)
+                    rr.dense.thr = NEVER_DENSE;
             }
-            round_thr[r] = rr.dense_thr;
+            if (r == 2 && share) {
+                rr.dense.shared_at = (uint16_t)(2 * (R + 2) - 2);
+                rr.dense.enough = share_enough(P);
+            }
+            round_rule[r] = rr.dense;
             e = launch_dense_reveal_later(P, W, n_chunks, rr, G, co, st);
             if (e == hipSuccess) e = launch_gather_round(P, W, rr, co, st);
         }
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
-        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, tr,
+        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, share && r == 1, tr,
                                                      cache_all && !co ? topk_ids : nullptr, topk_scores, st);
         pt.mark(PH_SELECT);
         // A gathered round in which every list fits the cell cache is the last one to launch:
         // k_select_prune runs all rounds of a cached query.
-        if (cache_all || (r >= 2 && rr.dense_thr == ~0ull && N <= (int64_t)W.cache_cap)) break;
+        if (cache_all || (r >= 2 && rr.dense.thr == NEVER_DENSE && N <= (int64_t)W.cache_cap)) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
     // (after cache_all every query's survivors have them, and k_select_prune has gone on to the top-K).  Where no
@@ -847,15 +863,15 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     int32_t* hist = (int32_t*)malloc(sizeof(int32_t) * nh);
     if (!hist) { pt.destroy(); return COLBANDIT_ERR_HIP; }
     hipError_t ce = hipMemcpyAsync(hist, W.cnt_hist, sizeof(int32_t) * nh, hipMemcpyDeviceToHost, st);
-    unsigned long long pairs_h[2 * (COLBANDIT_MAX_ROUNDS + 2)];
+    unsigned long long pairs_h[2 * (COLBANDIT_MAX_ROUNDS + 2) + 1];
     if (ce == hipSuccess)
-        ce = hipMemcpyAsync(pairs_h, W.pairs, sizeof(unsigned long long) * 2 * (size_t)(R + 2),
+        ce = hipMemcpyAsync(pairs_h, W.pairs, sizeof(unsigned long long) * (2 * (size_t)(R + 2) + 1),
                             hipMemcpyDeviceToHost, st);
     if (ce == hipSuccess) ce = hipStreamSynchronize(st);
     // the rounds whose device-side test took the corpus pass (the same test as the kernels')
     uint64_t corpus_rounds = 0;
     for (int r = 2; ce == hipSuccess && loop && r <= R; ++r)
-        if (round_thr[r] != ~0ull && pair_count(pairs_h[r]) > round_thr[r]) corpus_rounds |= 1ull << (r - 1);
+        if (round_rule[r].pass(pairs_h[r], r == 2 ? pairs_h[2 * (R + 2)] : 0ull)) corpus_rounds |= 1ull << (r - 1);
     float ms = 0.f, phase_ms[PH_COUNT] = {0.f, 0.f, 0.f, 0.f, 0.f};
     if (ce == hipSuccess) pt.collect(phase_ms, ms);
     pt.destroy();
@@ -900,7 +916,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         s.ms_select_prune = phase_ms[PH_SELECT];
         s.ms_rescore_topk = phase_ms[PH_RESCORE];
         s.corpus_pass_rounds = corpus_rounds;
-        s.pairs_round2 = R >= 2 ? pair_count(pairs_h[2]) : 0ull;
+        s.pairs_round2 = R >= 2 ? pair_count(pairs_h[2]) + pair_count(pairs_h[2 * (R + 2)]) : 0ull;
         s.tokens_round2 = R >= 2 ? pairs_h[(R + 2) + 2] : 0ull;
     }
     free(hist);

@@ -92,10 +92,10 @@ struct DenseArgs {
     const int32_t* pi;
     int lo, nb, G;
     float2* stat;
-    // a round >= 2: run only if dense_round(pairs_r, dense_thr); skip queries that are
+    // a round >= 2: run only if dense.pass(pairs_r); skip queries that are
     // finished or read their cells from the cache
     const unsigned long long* pairs_r;
-    unsigned long long dense_thr;
+    DenseRule dense;
     const QueryCtl* ctl;
     // int8 codes: a cell is the integer maximum times qscale[q] * dscale[0]
     const float* qscale;
@@ -140,6 +140,9 @@ void k_dense(DenseArgs A) {
     constexpr int KEY_MASK = NCH - 1;
     __shared__ __attribute__((aligned(16))) char ring[PLANES * RING_ROWS * PITCH];
 
+    if constexpr (REVEAL) {
+        if (A.pairs_r && !A.dense.pass(A.pairs_r)) return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in an SGPR
     const int col = lane & 15;
@@ -155,9 +158,6 @@ void k_dense(DenseArgs A) {
     const int k8 = slot / A.n_groups;
     const int chunk = k8 * 8 + ((xcd + k8 + (k8 >> 3) + (k8 >> 6) + (k8 >> 9)) & 7);
     if (chunk >= A.n_chunks) return;
-    if constexpr (REVEAL) {
-        if (A.pairs_r && !dense_round(A.pairs_r, A.dense_thr)) return;
-    }
     int i0 = A.chunk_doc[chunk], i1 = A.chunk_doc[chunk + 1];
     i0 = i0 < 0 ? 0 : (i0 > (int)A.N ? (int)A.N : i0);
     i1 = i1 < i0 ? i0 : (i1 > (int)A.N ? (int)A.N : i1);
@@ -875,7 +875,7 @@ hipError_t launch_dense_reveal(const Problem& P, const Work& W, int n_chunks,
 hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chunks,
                                      const RevealRound& rr, int G, const Coarse* co,
                                      hipStream_t st) {
-    if (rr.dense_thr == ~0ull) return hipSuccess;
+    if (rr.dense.thr == NEVER_DENSE) return hipSuccess;
     DenseArgs A{};
     fill_dense(A, P, W, n_chunks);
     A.lo = rr.lo;
@@ -883,7 +883,7 @@ hipError_t launch_dense_reveal_later(const Problem& P, const Work& W, int n_chun
     A.G = G;
     A.stat = W.stat2;
     A.pairs_r = W.pairs + rr.r;
-    A.dense_thr = rr.dense_thr;
+    A.dense = rr.dense;
     A.ctl = W.ctl;
     return dense_reveal_any(A, P, co, st);
 }

@@ -70,12 +70,31 @@ __device__ __forceinline__ void chunk_docs(int64_t i, const int64_t* off, int64_
     for (int64_t c = lo; c <= hi; ++c) chunk_doc[c] = doc;
 }
 
-// Device-side choice of a later round's reveal path (uniform over the launch): true = the
-// corpus-streaming pass serves every active ids-mode query, false = per-pair gather.
-__device__ __forceinline__ bool dense_round(const unsigned long long* pairs_r,
-                                            unsigned long long thr) {
-    return pairs_r != nullptr && pair_count(*pairs_r) > thr;
-}
+// Choice of a later round's reveal path (uniform over the launch): the corpus-streaming pass serves every active
+// ids-mode query if gathering their documents costs more than `thr` gathers of one pair.  The pairs of the shared word
+// (round 2: lists entered by document) are gathered by document if there are `enough` of them, reading no more than the
+// corpus (`base`) for a number of queries at a time.  (Rounds without pairs are launches of nothing else: some thirty
+// instructions here cost such a launch 0.4 us.)
+constexpr unsigned long long NEVER_DENSE = ~0ull;
+struct DenseRule {
+    unsigned long long thr;
+    uint32_t base;
+    uint32_t enough;                     // 0: no shared word
+    uint16_t lg_per;                     // 2^lg_per pairs, by document, cost as much as one of the others
+    uint16_t shared_at;                  // the shared word, from the round's own
+    __device__ __host__ __forceinline__ bool by_document(unsigned long long shared) const { return pair_count(shared) >= enough; }
+    __device__ __host__ __forceinline__ bool pass(unsigned long long head, unsigned long long shared) const {
+        unsigned long long p = pair_count(head);
+        if (enough) {
+            const unsigned long long s = pair_count(shared);
+            p += s >= enough ? base + (s >> lg_per) : s;
+        }
+        return p > thr;
+    }
+    __device__ __forceinline__ bool pass(const unsigned long long* pairs_r) const {
+        return pass(*pairs_r, enough ? pairs_r[shared_at] : 0ull);
+    }
+};
 
 // ---------------------------------------------------------------------------------
 // Operand fragments for the 16x16 MFMA family.  One fragment holds, for the lane's row

@@ -19,6 +19,12 @@ __device__ __forceinline__ uint64_t splitmix64_next(uint64_t& s) {
     return z ^ (z >> 31);
 }
 
+// Round 2's lists by document: held[id] queries hold document id, at holders[id * nq ..] in any order, as query and list
+// place.  They lie over stat2, two words a pair, which else only corpus passes of later rounds use.
+__device__ __host__ __forceinline__ const int* held_of(const float2* stat2, int nq, int64_t N) {
+    return (const int*)stat2 + (size_t)nq * (size_t)N;
+}
+
 struct InitArgs {
     QueryCtl* ctl;
     int32_t* pi;
@@ -35,6 +41,8 @@ struct InitArgs {
     const int64_t* off;
     int chunk_tokens, n_chunks;
     int32_t* chunk_doc;
+    int chunk_blocks;         // workgroups of the chunk table; those after them clear `held`
+    int* held;
 };
 
 // A wavefront per query.  The permutation is a Fisher-Yates shuffle driven by SplitMix64 (Sec. 4.2:
@@ -46,8 +54,8 @@ struct InitArgs {
 __device__ __forceinline__ void init_queries(const InitArgs& A, int block) {
     const int lane = threadIdx.x & 63;
     const int q = block * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (q == 0)                                     // pair counts, then their token counts
-        for (int r = lane; r < 2 * (A.R + 2); r += 64) A.pairs[r] = 0ull;
+    if (q == 0)                                     // pair counts, their token counts, shared pairs
+        for (int r = lane; r < 2 * (A.R + 2) + 1; r += 64) A.pairs[r] = 0ull;
     if (q >= A.nq) return;
     const int T = A.T;
     if (lane == 0) {
@@ -97,10 +105,14 @@ __device__ __forceinline__ void init_queries(const InitArgs& A, int block) {
     if (lane + 64 < T) p[lane + 64] = p1;
 }
 __global__ __launch_bounds__(256) void k_init(InitArgs A) {
-    if ((int)blockIdx.x >= A.init_blocks)
-        chunk_docs((int64_t)((int)blockIdx.x - A.init_blocks) * 256 + threadIdx.x, A.off, A.N, A.chunk_tokens,
-                   A.n_chunks, A.chunk_doc);
-    else init_queries(A, (int)blockIdx.x);
+    const int block = (int)blockIdx.x - A.init_blocks;
+    if (block < 0) init_queries(A, (int)blockIdx.x);
+    else if (block < A.chunk_blocks)
+        chunk_docs((int64_t)block * 256 + threadIdx.x, A.off, A.N, A.chunk_tokens, A.n_chunks, A.chunk_doc);
+    else {
+        const int64_t i = (int64_t)(block - A.chunk_blocks) * 256 + threadIdx.x;
+        if (i < A.N) A.held[i] = 0;
+    }
 }
 
 __global__ void k_fill_f32(float* p, size_t n, float v) {
@@ -147,11 +159,23 @@ static void fill_trace(const Problem& P, int R, const Trace& tr, hipStream_t st)
     k_fill_u8<<<g, 256, 0, st>>>(tr.alive, n, 0);
 }
 
+constexpr int SHARE_TOKENS = 256;
+bool shares_documents(const Problem& P, const Work& W, const Coarse* co) {
+    return (co || P.dt == DT_BF16) && W.cache_cap > 0 && P.nq >= 4 && P.total >= SHARE_TOKENS * P.N;
+}
+// Half as many as documents; 4,096 for a corpus of few, whose pairs fill the chip better than its documents.
+unsigned share_enough(const Problem& P) { return (unsigned)(P.N > 8192 ? P.N / 2 : 4096); }
+int share_group_lg(int T) { return T <= 16 ? 3 : T <= 32 ? 2 : T <= 64 ? 1 : 0; }
 hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
-                       const int32_t* user_pi, const Trace& tr, int n_chunks, hipStream_t st) {
-    const InitArgs A = init_args(P, W, kn, R, seed, user_pi, tr, n_chunks);
-    const unsigned chunk_blocks = n_chunks > 0 ? (unsigned)((P.N + 1 + 255) / 256) : 0u;
-    k_init<<<(unsigned)A.init_blocks + chunk_blocks, 256, 0, st>>>(A);
+                       const int32_t* user_pi, const Trace& tr, const Coarse* co, int n_chunks, hipStream_t st) {
+    InitArgs A = init_args(P, W, kn, R, seed, user_pi, tr, n_chunks);
+    A.chunk_blocks = n_chunks > 0 ? (int)((P.N + 1 + 255) / 256) : 0;
+    int64_t blocks = A.init_blocks + A.chunk_blocks;
+    if (shares_documents(P, W, co)) {
+        A.held = (int*)held_of(W.stat2, P.nq, P.N);
+        blocks += (P.N + 255) / 256;
+    }
+    k_init<<<(unsigned)blocks, 256, 0, st>>>(A);
     fill_trace(P, R, tr, st);
     return hipGetLastError();
 }
@@ -184,13 +208,15 @@ struct GatherArgs {
     const unsigned long long* pairs_r;   // pairs of the round (pair_count); nullptr: all N documents of
                                          // every query
     const unsigned long long* work;      // its queries (work_item)
-    unsigned long long dense_thr;        // ~0: this round cannot be a corpus pass
+    DenseRule dense;
     // cell cache
     int cache_all;            // slots are documents (k_cache_all)
     int cache_cap, TP;
     int32_t* cid;
     float2* cstat;
     float* ccell;
+    // k_gather_docs: stat2 (hold_documents)
+    const float2* holders;
     // score
     float* out;
     float* cells;
@@ -319,6 +345,53 @@ __device__ __forceinline__ bool load_query(const GatherArgs& A, int q, int col, 
     return __ballot(wild) != 0ull;
 }
 
+// Inclusive sum over the wavefront's lanes, in lane order (DPP: shifts by 1, 2, 4, 8 inside the
+// rows of 16 lanes, then the rows' totals are passed on).
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return v;
+}
+
+// The T cells of query q's k-th document to its cache slot.
+template <int TQ>
+__device__ __forceinline__ void store_cells(const GatherArgs& A, int q, int k, const float (&w)[Pack<TQ>::NW]) {
+    using P = Pack<TQ>;
+    const int row = (int)(threadIdx.x & 63) >> 4, col = threadIdx.x & 15;
+    float* crow = A.ccell + ((size_t)q * A.cache_cap + k) * A.TP;
+#pragma unroll
+    for (int j = 0; j < P::NW; ++j)
+        if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
+}
+// This round's batch of the same cells, merged into the pair's statistics, which go to the slot.  t: the batch's
+// query token of this lane; slot s of the batch (lane s of row 0) fetches its cell from its owner.
+template <int TQ>
+__device__ __forceinline__ void reveal_cached(const GatherArgs& A, int q, int k, int id, int t, const float (&w)[Pack<TQ>::NW]) {
+    using P = Pack<TQ>;
+    const int lane = threadIdx.x & 63;
+    const int tile = t >> 4;
+    const int src = P::row_of_tile(tile) * 16 + (t & 15);
+    float v = __shfl(w[0], src);
+    if constexpr (P::NW > 1) {
+        const float v1 = __shfl(w[1], src);
+        v = tile >= 4 ? v1 : v;
+    }
+    float sb, m2b;
+    batch_stats(v, (lane & 15) % A.G, A.nb, A.G, sb, m2b);
+    if (lane == 0) {
+        const size_t slot = (size_t)q * A.cache_cap + k;
+        float2 st = make_float2(0.f, 0.f);
+        if (A.n_prev > 0) st = A.stat[(size_t)q * A.N + id];
+        merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
+        A.cstat[slot] = st;
+        A.cid[slot] = id;
+    }
+}
+
 constexpr int64_t ALL_DOCS = 64;
 
 // One round's reveal.  The round's pairs (over all queries that hold ids) are spread evenly over
@@ -334,8 +407,8 @@ constexpr int64_t ALL_DOCS = 64;
 //   list longer than the cell cache   one 16-column tile, column c < nb is query token pi[lo+c]; the
 //                  epilogue merges the batch into the pair's (sum, M2).
 //   list that fits the cell cache     TQ tiles = all T tokens; the epilogue stores the pair's T
-//                  cells in the query's cell cache, merges this round's batch from them and turns the
-//                  list entry into a cache slot.  A gathered reveal is bound by the bytes of the
+//                  cells in the query's cell cache (slot = place in the list) and merges this round's batch
+//                  from them.  A gathered reveal is bound by the bytes of the
 //                  document, not by the cells computed from them, so a document is visited once
 //                  and the later rounds (and the rescore) read its cells back; the order in which
 //                  cells are REVEALED to the bounds is unchanged.  cache_all: the smallest calls visit all
@@ -348,15 +421,26 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
     __shared__ int ex[EX_FLOATS];
-    if (A.dense_thr != ~0ull && dense_round(A.pairs_r, A.dense_thr)) return;   // the corpus pass serves it
+    // The round's items: those of pairs_r, then, from the end of the array, those entered by document if k_gather_docs
+    // does not serve them.
+    unsigned long long head = (unsigned long long)A.nq * (unsigned long long)A.N, shared = 0ull;
+    if (!CACHE_ALL && A.pairs_r) {
+        head = *A.pairs_r;
+        if (A.dense.enough) shared = A.pairs_r[A.dense.shared_at];
+        if ((head | shared) == 0ull || A.dense.pass(head, shared)) return;   // no pairs, or the corpus pass serves the round
+        if (A.dense.enough && A.dense.by_document(shared)) shared = 0ull;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int col = lane & 15;
     const int kg = lane >> 4;
 
-    const unsigned long long head = A.pairs_r ? *A.pairs_r : (unsigned long long)A.nq * (unsigned long long)A.N;
-    const long long total = (long long)(A.pairs_r ? pair_count(head) : head);
-    const int n_work = A.pairs_r ? (int)work_count(head) : A.nq;
+    const int n_own = (int)work_count(head);
+    const long long total = (long long)(A.pairs_r ? pair_count(head) + pair_count(shared) : head);
+    const int n_work = A.pairs_r ? n_own + (int)work_count(shared) : A.nq;
+    auto item_at = [&](int i) {
+        return i < n_own ? A.work[i] : A.work[A.nq - 1 - (i - n_own)] + (pair_count(head) << 16);
+    };
     const bool coop = total <= (long long)n_blocks;
     const int parts = coop ? 4 : 1;
     const long long workers = coop ? n_blocks : 4ll * n_blocks;
@@ -381,7 +465,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
         while (n > 1) {
             const int step = (n + 63) / 64;
             const bool in = lane * step < n;
-            const long long s = in ? (long long)work_start(A.work[item + lane * step]) : 0;
+            const long long s = in ? (long long)work_start(item_at(item + lane * step)) : 0;
             const int hit = __popcll(__ballot(in && s <= x));       // >= 1: the item at hand starts at or before x
             item += (hit - 1) * step;
             n -= (hit - 1) * step;
@@ -403,7 +487,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
     for (; x < x_end; ++item) {
         int q, k, k_end;
         if (A.pairs_r) {
-            const unsigned long long it = A.work[item];
+            const unsigned long long it = item_at(item);
             q = work_query(it);
             const long long first = (long long)work_start(it);
             const int n = A.ctl[q].count;
@@ -452,14 +536,9 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
                 }
             }
         } else {
-            using P = Pack<TQ>;
             F bq[TQ];
             const bool query_wild = load_query<F, ROWB, TQ>(A, q, col, kg, bq);
-            const int row = lane >> 4;
-            // this round's batch: slot s (lane s of row 0) fetches cell pi[lo+s] from its owner
             const int t = CACHE_ALL ? 0 : A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
-            const int tile = t >> 4;
-            const int src = P::row_of_tile(tile) * 16 + (t & 15);
             for (; k < k_end; ++k) {
                 const int id = list ? list[k] : k;
                 int64_t o0, o1;
@@ -468,31 +547,111 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
 #pragma unroll
                 for (int tt = 0; tt < TQ; ++tt) h[tt] = lowest_val<V>();
                 fold_doc<ROWB, round_ahead<TQ, F>()>((const char*)A.docs, o0, o1, coop ? wave : 0, parts, col, kg, bq, query_wild, h);
-                float w[P::NW];
+                float w[Pack<TQ>::NW];
                 doc_cells(h, parts, scale, ex, w);
                 if (coop && wave > 0) continue;
-                const size_t slot = (size_t)q * A.cache_cap + k;
-                float* crow = A.ccell + slot * A.TP;
-#pragma unroll
-                for (int j = 0; j < P::NW; ++j)
-                    if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
-                if (CACHE_ALL) continue;
-                float v = __shfl(w[0], src);
-                if constexpr (P::NW > 1) {
-                    const float v1 = __shfl(w[1], src);
-                    v = tile >= 4 ? v1 : v;
-                }
-                float sb, m2b;
-                batch_stats(v, col % A.G, A.nb, A.G, sb, m2b);
-                if (lane == 0) {
-                    float2 st = make_float2(0.f, 0.f);
-                    if (A.n_prev > 0) st = A.stat[(size_t)q * A.N + id];
-                    merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
-                    A.cstat[slot] = st;
-                    A.cid[slot] = id;
-                    if (list) list[k] = k;          // the entry now names its cache slot
-                }
+                store_cells<TQ>(A, q, k, w);
+                if (!CACHE_ALL) reveal_cached<TQ>(A, q, k, id, t, w);
             }
+        }
+    }
+}
+
+// The same reveal of round 2, document by document, where many documents are long and held by several queries: a
+// wavefront (a workgroup of its own: they take different times) takes a document, reads once the list of the queries
+// that hold it (k_select_prune has entered them, hold_documents) and multiplies it with the rows of up to NQ of them at a
+// time, so that it is read once for those.  Bound by memory: 64 queries of T = 24 x 20,000 pages of 1,030 tokens, 62,600
+// pairs on 19,200 documents: 1.0 to 1.15 ms (5.3 GB, 6.2 with the documents read again for a fifth query on) in the
+// place of a second corpus pass of 1.15 and gathers of 0.5.  (A workgroup of four wavefronts per run of documents,
+// two queries and one block ahead each: 1.57; each wavefront searching the lists for its document: 1.29; three blocks in
+// flight as four; tokens with the non-temporal hint: 1.45, the documents read again miss the caches.)
+template <int TQ> constexpr int share_queries() { return 8 / TQ; }
+// blocks in flight: 64 registers
+template <class F> constexpr int share_depth() { return 64 / ((int)sizeof(F) / 4) < 8 ? 64 / ((int)sizeof(F) / 4) : 8; }
+
+// Folds the document [o0, o1) into h, DEPTH blocks in flight.  The last block is repeated up to a multiple of DEPTH.
+template <int ROWB, int DEPTH, int NT, class F>
+__device__ __forceinline__ void fold_long_doc(const char* docs, int64_t o0, int64_t o1, int col, int kg,
+                                              const F (&bq)[NT], typename F::val_t (&h)[NT]) {
+    const int n = (int)((o1 - o0 + 15) >> 4);
+    if (n <= 0) return;
+    F a[DEPTH];
+    auto load = [&](F& x, int b) {
+        b = b < n ? b : n - 1;
+        int64_t row = o0 + 16 * (int64_t)b + col;
+        row = row < o1 ? row : o1 - 1;
+        x.load(docs + (size_t)row * ROWB, kg);
+    };
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {               // the order of the loads is that in which they are waited for
+        __builtin_amdgcn_sched_barrier(0);
+        load(a[i], i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (int b = 0; b < n; b += DEPTH) {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            block_mma<NT>(a[i], bq, h, false);
+            load(a[i], b + i + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("" ::: "memory");              // else the compiler moves the loads into the next turn, to their use
+    }
+}
+
+template <typename Tag, int D, int TQ>
+__global__ __launch_bounds__(64, 2) void k_gather_docs(GatherArgs A) {
+    using F = Frag<Tag, D>;
+    using V = typename F::val_t;
+    constexpr int ROWB = D * F::ELEM_BYTES;
+    constexpr int NQ = share_queries<TQ>();
+    const unsigned long long shared = A.pairs_r[A.dense.shared_at];
+    if (!A.dense.by_document(shared) || A.dense.pass(*A.pairs_r, shared)) return;
+    const int lane = threadIdx.x;
+    const int col = lane & 15;
+    const int kg = lane >> 4;
+    for (int id = (int)blockIdx.x; id < (int)A.N; id += (int)gridDim.x) {
+        const uint32_t* holders = (const uint32_t*)A.holders + (size_t)id * A.nq;
+        const int m = (int)held_of(A.holders, A.nq, A.N)[id];
+        int64_t o0, o1;
+        doc_range(A, id, o0, o1);
+        for (int at = 0; at < m; at += NQ) {
+            const int left = m - at;
+            auto visit = [&](auto queries) {        // that many queries; past `left` the last one again
+                constexpr int M = decltype(queries)::value;
+                int q[M], k[M], t[M];
+                F bq[M * TQ];
+#pragma unroll
+                for (int i = 0; i < M; ++i) {
+                    const uint32_t x = holders[at + (i < left ? i : left - 1)];
+                    q[i] = (int)(x >> 14);
+                    k[i] = (int)(x & 16383u);
+                    F rows[TQ];
+                    load_query<F, ROWB, TQ>(A, q[i], col, kg, rows);
+#pragma unroll
+                    for (int tt = 0; tt < TQ; ++tt) bq[i * TQ + tt] = rows[tt];
+                    t[i] = A.pi[(size_t)q[i] * A.T + A.lo + (lane < A.nb ? lane : 0)];
+                }
+                V h[M * TQ];
+#pragma unroll
+                for (int tt = 0; tt < M * TQ; ++tt) h[tt] = lowest_val<V>();
+                fold_long_doc<ROWB, share_depth<F>()>((const char*)A.docs, o0, o1, col, kg, bq, h);
+#pragma unroll
+                for (int i = 0; i < M; ++i)
+                    if (i < left) {
+                        V hq[TQ];
+#pragma unroll
+                        for (int tt = 0; tt < TQ; ++tt) hq[tt] = h[i * TQ + tt];
+                        float w[Pack<TQ>::NW];
+                        doc_cells(hq, 1, A.qscale ? A.qscale[q[i]] * A.dscale[0] : 1.f, nullptr, w);
+                        store_cells<TQ>(A, q[i], k[i], w);
+                        reveal_cached<TQ>(A, q[i], k[i], id, t[i], w);
+                    }
+            };
+            if (NQ >= 8 && left > 4) visit(std::integral_constant<int, NQ < 8 ? 1 : 8>{});
+            else if (NQ >= 4 && left > 2) visit(std::integral_constant<int, NQ < 4 ? 1 : 4>{});
+            else if (NQ >= 2 && left > 1) visit(std::integral_constant<int, NQ < 2 ? 1 : 2>{});
+            else visit(std::integral_constant<int, 1>{});
         }
     }
 }
@@ -592,12 +751,16 @@ __global__ __launch_bounds__(256, (score_waves<TQ, Frag<Tag, D>>())) void k_gath
     }
 }
 
-enum { GM_ROUND = 0, GM_SURVIVORS = 1, GM_ALL = 2, GM_CACHE_ALL = 3 };
+enum { GM_ROUND = 0, GM_SURVIVORS = 1, GM_ALL = 2, GM_CACHE_ALL = 3, GM_DOCS = 4 };
 
 template <typename Tag, int D, int TQ>
 static hipError_t gather_mode(const GatherArgs& A, const InitArgs& I, int mode, dim3 grid, hipStream_t st) {
     const dim3 block(256);
     if (mode == GM_ROUND) k_gather_round<Tag, D, TQ><<<grid, block, 0, st>>>(A);
+    else if (mode == GM_DOCS) {
+        if constexpr (!cuts<Frag<Tag, D>>()) k_gather_docs<Tag, D, TQ><<<grid, 64, 0, st>>>(A);
+        else return hipErrorInvalidValue;
+    }
     else if (mode == GM_CACHE_ALL) k_cache_all<Tag, D, TQ><<<grid, block, 0, st>>>(A, I);
     else if constexpr (!__is_same(Tag, i8_tag)) {   // scores come from the stored embeddings
         if (mode == GM_SURVIVORS) k_gather_survivors<Tag, D, TQ><<<grid, block, 0, st>>>(A);
@@ -662,7 +825,6 @@ static hipError_t gather_any(GatherArgs& A, const InitArgs& I, int mode, const P
 // different lengths (eight or more per CU and several turns of them), few enough that a round
 // without pairs ends at once (8,192: 4.7 us; 256 per query at 128 queries: 9 us).
 constexpr long long GATHER_BLOCKS = 8192;
-
 hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, const Coarse* co, hipStream_t st) {
     GatherArgs A{};
     A.ctl = W.ctl;
@@ -673,15 +835,20 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
     while (A.G < rr.nb) A.G <<= 1;
     A.pairs_r = rr.r == 1 ? nullptr : W.pairs + rr.r;
     A.work = W.work;
-    A.dense_thr = rr.dense_thr;
+    A.dense = rr.dense;
     const long long blocks = (long long)P.nq * P.N;
+    if (rr.dense.enough) {
+        A.holders = W.stat2;
+        const hipError_t e = gather_any(A, InitArgs{}, GM_DOCS, P, W, dim3((unsigned)(P.N < 32768 ? P.N : 32768)), co, st);
+        if (e != hipSuccess) return e;
+    }
     return gather_any(A, InitArgs{}, GM_ROUND, P, W, dim3((unsigned)(blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS)), co, st);
 }
 
 hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
                             const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st) {
     GatherArgs A{};
-    A.dense_thr = ~0ull;
+    A.dense = kNeverDense;
     const InitArgs I = init_args(P, W, kn, R, seed, user_pi, tr, 0);
     long long blocks = (long long)P.nq * P.N;
     // A document shared by four wavefronts loads the query four times.  From some three pairs a CU a
@@ -775,19 +942,7 @@ struct SelShared {
     float round_tau[COLBANDIT_MAX_ROUNDS];
 };
 
-// Inclusive sum over the wavefront's lanes, in lane order (DPP: shifts by 1, 2, 4, 8 inside the
-// rows of 16 lanes, then the rows' totals are passed on).
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
-    return v;
-}
-
-// the same inside each row of 16 lanes
+// wave_incl_scan inside each row of 16 lanes
 __device__ __forceinline__ int row_incl_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
@@ -1122,12 +1277,12 @@ struct SelArgs {
     int32_t* list0;
     int32_t* list1;
     float2* stat;
-    const float2* stat2;
+    float2* stat2;
     unsigned long long* pairs;           // [R+2] pairs, then [R+2] document tokens of those pairs
     unsigned long long* work;            // [nq] queries of the next round
     const int64_t* off;                  // document offsets (token counts of the kept pairs)
     int R;
-    unsigned long long dense_thr;        // ~0: this round cannot be a dense one
+    DenseRule dense;
     int64_t N;
     int nq, T, B, K, KM;
     int r, n, n_prev, nb;                // this launch's round
@@ -1148,6 +1303,7 @@ struct SelArgs {
     uint8_t* tr_alive;
     int32_t* seg_cnt;                    // [nq][SEG_MAX]: candidates per segment (k_select_segments)
     float kappa;                         // radius per unit sigma_hat of the round
+    unsigned enough;                     // round 1, where round 2 may gather by document (DenseRule); else 0
 };
 // ... of every round.  A parameter of its own: indexed at run time, it would keep the whole of SelArgs, which
 // the compiler otherwise takes apart, in scratch memory.
@@ -1208,6 +1364,17 @@ __device__ __forceinline__ void note_round(SelShared& sh, int r, int count, floa
     sh.round_tau[r - 1] = tau;
 }
 
+// Enters a query's list (in the buffer nc.cur) with its documents (held_of).
+__device__ __forceinline__ void hold_documents(const SelArgs& A, int q, const QueryCtl& nc) {
+    const int32_t* list = (nc.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+    uint32_t* holders = (uint32_t*)A.stat2;
+    int* held = (int*)held_of(A.stat2, A.nq, A.N);
+    for (int k = (int)threadIdx.x; k < nc.count; k += SEL_THREADS) {
+        const int id = list[k];
+        holders[(size_t)id * A.nq + atomicAdd(held + id, 1)] = (uint32_t)q << 14 | (uint32_t)k;
+    }
+}
+
 // The end of a query's rounds in this launch: its state, and the documents (pairs and tokens) that
 // the next round would have to gather if the list holds ids.
 // Also writes the history of the rounds run, and of those that the query will not take part in.
@@ -1220,6 +1387,8 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
         if ((threadIdx.x & 63) == 0 && my_tokens != 0) atomicAdd(kept_tokens, (unsigned long long)my_tokens);
     }
     __syncthreads();
+    // Lists that may make a round worth gathering by document, if others are like them (DenseRule::enough).
+    const bool entered = A.enough != 0u && nc.active && nc.count <= A.cache_cap && 4ll * nc.count * A.nq >= (long long)A.enough;
     const int x = A.r + (int)threadIdx.x;           // round
     if (x <= (nc.active ? r : A.R)) {
         const int count = x <= r ? sh.round_count[x - 1] : nc.count;
@@ -1232,12 +1401,15 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
     }
     if (threadIdx.x == 0) {
         A.ctl[q] = nc;
-        if (nc.active) {                            // pairs and work item in one step: starts ascend with the items
-            const unsigned long long at = atomicAdd(A.pairs + r + 1, work_add(nc.count));
-            A.work[work_count(at)] = work_item(q, pair_count(at));
+        if (nc.active) {
+            // pairs and work item in one step: starts ascend with the items
+            const unsigned long long at = atomicAdd(entered ? A.pairs + 2 * (A.R + 2) : A.pairs + r + 1, work_add(nc.count));
+            const int place = (int)work_count(at);
+            A.work[entered ? A.nq - 1 - place : place] = work_item(q, pair_count(at));
             atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
         }
     }
+    if (entered) hold_documents(A, q, nc);
 }
 
 // Round 1 of a query all of whose cells are cached: the pairs that go on, and their tokens, for the
@@ -2057,11 +2229,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
     int32_t* out = (out_sel ? A.list1 : A.list0) + (size_t)q * A.N;
     // entries are cache slots if this round's gather has cached the cells (same rule as in
     // k_gather_round); an active query's list always came as ids, for cached rounds end here
-    const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
+    const bool dense = A.dense.thr != NEVER_DENSE && A.dense.pass(A.pairs + A.r);
     const bool slots = A.cache_all || (!c.implicit && count <= A.cache_cap && !dense);
     float2* stat = slots ? A.cstat + (size_t)q * A.cache_cap : A.stat + (size_t)q * A.N;
     const float2* bat = A.stat2 + (size_t)q * A.N;
     const bool fold_dense = dense && in != nullptr;   // a batch that a dense pass left in stat2
+    if (slots) in = nullptr;                        // slot = place in the list of ids
     if (threadIdx.x == 0) kept_tokens = 0ull;
     clear_hist(sh);
 
@@ -2197,7 +2370,7 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     const int len = seg_len(count);
     const int n_seg = seg_count(count);
     if ((int)blockIdx.x >= n_seg) return;
-    const bool dense = A.dense_thr != ~0ull && dense_round(A.pairs + A.r, A.dense_thr);
+    const bool dense = A.dense.thr != NEVER_DENSE && A.dense.pass(A.pairs + A.r);
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
     int32_t* out = (out_sel ? A.list1 : A.list0) + (size_t)q * A.N;
@@ -2311,7 +2484,7 @@ static TopkArgs topk_args(const Problem& P, const Work& W, bool use_ctl, bool ca
 
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st) {
+                               bool note_pairs, bool share, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st) {
     SelArgs A{};
     A.cache_all = cache_all ? 1 : 0;
     A.note_pairs = cache_all && note_pairs ? 1 : 0;
@@ -2326,7 +2499,7 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.work = W.work;
     A.off = P.off;
     A.R = R;
-    A.dense_thr = rr.dense_thr;
+    A.dense = rr.dense;
     A.N = P.N;
     A.nq = P.nq;
     A.T = P.T;
@@ -2354,6 +2527,7 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.tr_alive = tr.alive;
     A.seg_cnt = W.seg_cnt;
     A.kappa = kappa[rr.r];
+    A.enough = share ? share_enough(P) : 0u;
     Kappas kappas{};
     for (int r = 0; r <= R; ++r) kappas.of[r] = kappa[r];
     // lists that do not fit one workgroup's registers are first cut down, one workgroup per tile

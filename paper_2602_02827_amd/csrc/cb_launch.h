@@ -25,8 +25,9 @@ struct Work {
     float2* stat2;        // [nq][N] batch (sum, centred squares) of a later round's dense pass
     unsigned long long* pairs;   // [R+2] pairs[r]: (query, doc) pairs round r would have to gather
                                  // and the queries that hold them (pair_count, work_count);
-                                 // then [R+2]: the document tokens of those pairs
-    unsigned long long* work;    // [nq] the queries of the next round (work_item)
+                                 // then [R+2]: the document tokens of those pairs; then as [2], which does not
+                                 // count them, the pairs of round 2 whose lists are entered by document
+    unsigned long long* work;    // [nq] the queries of the next round (work_item), from the end those entered by document
     int32_t* seg_cnt;     // [nq][64] candidates per segment of a segmented pre-filter
     float* rescored;      // [nq][N] exact score of the k-th survivor
     float* scores;        // [nq][N] Full-MaxSim scores when the caller keeps none
@@ -70,10 +71,12 @@ struct RevealRound {
     int lo, nb;           // batch = pi[lo .. lo+nb)
     int n_prev, n;        // cells revealed before / after the round
     // Rounds >= 2 pick their reveal path on the device: the corpus-streaming pass if
-    // pairs[r] > dense_thr, else the per-pair gather.  Every kernel of the round evaluates the
-    // same test.  ~0: always gather (also round 1, whose path the host fixes).
-    unsigned long long dense_thr;
+    // pairs[r] says (DenseRule), else by gathering.  Every kernel of the round evaluates the
+    // same test.  Round 1, whose path the host fixes: never.
+    DenseRule dense;
 };
+
+constexpr DenseRule kNeverDense{NEVER_DENSE, 0u, 0u, 0, 0};
 
 struct Knobs {
     int K, M, B;
@@ -82,12 +85,17 @@ struct Knobs {
 
 // n_chunks > 0: also fills the chunk table of the corpus passes (launch_dense_prepare).
 hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
-                       const int32_t* user_pi, const Trace& tr, int n_chunks, hipStream_t st);
+                       const int32_t* user_pi, const Trace& tr, const Coarse* co, int n_chunks, hipStream_t st);
 
 // Reveal round rr by gathering the documents of every active (query, document) pair.  Queries whose
 // list fits the cell cache get all T cells of their documents computed once and cached;
 // k_select_prune and the rescore read them back.
 hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRound& rr, const Coarse* co, hipStream_t st);
+// Whether round 2 may gather documents for several queries at a time (rr.dense.enough, k_gather_docs), and the logarithm of
+// how many.
+bool shares_documents(const Problem& P, const Work& W, const Coarse* co);
+int share_group_lg(int T);
+unsigned share_enough(const Problem& P);
 // The smallest calls, in the place of launch_init: all cells of all documents go to the cell cache (slot =
 // document), and the queries are set up in the same launch.
 hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
@@ -137,10 +145,10 @@ int dense_chunks(const Problem& P, const Work& W);
 
 // Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
 // this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
-// per unit sigma_hat of round r.  topk_ids (after launch_cache_all, exact cells): the launch ends with the top-K.
+// per unit sigma_hat of round r.  share: round 1 of a call whose round 2 has rr.dense.enough.  topk_ids (after launch_cache_all, exact cells): the launch ends with the top-K.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
+                               bool note_pairs, bool share, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
 // list position); else all N documents (vals indexed by id).  cached: the queries whose list holds

@@ -740,6 +740,36 @@ def test_gathered_rounds_of_more_pairs_than_workers(B, S, N, nq, T, longest):
         _same_run(runs[0], r)
 
 
+@pytest.mark.parametrize("N,nq,T,d,alpha,coarse,shared", [
+    (600, 9, 24, 128, 1.0, False, True), (600, 9, 24, 128, 0.05, False, False), (1100, 5, 16, 64, 1.0, False, True),
+    (700, 21, 40, 96, 1.0, False, True), (500, 17, 100, 32, 1.0, False, True), (800, 11, 9, 128, 1.0, True, True),
+    (700, 13, 33, 64, 1.0, True, True), (17000, 6, 32, 32, 0.5, False, True)])
+def test_long_documents_are_gathered_for_several_queries_at_once(B, S, N, nq, T, d, alpha, coarse, shared):
+    """Round 2 by document (k_gather_docs): groups of queries of every size, documents of ragged length and without tokens,
+    all widths and the codes, lists that are too few for it, lists beyond the cell cache.  The decisions, bounds and bits
+    are those of gathers pair by pair in every round, and of corpus passes."""
+    rng = np.random.default_rng(N + T)
+    L = rng.integers(200, 460, N)
+    L[rng.integers(0, N, 5)] = 0
+    L[rng.integers(0, N, 40)] = rng.integers(1, 40, 40)
+    L[:3] = (16, 17, 1500)
+    w = _custom(S, L.tolist(), nq, T, d, "bf16", 3)
+    w.Q[0] *= 0.25                                           # lists of unequal length
+    more = {}
+    if coarse:
+        more["docs_i8"], more["docs_scale"] = B.colbandit_quantize_i8(w.docs)
+    call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 5, alpha, 0.01, 5, 3, trace=True, **more, **o)
+    names = _kernels(lambda: B.colbandit_topk(w.Q, w.docs, w.offsets, 5, alpha, 0.01, 5, 3, want_stats=False, **more))
+    assert "k_gather_docs<" in names
+    runs = [call(), call(no_cell_cache=True, later_rounds=2), call(later_rounds=1), call(later_rounds=2)]
+    torch.cuda.synchronize()
+    lists = runs[0]["trace"].count[1]
+    held = sum(int(c) for c in lists if c > 10 and c <= 16384)
+    assert (held >= (4096 if N <= 8192 else N // 2)) == shared
+    for r in runs[1:]:
+        _same_run(runs[0], r)
+
+
 @pytest.mark.parametrize("dtype,N,nq,T,d,Bsz,alpha,coarse",
                          [("bf16", 11, 1, 1, 128, 1, 1.0, None), ("bf16", 1000, 3, 32, 128, 4, 0.2, None),
                           ("bf16", 1025, 4, 128, 96, 7, 1.0, None), ("bf16", 4097, 1, 65, 32, 16, 1.0, None),
