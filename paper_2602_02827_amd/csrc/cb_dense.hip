@@ -36,17 +36,26 @@ namespace cb {
 // over eight where it can (a wavefront needs all tiles of a query): four tiles of pieces would leave
 // one wavefront per SIMD, and eight wavefronts share the cutting of the tokens (16 queries x 20,000
 // documents of d = 128: 1,417 us with four, 1,302 with eight; 32 of 16 tokens at d = 96 1,313 and 1,030).
-template <typename Tag, int D, int TILES, int TQ> constexpr int dense_waves() {
-    return !Tag::wide && D >= 96 && TILES == 4 && TQ <= 2 ? 8 : 4;
+// PAIR: sixteen tiles of 128-byte rows (codes of d = 128, bf16 of d = 64) go to two wavefronts of eight tiles, which
+// read an operand block from LDS half as often for its matrix instructions and meet half as often: Col-Bandit, 64
+// queries x 20,000 pages, codes 788 -> 762 us, 36 x 500,000 in d = 64 1,999 -> 1,908, exhaustive, 8 x 50,000 in d = 64 194 -> 186.
+// (Other widths lose registers or gain nothing: bf16 of d = 128 64 x 50,000 455 -> 464, 96 474 -> 604, 32 583 -> 614.)
+// Their chunks take longer, so there have to be enough for several turns (pair_pays): 4 queries of 60 tokens x 1,613
+// pages 64 -> 70 us, 11 x 868 documents 21 -> 22, 4 x 17,775 pages 529 -> 512, 7 x 41,000 documents 185 -> 180.
+constexpr int PAIR = -2;                           // in the place of a number of wavefronts that split the documents
+template <typename Tag, int D, int TILES, int TQ, int SPLIT> constexpr int dense_waves() {
+    return SPLIT == PAIR ? 2 : !Tag::wide && D >= 96 && TILES == 4 && TQ <= 2 ? 8 : 4;
 }
+template <typename Tag, int D> constexpr bool can_pair() { return Tag::wide && D * Frag<Tag, D>::ELEM_BYTES == 128; }
+static bool pair_pays(int64_t total, int64_t N) { return total >= 2100000 && N >= 2048; }
 // Ring geometry: four stages.  Kernels with few column tiles per wavefront (small query
 // batches: bound by memory, little register use) take 32-row stages, so that four workgroups fit
 // a CU instead of two and more wavefronts hide the latencies; the others take 64-row stages.
 // A_REGS: registers of one operand block (the query rows take NT of them, two token blocks are in
 // flight); four, three or two workgroups per CU by what that and the rings' LDS leave.
-template <int NT, int PITCH, int A_REGS, int PLANES> struct RingShape {
+template <int NT, int PITCH, int A_REGS, int PLANES, int WAVES> struct RingShape {
     static constexpr int ROWS_PER_LOAD = 64 / (PITCH / 16);
-    static constexpr bool SMALL = NT <= 4 && 32 / ROWS_PER_LOAD / 4 >= 1;
+    static constexpr bool SMALL = (NT <= 4 || WAVES == 2) && 32 / ROWS_PER_LOAD / WAVES >= 1;
     static constexpr int STAGE_ROWS = SMALL ? 32 : 64;
     static constexpr int RING_ROWS = 4 * STAGE_ROWS;
     static constexpr int REGS = (NT + 2) * A_REGS + 40;
@@ -54,12 +63,12 @@ template <int NT, int PITCH, int A_REGS, int PLANES> struct RingShape {
     static constexpr int BY_SHAPE = SMALL ? (NT <= 2 ? 4 : 3) : 2;
     static constexpr int BY_LDS = 160 * 1024 / (RING_ROWS * PITCH);
     static constexpr int FIT = BY_REGS < BY_SHAPE ? BY_REGS : BY_SHAPE;
-    static constexpr int MIN_BLOCKS = FIT < BY_LDS ? FIT : BY_LDS;
+    static constexpr int MIN_BLOCKS = FIT < BY_LDS ? FIT : BY_LDS;   // of four wavefronts: wavefronts per SIMD
     static_assert(MIN_BLOCKS >= 1 && MIN_BLOCKS * RING_ROWS * PITCH <= 160 * 1024, "the rings of a CU's workgroups");
 };
 // fp32: two slots of 32 rows, each row in three planes of bf16 pieces; the loads of the next stage are
 // in registers (16 at most).
-template <int NT, int PITCH, int A_REGS> struct RingShape<NT, PITCH, A_REGS, 3> {
+template <int NT, int PITCH, int A_REGS, int WAVES> struct RingShape<NT, PITCH, A_REGS, 3, WAVES> {
     static constexpr int STAGE_ROWS = 32;
     static constexpr int RING_ROWS = 2 * STAGE_ROWS;
     static constexpr int REGS = (NT + 2) * A_REGS + 60;
@@ -109,16 +118,18 @@ struct DenseArgs {
 // every width; 64 queries of 24 tokens over 20,000 pages of 1,030 tokens 6.84 -> 5.49 ms (d = 32: 1.82 ->
 // 1.43), of 40 tokens over 6.4 M tokens 4.43 -> 3.49.
 constexpr int PACKED_NT = 6;
-template <typename Tag, int D, int TILES, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
-__global__ __launch_bounds__((64 * dense_waves<Tag, D, TILES, TQ>()),
-                             (RingShape<TILES * 4 / dense_waves<Tag, D, TILES, TQ>(), RowShape<Frag<Tag, D>, D>::PITCH,
-                                        RowShape<Frag<Tag, D>, D>::A_REGS, RowShape<Frag<Tag, D>, D>::PLANES>::MIN_BLOCKS))
+template <typename Tag, int D, int TILES, int TQ, bool REVEAL, int SPLIT = 0, bool PACKED = false>
+__global__ __launch_bounds__((64 * dense_waves<Tag, D, TILES, TQ, SPLIT>()),
+                             (RingShape<TILES * 4 / dense_waves<Tag, D, TILES, TQ, SPLIT>(), RowShape<Frag<Tag, D>, D>::PITCH,
+                                        RowShape<Frag<Tag, D>, D>::A_REGS, RowShape<Frag<Tag, D>, D>::PLANES,
+                                        dense_waves<Tag, D, TILES, TQ, SPLIT>()>::MIN_BLOCKS))
 void k_dense(DenseArgs A) {
     using F = Frag<Tag, D>;
-    constexpr int WAVES = dense_waves<Tag, D, TILES, TQ>();
+    constexpr int SPLIT_DOCS = SPLIT > 0 ? SPLIT : 0;
+    constexpr int WAVES = dense_waves<Tag, D, TILES, TQ, SPLIT>();
     constexpr int NT = TILES * 4 / WAVES;          // column tiles of a wavefront
     constexpr int PLANES = RowShape<F, D>::PLANES;
-    using RS = RingShape<NT, RowShape<F, D>::PITCH, RowShape<F, D>::A_REGS, PLANES>;
+    using RS = RingShape<NT, RowShape<F, D>::PITCH, RowShape<F, D>::A_REGS, PLANES, WAVES>;
     constexpr int STAGE_ROWS = RS::STAGE_ROWS;
     constexpr int RING_ROWS = RS::RING_ROWS;
     using V = typename F::val_t;           // float, or int for int8 codes
@@ -132,7 +143,7 @@ void k_dense(DenseArgs A) {
     // always have: a token row is read once and should not push other lines out of L2 - above all those
     // of the (sum, M2) array, which fill up over several documents; such copies carry the non-temporal
     // hint (bit 1).
-    constexpr int LOAD_POLICY = (REVEAL || NT <= 4) ? 2 : 0;
+    constexpr int LOAD_POLICY = (REVEAL || TILES <= 4) ? 2 : 0;
     // Swizzle key of a ring row: rows whose 16-byte pieces would fall on the same banks (row
     // stride PITCH against the 256-byte bank window) get different keys.  The key's period must
     // divide the rows of one load of all wavefronts, of fp32 those of a stage.
@@ -223,7 +234,8 @@ void k_dense(DenseArgs A) {
     // lane at physical piece position p of LDS row r fetches the logical piece p ^ (r & (NCH-1)).
     const char* src = (const char*)A.docs + (size_t)tok_begin * ROWB;
     constexpr int ROWS_PER_LOAD = 64 / NCH;
-    constexpr int LOADS_PER_WAVE = STAGE_ROWS / ROWS_PER_LOAD / 4;    // not of fp32
+    constexpr int LOAD_WAVES = WAVES == 2 ? 2 : 4;                    // not of fp32
+    constexpr int LOADS_PER_WAVE = STAGE_ROWS / ROWS_PER_LOAD / LOAD_WAVES;
     // A lane's place inside a load does not depend on the stage or on the load's number (both
     // move the row by multiples of the swizzle period): row wave*ROWS_PER_LOAD + lane/NCH of the
     // load group, piece (lane % NCH) ^ key(row).  A complete stage therefore needs no per-lane
@@ -234,12 +246,13 @@ void k_dense(DenseArgs A) {
         const int c = (lane & (NCH - 1)) ^ ((row >> KEY_SHIFT) & KEY_MASK);
         return c < ROWB / 16 ? c : c - (NCH - ROWB / 16);
     };
+    static_assert(F32 || LOAD_WAVES * ROWS_PER_LOAD % ((KEY_MASK + 1) << KEY_SHIFT) == 0, "the swizzle's period");
     const unsigned fetch_off = (unsigned)(lrow0 * ROWB + piece_of(lrow0) * 16);
     auto stage_fetch = [&](int s) {
         if ((s + 1) * STAGE_ROWS <= ntok) {
 #pragma unroll
             for (int i = 0; i < LOADS_PER_WAVE; ++i) {
-                const int r0 = s * STAGE_ROWS + i * 4 * ROWS_PER_LOAD;               // uniform
+                const int r0 = s * STAGE_ROWS + i * LOAD_WAVES * ROWS_PER_LOAD;      // uniform
                 __builtin_amdgcn_global_load_lds(
                     (const __attribute__((address_space(1))) void*)(src + (size_t)r0 * ROWB + fetch_off),
                     (__attribute__((address_space(3))) void*)(ring + ((r0 + wave * ROWS_PER_LOAD) & (RING_ROWS - 1)) * PITCH),
@@ -250,7 +263,7 @@ void k_dense(DenseArgs A) {
         // the chunk's last, incomplete stage: rows past the end are clamped (they are never read)
 #pragma unroll
         for (int i = 0; i < LOADS_PER_WAVE; ++i) {
-            const int rbase = s * STAGE_ROWS + (i * 4 + wave) * ROWS_PER_LOAD;   // wave-uniform
+            const int rbase = s * STAGE_ROWS + (i * LOAD_WAVES + wave) * ROWS_PER_LOAD;   // wave-uniform
             if (rbase < ntok) {
                 const int lrow = rbase + lane / NCH;                  // the LDS row this lane fills
                 const int grow = lrow < ntok ? lrow : ntok - 1;
@@ -633,7 +646,7 @@ void k_dense(DenseArgs A) {
         ring_barrier();
 #pragma unroll
         for (int i = 0; i < LOADS_PER_WAVE; ++i) {
-            const int r0 = bs + 2 * STAGE_ROWS + i * 4 * ROWS_PER_LOAD;               // uniform
+            const int r0 = bs + 2 * STAGE_ROWS + i * LOAD_WAVES * ROWS_PER_LOAD;      // uniform
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void*)(src + (size_t)r0 * ROWB + fetch_off),
                 (__attribute__((address_space(3))) void*)(ring + ((r0 + wave * ROWS_PER_LOAD) & (RING_ROWS - 1)) * PITCH),
@@ -732,13 +745,13 @@ static void fill_dense(DenseArgs& A, const Problem& P, const Work& W, int n_chun
     A.stat = W.stat;
 }
 
-template <typename Tag, int D, int TILES, int TQ, bool REVEAL, int SPLIT_DOCS = 0, bool PACKED = false>
+template <typename Tag, int D, int TILES, int TQ, bool REVEAL, int SPLIT = 0, bool PACKED = false>
 static hipError_t dense_go(DenseArgs& A, int groups, hipStream_t st) {
     A.n_groups = groups;
     const int chunks8 = (A.n_chunks + 7) / 8 * 8;
     const long long blocks = (long long)chunks8 * A.n_groups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    k_dense<Tag, D, TILES, TQ, REVEAL, SPLIT_DOCS, PACKED><<<(unsigned)blocks, 64 * dense_waves<Tag, D, TILES, TQ>(), 0, st>>>(A);
+    k_dense<Tag, D, TILES, TQ, REVEAL, SPLIT, PACKED><<<(unsigned)blocks, 64 * dense_waves<Tag, D, TILES, TQ, SPLIT>(), 0, st>>>(A);
     return hipGetLastError();
 }
 
@@ -786,6 +799,9 @@ static hipError_t dense_score_nt(DenseArgs& A, const ScoreShape& s, hipStream_t 
         if (s.nt == 2) return dense_go<Tag, D, 2, TQ, false>(A, s.groups, st);
     }
     if constexpr (TQ <= 4) {
+        if constexpr (can_pair<Tag, D>()) {
+            if (s.nt == 4 && pair_pays(A.total, A.N)) return dense_go<Tag, D, 4, TQ, false, PAIR>(A, s.groups, st);
+        }
         if (s.nt == 4) return dense_go<Tag, D, 4, TQ, false>(A, s.groups, st);
     }
     if constexpr (Tag::wide) {
@@ -841,6 +857,9 @@ static hipError_t dense_reveal_d(DenseArgs& A, hipStream_t st) {
     const int tiles = (A.nq * A.G + 15) / 16;
     if (tiles <= 4) return dense_go<Tag, D, 1, 1, true>(A, 1, st);
     if (tiles <= 8) return dense_go<Tag, D, 2, 1, true>(A, 1, st);
+    if constexpr (can_pair<Tag, D>()) {
+        if (tiles <= 16 && pair_pays(A.total, A.N)) return dense_go<Tag, D, 4, 1, true, PAIR>(A, 1, st);
+    }
     if (!Tag::wide || tiles <= 16) return dense_go<Tag, D, 4, 1, true>(A, (tiles + 15) / 16, st);
     if constexpr (Tag::wide) return dense_go<Tag, D, 8, 1, true>(A, (tiles + 31) / 32, st);
     else return hipErrorInvalidValue;

@@ -242,6 +242,39 @@ def test_packed_query_tiles_give_the_bits_of_whole_tiles(B, S, oracle_mod, T, d)
             assert torch.equal(few["cells"], c["cells"][q:q + step])
 
 
+@pytest.mark.parametrize("codes,nq,T,Bsz", [(False, 5, 24, 4), (False, 9, 16, 3), (False, 3, 60, 4), (True, 40, 24, 4), (False, 33, 9, 4),
+                                            (True, 12, 40, 16)])
+def test_sixteen_tiles_of_two_wavefronts_give_the_bits_of_other_batches(B, codes, nq, T, Bsz):
+    """The corpus kernel of two wavefronts (9 to 16 tiles of 128-byte rows, 2.1 M tokens or more) on ragged documents: scores and
+    cells are those of single queries, a round's decisions and bounds those of gathers."""
+    g = torch.Generator(device="cuda"); g.manual_seed(nq)
+    d = 128 if codes else 64
+    L = torch.randint(900, 1180, (2048,), device="cuda", generator=g)
+    L[:900] = torch.randint(1, 2070, (900,), device="cuda", generator=g)
+    L[40:200] = torch.randint(1, 20, (160,), device="cuda", generator=g)
+    L[-1] += max(0, 2100000 - int(L.sum()))
+    off = torch.zeros(2049, dtype=torch.int64, device="cuda"); off[1:] = L.cumsum(0)
+    unit = lambda *s: torch.nn.functional.normalize(torch.randn(*s, device="cuda", generator=g), dim=-1).bfloat16()
+    E, Q = unit(int(off[-1]), d), unit(nq, T, d)
+    more = {}
+    if codes:
+        more["docs_i8"], more["docs_scale"] = B.colbandit_quantize_i8(E)
+    else:
+        if nq < 20:
+            full = lambda q: B.colbandit_full_maxsim(q.contiguous(), E, off, K=3, want_cells=True)
+            res = []
+            names = _kernels(lambda: full(Q), res)
+            assert "k_dense<cb::bf16_tag, 64, 4, " in names and "false, -2, false>" in names
+            for q in (0, nq // 2, nq - 1):
+                one = full(Q[q:q + 1])
+                assert torch.equal(one["scores"][0], res[0]["scores"][q]) and torch.equal(one["cells"][0], res[0]["cells"][q])
+    call = lambda **o: B.colbandit_topk(Q, E, off, 5, 0.3, 0.01, 5, 3, B=Bsz, trace=True, **more, **o)
+    rows = nq * (16 if Bsz > 8 else 4)
+    if 128 < rows <= 256:
+        assert f"k_dense<cb::{'i8' if codes else 'bf16'}_tag, {d}, 4, 1, true, -2, false>" in _kernels(call)
+    _same_run(call(), call(force_gather=True))
+
+
 def test_documents_much_longer_than_a_token_chunk(B, S, oracle_mod):
     """Documents of several chunks leave runs of empty chunks behind them (a chunk belongs to the
     document that starts in it); every workgroup with an empty chunk must exit and the others
