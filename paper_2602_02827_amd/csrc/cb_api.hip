@@ -800,57 +800,70 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     DenseRule round_rule[COLBANDIT_MAX_ROUNDS + 2];
     for (int r = 0; r <= R + 1; ++r) round_rule[r] = kNeverDense;
     const bool share = loop && !cache_all && shares_documents(P, W, co);
-    for (int r = 1; e == hipSuccess && loop && r <= R; ++r) {
+    auto round_of = [&](int r) {
         RevealRound rr{};
         rr.r = r;
         rr.lo = (r - 1) * kn.B;
         rr.nb = (r * kn.B < T ? r * kn.B : T) - rr.lo;
         rr.n_prev = rr.lo;
         rr.n = rr.lo + rr.nb;
+        rr.dense = kNeverDense;
+        if (r == 1 || cache_all) return rr;
+        if (dense && later_rounds != 2) {
+            double t_pair = 0.0;
+            int G = 1;
+            while (G < rr.nb) G <<= 1;
+            const unsigned long long thr = later_rounds == 1 ? 0ull
+                : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap, &t_pair);
+            if (thr < (unsigned long long)n_queries * (unsigned long long)N) rr.dense.thr = thr;
+            // by document: the corpus at 5.5 TB/s, and the documents again, from the last-level cache, for every
+            // group of queries
+            if (t_pair > 0.0) rr.dense.base = (uint32_t)fmin((double)P.total * P.d * (co ? 1.0 : 2.0) / 5.5e12 / t_pair, 4e9);
+            rr.dense.lg_per = (uint16_t)(1 + share_group_lg(T));
+            // Lists that fit the cache, and cost no more even if they are full (and those that are not entered by document
+            // hold N pairs): round 2 is the last to launch.
+            if (share && later_rounds != 1 && N <= (int64_t)W.cache_cap &&
+                rr.dense.base + (((unsigned long long)N * (unsigned)n_queries) >> rr.dense.lg_per) + (unsigned long long)N <= rr.dense.thr)
+                rr.dense.thr = NEVER_DENSE;
+        }
+        if (r == 2 && share) {
+            rr.dense.shared_at = (uint16_t)(2 * (R + 2) - 2);
+            rr.dense.enough = share_enough(P);
+        }
+        return rr;
+    };
+    // A gathered round in which every list fits the cell cache is the last one to launch: k_select_prune runs all rounds
+    // of a cached query.
+    auto last_launched = [&](const RevealRound& rr) {
+        return cache_all || (rr.r >= 2 && rr.dense.thr == NEVER_DENSE && N <= (int64_t)W.cache_cap);
+    };
+    // ... and, with exact cells, goes on to the top-K (cache_all: in round 1)
+    const bool finish = !co && (cache_all || (loop && R >= 2 && last_launched(round_of(2))));
+    for (int r = 1; e == hipSuccess && loop && r <= R; ++r) {
+        const RevealRound rr = round_of(r);
         int G = 1;
         while (G < rr.nb) G <<= 1;
-        rr.dense = kNeverDense;
+        round_rule[r] = rr.dense;
         if (r == 1 && dense) {
             e = launch_dense_reveal(P, W, n_chunks, rr, G, co, st);
         } else if (!cache_all) {
-            if (r >= 2 && dense && later_rounds != 2) {
-                double t_pair = 0.0;
-                const unsigned long long thr = later_rounds == 1 ? 0ull
-                    : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap, &t_pair);
-                if (thr < (unsigned long long)n_queries * (unsigned long long)N) rr.dense.thr = thr;
-                // by document: the corpus at 5.5 TB/s, and the documents again, from the last-level cache, for every
-                // group of queries
-                if (t_pair > 0.0) rr.dense.base = (uint32_t)fmin((double)P.total * P.d * (co ? 1.0 : 2.0) / 5.5e12 / t_pair, 4e9);
-                rr.dense.lg_per = (uint16_t)(1 + share_group_lg(T));
-                // Lists that fit the cache, and cost no more even if they are full (and those that are not entered by document
-                // hold N pairs): round 2 is the last to launch.
-                if (share && later_rounds != 1 && N <= (int64_t)W.cache_cap &&
-                    rr.dense.base + (((unsigned long long)N * (unsigned)n_queries) >> rr.dense.lg_per) + (unsigned long long)N <= rr.dense.thr)
-                    rr.dense.thr = NEVER_DENSE;
-            }
-            if (r == 2 && share) {
-                rr.dense.shared_at = (uint16_t)(2 * (R + 2) - 2);
-                rr.dense.enough = share_enough(P);
-            }
-            round_rule[r] = rr.dense;
             e = launch_dense_reveal_later(P, W, n_chunks, rr, G, co, st);
             if (e == hipSuccess) e = launch_gather_round(P, W, rr, co, st);
         }
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
-        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, share && r == 1, tr,
-                                                     cache_all && !co ? topk_ids : nullptr, topk_scores, st);
+        const bool last = last_launched(rr);
+        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, share && r == 1,
+                                                     finish && !last, tr, finish && last ? topk_ids : nullptr, topk_scores, st);
         pt.mark(PH_SELECT);
-        // A gathered round in which every list fits the cell cache is the last one to launch:
-        // k_select_prune runs all rounds of a cached query.
-        if (cache_all || (r >= 2 && rr.dense.thr == NEVER_DENSE && N <= (int64_t)W.cache_cap)) break;
+        if (last) break;
     }
     // exact rescore from the stored embeddings; cached cells give it only when they are exact
-    // (after cache_all every query's survivors have them, and k_select_prune has gone on to the top-K).  Where no
+    // (where the last launched round has gathered every query's survivors, k_select_prune has gone on to the top-K).  Where no
     // round ran, all documents survive: shared by wavefronts only if they are few (296 documents of 18
     // tokens x 74 queries 86 -> 44 us a call)
     if (e == hipSuccess && !loop) e = launch_gather_all(P, W, W.rescored, nullptr, st);    // no round: all documents
-    else if (e == hipSuccess && !(cache_all && !co)) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, cache_all, st);
-    if (e == hipSuccess && !(cache_all && !co)) e = launch_topk(P, W, true, !co, cache_all, W.rescored, K, topk_ids, topk_scores, st);
+    else if (e == hipSuccess && !finish) e = launch_gather_survivors(P, W, kn, W.rescored, co != nullptr, cache_all, st);
+    if (e == hipSuccess && !finish) e = launch_topk(P, W, true, !co, cache_all, W.rescored, K, topk_ids, topk_scores, st);
     pt.mark(PH_RESCORE);
     if (e != hipSuccess) {
         pt.destroy();
@@ -863,9 +876,9 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     int32_t* hist = (int32_t*)malloc(sizeof(int32_t) * nh);
     if (!hist) { pt.destroy(); return COLBANDIT_ERR_HIP; }
     hipError_t ce = hipMemcpyAsync(hist, W.cnt_hist, sizeof(int32_t) * nh, hipMemcpyDeviceToHost, st);
-    unsigned long long pairs_h[2 * (COLBANDIT_MAX_ROUNDS + 2) + 1];
+    unsigned long long pairs_h[2 * (COLBANDIT_MAX_ROUNDS + 2) + 2];
     if (ce == hipSuccess)
-        ce = hipMemcpyAsync(pairs_h, W.pairs, sizeof(unsigned long long) * (2 * (size_t)(R + 2) + 1),
+        ce = hipMemcpyAsync(pairs_h, W.pairs, sizeof(unsigned long long) * (2 * (size_t)(R + 2) + 2),
                             hipMemcpyDeviceToHost, st);
     if (ce == hipSuccess) ce = hipStreamSynchronize(st);
     // the rounds whose device-side test took the corpus pass (the same test as the kernels')
@@ -916,7 +929,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         s.ms_select_prune = phase_ms[PH_SELECT];
         s.ms_rescore_topk = phase_ms[PH_RESCORE];
         s.corpus_pass_rounds = corpus_rounds;
-        s.pairs_round2 = R >= 2 ? pair_count(pairs_h[2]) + pair_count(pairs_h[2 * (R + 2)]) : 0ull;
+        s.pairs_round2 = R >= 2 ? pair_count(pairs_h[2]) + pair_count(pairs_h[2 * (R + 2)]) - pairs_h[2 * (R + 2) + 1] : 0ull;
         s.tokens_round2 = R >= 2 ? pairs_h[(R + 2) + 2] : 0ull;
     }
     free(hist);

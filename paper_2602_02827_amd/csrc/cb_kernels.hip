@@ -45,17 +45,42 @@ struct InitArgs {
     int* held;
 };
 
-// A wavefront per query.  The permutation is a Fisher-Yates shuffle driven by SplitMix64 (Sec. 4.2:
-// one seeded uniform permutation per query); the generator's state after s steps is known in closed
-// form, so the lanes draw the T - 1 positions side by side (64-bit remainders, the costly part) and
-// only the exchanges run one after the other, between lanes' registers.  One thread per query drawing
-// them in turn took 14 us and the chunk table of the corpus pass 5 in a launch of its own, both together
-// take 7 here (T = 32).
+// The reveal order of query q, a Fisher-Yates shuffle driven by SplitMix64 (Sec. 4.2: one seeded uniform permutation per
+// query): lane x gets the tokens at places x and x + 64.  The generator's state after s steps is known in closed form, so
+// the lanes draw the T - 1 positions side by side; a place's token is found by following the place back through the
+// exchanges, five instructions each.  (One thread drawing and exchanging them in turn took 14 us, T = 32.)
+__device__ __forceinline__ void reveal_order(uint64_t seed, int q, int T, int& p0, int& p1) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t s0 = seed + ((uint64_t)q + 1ull) * 0x9E3779B97F4A7C15ull;
+    auto draw = [&](int i) -> int {                 // the position that i is exchanged with: step T - i
+        uint64_t s = s0 + (uint64_t)(T - 1 - i) * 0x9E3779B97F4A7C15ull;
+        const uint64_t z = splitmix64_next(s);
+        const uint32_t m = (uint32_t)i + 1u;        // z mod m, at most 128: in halves
+        const uint32_t high = (uint32_t)(z >> 32) % m * ((0u - m) % m);
+        return (int)((high + (uint32_t)z % m) % m);
+    };
+    int j0 = 0, j1 = 0;
+    if (lane >= 1 && lane < T) j0 = draw(lane);
+    if (lane + 64 < T) j1 = draw(lane + 64);
+    p0 = lane;
+    p1 = lane + 64;
+    for (int i = 1; i < T && i < 64; ++i) {
+        const int j = __builtin_amdgcn_readlane(j0, i);
+        p0 = p0 == i ? j : p0 == j ? i : p0;        // (places from 64 on are not reached yet)
+    }
+    for (int i = 64; i < T; ++i) {
+        const int j = __builtin_amdgcn_readlane(j1, i - 64);
+        p0 = p0 == i ? j : p0 == j ? i : p0;
+        p1 = p1 == i ? j : p1 == j ? i : p1;
+    }
+}
+
+// A wavefront per query, the chunk table of the corpus passes by other workgroups.
 __device__ __forceinline__ void init_queries(const InitArgs& A, int block) {
     const int lane = threadIdx.x & 63;
     const int q = block * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (q == 0)                                     // pair counts, their token counts, shared pairs
-        for (int r = lane; r < 2 * (A.R + 2) + 1; r += 64) A.pairs[r] = 0ull;
+    if (q == 0)                                     // pair counts, their token counts, shared and finished pairs
+        for (int r = lane; r < 2 * (A.R + 2) + 2; r += 64) A.pairs[r] = 0ull;
     if (q >= A.nq) return;
     const int T = A.T;
     if (lane == 0) {
@@ -84,23 +109,8 @@ __device__ __forceinline__ void init_queries(const InitArgs& A, int block) {
         }
         return;
     }
-    const uint64_t s0 = A.seed + ((uint64_t)q + 1ull) * 0x9E3779B97F4A7C15ull;
-    auto draw = [&](int i) -> int {                 // the position that i is exchanged with: step T - i
-        uint64_t s = s0 + (uint64_t)(T - 1 - i) * 0x9E3779B97F4A7C15ull;
-        return (int)(splitmix64_next(s) % (uint64_t)(i + 1));
-    };
-    int j0 = 0, j1 = 0, p0 = lane, p1 = lane + 64;
-    if (lane >= 1 && lane < T) j0 = draw(lane);
-    if (lane + 64 < T) j1 = draw(lane + 64);
-    for (int i = T - 1; i >= 1; --i) {
-        const int j = i < 64 ? __builtin_amdgcn_readlane(j0, i) : __builtin_amdgcn_readlane(j1, i - 64);
-        const int a = i < 64 ? __builtin_amdgcn_readlane(p0, i) : __builtin_amdgcn_readlane(p1, i - 64);
-        const int b = j < 64 ? __builtin_amdgcn_readlane(p0, j) : __builtin_amdgcn_readlane(p1, j - 64);
-        if (i < 64) p0 = lane == i ? b : p0;
-        else p1 = lane + 64 == i ? b : p1;
-        if (j < 64) p0 = lane == j ? a : p0;
-        else p1 = lane + 64 == j ? a : p1;
-    }
+    int p0, p1;
+    reveal_order(A.seed, q, T, p0, p1);
     if (lane < T) p[lane] = p0;
     if (lane + 64 < T) p[lane + 64] = p1;
 }
@@ -369,7 +379,7 @@ __device__ __forceinline__ void store_cells(const GatherArgs& A, int q, int k, c
 }
 // This round's batch of the same cells, merged into the pair's statistics, which go to the slot.  t: the batch's
 // query token of this lane; slot s of the batch (lane s of row 0) fetches its cell from its owner.
-template <int TQ>
+template <int TQ, bool NAMED = true>
 __device__ __forceinline__ void reveal_cached(const GatherArgs& A, int q, int k, int id, int t, const float (&w)[Pack<TQ>::NW]) {
     using P = Pack<TQ>;
     const int lane = threadIdx.x & 63;
@@ -388,7 +398,7 @@ __device__ __forceinline__ void reveal_cached(const GatherArgs& A, int q, int k,
         if (A.n_prev > 0) st = A.stat[(size_t)q * A.N + id];
         merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
         A.cstat[slot] = st;
-        A.cid[slot] = id;
+        if (NAMED) A.cid[slot] = id;                // else slots are documents
     }
 }
 
@@ -415,8 +425,9 @@ constexpr int64_t ALL_DOCS = 64;
 //                  documents so before round 1, which takes its batch from the cells as well; the
 //                  launch also sets the queries up, which nothing in it needs, and two launches make
 //                  the call (1 query x 1,000 documents of 48 fp32 tokens: 45 -> 39 us).
-template <typename Tag, int D, int TQ, bool CACHE_ALL>
-__device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) {
+// batch_token(q): this lane's token of the round's batch (REVEAL).
+template <typename Tag, int D, int TQ, bool CACHE_ALL, bool REVEAL, class TokenFn>
+__device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks, TokenFn batch_token) {
     using F = Frag<Tag, D>;
     using V = typename F::val_t;
     constexpr int ROWB = D * F::ELEM_BYTES;
@@ -538,7 +549,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
         } else {
             F bq[TQ];
             const bool query_wild = load_query<F, ROWB, TQ>(A, q, col, kg, bq);
-            const int t = CACHE_ALL ? 0 : A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
+            const int t = REVEAL ? batch_token(q) : 0;
             for (; k < k_end; ++k) {
                 const int id = list ? list[k] : k;
                 int64_t o0, o1;
@@ -551,7 +562,7 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks) 
                 doc_cells(h, parts, scale, ex, w);
                 if (coop && wave > 0) continue;
                 store_cells<TQ>(A, q, k, w);
-                if (!CACHE_ALL) reveal_cached<TQ>(A, q, k, id, t, w);
+                if (REVEAL) reveal_cached<TQ, !CACHE_ALL>(A, q, k, id, t, w);
             }
         }
     }
@@ -658,13 +669,25 @@ __global__ __launch_bounds__(64, 2) void k_gather_docs(GatherArgs A) {
 
 template <typename Tag, int D, int TQ>
 __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_gather_round(GatherArgs A) {
-    gather_round<Tag, D, TQ, false>(A, (int)gridDim.x);
+    gather_round<Tag, D, TQ, false, true>(A, (int)gridDim.x, [&](int q) {
+        const int lane = threadIdx.x & 63;
+        return A.pi[(size_t)q * A.T + A.lo + (lane < A.nb ? lane : 0)];
+    });
 }
 // (a kernel of its own: the longer argument list cost every launch of a round 1 us)
-template <typename Tag, int D, int TQ>
+template <typename Tag, int D, int TQ, bool REVEAL>
 __global__ __launch_bounds__(256, (round_waves<TQ, Frag<Tag, D>>())) void k_cache_all(GatherArgs A, InitArgs I) {
     const int n_blocks = (int)gridDim.x - I.init_blocks;
-    if ((int)blockIdx.x < n_blocks) gather_round<Tag, D, TQ, true>(A, n_blocks);
+    if ((int)blockIdx.x < n_blocks) gather_round<Tag, D, TQ, true, REVEAL>(A, n_blocks, [&](int q) {
+        const int lane = threadIdx.x & 63;
+        int p0, p1;
+        if (I.user_pi) {
+            p0 = I.user_pi[(size_t)q * A.T + (lane < A.nb ? lane : 0)];
+            return p0 < 0 ? 0 : (p0 >= A.T ? A.T - 1 : p0);
+        }
+        reveal_order(I.seed, q, A.T, p0, p1);       // the table is being written by this launch
+        return lane < A.nb ? p0 : __builtin_amdgcn_readfirstlane(p0);
+    });
     else init_queries(I, (int)blockIdx.x - n_blocks);
 }
 
@@ -761,7 +784,10 @@ static hipError_t gather_mode(const GatherArgs& A, const InitArgs& I, int mode, 
         if constexpr (!cuts<Frag<Tag, D>>()) k_gather_docs<Tag, D, TQ><<<grid, 64, 0, st>>>(A);
         else return hipErrorInvalidValue;
     }
-    else if (mode == GM_CACHE_ALL) k_cache_all<Tag, D, TQ><<<grid, block, 0, st>>>(A, I);
+    else if (mode == GM_CACHE_ALL) {
+        if (A.nb) k_cache_all<Tag, D, TQ, true><<<grid, block, 0, st>>>(A, I);
+        else k_cache_all<Tag, D, TQ, false><<<grid, block, 0, st>>>(A, I);
+    }
     else if constexpr (!__is_same(Tag, i8_tag)) {   // scores come from the stored embeddings
         if (mode == GM_SURVIVORS) k_gather_survivors<Tag, D, TQ><<<grid, block, 0, st>>>(A);
         else k_gather_all<Tag, D, TQ><<<grid, block, 0, st>>>(A);
@@ -845,11 +871,21 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
     return gather_any(A, InitArgs{}, GM_ROUND, P, W, dim3((unsigned)(blocks < GATHER_BLOCKS ? blocks : GATHER_BLOCKS)), co, st);
 }
 
+// k_cache_all takes round 1's batch from the cells as it computes them: each wavefront works out the reveal order, while
+// its loads are under way, and k_select_prune reads 8 bytes a document side by side instead of cells from as many lines
+// (1 query x 1,000 documents: 13 us from its start to the threshold with cells, 7 so; 34.4 -> 29.2 us a call, 2 x 487
+// 28 -> 20).  A query's list gains some 6 ns a document, a pair costs 0.6 beyond those that leave the SIMDs idle anyhow
+// (12 x 2,286 66 -> 69 us, 9 x 709 45 -> 39, 12 x 522 38 -> 34).
+static bool cache_all_reveals(const Problem& P) { return P.nq <= 8 || (int64_t)P.nq * P.N <= 12288; }
+
 hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
                             const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st) {
     GatherArgs A{};
     A.dense = kNeverDense;
     const InitArgs I = init_args(P, W, kn, R, seed, user_pi, tr, 0);
+    if (cache_all_reveals(P)) A.nb = kn.B < P.T ? kn.B : P.T;
+    A.G = 1;
+    while (A.G < A.nb) A.G <<= 1;
     long long blocks = (long long)P.nq * P.N;
     // A document shared by four wavefronts loads the query four times.  From some three pairs a CU a
     // wavefront per pair is faster (us a call: 1,000 pairs of 48 fp32 tokens 112 -> 104, 2,000 of bf16 56 -> 50),
@@ -1289,7 +1325,9 @@ struct SelArgs {
     float a, b;
     const int32_t* pi;
     int cache_all;                       // round 1 has cached the cells of all documents
-    int note_pairs;                      // ... then the pairs going on to round 2 are counted for the statistics
+    int fold_cells;                      // ... and not revealed them
+    int finish_next;                     // round 1: round 2 ends with the top-K of all queries
+    int note_pairs;                      // cache_all: then the pairs going on to round 2 are counted for the statistics
     int cache_cap, TP;
     const int32_t* cid;
     float2* cstat;
@@ -1401,12 +1439,13 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
     }
     if (threadIdx.x == 0) {
         A.ctl[q] = nc;
-        if (nc.active) {
+        if (nc.active || A.finish_next) {           // (finished: the round's gather is to cache its survivors' cells)
             // pairs and work item in one step: starts ascend with the items
             const unsigned long long at = atomicAdd(entered ? A.pairs + 2 * (A.R + 2) : A.pairs + r + 1, work_add(nc.count));
             const int place = (int)work_count(at);
             A.work[entered ? A.nq - 1 - place : place] = work_item(q, pair_count(at));
-            atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
+            if (nc.active) atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
+            else atomicAdd(A.pairs + 2 * (A.R + 2) + 1, (unsigned long long)nc.count);
         }
     }
     if (entered) hold_documents(A, q, nc);
@@ -1457,7 +1496,7 @@ __device__ __forceinline__ void prune_wave(const SelArgs& A, const Kappas& kappa
         e[u] = in ? in[at] : at;
     }
 #pragma unroll
-    for (int u = 0; u < E; ++u) st[u] = stat[e[u]];     // (before round 1: not read)
+    for (int u = 0; u < E; ++u) st[u] = stat[e[u]];
     const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
     float cv[E][4];
     auto fetch = [&](int round) {                   // a batch of at most four
@@ -2076,12 +2115,12 @@ __device__ __forceinline__ void topk_regs(const float* vals, const int32_t* list
         if (((eq >> u) & 1u) && n_gt + pl.place(u) < Kq) put(n_gt + pl.place(u), u);
 }
 
-// Scores of a query's survivors from its cached cells, a wavefront each, by list position.
+// Scores of a query's survivors from its cached cells, a wavefront each, by list position (no list: the slots themselves).
 __device__ __forceinline__ void score_cached(const TopkArgs& A, int q, int count, const int32_t* list) {
     float* v = A.vals + (size_t)q * A.N;
     const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
     for (int k = my_wave(); k < count; k += SEL_WAVES) {
-        const float* crow = rows + (size_t)list[k] * A.TP;
+        const float* crow = rows + (size_t)(list ? list[k] : k) * A.TP;
         const float x = A.TP == 16 ? cached_score<1>(crow, A.T)
                       : A.TP == 32 ? cached_score<2>(crow, A.T)
                       : A.TP == 64 ? cached_score<4>(crow, A.T) : cached_score<8>(crow, A.T);
@@ -2210,9 +2249,12 @@ __device__ __forceinline__ void topk_query(const TopkArgs& A, int q, int count, 
 
 // Bound by latency and instructions, not by bytes: a list that fits the registers is read once, and
 // selection, prune and count of all its rounds run there.
-// TOPK (cache_all): every query ends in this launch, which goes on to its top-K; a launch for that cost
-// 6 us of a call of 50.
-template <bool TOPK>
+// TOPK (cache_all, or lists that all fit the cell cache and are revealed by no corpus pass): every query ends in this
+// launch, which goes on to its top-K; a launch for that cost 6 us of a call of 50, and one for the survivors of queries that
+// ended in round 1 as much.
+// LONG: lists may be longer than a tile (what they need costs the others registers).
+enum { END_NONE = 0, END_CACHE_ALL = 1, END_LAST = 2 };
+template <int END, bool LONG>
 __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas kappas, TopkArgs P) {
     __shared__ SelShared sh;
     __shared__ int seg_first[SEG_MAX + 1];
@@ -2221,8 +2263,13 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
     QueryCtl c{};
     c.count = (int)A.N;
     c.implicit = c.active = 1;
-    if constexpr (!TOPK) c = A.ctl[q];              // (cache_all: round 1, all documents)
-    if (!c.active) return;
+    constexpr bool TOPK = END != END_NONE;
+    if constexpr (END != END_CACHE_ALL) c = A.ctl[q];   // (cache_all: round 1, all documents)
+    if (!TOPK && !c.active) return;
+    // what is left (TOPK): of a query that finished in round 1 all of its list, whose cells are cached since
+    int left = c.count;
+    const int32_t* survivors = nullptr;
+    if (END != END_LAST || c.active) {
     const int count = c.count;
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
@@ -2238,7 +2285,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
     if (threadIdx.x == 0) kept_tokens = 0ull;
     clear_hist(sh);
 
-    const bool segmented = count > SEL_TILE;        // then k_select_segments has run
+    const bool segmented = LONG && count > SEL_TILE;        // then k_select_segments has run
     int ncand = count;
     if (segmented) ncand = segment_starts(A.seg_cnt + (size_t)q * SEG_MAX, count, seg_first);
 
@@ -2248,11 +2295,13 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
     nc.mode = slots ? 1 : 0;
     nc.bound = nc.pad1 = nc.pad2 = 0;
     int r = A.r;
-    bool from_cells = A.cache_all != 0;             // the round's batch still has to be folded in
-    bool seg = segmented, fold = fold_dense;
-    if (ncand > SEL_TILE) {
-        prune_list(A, q, count, nc, out, stat, bat, fold, ncand, r, sh, &kept_tokens);
-        return;
+    bool from_cells = A.fold_cells != 0;            // the round's batch still has to be folded in
+    bool seg = segmented, fold = fold_dense;        // (of the launch's round)
+    if constexpr (LONG) {
+        if (ncand > SEL_TILE) {
+            prune_list(A, q, count, nc, out, stat, bat, fold, ncand, r, sh, &kept_tokens);
+            return;
+        }
     }
     for (;;) {
         bool done = true;
@@ -2268,14 +2317,8 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
                 ? prune_regs(A, kappas, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens)
                 : prune_tile(A, kappas, q, count, nc, in, out, stat, bat, slots, fold, seg, ncand, r, from_cells, sh, seg_first, &kept_tokens);
         if (done) {
-            if constexpr (TOPK) {
-                __shared__ TopkShared tk;
-                __syncthreads();                    // the list is read by other threads next
-                const int left = sh.round_count[r - 1];
-                score_cached(P, q, left, out);
-                topk_query(P, q, left, out, nullptr, nullptr, false, sh, seg_first, tk);
-            }
-            return;
+            if constexpr (!TOPK) return;
+            break;
         }
         // cached rounds remain: on from the shorter list, into the other buffer
         from_cells = true;
@@ -2283,6 +2326,17 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
         in = out;
         nc.cur ^= 1;
         out = (nc.cur ? A.list1 : A.list0) + (size_t)q * A.N;
+    }
+    if constexpr (TOPK) {
+        __syncthreads();                            // the list is read by other threads next
+        left = sh.round_count[r - 1];
+        survivors = out;
+    }
+    }
+    if constexpr (TOPK) {
+        __shared__ TopkShared tk;
+        score_cached(P, q, left, survivors);
+        topk_query(P, q, left, survivors, END == END_CACHE_ALL ? nullptr : A.cid + (size_t)q * A.cache_cap, nullptr, false, sh, seg_first, tk);
     }
 }
 
@@ -2484,9 +2538,11 @@ static TopkArgs topk_args(const Problem& P, const Work& W, bool use_ctl, bool ca
 
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, bool share, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st) {
+                               bool note_pairs, bool share, bool finish_next, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st) {
     SelArgs A{};
     A.cache_all = cache_all ? 1 : 0;
+    A.finish_next = finish_next ? 1 : 0;
+    A.fold_cells = cache_all && !cache_all_reveals(P) ? 1 : 0;
     A.note_pairs = cache_all && note_pairs ? 1 : 0;
     TopkArgs top{};
     if (topk_ids) top = topk_args(P, W, false, true, W.rescored, kn.K, topk_ids, topk_scores);
@@ -2542,8 +2598,10 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
         }
         k_select_segments<<<dim3(gx, P.nq), SEL_THREADS, 0, st>>>(A);
     }
-    if (topk_ids) k_select_prune<true><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
-    else k_select_prune<false><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
+    if (P.N > SEL_TILE) k_select_prune<END_NONE, true><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
+    else if (topk_ids && cache_all) k_select_prune<END_CACHE_ALL, false><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
+    else if (topk_ids) k_select_prune<END_LAST, false><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);   // (lists fit the cache)
+    else k_select_prune<END_NONE, false><<<P.nq, SEL_THREADS, 0, st>>>(A, kappas, top);
     return hipGetLastError();
 }
 

@@ -26,7 +26,8 @@ struct Work {
     unsigned long long* pairs;   // [R+2] pairs[r]: (query, doc) pairs round r would have to gather
                                  // and the queries that hold them (pair_count, work_count);
                                  // then [R+2]: the document tokens of those pairs; then as [2], which does not
-                                 // count them, the pairs of round 2 whose lists are entered by document
+                                 // count them, the pairs of round 2 whose lists are entered by document; then how many of
+                                 // pairs[2] are the survivors of finished queries
     unsigned long long* work;    // [nq] the queries of the next round (work_item), from the end those entered by document
     int32_t* seg_cnt;     // [nq][64] candidates per segment of a segmented pre-filter
     float* rescored;      // [nq][N] exact score of the k-th survivor
@@ -145,10 +146,13 @@ int dense_chunks(const Problem& P, const Work& W);
 
 // Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
 // this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
-// per unit sigma_hat of round r.  share: round 1 of a call whose round 2 has rr.dense.enough.  topk_ids (after launch_cache_all, exact cells): the launch ends with the top-K.
+// per unit sigma_hat of round r.  share: round 1 of a call whose round 2 has rr.dense.enough.  finish_next: round 1 of a
+// call whose round 2 is the last to launch and ends with the top-K: the survivors of queries that end in round 1 are
+// then gathered with it.  topk_ids (after launch_cache_all, or in that round 2; exact cells): the launch ends with the
+// top-K.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, bool share, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
+                               bool note_pairs, bool share, bool finish_next, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
 // list position); else all N documents (vals indexed by id).  cached: the queries whose list holds

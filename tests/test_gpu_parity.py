@@ -830,6 +830,40 @@ def test_smallest_calls_that_visit_every_document_once(B, S, oracle_mod, dtype, 
         _run_colbandit_case(B, oracle_mod, w, 5, 5, Bsz, alpha, seed=3)
 
 
+@pytest.mark.parametrize("nq,N,T,Bsz", [(8, 2100, 32, 4), (9, 1365, 24, 4), (9, 1366, 24, 4), (13, 1000, 70, 16), (12, 1000, 128, 3)])
+def test_round_one_revealed_as_the_cells_are_cached(B, S, nq, N, T, Bsz):
+    """Both sides of the rule by which the smallest calls reveal round 1 while they compute the cells, with the seeded order and
+    with a table (one that holds a token twice among them): the run of gathers that keep no cells."""
+    w = _custom(S, np.random.default_rng(nq).integers(1, 12, N).tolist(), nq, T, 64, "bf16", 11)
+    pi = torch.stack([torch.randperm(T, generator=torch.Generator().manual_seed(q)) for q in range(nq)]).to(torch.int32)
+    pi[-1, 1] = pi[-1, 0]
+    for more in ({}, {"pi": pi.cuda()}):
+        call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.3, 0.01, 5, 3, B=Bsz, **more, **o)
+        assert "k_cache_all<" in _kernels(lambda: call(want_stats=False))
+        _same_run(call(trace=True), call(trace=True, no_cell_cache=True))
+
+
+def test_queries_that_end_in_round_one_are_finished_with_the_others(B, S):
+    """Lists that all fit the cell cache: the prune of round 2 ends the call, also for queries that had ended in round 1 or
+    hold K documents or fewer by then; without a launch for their scores, and with the run of gathers that keep no cells."""
+    w = _custom(S, np.random.default_rng(2).integers(20, 90, 3000).tolist(), 6, 32, 128, "bf16", 12)
+    off = w.offsets.cpu().tolist()
+    for q, docs in ((0, range(40, 50)), (3, range(7, 12)), (4, range(100, 160))):
+        for i in docs:                                       # every token of the query found in the document
+            n = min(32, off[i + 1] - off[i])
+            w.docs[off[i]:off[i] + n] = w.Q[q, :n]
+    for K, M in ((5, 5), (5, 0), (70, 3)):
+        call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, K, 0.05, 0.01, M, 3, **o)
+        names = _kernels(lambda: call(want_stats=False))
+        assert names.count("k_select_prune<") == 2 and "k_gather_survivors" not in names and "k_topk" not in names
+        runs = [call(trace=True), call(trace=True, no_cell_cache=True), call(trace=True, later_rounds=1)]
+        torch.cuda.synchronize()
+        rounds = [s["rounds"] for s in runs[0]["stats"]]
+        assert max(rounds) > 1 and (K > 5 or min(rounds) == 1)
+        for r in runs[1:]:
+            _same_run(runs[0], r)
+
+
 @pytest.mark.parametrize("N,T,Bsz,K,M,coarse", [(64, 32, 4, 5, 0, False), (65, 32, 4, 5, 5, False), (128, 21, 4, 1, 0, False),
                                               (129, 100, 3, 7, 0, False), (192, 70, 16, 30, 3, False), (255, 32, 5, 60, 4, False),
                                               (256, 32, 4, 250, 0, False), (257, 24, 2, 5, 0, False), (300, 32, 4, 64, 0, True),
