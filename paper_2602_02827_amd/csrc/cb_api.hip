@@ -694,7 +694,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     if (K > COLBANDIT_MAX_K) return COLBANDIT_ERR_UNSUPPORTED;
     if (!(alpha_ef > 0.f) || !(alpha_ef <= 1.f) || !(delta > 0.f) || !(delta < 1.f) || M < 0)
         return COLBANDIT_ERR_KNOB;
-    Knobs kn{K, M, 4, -1.f, 1.f};
+    Knobs kn{K, M, 4, -1.f, 1.f, alpha_ef <= 0.25f};
     const int32_t* user_pi = nullptr;
     void* trace = nullptr;
     size_t trace_bytes = 0;

@@ -33,7 +33,8 @@ struct QueryCtl {
     int active;    // 1: the query still takes part in elimination rounds
     int mode;      // 0: list entries are document ids; 1: they are slots of the cell cache
     int bound;     // round 1: order-preserving key of a lower threshold (k_select_sample)
-    int pad1, pad2;
+    int done;      // workgroups of a long list that have ended their segments (k_select_round)
+    int pad;
 };
 
 // A round's pairs that are still held as document ids: their number, and the queries that hold

@@ -90,7 +90,7 @@ __device__ __forceinline__ void init_queries(const InitArgs& A, int block) {
         c.implicit = 1;
         c.active = A.N > (int64_t)A.KM;
         c.mode = 0;
-        c.bound = c.pad1 = c.pad2 = 0;
+        c.bound = c.done = c.pad = 0;
         A.ctl[q] = c;
     }
     for (int r = lane; r <= A.R; r += 64) {
@@ -2255,11 +2255,9 @@ __device__ __forceinline__ void topk_query(const TopkArgs& A, int q, int count, 
 // LONG: lists may be longer than a tile (what they need costs the others registers).
 enum { END_NONE = 0, END_CACHE_ALL = 1, END_LAST = 2 };
 template <int END, bool LONG>
-__global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas kappas, TopkArgs P) {
-    __shared__ SelShared sh;
+__device__ __forceinline__ void prune_query(const SelArgs& A, const Kappas& kappas, const TopkArgs& P, int q, SelShared& sh) {
     __shared__ int seg_first[SEG_MAX + 1];
     __shared__ unsigned long long kept_tokens;
-    const int q = blockIdx.x;
     QueryCtl c{};
     c.count = (int)A.N;
     c.implicit = c.active = 1;
@@ -2293,7 +2291,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
     nc.cur = out_sel;
     nc.implicit = 0;
     nc.mode = slots ? 1 : 0;
-    nc.bound = nc.pad1 = nc.pad2 = 0;
+    nc.bound = nc.done = nc.pad = 0;
     int r = A.r;
     bool from_cells = A.fold_cells != 0;            // the round's batch still has to be folded in
     bool seg = segmented, fold = fold_dense;        // (of the launch's round)
@@ -2338,6 +2336,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas 
         score_cached(P, q, left, survivors);
         topk_query(P, q, left, survivors, END == END_CACHE_ALL ? nullptr : A.cid + (size_t)q * A.cache_cap, nullptr, false, sh, seg_first, tk);
     }
+}
+
+template <int END, bool LONG>
+__global__ __launch_bounds__(SEL_THREADS) void k_select_prune(SelArgs A, Kappas kappas, TopkArgs P) {
+    __shared__ SelShared sh;
+    prune_query<END, LONG>(A, kappas, P, (int)blockIdx.x, sh);
 }
 
 // Cheap outer estimate of interval() for the pre-filter: reciprocal multiplications and the
@@ -2415,15 +2419,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
 // workgroup sampled for itself.
 // In a corpus-pass round the round's batch (stat2) is merged in registers only: k_select_prune
 // stores the merged statistics of the survivors, the only entries that are ever read again.
-__global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
-    __shared__ SelShared sh;
-    const int q = blockIdx.y;
-    const QueryCtl c = A.ctl[q];
+__device__ __forceinline__ void filter_segments(const SelArgs& A, int q, const QueryCtl& c, SelShared& sh) {
     const int count = c.count;
-    if (!c.active || count <= SEL_TILE) return;     // cached lists are never this long
     const int len = seg_len(count);
     const int n_seg = seg_count(count);
-    if ((int)blockIdx.x >= n_seg) return;
     const bool dense = A.dense.thr != NEVER_DENSE && A.dense.pass(A.pairs + A.r);
     const int32_t* in = c.implicit ? nullptr : (c.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     const int out_sel = c.implicit ? 0 : (c.cur ^ 1);
@@ -2507,6 +2506,43 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
         }
         if (threadIdx.x == 0) A.seg_cnt[(size_t)q * SEG_MAX + sg] = base - lo;
     }
+}
+
+__global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
+    __shared__ SelShared sh;
+    const int q = blockIdx.y;
+    const QueryCtl c = A.ctl[q];
+    if (!c.active || c.count <= SEL_TILE) return;   // cached lists are never this long
+    if ((int)blockIdx.x >= seg_count(c.count)) return;
+    filter_segments(A, q, c, sh);
+}
+
+// Pre-filter and prune of a round >= 2 in one launch, for calls whose lists are expected to be short by then
+// (Knobs::narrow) and whose workgroups, which need a CU each, take two turns at most.  Of a short list the first workgroup
+// prunes at once, and the launch spared is 2.6 us in every round (64 queries x 50,000 465 -> 455 us, 13 x 91,000 in rounds
+// of 4 out of 123 tokens 634 -> 582).  Of a long list the last workgroup to come prunes (QueryCtl::done, which the prune
+// clears); what the others wrote has to go through memory to it, some 8 us a round (38 x 66,000 with alpha 1.0
+// 1,505 -> 1,545 us, 3 x 134,600 9,375 -> 9,463, with a fence by every wavefront 1,973 and 9,723).
+__global__ __launch_bounds__(SEL_THREADS) void k_select_round(SelArgs A, Kappas kappas) {
+    __shared__ SelShared sh;
+    __shared__ int last;
+    const int q = blockIdx.y;
+    const QueryCtl c = A.ctl[q];
+    if (!c.active) return;
+    if (c.count > SEL_TILE) {
+        if ((int)blockIdx.x < seg_count(c.count)) filter_segments(A, q, c, sh);
+        __syncthreads();
+        // All workgroups count, also those without a segment: none reads the control after the prune has changed it.  (One
+        // thread's fences, between the barriers, serve them all; each writes a whole L2 back.)
+        if (threadIdx.x == 0) {
+            __threadfence();                        // the segments, for whichever workgroup prunes
+            last = atomicAdd(&A.ctl[q].done, 1) == (int)gridDim.x - 1;
+            if (last) __threadfence();
+        }
+        __syncthreads();
+        if (!last) return;
+    } else if (blockIdx.x > 0) return;              // (a list is never longer after a round)
+    prune_query<END_NONE, true>(A, kappas, TopkArgs{}, q, sh);
 }
 
 // Segment workgroups per query: a list of any length up to N has at most this many segments
@@ -2595,6 +2631,10 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
             // later lists are seldom long: no more workgroups than end quickly with nothing to do
             const unsigned few = (unsigned)(2048 / P.nq > 1 ? 2048 / P.nq : 1);
             gx = gx < few ? gx : few;
+            if (kn.narrow && gx * (unsigned)P.nq <= 512u) {
+                k_select_round<<<dim3(gx, P.nq), SEL_THREADS, 0, st>>>(A, kappas);
+                return hipGetLastError();
+            }
         }
         k_select_segments<<<dim3(gx, P.nq), SEL_THREADS, 0, st>>>(A);
     }

@@ -1004,6 +1004,19 @@ def test_long_lists_stay_long_under_a_conservative_radius(B, S, oracle_mod, nq):
     _run_colbandit_case(B, oracle_mod, w, 5, 5, 4, 1.0, seed=6, later_rounds=1)
 
 
+@pytest.mark.parametrize("N,nq,later", [(40000, 3, 0), (40000, 3, 1), (90000, 2, 2)])
+def test_long_lists_under_a_small_radius_are_pruned_by_the_last_workgroup_to_come(B, S, oracle_mod, N, nq, later):
+    """k_select_round (small alpha_ef, few workgroups) on lists that stay longer than a tile for some rounds and fall below
+    it, in gathered rounds and corpus passes: every round as the oracle has it."""
+    w = _custom(S, np.random.default_rng(N).integers(1, 4, N).tolist(), nq, 32, 64, "bf16", 23)
+    call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 200, 0.25, 1e-30, 5, 4, B=2, later_rounds=later, **o)
+    names = _kernels(lambda: call(want_stats=False))
+    assert "k_select_round" in names and names.count("k_select_segments") == 1
+    counts = call(trace=True)["trace"].count
+    assert (counts[2] > 16384).all() and (counts[-2] < 16384).any()
+    _run_colbandit_case(B, oracle_mod, w, 200, 5, 2, 0.25, delta=1e-30, seed=4, later_rounds=later)
+
+
 @pytest.mark.parametrize("N,K,alpha", [(1024, 5, 0.2), (1025, 32, 1.0), (4096, 5, 1.0), (4097, 33, 1.0), (8192, 5, 1.0),
                                        (8193, 1, 1.0), (16384, 300, 1.0), (16385, 5, 1.0), (24577, 1000, 1.0),
                                        (40961, 500, 0.9), (33000, 508, 1.0), (33100, 508, 1.0)])
