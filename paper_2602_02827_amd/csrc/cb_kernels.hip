@@ -1069,7 +1069,8 @@ __device__ __forceinline__ void clear_hist(SelShared& sh) {
 }
 
 // K-th largest (K >= 1) of the 64 lanes' keys, bit by bit from the top: a step is one comparison
-// and a count of its mask.  BITS < 32: only the leading bits, i.e. a lower bound.
+// and a count of its mask.  BITS < 32: only the leading bits, i.e. a lower bound.  (Two bits a step with three masks, a
+// loop of one or four steps, or ranks of few lanes: no faster, 1 query x 1,000 documents 28.5 us so and 28.3 to 30.3.)
 template <int BITS>
 __device__ __forceinline__ uint32_t wave_kth_largest(uint32_t v, int K) {
     uint32_t best = 0;
@@ -1499,15 +1500,19 @@ __device__ __forceinline__ void prune_wave(const SelArgs& A, const Kappas& kappa
     for (int u = 0; u < E; ++u) st[u] = stat[e[u]];
     const float* rows = A.ccell + (size_t)q * A.cache_cap * A.TP;
     float cv[E][4];
-    auto fetch = [&](int round) {                   // a batch of at most four
+    // A batch of at most four: its tokens first, then one branch for each entry (716 documents in rounds of two 62 -> 59 us).
+    auto fetch = [&](int round) {
         const int lo = (round - 1) * A.B, nb = lo + A.B < T ? A.B : T - lo;
+        int t[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = token(lo + (i < nb ? i : 0));
+        for (int i = 0; i < 4; ++i) t[i] = token(lo + (i < nb ? i : 0));
 #pragma unroll
-            for (int u = 0; u < E; ++u)
-                if (u < parts) cv[u][i] = rows[(unsigned)(e[u] * A.TP + t)];
-        }
+        for (int u = 0; u < E; ++u)
+            if (u < parts) {
+                const unsigned at = (unsigned)(e[u] * A.TP);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cv[u][i] = rows[at + (unsigned)t[i]];
+            }
     };
     if (A.B <= 4 && from_cells) fetch(r);
     int count;
