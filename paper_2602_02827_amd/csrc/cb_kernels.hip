@@ -198,6 +198,7 @@ hipError_t launch_init(const Problem& P, const Work& W, const Knobs& kn, int R, 
 // last token, which cannot change a max), runs the MFMA chain over d and folds the 16x16 result
 // into a running per-column maximum.
 //   k_gather_round     the reveal of one round (Algorithm 1, reveal step), see there
+//   k_gather_docs      the same, a document for several queries at once
 //   k_gather_survivors exact scores of the survivors (Eq. (2); rescore)
 //   k_gather_all       all documents of all queries: the smallest calls, fp32 where it beats the corpus
 //                      pass, Ball-carving in fp32 and in the widths without a group pass
