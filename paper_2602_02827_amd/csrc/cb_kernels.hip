@@ -2537,6 +2537,9 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_round(SelArgs A, Kappas 
     if (!c.active) return;
     if (c.count > SEL_TILE) {
         if ((int)blockIdx.x < seg_count(c.count)) filter_segments(A, q, c, sh);
+        // Every wavefront waits until its own stores are in L2, which the barrier alone does not wait for: the write-back of
+        // one thread's fence takes what is there.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // All workgroups count, also those without a segment: none reads the control after the prune has changed it.  (One
         // thread's fences, between the barriers, serve them all; each writes a whole L2 back.)

@@ -4,6 +4,8 @@ helpers (reveal permutation, radius pre-factor) agree with the oracle's."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -203,7 +205,6 @@ def test_ball_carving_reports_a_failure_after_its_first_launch(B, tmp_path):
     """A launch or wait that fails half way (a stream under capture cannot be waited for) is an error
     code, not a signal: the group count that the rest of the call is sized by has not arrived.  The two
     launches before it are replaced by a success and a failure."""
-    import subprocess
     import sys
     src, so = tmp_path / "stub.cpp", tmp_path / "stub.so"
     src.write_text(
@@ -267,7 +268,6 @@ def test_topk_static_argument_errors_need_no_device(B):
 def test_segments_of_a_list_cover_it_up_to_the_largest_size(tmp_path):
     """The pre-filter's segments (cb_segments.h, the kernels' own arithmetic) against 64-bit sums: at
     most 64 of them, whole tiles, together the list, from one entry to the largest N accepted."""
-    import subprocess
     src, exe = tmp_path / "seg.cpp", tmp_path / "seg"
     src.write_text("""
 #include <cstdio>
@@ -310,7 +310,6 @@ def test_the_quantisers_sample_sees_every_column(tmp_path, pieces):
     """cb_sample.h, the kernel's own arithmetic: one piece in every run of `step`, ascending and in range,
     and over rows of `pieces` pieces (d = 32 to 128 of bf16) every column about equally often, whatever
     factors the step shares with the row: a share of 16384 / pieces within six standard deviations."""
-    import subprocess
     src, exe = tmp_path / "sample.cpp", tmp_path / "sample"
     src.write_text("""
 #include <cmath>
@@ -385,7 +384,6 @@ def test_product_package_does_not_import_the_oracle():
 def test_header_is_plain_c(tmp_path):
     """The boundary is a C ABI: the header must compile as C99 and as C++ without any HIP or
     torch type in sight, and every declaration must be usable from C."""
-    import subprocess
     src = tmp_path / "use_header.c"
     src.write_text(
         '#include <string.h>\n'
@@ -404,3 +402,23 @@ def test_header_is_plain_c(tmp_path):
                             "c" if cc == "gcc" else "c++", "-I", inc, str(src)],
                            capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def test_stores_are_waited_for_before_another_workgroup_reads_them(B, tmp_path):
+    """k_select_round: a list's segments are read by whichever workgroup comes last, after one thread's release.  Its
+    write-back of L2 takes the other wavefronts' stores only if each has waited for its own before the barrier, which the
+    compiler's barrier does not do: the barrier ahead of each release follows a wait for vector stores."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    lib = shutil.copy(B.LIB_PATH, tmp_path)                  # the code objects are extracted beside it
+    subprocess.run([objdump, "--offloading", lib], check=True, capture_output=True)
+    text = "".join(subprocess.run([objdump, "-d", "--no-show-raw-insn", "--symbolize-operands", str(f)], check=True, capture_output=True, text=True).stdout
+                   for f in tmp_path.glob("*gfx950") if b"k_select_round" in f.read_bytes())
+    body = re.search(r"^\S+ <_ZN2cb14k_select_round[^>]*>:\n(.*?)(?=^\S+ <_Z|\Z)", text, re.S | re.M).group(1)
+    ops = [re.sub(r"\s*//.*", "", line).strip() for line in body.splitlines()]
+    release = next(i for i, op in enumerate(ops) if op.startswith("buffer_wbl2"))
+    barrier = max(i for i in range(release) if ops[i] == "s_barrier")
+    between = ops[max((i for i in range(barrier) if re.match(r"s_waitcnt\b.*vmcnt\(0\)", ops[i])), default=0) + 1:barrier]
+    # in between nothing is stored, and no jump leads there (labels end in a colon)
+    assert not any(re.match(r"(global|flat|buffer|scratch)_|.*:$", op) for op in between), between
