@@ -49,8 +49,12 @@ struct InitArgs {
 // query): lane x gets the tokens at places x and x + 64.  The generator's state after s steps is known in closed form, so
 // the lanes draw the T - 1 positions side by side; a place's token is found by following the place back through the
 // exchanges, five instructions each.  (One thread drawing and exchanging them in turn took 14 us, T = 32.)
+// What the draws need of the lane alone is worked out in place: the compiler would keep it, some 18 registers, over a
+// caller's loop, which k_cache_all has not (fp32, d = 128, T = 32 two wavefronts a SIMD fell to one: 1 query x 4,000
+// documents of 17 tokens 59 us so and 47, 8 x 1,000 of 9 80 and 60).
 __device__ __forceinline__ void reveal_order(uint64_t seed, int q, int T, int& p0, int& p1) {
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
+    asm("" : "+v"(lane) : "s"(q));
     const uint64_t s0 = seed + ((uint64_t)q + 1ull) * 0x9E3779B97F4A7C15ull;
     auto draw = [&](int i) -> int {                 // the position that i is exchanged with: step T - i
         uint64_t s = s0 + (uint64_t)(T - 1 - i) * 0x9E3779B97F4A7C15ull;
@@ -379,7 +383,8 @@ __device__ __forceinline__ void store_cells(const GatherArgs& A, int q, int k, c
         if (P::row_is_primary(row)) crow[P::tile_of_row(j, row) * 16 + col] = w[j];
 }
 // This round's batch of the same cells, merged into the pair's statistics, which go to the slot.  t: the batch's
-// query token of this lane; slot s of the batch (lane s of row 0) fetches its cell from its owner.
+// query token of this lane; slot s of the batch (lane s of row 0) fetches its cell from its owner.  NAMED: slots are places
+// of a list; else documents, before round 1, so that there are no statistics yet.
 template <int TQ, bool NAMED = true>
 __device__ __forceinline__ void reveal_cached(const GatherArgs& A, int q, int k, int id, int t, const float (&w)[Pack<TQ>::NW]) {
     using P = Pack<TQ>;
@@ -395,11 +400,14 @@ __device__ __forceinline__ void reveal_cached(const GatherArgs& A, int q, int k,
     batch_stats(v, (lane & 15) % A.G, A.nb, A.G, sb, m2b);
     if (lane == 0) {
         const size_t slot = (size_t)q * A.cache_cap + k;
-        float2 st = make_float2(0.f, 0.f);
-        if (A.n_prev > 0) st = A.stat[(size_t)q * A.N + id];
-        merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
+        float2 st = make_float2(sb, m2b);
+        if constexpr (NAMED) {
+            st = make_float2(0.f, 0.f);
+            if (A.n_prev > 0) st = A.stat[(size_t)q * A.N + id];
+            merge_stats(st.x, st.y, A.n_prev, sb, m2b, A.nb);
+            A.cid[slot] = id;
+        }
         A.cstat[slot] = st;
-        if (NAMED) A.cid[slot] = id;                // else slots are documents
     }
 }
 

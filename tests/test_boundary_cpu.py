@@ -404,17 +404,27 @@ def test_header_is_plain_c(tmp_path):
         assert r.returncode == 0, r.stderr
 
 
-def test_stores_are_waited_for_before_another_workgroup_reads_them(B, tmp_path):
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.fixture(scope="module")
+def code_objects(B, tmp_path_factory):
+    """The device code objects of the built library."""
+    if not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
+        pytest.skip("no llvm-objdump")
+    at = tmp_path_factory.mktemp("objects")
+    lib = shutil.copy(B.LIB_PATH, at)                        # they are extracted beside it
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", lib], check=True, capture_output=True)
+    return sorted(at.glob("*gfx950"))
+
+
+def test_stores_are_waited_for_before_another_workgroup_reads_them(code_objects):
     """k_select_round: a list's segments are read by whichever workgroup comes last, after one thread's release.  Its
     write-back of L2 takes the other wavefronts' stores only if each has waited for its own before the barrier, which the
-    compiler's barrier does not do: the barrier ahead of each release follows a wait for vector stores."""
-    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
-    if not os.path.exists(objdump):
-        pytest.skip("no llvm-objdump")
-    lib = shutil.copy(B.LIB_PATH, tmp_path)                  # the code objects are extracted beside it
-    subprocess.run([objdump, "--offloading", lib], check=True, capture_output=True)
-    text = "".join(subprocess.run([objdump, "-d", "--no-show-raw-insn", "--symbolize-operands", str(f)], check=True, capture_output=True, text=True).stdout
-                   for f in tmp_path.glob("*gfx950") if b"k_select_round" in f.read_bytes())
+    compiler's barrier does not do: the barrier ahead of the release follows a wait for vector stores."""
+    text = "".join(subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", "--symbolize-operands", str(f)],
+                                  check=True, capture_output=True, text=True).stdout
+                   for f in code_objects if b"k_select_round" in f.read_bytes())
     body = re.search(r"^\S+ <_ZN2cb14k_select_round[^>]*>:\n(.*?)(?=^\S+ <_Z|\Z)", text, re.S | re.M).group(1)
     ops = [re.sub(r"\s*//.*", "", line).strip() for line in body.splitlines()]
     release = next(i for i, op in enumerate(ops) if op.startswith("buffer_wbl2"))
@@ -422,3 +432,23 @@ def test_stores_are_waited_for_before_another_workgroup_reads_them(B, tmp_path):
     between = ops[max((i for i in range(barrier) if re.match(r"s_waitcnt\b.*vmcnt\(0\)", ops[i])), default=0) + 1:barrier]
     # in between nothing is stored, and no jump leads there (labels end in a colon)
     assert not any(re.match(r"(global|flat|buffer|scratch)_|.*:$", op) for op in between), between
+
+
+def test_revealing_as_the_cells_are_cached_costs_no_wavefront(code_objects):
+    """k_cache_all<.., true> does for all documents what k_gather_round does for a list's: no registers go to scratch
+    memory, and their number leaves as many wavefronts per SIMD."""
+    regs = {}
+    for f in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", str(f)], check=True, capture_output=True, text=True).stdout
+        regs.update({m[0]: (int(m[1]), int(m[2])) for m in
+                     re.findall(r"\.name: +(_Z\S+)\n.*?\.vgpr_count: +(\d+)\n +\.vgpr_spill_count: +(\d+)", notes, re.S)})
+    waves = lambda count: min(8, 512 // ((count + 7) // 8 * 8))
+    pairs = 0
+    for name, (count, spilled) in regs.items():
+        m = re.match(r"_ZN2cb11k_cache_all(I\w+?)Lb1EEEv", name)
+        if not m:
+            continue
+        like = next(v for k, v in regs.items() if k.startswith("_ZN2cb14k_gather_round" + m.group(1) + "EE"))
+        assert spilled == 0 and waves(count) >= waves(like[0]), (name, count, spilled, like)
+        pairs += 1
+    assert pairs > 30
