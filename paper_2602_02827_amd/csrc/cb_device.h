@@ -84,6 +84,11 @@ struct DenseRule {
     uint16_t lg_per;                     // 2^lg_per pairs, by document, cost as much as one of the others
     uint16_t shared_at;                  // the shared word, from the round's own
     __device__ __host__ __forceinline__ bool by_document(unsigned long long shared) const { return pair_count(shared) >= enough; }
+    // Whether the pass is certain from a part of the shared word alone: what else is counted makes its price no lower.
+    __device__ __host__ __forceinline__ bool sure_to_pass(unsigned long long shared) const {
+        const unsigned long long s = pair_count(shared);
+        return s >= enough && base + (s >> lg_per) > thr;
+    }
     __device__ __host__ __forceinline__ bool pass(unsigned long long head, unsigned long long shared) const {
         unsigned long long p = pair_count(head);
         if (enough) {

@@ -147,13 +147,13 @@ int dense_chunks(const Problem& P, const Work& W);
 
 // Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
 // this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
-// per unit sigma_hat of round r.  share: round 1 of a call whose round 2 has rr.dense.enough.  finish_next: round 1 of a
+// per unit sigma_hat of round r.  next: in round 1 the rule of round 2, else kNeverDense.  finish_next: round 1 of a
 // call whose round 2 is the last to launch and ends with the top-K: the survivors of queries that end in round 1 are
 // then gathered with it.  topk_ids (after launch_cache_all, or in that round 2; exact cells): the launch ends with the
 // top-K.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
                                const RevealRound& rr, int R, const float* kappa, bool cache_all,
-                               bool note_pairs, bool share, bool finish_next, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
+                               bool note_pairs, const DenseRule& next, bool finish_next, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by
 // list position); else all N documents (vals indexed by id).  cached: the queries whose list holds

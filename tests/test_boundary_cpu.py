@@ -452,3 +452,39 @@ def test_revealing_as_the_cells_are_cached_costs_no_wavefront(code_objects):
         assert spilled == 0 and waves(count) >= waves(like[0]), (name, count, spilled, like)
         pairs += 1
     assert pairs > 30
+
+
+def test_a_round_that_is_sure_to_be_a_corpus_pass_is_one(tmp_path):
+    """DenseRule, the choice between corpus pass and gathers: what sure_to_pass says of a part of the pairs entered by
+    document, pass() says of all of them, whatever else the round holds; so the table of a query that ends later is not read."""
+    src = tmp_path / "rule.cpp"
+    src.write_text(r'''
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include "cb_device.h"
+int main() {
+    unsigned long long s = 12345, sure = 0, wrong = 0, open = 0;
+    auto rnd = [&](unsigned long long below) { s = s * 6364136223846793005ull + 1442695040888963407ull; return (s >> 16) % below; };
+    for (int i = 0; i < 2000000; ++i) {
+        cb::DenseRule r{};
+        r.thr = i % 5 ? rnd(1ull << (1 + rnd(30))) : cb::NEVER_DENSE;
+        r.base = (uint32_t)rnd(1ull << (1 + rnd(20)));
+        r.enough = (uint32_t)(1 + rnd(1ull << (1 + rnd(22))));
+        r.lg_per = (uint16_t)rnd(5);
+        const unsigned long long whole = rnd(1ull << (1 + rnd(26))), part = rnd(whole + 1), head = i % 3 ? 0 : rnd(1 << 20);
+        const unsigned long long queries = 1 + rnd(256), some = 1 + rnd(queries);
+        if (!r.sure_to_pass(some << 40 | part)) { open += r.pass(head, queries << 40 | whole); continue; }
+        ++sure;
+        wrong += !r.pass(head, queries << 40 | whole);
+    }
+    std::printf("%llu %llu %llu\n", sure, wrong, open);
+}
+''')
+    exe = tmp_path / "rule"
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    subprocess.run([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-x", "hip", "-I", os.path.join(ROOT, "paper_2602_02827_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True, capture_output=True)
+    sure, wrong, others = map(int, subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
+    assert wrong == 0 and sure > 100000 and others > 100000

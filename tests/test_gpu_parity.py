@@ -803,6 +803,17 @@ def test_long_documents_are_gathered_for_several_queries_at_once(B, S, N, nq, T,
         _same_run(runs[0], r)
 
 
+def test_lists_entered_by_document_before_a_corpus_pass(B, S):
+    """Round 2 is a corpus pass although lists have been entered by document: the last of them leave the table unfilled."""
+    w = _custom(S, np.random.default_rng(8).integers(270, 310, 1113).tolist(), 166, 24, 64, "bf16", 8)
+    call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 1.0, 0.01, 5, 3, **o)
+    assert "k_gather_docs<" in _kernels(lambda: call(want_stats=False))
+    runs = [call(trace=True), call(trace=True, later_rounds=2)]
+    torch.cuda.synchronize()
+    assert 2 in runs[0]["stats"][0]["corpus_pass_rounds"] and not runs[1]["stats"][0]["corpus_pass_rounds"]
+    _same_run(*runs)
+
+
 @pytest.mark.parametrize("dtype,N,nq,T,d,Bsz,alpha,coarse",
                          [("bf16", 11, 1, 1, 128, 1, 1.0, None), ("bf16", 1000, 3, 32, 128, 4, 0.2, None),
                           ("bf16", 1025, 4, 128, 96, 7, 1.0, None), ("bf16", 4097, 1, 65, 32, 16, 1.0, None),
