@@ -816,15 +816,17 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
             const unsigned long long thr = later_rounds == 1 ? 0ull
                 : dense_pairs_threshold(P, G, co != nullptr, r, R, N <= (int64_t)W.cache_cap, &t_pair);
             if (thr < (unsigned long long)n_queries * (unsigned long long)N) rr.dense.thr = thr;
-            // by document: the corpus at 5.5 TB/s, and the documents again, from the last-level cache, for every
-            // group of queries
-            if (t_pair > 0.0) rr.dense.base = (uint32_t)fmin((double)P.total * P.d * (co ? 1.0 : 2.0) / 5.5e12 / t_pair, 4e9);
-            rr.dense.lg_per = (uint16_t)(1 + share_group_lg(T));
-            // Lists that fit the cache, and cost no more even if they are full (and those that are not entered by document
-            // hold N pairs): round 2 is the last to launch.
-            if (share && later_rounds != 1 && N <= (int64_t)W.cache_cap &&
-                rr.dense.base + (((unsigned long long)N * (unsigned)n_queries) >> rr.dense.lg_per) + (unsigned long long)N <= rr.dense.thr)
-                rr.dense.thr = NEVER_DENSE;
+            // Round 2 by document: the corpus at 5.5 TB/s, and the documents again, from the last-level cache, for every
+            // group of queries.
+            if (r == 2 && share) {
+                if (t_pair > 0.0) rr.dense.base = (uint32_t)fmin((double)P.total * P.d * (co ? 1.0 : 2.0) / 5.5e12 / t_pair, 4e9);
+                rr.dense.lg_per = (uint16_t)(1 + share_group_lg(T));
+                // Lists that fit the cache, and cost no more even if they are full (and those that are not entered by
+                // document hold N pairs): it is the last round to launch.
+                if (later_rounds != 1 && N <= (int64_t)W.cache_cap &&
+                    rr.dense.base + (((unsigned long long)N * (unsigned)n_queries) >> rr.dense.lg_per) + (unsigned long long)N <= rr.dense.thr)
+                    rr.dense.thr = NEVER_DENSE;
+            }
         }
         if (r == 2 && share) {
             rr.dense.shared_at = (uint16_t)(2 * (R + 2) - 2);
