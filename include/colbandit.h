@@ -145,9 +145,12 @@ typedef struct {
     uint64_t pairs_round2;                            /* (query, document) pairs of the whole
                                                          batch that entered round 2 still
                                                          held as document ids, and           */
-    uint64_t tokens_round2;                           /* the document tokens of those pairs:
-                                                         what a gathered round 2 has to
-                                                         read (same for all queries)       */
+    uint64_t tokens_round2;                           /* the document tokens of those pairs,
+                                                         which a gathered round 2 reads
+                                                         pair by pair; long documents that
+                                                         several queries hold it may read
+                                                         once for a number of them (same
+                                                         for all queries)                  */
 } colbandit_stats;
 
 /* sizeof(colbandit_opts) / sizeof(colbandit_stats) as this library was compiled: lets a

@@ -76,3 +76,13 @@ def test_committed_traffic_file_matches_the_committed_kernel_sources():
         assert 13.5e9 < got["full_maxsim"] < 20e9     # at least the corpus, not a multiple of it
     else:
         pytest.skip("counter records were taken on other kernel sources; bench.py reports null")
+
+
+def test_gathered_bytes_are_rated_only_where_each_pair_reads_its_document():
+    alone = bench.gathers_alone
+    assert alone(128, 500000, 53000000, 258062, "bf16")             # short documents
+    assert not alone(64, 20000, 20600000, 62600, "bf16")            # pages, more pairs than documents
+    assert not alone(64, 20000, 20600000, 15000, "bf16")            # ... fewer, but enough to share documents
+    assert alone(64, 20000, 20600000, 9999, "bf16") and alone(3, 20000, 20600000, 62600, "bf16")
+    assert not alone(64, 5000, 256 * 5000, 4096, "bf16") and alone(64, 5000, 256 * 5000 - 1, 4096, "bf16")
+    assert alone(64, 5000, 256 * 5000, 4095, "bf16") and alone(64, 20000, 20600000, 62600, "f32")
