@@ -56,7 +56,8 @@ Layout make_layout(int nq, int T, int d, int64_t N, int64_t total_tokens) {
     // Two arrays share storage with arrays that are dead while they live: the exhaustive
     // path's score rows (no call uses them together with the running statistics) lie over
     // `stat`, and the rescored survivors (written after the last round) over `stat2`, which
-    // only a round's corpus pass and the prune right after it use.
+    // only a round's corpus pass and the prune right after it use, and round 2's table of lists by
+    // document (held_of), which is read only where that round is no corpus pass.
     L.scores = L.stat;
     L.rescored = L.stat2;
     L.cnt_hist = take(4 * (size_t)(COLBANDIT_MAX_ROUNDS + 2) * nq);

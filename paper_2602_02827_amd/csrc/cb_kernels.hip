@@ -433,7 +433,8 @@ constexpr int64_t ALL_DOCS = 64;
 //                  cells are REVEALED to the bounds is unchanged.  cache_all: the smallest calls visit all
 //                  documents so before round 1, which takes its batch from the cells as well; the
 //                  launch also sets the queries up, which nothing in it needs, and two launches make
-//                  the call (1 query x 1,000 documents of 48 fp32 tokens: 45 -> 39 us).
+//                  the call (1 query x 1,000 documents of 48 fp32 tokens: 45 -> 39 us; 25 to 33, by the inputs, since
+//                  round 1 is revealed there, cache_all_reveals).
 // batch_token(q): this lane's token of the round's batch (REVEAL).
 template <typename Tag, int D, int TQ, bool CACHE_ALL, bool REVEAL, class TokenFn>
 __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks, TokenFn batch_token) {
@@ -580,11 +581,13 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks, 
 // The same reveal of round 2, document by document, where many documents are long and held by several queries: a
 // wavefront (a workgroup of its own: they take different times) takes a document, reads once the list of the queries
 // that hold it (k_select_prune has entered them, hold_documents) and multiplies it with the rows of up to NQ of them at a
-// time, so that it is read once for those.  Bound by memory: 64 queries of T = 24 x 20,000 pages of 1,030 tokens, 62,600
-// pairs on 19,200 documents: 1.0 to 1.15 ms (5.3 GB, 6.2 with the documents read again for a fifth query on) in the
-// place of a second corpus pass of 1.15 and gathers of 0.5.  (A workgroup of four wavefronts per run of documents,
+// time, so that it is read once for those.  Bound by memory: 64 queries of T = 24 x 20,000 pages of 1,030 tokens, 58,100
+// pairs on 19,000 documents: 1.05 to 1.25 ms for 5.0 GB of documents, 5.9 with those read again for a fifth query on, of
+// which HBM delivers all (6.0 by its counters, 5.3 TB/s), in the place of a second corpus pass of 1.15 and gathers of 0.5.  (A workgroup of four wavefronts per run of documents,
 // two queries and one block ahead each: 1.57; each wavefront searching the lists for its document: 1.29; three blocks in
-// flight as four; tokens with the non-temporal hint: 1.45, the documents read again miss the caches.)
+// flight as four; tokens with the non-temporal hint: 1.45, the documents read again miss the caches.)  The query rows of
+// eight tiles and the blocks fill the 256 registers of two wavefronts a SIMD: in bf16 at d = 128, queries of 33 to 64
+// tokens put 3 in scratch memory and longer ones 11, outside the loop over a document's blocks.
 template <int TQ> constexpr int share_queries() { return 8 / TQ; }
 // blocks in flight: 64 registers
 template <class F> constexpr int share_depth() { return 64 / ((int)sizeof(F) / 4) < 8 ? 64 / ((int)sizeof(F) / 4) : 8; }
@@ -2539,10 +2542,13 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
 
 // Pre-filter and prune of a round >= 2 in one launch, for calls whose lists are expected to be short by then
 // (Knobs::narrow) and whose workgroups, which need a CU each, take two turns at most.  Of a short list the first workgroup
-// prunes at once, and the launch spared is 2.6 us in every round (64 queries x 50,000 465 -> 455 us, 13 x 91,000 in rounds
-// of 4 out of 123 tokens 634 -> 582).  Of a long list the last workgroup to come prunes (QueryCtl::done, which the prune
-// clears); what the others wrote has to go through memory to it, some 8 us a round (38 x 66,000 with alpha 1.0
-// 1,505 -> 1,545 us, 3 x 134,600 9,375 -> 9,463, with a fence by every wavefront 1,973 and 9,723).
+// prunes at once, and the launch spared is 2.6 us in every round (64 queries x 50,000 472 -> 463 us, 13 x 91,000 in rounds
+// of 4 out of 123 tokens 867 -> 805).  Of a long list the last workgroup to come prunes (QueryCtl::done, which the prune
+// clears); what the others wrote has to go through memory to it, some 8 us a round, so that a call gains unless its lists
+// are long in a quarter of its rounds: 38 x 66,000 with alpha 0.25 479 -> 469 us, 0.3 534 -> 526, 0.5 844 -> 834, but
+// 1.0 (34,000, then 22,000 entries) 1,881 -> 1,898.  K and delta lengthen lists as well, by less: alpha 0.25, K = 200, delta
+// 1e-30 and rounds of 2, 3 x 130,000 (72,000 and 51,000 entries) 2,682 -> 2,655; K = 1,000 in rounds of 4, 4 x 500,000
+// (264,000, 113,000, 30,000) 7,724 -> 7,759.  (With a fence by every wavefront 38 x 66,000 took 1,973.)
 __global__ __launch_bounds__(SEL_THREADS) void k_select_round(SelArgs A, Kappas kappas) {
     __shared__ SelShared sh;
     __shared__ int last;

@@ -82,7 +82,7 @@ constexpr DenseRule kNeverDense{NEVER_DENSE, 0u, 0u, 0, 0};
 struct Knobs {
     int K, M, B;
     float a, b;
-    bool narrow;          // the radius is small: after round 1 lists are seldom longer than a tile
+    bool narrow;          // the radius is small: lists are longer than a tile in few rounds (k_select_round has the figures)
 };
 
 // n_chunks > 0: also fills the chunk table of the corpus passes (launch_dense_prepare).
