@@ -856,7 +856,7 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
         pt.mark(r == 1 ? PH_FIRST_REVEAL : (r == 2 ? PH_ROUND2_REVEAL : PH_LATER_REVEAL));
         const bool last = last_launched(rr);
         const DenseRule next = share && r == 1 && R >= 2 ? round_of(2).dense : kNeverDense;
-        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, stats != nullptr, next,
+        if (e == hipSuccess) e = launch_select_prune(P, W, kn, rr, R, kappa, cache_all, cache_all && !cache_all_reveals(P, co), stats != nullptr, next,
                                                      finish && !last, tr, finish && last ? topk_ids : nullptr, topk_scores, st);
         pt.mark(PH_SELECT);
         if (last) break;

@@ -885,17 +885,27 @@ hipError_t launch_gather_round(const Problem& P, const Work& W, const RevealRoun
 
 // k_cache_all takes round 1's batch from the cells as it computes them: each wavefront works out the reveal order, while
 // its loads are under way, and k_select_prune reads 8 bytes a document side by side instead of cells from as many lines
-// (1 query x 1,000 documents: 13 us from its start to the threshold with cells, 7 so; 34.4 -> 29.2 us a call, 2 x 487
-// 28 -> 20).  A query's list gains some 6 ns a document, a pair costs 0.6 beyond those that leave the SIMDs idle anyhow
-// (12 x 2,286 66 -> 69 us, 9 x 709 45 -> 39, 12 x 522 38 -> 34).
-static bool cache_all_reveals(const Problem& P) { return P.nq <= 8 || (int64_t)P.nq * P.N <= 12288; }
+// (1 query x 1,000 documents: 13 us from its start to the threshold with cells, 7 so; 37.0 -> 31.5 us a call, 2 x 487
+// 25.0 -> 22.5).  A query's list gains some ns a document, a pair costs as many, shared by the wavefronts that the query
+// rows leave on a SIMD: four or three of them 9 x 709 46.9 -> 43.1, 12 x 522 39.8 -> 37.2; two (96 registers of query rows
+// or more: fp32 from 17 tokens in d = 128 and from 33 in d = 64 on, bf16 of more than 64 in d = 96 and 128) 4 x 1,000
+// of 32 fp32 tokens in d = 128 53.6 -> 50.5, but 8 x 1,400 61.9 -> 66.6, 12 x 400 50.6 -> 52.2; one (fp32 from 33 tokens in d = 128
+// on) 1 x 4,000 93.4 -> 87.6, 3 x 1,000 76.4 -> 73.5, but 3 x 2,700 108.6 -> 112.8, 8 x 1,400 112.4 -> 128.9.
+bool cache_all_reveals(const Problem& P, const Coarse* co) {
+    const int tq = (P.T + 15) / 16;
+    const int row_regs = (tq <= 1 ? 1 : tq <= 2 ? 2 : tq <= 4 ? 4 : 8) * P.d * (co ? 2 : P.dt == DT_BF16 ? 4 : 12) / 32;
+    const int64_t pairs = (int64_t)P.nq * P.N;
+    if (row_regs >= 192) return P.nq <= 1 || (P.nq <= 3 && pairs <= 4096);
+    if (row_regs >= 96) return P.nq <= 5;
+    return P.nq <= 8 || pairs <= 12288;
+}
 
 hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
                             const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st) {
     GatherArgs A{};
     A.dense = kNeverDense;
     const InitArgs I = init_args(P, W, kn, R, seed, user_pi, tr, 0);
-    if (cache_all_reveals(P)) A.nb = kn.B < P.T ? kn.B : P.T;
+    if (cache_all_reveals(P, co)) A.nb = kn.B < P.T ? kn.B : P.T;
     A.G = 1;
     while (A.G < A.nb) A.G <<= 1;
     long long blocks = (long long)P.nq * P.N;
@@ -2602,12 +2612,12 @@ static TopkArgs topk_args(const Problem& P, const Work& W, bool use_ctl, bool ca
 }
 
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
-                               const RevealRound& rr, int R, const float* kappa, bool cache_all,
+                               const RevealRound& rr, int R, const float* kappa, bool cache_all, bool fold_cells,
                                bool note_pairs, const DenseRule& next, bool finish_next, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st) {
     SelArgs A{};
     A.cache_all = cache_all ? 1 : 0;
     A.finish_next = finish_next ? 1 : 0;
-    A.fold_cells = cache_all && !cache_all_reveals(P) ? 1 : 0;
+    A.fold_cells = fold_cells ? 1 : 0;
     A.note_pairs = cache_all && note_pairs ? 1 : 0;
     TopkArgs top{};
     if (topk_ids) top = topk_args(P, W, false, true, W.rescored, kn.K, topk_ids, topk_scores);

@@ -102,6 +102,8 @@ unsigned share_enough(const Problem& P);
 // document), and the queries are set up in the same launch.
 hipError_t launch_cache_all(const Problem& P, const Work& W, const Knobs& kn, int R, uint64_t seed,
                             const int32_t* user_pi, const Trace& tr, const Coarse* co, hipStream_t st);
+// Whether it reveals round 1 from them.
+bool cache_all_reveals(const Problem& P, const Coarse* co);
 
 // Exact scores from the stored embeddings.  Survivors: of the current active sets, written by
 // list position (score_slots: including the queries whose list holds cache slots, whose cached
@@ -147,12 +149,12 @@ int dense_chunks(const Problem& P, const Work& W);
 
 // Threshold and prune of round rr; a query whose cells are cached runs all its remaining rounds in
 // this launch.  R: number of rounds of the call (layout of W.pairs); kappa[r], r = 1..R: radius
-// per unit sigma_hat of round r.  next: in round 1 the rule of round 2, else kNeverDense.  finish_next: round 1 of a
+// per unit sigma_hat of round r.  fold_cells: after launch_cache_all, if that has not revealed round 1.  next: in round 1 the rule of round 2, else kNeverDense.  finish_next: round 1 of a
 // call whose round 2 is the last to launch and ends with the top-K: the survivors of queries that end in round 1 are
 // then gathered with it.  topk_ids (after launch_cache_all, or in that round 2; exact cells): the launch ends with the
 // top-K.
 hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
-                               const RevealRound& rr, int R, const float* kappa, bool cache_all,
+                               const RevealRound& rr, int R, const float* kappa, bool cache_all, bool fold_cells,
                                bool note_pairs, const DenseRule& next, bool finish_next, const Trace& tr, int64_t* topk_ids, float* topk_scores, hipStream_t st);
 
 // Top-K of `vals` per query.  use_ctl: candidates are the active set (vals indexed by

@@ -867,16 +867,23 @@ def test_smallest_calls_that_visit_every_document_once(B, S, oracle_mod, dtype, 
         _run_colbandit_case(B, oracle_mod, w, 5, 5, Bsz, alpha, seed=3)
 
 
-@pytest.mark.parametrize("nq,N,T,Bsz", [(8, 2100, 32, 4), (9, 1365, 24, 4), (9, 1366, 24, 4), (13, 1000, 70, 16), (12, 1000, 128, 3)])
-def test_round_one_revealed_as_the_cells_are_cached(B, S, nq, N, T, Bsz):
+@pytest.mark.parametrize("dtype,d,nq,N,T,Bsz,reveals", [
+    ("bf16", 64, 8, 2100, 32, 4, True), ("bf16", 64, 9, 1365, 24, 4, True), ("bf16", 64, 9, 1366, 24, 4, False),
+    ("bf16", 64, 13, 1000, 70, 16, False), ("bf16", 64, 12, 1000, 128, 3, True),
+    ("f32", 128, 1, 4500, 48, 4, True), ("f32", 128, 3, 1365, 40, 4, True), ("f32", 128, 3, 1366, 40, 4, False),
+    ("f32", 128, 4, 300, 64, 3, False), ("f32", 128, 5, 900, 32, 4, True), ("f32", 128, 6, 900, 32, 4, False),
+    ("f32", 96, 6, 800, 33, 2, False), ("f32", 96, 8, 900, 32, 4, True), ("bf16", 128, 5, 900, 65, 4, True),
+    ("bf16", 128, 6, 900, 65, 4, False), ("bf16", 128, 8, 900, 64, 4, True)])
+def test_round_one_revealed_as_the_cells_are_cached(B, S, dtype, d, nq, N, T, Bsz, reveals):
     """Both sides of the rule by which the smallest calls reveal round 1 while they compute the cells, with the seeded order and
     with a table (one that holds a token twice among them): the run of gathers that keep no cells."""
-    w = _custom(S, np.random.default_rng(nq).integers(1, 12, N).tolist(), nq, T, 64, "bf16", 11)
+    w = _custom(S, np.random.default_rng(nq).integers(1, 12, N).tolist(), nq, T, d, dtype, 11)
     pi = torch.stack([torch.randperm(T, generator=torch.Generator().manual_seed(q)) for q in range(nq)]).to(torch.int32)
     pi[-1, 1] = pi[-1, 0]
+    tiles = next(t for t in (1, 2, 4, 8) if 16 * t >= T)
     for more in ({}, {"pi": pi.cuda()}):
         call = lambda **o: B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.3, 0.01, 5, 3, B=Bsz, **more, **o)
-        assert "k_cache_all<" in _kernels(lambda: call(want_stats=False))
+        assert f"k_cache_all<cb::{dtype}_tag, {d}, {tiles}, {str(reveals).lower()}>" in _kernels(lambda: call(want_stats=False))
         _same_run(call(trace=True), call(trace=True, no_cell_cache=True))
 
 
