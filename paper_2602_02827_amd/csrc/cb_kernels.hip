@@ -2452,7 +2452,8 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
 // workgroup sampled for itself.
 // In a corpus-pass round the round's batch (stat2) is merged in registers only: k_select_prune
 // stores the merged statistics of the survivors, the only entries that are ever read again.
-__device__ __forceinline__ void filter_segments(const SelArgs& A, int q, const QueryCtl& c, SelShared& sh) {
+// Workgroup `first` of `step` that share the query's segments.
+__device__ __forceinline__ void filter_segments(const SelArgs& A, int q, const QueryCtl& c, int first, int step, SelShared& sh) {
     const int count = c.count;
     const int len = seg_len(count);
     const int n_seg = seg_count(count);
@@ -2468,7 +2469,7 @@ __device__ __forceinline__ void filter_segments(const SelArgs& A, int q, const Q
     const FastBounds fb = fast_bounds_consts(n, T, kappa, a, b);
     const size_t tro = ((size_t)(A.r - 1) * A.nq + q) * A.N;
     clear_hist(sh);
-    for (int sg = blockIdx.x; sg < n_seg; sg += gridDim.x) {
+    for (int sg = first; sg < n_seg; sg += step) {
         const int lo = sg * len;
         const int hi = seg_end(lo, len, count);
         int base = lo;
@@ -2547,7 +2548,7 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     const QueryCtl c = A.ctl[q];
     if (!c.active || c.count <= SEL_TILE) return;   // cached lists are never this long
     if ((int)blockIdx.x >= seg_count(c.count)) return;
-    filter_segments(A, q, c, sh);
+    filter_segments(A, q, c, (int)blockIdx.x, (int)gridDim.x, sh);
 }
 
 // Pre-filter and prune of a round >= 2 in one launch, for calls whose lists are expected to be short by then
@@ -2559,14 +2560,17 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
 // 1.0 (34,000, then 22,000 entries) 1,881 -> 1,898.  K and delta lengthen lists as well, by less: alpha 0.25, K = 200, delta
 // 1e-30 and rounds of 2, 3 x 130,000 (72,000 and 51,000 entries) 2,682 -> 2,655; K = 1,000 in rounds of 4, 4 x 500,000
 // (264,000, 113,000, 30,000) 7,724 -> 7,759.  (With a fence by every wavefront 38 x 66,000 took 1,973.)
+// The queries are the fast axis of the grid: workgroups go to the XCDs in turn, and with eight or sixteen to a query those
+// that prune short lists, the first of each, all ran on one XCD of the eight (64 queries x 60,000 documents of 51 tokens, lists
+// of some 500 entries in round 2: two turns on its 32 CUs, 112 us, 60 now; a call 405 -> 358, on codes of d = 128 431 -> 372).
 __global__ __launch_bounds__(SEL_THREADS) void k_select_round(SelArgs A, Kappas kappas) {
     __shared__ SelShared sh;
     __shared__ int last;
-    const int q = blockIdx.y;
+    const int q = blockIdx.x;
     const QueryCtl c = A.ctl[q];
     if (!c.active) return;
     if (c.count > SEL_TILE) {
-        if ((int)blockIdx.x < seg_count(c.count)) filter_segments(A, q, c, sh);
+        if ((int)blockIdx.y < seg_count(c.count)) filter_segments(A, q, c, (int)blockIdx.y, (int)gridDim.y, sh);
         // Every wavefront waits until its own stores are in L2, which the barrier alone does not wait for: the write-back of
         // one thread's fence takes what is there.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -2575,12 +2579,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_round(SelArgs A, Kappas 
         // thread's fences, between the barriers, serve them all; each writes a whole L2 back.)
         if (threadIdx.x == 0) {
             __threadfence();                        // the segments, for whichever workgroup prunes
-            last = atomicAdd(&A.ctl[q].done, 1) == (int)gridDim.x - 1;
+            last = atomicAdd(&A.ctl[q].done, 1) == (int)gridDim.y - 1;
             if (last) __threadfence();
         }
         __syncthreads();
         if (!last) return;
-    } else if (blockIdx.x > 0) return;              // (a list is never longer after a round)
+    } else if (blockIdx.y > 0) return;              // (a list is never longer after a round)
     prune_query<END_NONE, true>(A, kappas, TopkArgs{}, q, sh);
 }
 
@@ -2671,7 +2675,7 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
             const unsigned few = (unsigned)(2048 / P.nq > 1 ? 2048 / P.nq : 1);
             gx = gx < few ? gx : few;
             if (kn.narrow && gx * (unsigned)P.nq <= 512u) {
-                k_select_round<<<dim3(gx, P.nq), SEL_THREADS, 0, st>>>(A, kappas);
+                k_select_round<<<dim3(P.nq, gx), SEL_THREADS, 0, st>>>(A, kappas);
                 return hipGetLastError();
             }
         }

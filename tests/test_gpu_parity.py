@@ -1061,6 +1061,25 @@ def test_long_lists_under_a_small_radius_are_pruned_by_the_last_workgroup_to_com
     _run_colbandit_case(B, oracle_mod, w, 200, 5, 2, 0.25, delta=1e-30, seed=4, later_rounds=later)
 
 
+def test_first_workgroups_of_the_merged_rounds_lie_side_by_side(B, S, tmp_path):
+    """k_select_round: of a query's eight workgroups the first prunes a short list alone; consecutive workgroups go to the eight
+    XCDs in turn, so the queries are the grid's fast axis."""
+    import json
+    from torch.profiler import ProfilerActivity, profile
+    w = _custom(S, np.random.default_rng(3).integers(1, 8, 60000).tolist(), 16, 32, 32, "bf16", 3)
+    for _ in range(5):
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            B.colbandit_topk(w.Q, w.docs, w.offsets, 5, 0.1, 0.01, 5, 3, want_stats=False)
+            torch.cuda.synchronize()
+        p.export_chrome_trace(str(tmp_path / "t.json"))
+        events = json.load(open(tmp_path / "t.json"))["traceEvents"]
+        grids = [e["args"]["grid"] for e in events if "k_select_round" in e.get("name", "") and "grid" in e.get("args", {})]
+        if grids:
+            break
+    assert grids and all(g == [16, 8, 1] for g in grids)
+
+
 def test_wild_documents_in_long_lists_pruned_by_the_last_workgroup_to_come(B, S):
     """k_select_round on lists that hold documents outside the contract, in any segment: the run of the same queries in a batch
     too large for it, whose rounds are filtered and pruned by two launches."""
