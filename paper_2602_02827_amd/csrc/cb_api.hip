@@ -110,17 +110,32 @@ Work carve(void* ws, const Layout& L) {
 
 // Sets the chunk length for passes over `tiles` column tiles, and the place of the chunk table.
 // A group of fp32 tiles has half as many.
-void choose_chunks(Work& W, const Problem& P, int64_t tiles, bool codes = false) {
+// pairs: workgroups of two wavefronts (in_pairs), of which a turn is 1,536 that take longer each: a last turn that is less than
+// half full, or chunks of one or two documents, cost them more than the others, so their chunks are halved where that saves
+// a turn of halves, or makes chunks of a document at most (exhaustive in d = 64, 10 queries of 16 tokens, us, four
+// wavefronts / whole chunks / halved: 172,000 documents of 25 tokens 252 / 255 / 225, 85,000 of 100 322 / 310 / 292, 5,898
+// pages of 729 147 / 153 / 145, 4,000 of 1,500 196 / 202 / 185; 30,000 of 100, which fill their turns, 125 / 119 / 122).
+void choose_chunks(Work& W, const Problem& P, int64_t tiles, bool codes = false, bool pairs = false) {
     const bool f32 = P.dt == DT_F32 && !codes;
     const int64_t per_group = f32 ? 16 : 32;
     const int64_t groups = (tiles + per_group - 1) / per_group;
     const int64_t wanted = kBlocksWanted / groups > 1 ? kBlocksWanted / groups : 1;
     int c = kChunkTokens;
     while (c > 128 && P.total <= wanted * (c / 2)) c /= 2;
+    constexpr int64_t kTurn = 1536, kMostHalved = 3 * kBlocksWanted;
+    auto chunks = [&](int tokens) { return (P.total + tokens - 1) / tokens; };
+    auto turns = [&](int tokens) { return (chunks(tokens) + kTurn - 1) / kTurn; };
+    auto halves_pay = [&]() {
+        const int64_t doc20 = 20 * P.total / P.N;               // twentieths of a mean document's tokens
+        return doc20 < 20 * (int64_t)c && (turns(c / 2) < 2 * turns(c) || (doc20 > 11 * (int64_t)c && doc20 < 19 * (int64_t)c));
+    };
+    if (pairs)
+        while (c > 512 && chunks(c / 2) <= kMostHalved && halves_pay()) c /= 2;
     W.chunk_tokens = c;
-    // The table of short chunks (at most kBlocksWanted entries per query, and one) lies over the
+    // The table of short chunks (at most kBlocksWanted entries per query, and one; of halved ones three times as
+    // many for three queries or more) lies over the
     // quantiser's scratch, which the coding of queries (one workgroup per query) does not use.
-    static_assert((kBlocksWanted + 1) * 4 <= 16384, "quantize_scratch_bytes holds 16 KB per segment");
+    static_assert((kBlocksWanted + 1) * 4 <= 16384 && (kMostHalved + 1) * 4 <= 3 * 16384, "quantize_scratch_bytes holds 16 KB per segment");
     if (c < kChunkTokens) W.chunk_doc = (int32_t*)W.qscratch;
 }
 
@@ -151,7 +166,7 @@ bool small_call(const Problem& P) {
 // and 728, 8 2,683 and 1,451.
 bool score_by_gather(Work& W, const Problem& P) {
     const ScoreShape s = score_shape(P, false);
-    choose_chunks(W, P, s.tiles);
+    choose_chunks(W, P, s.tiles, false, s.nt == 4 && !s.split && in_pairs(P, s.tiles, false));
     if (small_call(P)) return true;
     if (P.dt != DT_F32) return false;
     const double d = P.d, total = (double)P.total, nq = P.nq, blocks = total / (double)P.N / 16.0;
@@ -436,7 +451,8 @@ int colbandit_coarse_maxsim(const void* Q, int n_queries, int T, int d, colbandi
     if (rc) return rc;
     Work W = carve(workspace, L);
     const Problem P{Q, n_queries, T, d, (int)dt, docs_i8, doc_offsets, N, total_tokens};
-    choose_chunks(W, P, score_shape(P, true).tiles, true);
+    const ScoreShape s = score_shape(P, true);
+    choose_chunks(W, P, s.tiles, true, s.nt == 4 && !s.split && in_pairs(P, s.tiles, true));
     hipStream_t st = (hipStream_t)stream;
     Coarse co{docs_i8, docs_scale, W.q8, W.qscale};
     if (!dense_supported(P, &co)) return COLBANDIT_ERR_UNSUPPORTED;
@@ -786,7 +802,8 @@ static int topk_impl(const void* Q, int n_queries, int T, int d, colbandit_dtype
     const bool dense = dense_supported(P, co) && !force_gather && !(small_call(P) && later_rounds != 1);
     int G_max = 1;                                   // columns of a full batch
     while (G_max < kn.B) G_max <<= 1;
-    choose_chunks(W, P, ((int64_t)n_queries * G_max + 15) / 16, co != nullptr);
+    const int64_t reveal_tiles = ((int64_t)n_queries * G_max + 15) / 16;
+    choose_chunks(W, P, reveal_tiles, co != nullptr, in_pairs(P, reveal_tiles, co != nullptr));
     const int n_chunks = loop && dense ? dense_chunks(P, W) : 0;
     // the smallest calls visit every document once: round 1 caches all cells of all documents
     const bool cache_all = loop && !dense && !force_gather && later_rounds == 0 && small_call(P) &&

@@ -40,7 +40,7 @@ namespace cb {
 // read an operand block from LDS half as often for its matrix instructions and meet half as often: Col-Bandit, 64
 // queries x 20,000 pages, codes 788 -> 762 us, 36 x 500,000 in d = 64 1,999 -> 1,908, exhaustive, 8 x 50,000 in d = 64 194 -> 186.
 // (Other widths lose registers or gain nothing: bf16 of d = 128 64 x 50,000 455 -> 464, 96 474 -> 604, 32 583 -> 614.)
-// Their chunks take longer, so there have to be enough for several turns (pair_pays): 4 queries of 60 tokens x 1,613
+// Their chunks take longer, so they are halved where that fills their turns better (choose_chunks), and there have to be enough (pair_pays): 4 queries of 60 tokens x 1,613
 // pages 64 -> 70 us, 11 x 868 documents 21 -> 22, 4 x 17,775 pages 529 -> 512, 7 x 41,000 documents 185 -> 180.
 constexpr int PAIR = -2;                           // in the place of a number of wavefronts that split the documents
 template <typename Tag, int D, int TILES, int TQ, int SPLIT> constexpr int dense_waves() {
@@ -753,6 +753,10 @@ static hipError_t dense_go(DenseArgs& A, int groups, hipStream_t st) {
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     k_dense<Tag, D, TILES, TQ, REVEAL, SPLIT, PACKED><<<(unsigned)blocks, 64 * dense_waves<Tag, D, TILES, TQ, SPLIT>(), 0, st>>>(A);
     return hipGetLastError();
+}
+
+bool in_pairs(const Problem& P, int64_t tiles, bool codes) {
+    return (codes || P.dt == DT_BF16) && P.d * (codes ? 1 : 2) == 128 && tiles > 8 && tiles <= 16 && pair_pays(P.total, P.N);
 }
 
 ScoreShape score_shape(const Problem& P, bool codes) {

@@ -138,6 +138,8 @@ struct ScoreShape {
 };
 // codes: a pass on int8 codes.
 ScoreShape score_shape(const Problem& P, bool codes);
+// Whether a pass over that many column tiles, in one group and no split of the documents, goes to two wavefronts of eight.
+bool in_pairs(const Problem& P, int64_t tiles, bool codes);
 // fp32 batches that always gather, whatever the corpus (us, 100,000 documents of 100 tokens or 4,000 of 1,030: one query of
 // 32 tokens 367 and 487 by a pass, of 48 in d = 64 222 and 391, two of 48 in d = 128 2,467 and 3,410, in d = 32 579 and
 // 581, two of 32 in d = 96 within 6 %): there is no corpus kernel for them.

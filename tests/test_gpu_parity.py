@@ -277,6 +277,40 @@ def test_sixteen_tiles_of_two_wavefronts_give_the_bits_of_other_batches(B, codes
     _same_run(call(), call(force_gather=True))
 
 
+@pytest.mark.parametrize("codes,N,longest,nq,T", [(False, 3017, 0, 3, 60), (True, 3017, 0, 12, 16), (False, 172000, 49, 10, 16),
+                                                  (True, 172000, 49, 4, 60), (False, 44000, 1100, 3, 33), (True, 44000, 1100, 40, 9)])
+def test_halved_chunks_of_two_wavefronts(B, codes, N, longest, nq, T):
+    """The corpus kernel of two wavefronts where chunks are halved: pages of 729 tokens (one or two to a chunk), short ragged
+    documents whose chunks would leave a turn half empty, and as many chunks as the table of three queries holds."""
+    g = torch.Generator(device="cuda"); g.manual_seed(nq)
+    d = 128 if codes else 64
+    L = torch.randint(1, longest + 1, (N,), device="cuda", generator=g) if longest else torch.full((N,), 729, device="cuda")
+    L[N // 3:N // 3 + 5] = 0
+    off = torch.zeros(N + 1, dtype=torch.int64, device="cuda"); off[1:] = L.cumsum(0)
+    unit = lambda *s: torch.nn.functional.normalize(torch.randn(*s, device="cuda", generator=g), dim=-1).bfloat16()
+    E, Q = torch.empty((int(off[-1]), d), dtype=torch.bfloat16, device="cuda"), unit(nq, T, d)
+    for part in E.split(4000000):
+        part.copy_(unit(*part.shape))
+    more = {}
+    if codes:
+        more["docs_i8"], more["docs_scale"] = B.colbandit_quantize_i8(E)
+        full = lambda q: B.colbandit_coarse_maxsim(q.contiguous(), more["docs_i8"], more["docs_scale"], off)["scores"]
+    else:
+        full = lambda q: B.colbandit_full_maxsim(q.contiguous(), E, off, K=3)["scores"]
+    tq = 1 if T <= 16 else 4
+    if nq * tq <= 16:
+        res = []
+        assert f"k_dense<cb::{'i8' if codes else 'bf16'}_tag, {d}, 4, {tq}, false, -2, false>" in _kernels(lambda: full(Q), res)
+        for q in (0, nq - 1):
+            assert torch.equal(full(Q[q:q + 1])[0], res[0][q])
+    if nq * 4 > 128:
+        call = lambda **o: B.colbandit_topk(Q, E, off, 5, 0.2, 0.01, 5, 3, **more, **o)
+        assert f"k_dense<cb::i8_tag, {d}, 4, 1, true, -2, false>" in _kernels(lambda: call(want_stats=False))
+        a, b = call(), call(force_gather=True)
+        assert torch.equal(a["topk_ids"], b["topk_ids"]) and torch.equal(a["topk_scores"], b["topk_scores"])
+        assert [s["survivors"] for s in a["stats"]] == [s["survivors"] for s in b["stats"]]
+
+
 def test_documents_much_longer_than_a_token_chunk(B, S, oracle_mod):
     """Documents of several chunks leave runs of empty chunks behind them (a chunk belongs to the
     document that starts in it); every workgroup with an empty chunk must exit and the others
