@@ -84,10 +84,14 @@ struct DenseRule {
     uint16_t lg_per;                     // 2^lg_per pairs, by document, cost as much as one of the others
     uint16_t shared_at;                  // the shared word, from the round's own
     __device__ __host__ __forceinline__ bool by_document(unsigned long long shared) const { return pair_count(shared) >= enough; }
-    // Whether the pass is certain from a part of the shared word alone: what else is counted makes its price no lower.
-    __device__ __host__ __forceinline__ bool sure_to_pass(unsigned long long shared) const {
-        const unsigned long long s = pair_count(shared);
-        return s >= enough && base + (s >> lg_per) > thr;
+    // From how many pairs of the shared word on the pass is certain: what else is counted makes the price of gathering no
+    // lower.
+    __host__ unsigned long long certain() const {
+        if (!enough || thr == NEVER_DENSE) return ~0ull;
+        if (base > thr) return enough;
+        const unsigned long long more = thr - base + 1;     // base + (s >> lg_per) > thr from here on
+        if (more > (~0ull >> lg_per)) return ~0ull;
+        return more << lg_per > enough ? more << lg_per : enough;
     }
     __device__ __host__ __forceinline__ bool pass(unsigned long long head, unsigned long long shared) const {
         unsigned long long p = pair_count(head);

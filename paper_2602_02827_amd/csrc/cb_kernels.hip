@@ -1364,7 +1364,8 @@ struct SelArgs {
     uint8_t* tr_alive;
     int32_t* seg_cnt;                    // [nq][SEG_MAX]: candidates per segment (k_select_segments)
     float kappa;                         // radius per unit sigma_hat of the round
-    DenseRule next;                      // round 1: round 2's, where that may gather by document; else enough = 0
+    unsigned enough;                     // round 1, where round 2 may gather by document (DenseRule); else 0
+    unsigned long long certain;          // ... from how many pairs on it is sure to be a corpus pass (DenseRule::certain)
 };
 // ... of every round.  A parameter of its own: indexed at run time, it would keep the whole of SelArgs, which
 // the compiler otherwise takes apart, in scratch memory.
@@ -1425,8 +1426,14 @@ __device__ __forceinline__ void note_round(SelShared& sh, int r, int count, floa
     sh.round_tau[r - 1] = tau;
 }
 
-// Enters a query's list (in the buffer nc.cur) with its documents (held_of).
+// Enters a query's list (in the buffer nc.cur) with its documents (held_of).  Once what is entered costs more than the corpus
+// pass, the round is one and nobody reads the table: the last queries, for which the others wait, need not fill it in (alpha
+// 1.0, pages, us longer than a call without any table: 229 queries x 4,778 of 292 tokens 6 -> 4 of 1,740, 166 x 1,113 2.5 -> 1.6
+// of 876, 64 x 20,000 of 1,030 55 -> 0 of 6,870).  The number only grows, so each thread asks for itself, here, out of the way of the
+// calls that enter nothing: asked once for the workgroup, after a barrier at the end of the prune, it took k_select_prune
+// from 14.1 to 15.2 us wherever that runs (67,406 documents x 30).
 __device__ __forceinline__ void hold_documents(const SelArgs& A, int q, const QueryCtl& nc) {
+    if (pair_count(__hip_atomic_load(A.pairs + 2 * (A.R + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= A.certain) return;
     const int32_t* list = (nc.cur ? A.list1 : A.list0) + (size_t)q * A.N;
     uint32_t* holders = (uint32_t*)A.stat2;
     int* held = (int*)held_of(A.stat2, A.nq, A.N);
@@ -1449,7 +1456,7 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
     }
     __syncthreads();
     // Lists that may make a round worth gathering by document, if others are like them (DenseRule::enough).
-    const bool entered = A.next.enough != 0u && nc.active && nc.count <= A.cache_cap && 4ll * nc.count * A.nq >= (long long)A.next.enough;
+    const bool entered = A.enough != 0u && nc.active && nc.count <= A.cache_cap && 4ll * nc.count * A.nq >= (long long)A.enough;
     const int x = A.r + (int)threadIdx.x;           // round
     if (x <= (nc.active ? r : A.R)) {
         const int count = x <= r ? sh.round_count[x - 1] : nc.count;
@@ -1469,15 +1476,9 @@ __device__ __forceinline__ void end_rounds(const SelArgs& A, int q, const QueryC
             A.work[entered ? A.nq - 1 - place : place] = work_item(q, pair_count(at));
             if (nc.active) atomicAdd(A.pairs + (A.R + 2) + r + 1, *kept_tokens);
             else atomicAdd(A.pairs + 2 * (A.R + 2) + 1, (unsigned long long)nc.count);
-            if (entered) *kept_tokens = at + work_add(nc.count);
         }
     }
-    if (!entered) return;
-    // Once what is entered costs more than the corpus pass, the round is one and nobody reads the table: the last queries,
-    // for which the others wait, need not fill it in (200 queries x 5,000 documents of 300 tokens, alpha 1.0,
-    // 1,886 -> 1,880 us, and 1,867 in a call without any table; 166 x 1,113 886 -> 883 and 880).
-    __syncthreads();
-    if (!A.next.sure_to_pass(*kept_tokens)) hold_documents(A, q, nc);
+    if (entered) hold_documents(A, q, nc);
 }
 
 // Round 1 of a query all of whose cells are cached: the pairs that go on, and their tokens, for the
@@ -2662,7 +2663,8 @@ hipError_t launch_select_prune(const Problem& P, const Work& W, const Knobs& kn,
     A.tr_alive = tr.alive;
     A.seg_cnt = W.seg_cnt;
     A.kappa = kappa[rr.r];
-    A.next = next;
+    A.enough = next.enough;
+    A.certain = next.certain();
     Kappas kappas{};
     for (int r = 0; r <= R; ++r) kappas.of[r] = kappa[r];
     // lists that do not fit one workgroup's registers are first cut down, one workgroup per tile

@@ -455,8 +455,9 @@ def test_revealing_as_the_cells_are_cached_costs_no_wavefront(code_objects):
 
 
 def test_a_round_that_is_sure_to_be_a_corpus_pass_is_one(tmp_path):
-    """DenseRule, the choice between corpus pass and gathers: what sure_to_pass says of a part of the pairs entered by
-    document, pass() says of all of them, whatever else the round holds; so the table of a query that ends later is not read."""
+    """DenseRule, the choice between corpus pass and gathers: from certain() pairs entered by document on, pass() is true
+    whatever else the round holds, so the table of a query that ends later is not read; with one pair less, and nothing else, it
+    is not."""
     src = tmp_path / "rule.cpp"
     src.write_text(r'''
 #include <hip/hip_runtime.h>
@@ -472,8 +473,10 @@ int main() {
         r.enough = (uint32_t)(1 + rnd(1ull << (1 + rnd(22))));
         r.lg_per = (uint16_t)rnd(5);
         const unsigned long long whole = rnd(1ull << (1 + rnd(26))), part = rnd(whole + 1), head = i % 3 ? 0 : rnd(1 << 20);
-        const unsigned long long queries = 1 + rnd(256), some = 1 + rnd(queries);
-        if (!r.sure_to_pass(some << 40 | part)) { open += r.pass(head, queries << 40 | whole); continue; }
+        const unsigned long long queries = 1 + rnd(256);
+        const unsigned long long certain = r.certain();
+        if (certain < 1ull << 40) wrong += !r.pass(0, certain) || (certain > r.enough && r.pass(0, certain - 1));
+        if (part < certain) { open += r.pass(head, queries << 40 | whole); continue; }
         ++sure;
         wrong += !r.pass(head, queries << 40 | whole);
     }
