@@ -2453,8 +2453,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_sample(SelArgs A) {
 // workgroup sampled for itself.
 // In a corpus-pass round the round's batch (stat2) is merged in registers only: k_select_prune
 // stores the merged statistics of the survivors, the only entries that are ever read again.
-// Workgroup `first` of `step` that share the query's segments.
-__device__ __forceinline__ void filter_segments(const SelArgs& A, int q, const QueryCtl& c, int first, int step, SelShared& sh) {
+// Workgroup `first` of `step` that share the query's segments (none, if there are fewer).  The control is a copy, and
+// k_select_segments leaves the look at `first` to the loop: with a reference and a look of its own the compiled loop took
+// 9.9 us in the place of 9.3 (67,406 documents x 30, round 1).
+__device__ __forceinline__ void filter_segments(const SelArgs& A, int q, const QueryCtl c, int first, int step, SelShared& sh) {
     const int count = c.count;
     const int len = seg_len(count);
     const int n_seg = seg_count(count);
@@ -2548,7 +2550,6 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void k_select_segments(SelArgs A) {
     const int q = blockIdx.y;
     const QueryCtl c = A.ctl[q];
     if (!c.active || c.count <= SEL_TILE) return;   // cached lists are never this long
-    if ((int)blockIdx.x >= seg_count(c.count)) return;
     filter_segments(A, q, c, (int)blockIdx.x, (int)gridDim.x, sh);
 }
 
