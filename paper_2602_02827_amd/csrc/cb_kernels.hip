@@ -581,9 +581,10 @@ __device__ __forceinline__ void gather_round(const GatherArgs& A, int n_blocks, 
 // The same reveal of round 2, document by document, where many documents are long and held by several queries: a
 // wavefront (a workgroup of its own: they take different times) takes a document, reads once the list of the queries
 // that hold it (k_select_prune has entered them, hold_documents) and multiplies it with the rows of up to NQ of them at a
-// time, so that it is read once for those.  Bound by memory: 64 queries of T = 24 x 20,000 pages of 1,030 tokens, 58,100
-// pairs on 19,000 documents: 1.05 to 1.25 ms for 5.0 GB of documents, 5.9 with those read again for a fifth query on, of
-// which HBM delivers all (6.0 by its counters, 5.3 TB/s), in the place of a second corpus pass of 1.15 and gathers of 0.5.  (A workgroup of four wavefronts per run of documents,
+// time, so that it is read once for those.  Bound by memory: 64 queries of T = 24 x 20,000 pages of 1,030 tokens, 62,900
+// pairs on some 19,200 documents: 1.07 ms for 5.1 GB of documents, 6.3 with those read again for a fifth query on, of
+// which HBM delivers all (by its counters, 5.9 TB/s; 1.05 to 1.25 ms on other machines and inputs), in the place of a second
+// corpus pass of 1.15 and gathers of 0.5.  (A workgroup of four wavefronts per run of documents,
 // two queries and one block ahead each: 1.57; each wavefront searching the lists for its document: 1.29; three blocks in
 // flight as four; tokens with the non-temporal hint: 1.45, the documents read again miss the caches.)  The query rows of
 // eight tiles and the blocks fill the 256 registers of two wavefronts a SIMD: in bf16 at d = 128, queries of 33 to 64
